@@ -8,18 +8,21 @@ at 1 m, 2^18 observer grid points per pixel (16 per first-harmonic period), exac
 acceleration field.  The initial conditions and pixels are resident in HBM before timing.
 
 One step = lw_deposit_td with the trajectories recomputed inside the call by the FP64 Boris
-pusher, span by span (LW_TRAJ_BORIS: the 144 GB of samples never exist whole), i.e. the arrival
-time of every particle x sample x pixel, the field where the interpolation reads it and the
-linear-interpolation deposit, + lw_spectrum_fft (|E(w)|^2), in mixed precision (arrival times in
-FP64, fields/trace/FFT in FP32).  ``value`` counts particle * sample * pixel triples per second
-of step time.
+pusher, span by span (LW_TRAJ_BORIS: the 144 GB of samples never exist whole), i.e. the field of
+every particle x sample x pixel that the interpolation reads and the linear-interpolation deposit,
++ lw_spectrum_fft (|E(w)|^2), in mixed precision (arrival times in FP64, fields/trace/FFT in
+FP32).  ``value`` counts particle * sample * pixel triples of the workload per second of step time:
+the size of the problem solved, not the arrival times formed.  The deposit looks the window's grid
+points up among each particle's increasing arrival times, so it forms arrival times at the ends of
+blocks of 255 intervals and, per deposited grid point, at a few samples; the trace is that of the
+evaluation of every triple (``covered`` in the line says so beside the value).
 
 In the same line: the all-FP64 pass of the same workload (speedup of mixed over FP64) and the
 band-L2 error of mixed against FP64 in the harmonic bands h = 1..5 of every pixel; the deposit
 kernel against the roofline of the work it performs (an FP64 arrival time for every triple, the
 field at both ends and the interpolation for every deposited grid point; kernel time from HIP
 events the library records around its launches), with counter figures from committed rocprofv3
-summaries while the deposit sources are unchanged; the culled variant (same spectra); the FFT
+summaries while the deposit sources are unchanged; the call with LW_CULL (same spectra); the FFT
 against HBM bandwidth; the Boris pusher's trajectory write rate; the observer-window
 diagnostics; the bunch workload (1e4 e-, 64 x 64 px, stored trajectories) with its own
 roofline; the direct frequency-domain sum on 64 of its pixels; the gradient of a band objective
@@ -53,12 +56,12 @@ PEAK_HBM_GBS = 8000.0
 CUS, CLOCK_GHZ, LANES = 256, 2.4, 64
 PEAK_F32_TFLOPS = 157.3  # vector FP32 (256 CUs x 2.4 GHz x 128 lanes x 2 flops, packed)
 PEAK_F64_TFLOPS = 78.6   # vector FP64
-# Work the deposit performs (its roofline): the arrival time of every (particle, sample, pixel)
-# triple, 6 FP64 flops (three fused multiply-adds: the sample's time base minus n.r/(c dt_obs)),
-# and for every deposited grid point the field at the interval's two ends (68 FP32 flops each:
-# n x ((n - b) x bd), the 1/kappa^3 factor and the prefactors) plus the interpolation (13 FP32
-# flops: weight, its complement, three lerps).  Roofline time = F64/P64 + F32/P32.
-TRIPLE_F64_FLOPS = 6
+# Work the deposit cannot do without (its roofline), per deposited grid point: the arrival times of
+# its interval's two ends, 6 FP64 flops each (three fused multiply-adds: the sample's time base minus
+# n.r/(c dt_obs)), the field at both (68 FP32 flops each: n x ((n - b) x bd), the 1/kappa^3 factor and
+# the prefactors) and the interpolation (13 FP32 flops: weight, its complement, three lerps).
+# Roofline time = F64/P64 + F32/P32.
+POINT_F64_FLOPS = 2 * 6
 FIELD_F32_FLOPS = 68
 HIT_F32_FLOPS = 2 * FIELD_F32_FLOPS + 13
 # the per-evaluation figure of a method that forms the field for every triple (dense)
@@ -155,10 +158,10 @@ def main():
 
 
 def deposit_roofline(triples, hits, kernel_s, launches, summaries=None, profiled=False):
-    """Roofline of the deposit kernel on the work it performs (TRIPLE_F64_FLOPS per triple,
+    """Roofline of the deposit kernel on the work it cannot do without (POINT_F64_FLOPS and
     HIT_F32_FLOPS per deposited grid point) over its measured time (HIP events around its
     launches), with the dense per-evaluation figure and the committed counter figures beside it."""
-    f64 = triples * TRIPLE_F64_FLOPS
+    f64 = hits * POINT_F64_FLOPS
     f32 = hits * HIT_F32_FLOPS
     t_roof = f64 / (PEAK_F64_TFLOPS * 1e12) + f32 / (PEAK_F32_TFLOPS * 1e12)
     work = f64 + f32
@@ -167,7 +170,8 @@ def deposit_roofline(triples, hits, kernel_s, launches, summaries=None, profiled
     roof = {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
             "traffic": None, "kernel": "k_scan", "launches": launches, "kernel_ms": kernel_s * 1e3,
             "work": {"f64_flops": f64, "f32_flops": f32, "triples": triples, "deposited_points": hits,
-                     "f64_flops_per_triple": TRIPLE_F64_FLOPS, "f32_flops_per_deposited_point": HIT_F32_FLOPS},
+                     "f64_flops_per_deposited_point": POINT_F64_FLOPS,
+                     "f32_flops_per_deposited_point": HIT_F32_FLOPS},
             "roofline_ms": t_roof * 1e3}
     dense_s = triples * (DENSE_F32_FLOPS / (PEAK_F32_TFLOPS * 1e12) + DENSE_F64_FLOPS / (PEAK_F64_TFLOPS * 1e12))
     roof["dense_per_eval_figure"] = {"note": "68 FP32 + 6 FP64 flops credited to every triple (a method "
@@ -316,8 +320,7 @@ def headline(torch, dev, args):
         del S64
         torch.cuda.empty_cache()
     if not args.no_cull:
-        # culled variant (LW_CULL): particles whose arrivals miss a wavefront's window are
-        # skipped after two arrival-time evaluations; same spectra, reported separately
+        # the same call with LW_CULL: same spectra (the deposit skips what misses the window either way)
         cul = run("mixed", 1, 0, cull=True)
         S_c = cul.pop("S")
         diff = float(torch.max(torch.abs(S_c - S_mixed)) / torch.max(torch.abs(S_mixed)))
@@ -353,6 +356,8 @@ def headline(torch, dev, args):
     rec = {
         "metric": METRIC, "value": value, "unit": "evals/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": mixed["ms_per_step"], "higher_is_better": True, "scaling": "weak",
+        "covered": "value counts the workload's particle*sample*pixel triples; arrival times are formed only where "
+                   "the search for the window's grid points needs them (the full evaluation's trace and counters)",
         "vs_baseline": None, "dtype": "f64 tau + f32 field/trace/FFT", "data": "synthetic",
         "config": {"workload": desc, "n_particles": W.n_p, "n_samples": W.n_samples, "n_pix": n_pix,
                    "n_obs": n_obs, "geom": args.geom, "field": "accel", "prec": "mixed",

@@ -66,11 +66,10 @@ typedef enum {
  * diag) instead of overwriting them (for particle-chunked calls). */
 #define LW_ACCUMULATE (1 << 8)
 
-/* flag OR-ed into the geometry argument of lw_deposit_td: skip every particle whose
- * arrival times at a wavefront's pixels hold no observer grid point (tested on the
- * first and last sample where the arrival times are provably increasing; particles
- * that take the careful path are never skipped).  E and diag are exactly those of the
- * full evaluation; only the work changes.  Not set in the headline measurement. */
+/* flag OR-ed into the geometry argument of lw_deposit_td: skip what holds no observer grid
+ * point of the window.  E and diag are exactly those of the call without it.  The fast path
+ * does so with or without the flag (it looks the window's grid points up among a particle's
+ * increasing arrival times); particles that take the careful path are never skipped. */
 #define LW_CULL (1 << 9)
 
 /* trajectory source */

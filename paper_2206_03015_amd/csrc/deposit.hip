@@ -8,37 +8,35 @@
 //     coefficients of the arrival time as a polynomial in the pixel variable b
 //     (tau = sum_j c_j b^j, b = C((1 - n_z) z - n_x x - n_y y): one fused multiply-add per
 //     degree and pixel, at a lower degree where kModeRecLow applies); it also flags particles
-//     whose arrival times are provably increasing and finds each particle's max |r|^2; a pixel
+//     whose arrival times are not provably increasing and finds each particle's max |r|^2; a pixel
 //     table holds each pixel's constants;
-//   * fast path (k_scan): a wavefront owns a tile of kTilePix pixels and a group of particles.
-//     For each particle it walks the samples in chunks of 64 (lane j holds sample 63 q + j of
-//     chunk q, so consecutive chunks share one sample and every interval has both ends in one
-//     chunk), three chunks at a time, the first value of each record of the next three loaded
-//     ahead.  The records sit in vector registers; for each pixel of the tile its next grid point
-//     and its constants come from LDS, the same address in every lane (the constants from the
-//     pixel table with scalar loads where each pixel takes its own arrival-time form), and every
-//     lane forms the arrival time of its sample and compares it with that grid point.  If any
-//     lane reaches it, the intervals of the chunk that hold window grid points follow from the two
-//     ends' arrival times (the neighbouring lane's value) and are queued in LDS with both arrival
-//     times;
+//   * fast path (k_sweep, particles whose arrival times provably increase): for each pixel the grid
+//     points of the window are looked up among the samples, not the samples among the grid points.
+//     A block takes a particle in steps of 256 samples, finds from the arrival times at the steps'
+//     ends which steps hold window grid points for its 128 pixels, stages those steps' samples in
+//     LDS and gives every lane one (pixel, grid point) pair: the lane finds the sample interval of
+//     its grid point, evaluates the field at the interval's two ends and adds the interpolated
+//     value to the trace.  Arrival times are formed where that needs them: at the steps' ends and,
+//     per grid point, at about four samples, instead of at every sample (bunch workload: 21 samples
+//     per grid point inside the window and 71 % of the samples outside it; precision workload: 99 %
+//     outside).  Steps with many grid points per sample form every arrival time and field once
+//     instead;
 //   * careful path (k_careful, particles the pre-pass could not clear): lanes own pixels; the
-//     skip rules of lw_deposit_td are applied interval by interval, and crossings go to the same
-//     queue;
-//   * the queue is drained 64 entries at a time, one per lane (see Wave::drain): the field at the
-//     interval's two ends and the interpolated values at its grid points, added to the trace with
-//     global atomics.  An interval holding more than kLongRun grid points (an observer grid much
-//     finer than the samples) is deposited by the whole wavefront, 64 grid points per pass.
+//     skip rules of lw_deposit_td are applied interval by interval, crossings go to a queue in LDS
+//     that is drained 64 entries at a time, one per lane (see Wave::drain): the field at the
+//     interval's two ends and the interpolated values at its grid points, added to the trace.  An
+//     interval holding more than kLongRun grid points (an observer grid much finer than the samples)
+//     is deposited by the whole wavefront, 64 grid points per pass.
 // The field is therefore evaluated only at samples that the interpolation reads.  Every decision
-// and weight uses one arrival-time value per (sample, pixel): both orientations evaluate it with
-// the same operations (tau_eval).  With LW_CULL (a separate instantiation) a fast-path particle
-// is skipped when its first and last arrival times at the wavefront's pixels bracket no window
-// grid point.
+// and weight uses one arrival-time value per (sample, pixel): every path evaluates it with the
+// same operations (tau_eval), and the field with one function, so a contribution's bits do not
+// depend on the path that finds it.  LW_CULL asks for what the fast path does anyway.
 //
 // Arrival-time forms (exact geometry): the polynomial records hold the path term's series
 // (first order with single-precision fields, third order with double ones; valid where
 // |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory) for pixels at the records' distance
 // (|x_m| of the first pixel), evaluated to a lower degree where the terms above it are provably
-// negligible for the particle and the wavefront's pixels (kModeRecLow); a wavefront whose pixels
+// negligible for the particle and the tile's pixels (kModeRecLow); a tile whose pixels
 // sit at another distance, or a particle outside the series bound, evaluates arrival_tau per
 // pixel instead (series or square-root form), from the same d.
 //
@@ -49,27 +47,31 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace lw {
 namespace {
 
 constexpr int kPPL = 2;                 // pixels per lane
-constexpr int kTilePix = 64 * kPPL;     // pixels per wavefront
+constexpr int kTilePix = 64 * kPPL;     // pixels per tile
 constexpr int kPixBits = 7;
 static_assert((1 << kPixBits) == kTilePix, "tile of 128 pixels");
 constexpr int kBlockThreads = 64;
 // queue ring: up to 63 pending entries plus one push (at most 64 crossings: one sample's pixels
-// of one half of the tile on the careful path, one chunk's intervals on the fast path)
+// of one half of the tile)
 constexpr uint32_t kQCap = 128;
 // intervals with more grid points than this are deposited by the whole wavefront
 constexpr int kLongRun = 8;
-// wavefronts per launch to aim for (particle groups x pixel tiles): ~26 rounds of the 3072
-// resident wavefronts (12 per CU), so that the last, partly filled round is a small share
-constexpr int kTargetWaves = 98304;
-// at most this many particles per group: the wavefronts of a group (one per pixel tile, started
-// together on one XCD) read the same records, and stay close enough to share them in L2
+// particles per block of the fast path: one until there are kTargetBlocks blocks (16 rounds of the
+// 1024 resident ones), then up to kMaxPartsPerGroup; with fewer than kFillBlocks blocks each
+// particle's samples are split into segments
+constexpr int64_t kTargetBlocks = 16384;
 constexpr int kMaxPartsPerGroup = 4;
+constexpr int64_t kFillBlocks = 2048;
+// samples per block of the pre-pass: at most kPrepassChunk, less where that leaves fewer than
+// kPrepassBlocks blocks (one electron of 20001 samples: 65 us in 3 blocks)
 constexpr int kPrepassChunk = 8192;
+constexpr int64_t kPrepassBlocks = 2048;
 // pixel table: kPT doubles per pixel (o, px, py, ok, nx, ny, nz, D, invD, padding), at most
 // kPixTabMax pixels per pass (its share of the workspace); larger grids take several passes
 constexpr int kPT = 16;
@@ -78,14 +80,14 @@ static_assert(kPixTabMax % kTilePix == 0, "whole tiles per pixel pass");
 
 // scan modes: polynomial records (degree 3 or 5 in b, exact geometry), far field (tau = d + b),
 // or arrival_tau per pixel in one of its forms
-constexpr int kModeRec3 = 0, kModeRec5 = 1, kModeFar = 2, kModeSqrt = 3, kModeSeries = 4, kModeShort = 5;
+constexpr int kModeRec3 = 0, kModeRec5 = 1, kModeFar = 2;
 // arrival_tau per pixel with the form of each pixel (series where rb2 |x_m|^-2 <= kSeriesBound)
 constexpr int kModeMixed = 6;
 // polynomial records evaluated to a lower degree (RecLayout::LOW: 2 of 3 with single-precision
 // fields, 3 of 5 with double ones) where tail_negligible holds for the particle and the tile
 constexpr int kModeRecLow = 7;
 
-// Record of one sample (doubles), read by the scan with scalar loads:
+// Record of one sample (doubles):
 //   far field:          d, x, y, z
 //   exact, degree 3:    c_0, c_1, c_2, x, y, z, d, (pad)
 //   exact, degree 5:    c_0, c_1, c_2, c_3, c_4, x, y, z, d, (pad)
@@ -102,12 +104,6 @@ __host__ __device__ constexpr int rec_width(int geom, bool f64)
 {
     return geom == LW_GEOM_FARFIELD ? RecLayout<LW_GEOM_FARFIELD, false>::W
                                     : (f64 ? RecLayout<LW_GEOM_EXACT, true>::W : RecLayout<LW_GEOM_EXACT, false>::W);
-}
-
-__device__ __forceinline__ double next_grid(double tau, double n_obs)
-{
-    double f = fmax(floor(tau) + 1.0, 0.0);
-    return f >= n_obs ? INFINITY : f;
 }
 
 // number of window grid points <= tau: clamp(floor(tau) + 1, 0, n_obs)
@@ -133,15 +129,6 @@ __device__ __forceinline__ float readlane_t(float v, int src)
 }
 __device__ __forceinline__ double readlane_t(double v, int src) { return readlane_double(v, src); }
 
-// The previous lane's value (lane l gets lane l - 1's; lane 0 gets 0): a DPP shift of the
-// wavefront by one lane, no LDS round trip
-__device__ __forceinline__ double lane_shift_up(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-
 __device__ __forceinline__ double uniform_double(double v)
 {
     const uint64_t b = (uint64_t)__double_as_longlong(v);
@@ -151,7 +138,7 @@ __device__ __forceinline__ double uniform_double(double v)
 }
 
 // The records are written by the pre-pass launch and only read while the deposit kernel runs, so
-// the scan reads them through the constant address space: with a wavefront-uniform address in
+// a wavefront-uniform sample's is read through the constant address space: with the address in
 // scalar registers these become scalar loads.
 typedef const __attribute__((address_space(4))) double *cdptr;
 __device__ __forceinline__ cdptr uniform_ptr(const double *p)
@@ -163,7 +150,7 @@ __device__ __forceinline__ cdptr uniform_ptr(const double *p)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pixel table and the arrival time shared by both orientations of the scan
+// Pixel table and the arrival time
 
 // rows [0, n_rows): the pixels [0, n_pix), then padding rows (all zero, not usable) up to the end
 // of the last tile, whose arrival times stay finite
@@ -225,9 +212,8 @@ struct ScanVals {
 // Arrival time of one (sample, pixel) in scan mode MODE from the record values v and the pixel
 // constants P: far field tau = d + b; polynomial records tau = sum_j c_j b^j (c_DEG = cK; up to
 // j = LOW in kModeRecLow); else
-// arrival_tau in the pixel's form (series where rb2 |x_m|^-2 <= kSeriesBound).  Both orientations
-// (lanes over pixels, v uniform; lanes over samples, P uniform) run these same operations, so a
-// (sample, pixel) gets the same bits wherever it is evaluated.
+// arrival_tau in the pixel's form (series where rb2 |x_m|^-2 <= kSeriesBound).  A (sample, pixel)
+// gets the same bits wherever it is evaluated.
 template <int GEOM, bool F64, int MODE>
 __device__ __forceinline__ double tau_eval(const PixC &P, const double *v, double cK, double rb2, double C)
 {
@@ -252,37 +238,6 @@ __device__ __forceinline__ double tau_eval(const PixC &P, const double *v, doubl
         const double x = v[0], y = v[1], z = v[2], rr = sq3(x, y, z);
         if (rb2 * (P.g.invD * P.g.invD) <= kSeriesBound) return arrival_tau<GEOM, FORM>(P, v[3], x, y, z, rr, C);
         return arrival_tau<GEOM, kTauSqrt>(P, v[3], x, y, z, rr, C);
-    }
-}
-
-// tau_eval of NB records at one pixel: with polynomial records the operations of each record are
-// tau_eval's, in its order, interleaved across the records, so that a wavefront has NB
-// independent chains to issue from instead of one dependent chain at a time (same bits)
-template <int GEOM, bool F64, int MODE, int NB, int N>
-__device__ __forceinline__ void tau_eval_block(const PixC &P, const double (*R)[N], double cK, double rb2, double C,
-                                               double *t)
-{
-    if constexpr (MODE == kModeRec3 || MODE == kModeRec5 || MODE == kModeRecLow) {
-        constexpr int DEG = RecLayout<GEOM, F64>::DEG, LOW = RecLayout<GEOM, F64>::LOW;
-        double b[NB];
-#pragma unroll
-        for (int c = 0; c < NB; ++c) b[c] = P.o * R[c][DEG + 2];
-#pragma unroll
-        for (int c = 0; c < NB; ++c) b[c] = fma(P.px, R[c][DEG], b[c]);
-#pragma unroll
-        for (int c = 0; c < NB; ++c) b[c] = fma(P.py, R[c][DEG + 1], b[c]);
-        // the highest power: cK, or c_LOW in kModeRecLow
-        constexpr int TOP = MODE == kModeRecLow ? LOW - 1 : DEG - 1;
-#pragma unroll
-        for (int c = 0; c < NB; ++c) t[c] = MODE == kModeRecLow ? fma(b[c], R[c][LOW], R[c][LOW > 0 ? LOW - 1 : 0])
-                                                               : fma(b[c], cK, R[c][DEG - 1]);
-#pragma unroll
-        for (int j = TOP - 1; j >= 0; --j)
-#pragma unroll
-            for (int c = 0; c < NB; ++c) t[c] = fma(b[c], t[c], R[c][j]);
-    } else {
-#pragma unroll
-        for (int c = 0; c < NB; ++c) t[c] = tau_eval<GEOM, F64, MODE>(P, R[c], cK, rb2, C);
     }
 }
 
@@ -325,7 +280,7 @@ DepWs carve(void *ws, int64_t n_p)
 template <int GEOM, int DEG>
 __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, const double *__restrict__ beta,
                                                  const double *__restrict__ beta_dot,
-                                                 const double *__restrict__ x_det, int64_t n_samples,
+                                                 const double *__restrict__ x_det, int64_t n_samples, int chunk,
                                                  int64_t sample0, double t_start, double dt, double t0,
                                                  double dt_obs, double C, double *__restrict__ rec,
                                                  int *__restrict__ pflag, unsigned long long *__restrict__ rmax2)
@@ -334,8 +289,8 @@ __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, c
     __shared__ unsigned long long s_max[4];
     __shared__ int s_bad[4];
     const int64_t k = blockIdx.x;
-    const int64_t i_begin = (int64_t)blockIdx.y * kPrepassChunk;
-    const int64_t i_end = std::min<int64_t>(i_begin + kPrepassChunk, n_samples);
+    const int64_t i_begin = (int64_t)blockIdx.y * chunk;
+    const int64_t i_end = std::min<int64_t>(i_begin + chunk, n_samples);
     const double cdt_step = kC * dt;
     const double Dref = pix_geo(x_det, 0).D;  // the records' pixel distance
     double mx = 0.0;
@@ -411,6 +366,31 @@ struct DepShape {
     int fmask;
 };
 
+// contribution v to element j of the trace, row `row` (the row only matters in kAccFixed; the
+// order-independent modes are FP64 only)
+template <int ACC, typename T>
+__device__ __forceinline__ void put(T *E, const DetAcc &det, size_t j, size_t row, T v)
+{
+    if constexpr (ACC == kAccFloat) {
+        atomic_add(E + j, v);
+    } else if constexpr (ACC == kAccMaxAbs) {
+        atomicMax((unsigned long long *)E + j, (unsigned long long)__double_as_longlong(fabs(v)));
+    } else {
+        // |v * scale| < 2^62 by the choice of scale, and any term below 2^63 is taken, so a
+        // last-bit difference between the two passes' v cannot drop one (a NaN scale drops
+        // all: the row is NaN in the result).  The sign-extended term is added to the 128-bit
+        // sum as its low word and, with the carry out of the low word, its high word.
+        const double t = v * det.scale[row];
+        const long long n = fabs(t) < 0x1p63 ? (long long)__builtin_rint(t) : 0ll;
+        if (n != 0) {
+            const unsigned long long un = (unsigned long long)n;
+            const unsigned long long old = atomicAdd((unsigned long long *)E + j, un);
+            const long long dh = (n < 0 ? -1ll : 0ll) + (old + un < old ? 1ll : 0ll);
+            if (dh != 0) atomicAdd(det.hi + j, (unsigned long long)dh);
+        }
+    }
+}
+
 // Per-wavefront state of the careful path (k_careful): lanes own pixels (kPPL each); a particle's
 // samples are taken one at a time, with the skip rules applied per interval; crossings are queued
 // in LDS and drained 64 at a time, each lane adding one interval's grid points to the trace with
@@ -437,28 +417,6 @@ struct Wave {
     DetAcc det;        // high words and row scales (ACC == kAccFixed)
 
     __device__ __forceinline__ static uint32_t qwrap(uint32_t v) { return v >= kQCap ? v - kQCap : v; }
-
-    // contribution v to element j of the trace, in the order-independent modes (FP64 only)
-    __device__ __forceinline__ void put_det(size_t j, size_t row, double v) const
-    {
-        unsigned long long *lo = (unsigned long long *)E + j;
-        if (ACC == kAccMaxAbs) {
-            atomicMax(lo, (unsigned long long)__double_as_longlong(fabs(v)));
-        } else {
-            // |v * scale| < 2^62 by the choice of scale, and any term below 2^63 is taken, so a
-            // last-bit difference between the two passes' v cannot drop one (a NaN scale drops
-            // all: the row is NaN in the result).  The sign-extended term is added to the 128-bit
-            // sum as its low word and, with the carry out of the low word, its high word.
-            const double t = v * det.scale[row];
-            const long long n = fabs(t) < 0x1p63 ? (long long)__builtin_rint(t) : 0ll;
-            if (n != 0) {
-                const unsigned long long un = (unsigned long long)n;
-                const unsigned long long old = atomicAdd(lo, un);
-                const long long dh = (n < 0 ? -1ll : 0ll) + (old + un < old ? 1ll : 0ll);
-                if (dh != 0) atomicAdd(det.hi + j, (unsigned long long)dh);
-            }
-        }
-    }
 
     using Lay = RecLayout<GEOM, sizeof(T) == 8>;
     // the part of a record a scan mode reads: offset and count of doubles
@@ -534,19 +492,12 @@ struct Wave {
             // interpolation weight w = (u - ta)/(tb - ta), in the precision of the trace
             idt = sizeof(T) == 4 ? (T)__builtin_amdgcn_rcpf((float)(tb - ta)) : (T)(1.0 / (tb - ta));
             if (u1 - u0 <= kLongRun) {
-                T *Em = E + (size_t)m * 3 * sh.n_obs;
                 for (int u = u0; u < u1; ++u) {
                     const T w = (T)((double)u - ta) * idt, w1 = (T)1 - w;
-                    if constexpr (ACC == kAccFloat) {
-                        atomic_add(Em + u, w1 * eax + w * ebx);
-                        atomic_add(Em + sh.n_obs + u, w1 * eay + w * eby);
-                        atomic_add(Em + 2 * sh.n_obs + u, w1 * eaz + w * ebz);
-                    } else {
-                        const size_t row = (size_t)m * 3, j = row * sh.n_obs + u;
-                        put_det(j, row, w1 * eax + w * ebx);
-                        put_det(j + sh.n_obs, row + 1, w1 * eay + w * eby);
-                        put_det(j + 2 * sh.n_obs, row + 2, w1 * eaz + w * ebz);
-                    }
+                    const size_t row = (size_t)m * 3, j = row * sh.n_obs + u;
+                    put<ACC>(E, det, j, row, w1 * eax + w * ebx);
+                    put<ACC>(E, det, j + sh.n_obs, row + 1, w1 * eay + w * eby);
+                    put<ACC>(E, det, j + 2 * sh.n_obs, row + 2, w1 * eaz + w * ebz);
                 }
             }
         }
@@ -562,20 +513,13 @@ struct Wave {
             const T sidt = readlane_t(idt, src);
             const T sax = readlane_t(eax, src), say = readlane_t(eay, src), saz = readlane_t(eaz, src);
             const T sbx = readlane_t(ebx, src), sby = readlane_t(eby, src), sbz = readlane_t(ebz, src);
-            T *Em = E + (size_t)(tile * kTilePix + sml) * 3 * sh.n_obs;
             // 64-bit index: su1 may sit within 64 of the largest int (n_obs up to 2^31 - 1)
             for (int64_t u = (int64_t)su0 + lane; u < su1; u += 64) {
                 const T w = (T)((double)u - sta) * sidt, w1 = (T)1 - w;
-                if constexpr (ACC == kAccFloat) {
-                    atomic_add(Em + u, w1 * sax + w * sbx);
-                    atomic_add(Em + sh.n_obs + u, w1 * say + w * sby);
-                    atomic_add(Em + 2 * sh.n_obs + u, w1 * saz + w * sbz);
-                } else {
-                    const size_t row = (size_t)(tile * kTilePix + sml) * 3, j = row * sh.n_obs + u;
-                    put_det(j, row, w1 * sax + w * sbx);
-                    put_det(j + sh.n_obs, row + 1, w1 * say + w * sby);
-                    put_det(j + 2 * sh.n_obs, row + 2, w1 * saz + w * sbz);
-                }
+                const size_t row = (size_t)(tile * kTilePix + sml) * 3, j = row * sh.n_obs + u;
+                put<ACC>(E, det, j, row, w1 * sax + w * sbx);
+                put<ACC>(E, det, j + sh.n_obs, row + 1, w1 * say + w * sby);
+                put<ACC>(E, det, j + 2 * sh.n_obs, row + 2, w1 * saz + w * sbz);
             }
         }
         // the entries are read: later pushes may take their slots
@@ -676,7 +620,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 {
     constexpr bool kF64 = sizeof(T) == 8;
     constexpr int kRec = kF64 ? kModeRec5 : kModeRec3;
-    // block -> (particle group, tile) as in k_scan
+    // block -> (particle group, tile) as in k_sweep
     const int64_t b = blockIdx.x;
     const int64_t xcd = b & 7, slot = b >> 3;
     const int64_t grp = (slot / sh.n_tiles) * 8 + xcd;
@@ -748,7 +692,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 
     unsigned long long c0 = 0, c1 = 0, c2 = 0, c3 = 0;
     for (int64_t k = k0; k < k1; ++k) {
-        if (pflag[k] == 0) continue;  // fast path: k_scan
+        if (pflag[k] == 0) continue;  // fast path: k_sweep
         // series forms where |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory (the max over the
         // whole trajectory when given, else over the samples of this call), decided per pixel
         w.rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
@@ -775,330 +719,479 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fast path.  Lanes over samples: lane j of chunk q holds sample 63 q + j (chunks share their
-// boundary sample, so interval (63 q + j - 1, 63 q + j] has both ends in chunk q for j >= 1).
+// Fast path.  A block owns a tile of kTilePix pixels and a group of particles (and, where there are
+// few of those, a segment of the samples).  For each particle:
+//   * a mask of the steps (kStep samples, kStep - 1 intervals; neighbouring steps share a sample)
+//     that hold window grid points for some pixel of the tile, from the arrival times at the steps'
+//     boundaries alone, lanes over pixels (arrival times increase on this path);
+//   * per such step the samples are staged in LDS (the record's scan values, beta, 1/|beta|,
+//     beta_dot) and every pixel's grid points in the step counted;
+//   * sparse steps (deposit_points): lanes over the step's (pixel, grid point) pairs.  A lane finds
+//     the interval of its grid point (bracket from the pixel's arrival times at five samples, then
+//     three-point interpolation), evaluates the field at its two ends and adds the interpolated
+//     value to the trace;
+//   * dense steps (deposit_dense; at least kDensePoints grid points per interval): per pixel, lanes
+//     over samples form every arrival time and field of the step in LDS, then lanes over grid
+//     points interpolate.
+// The interval found is the one with tau_{i-1} < u <= tau_i whichever way it is found, and the
+// contribution's arithmetic is the same in both, so a contribution has the same bits.
+constexpr int kStep = 256;      // samples per step, one per thread of the block
+constexpr int kSteps = 64;      // steps per mask
+// grid points per interval of the step's live pixels from which a step is dense
+constexpr float kDensePoints = 0.6f;
 
-template <typename T, int GEOM, int ACC = kAccFloat>
-struct ScanWave {
+template <typename T, int GEOM>
+struct SweepLds {
+    using Lay = RecLayout<GEOM, sizeof(T) == 8>;
+    static constexpr int NP = GEOM == LW_GEOM_FARFIELD ? 2 : (Lay::DEG + 3) / 2;  // pairs of scan values
+    static constexpr int PX = GEOM == LW_GEOM_FARFIELD ? 8 : 6;  // doubles per pixel: o, px, py, then x_m or n, 1/|x_m|
+    double2 rec[NP][kStep];
+    double2 be[2][kStep];  // beta_x, beta_y; beta_z, 1/|beta| (0 at rest)
+    T acc[3][kStep];       // beta_dot
+    double2 px[kTilePix][PX / 2];
+    double tl[kTilePix], th[kTilePix];  // a pixel's arrival times at the step's first and last sample
+    union {
+        double node[3][kTilePix];  // and at a quarter, half and three quarters of it
+        T e[3][kStep];             // dense steps: one pixel's fields
+    };
+    double tau[kStep];  // dense steps: one pixel's arrival times
+    int cum[kTilePix];  // grid points of the tile half's pixels before this one
+    int tot[2];
+    uint64_t live[2];  // pixels with grid points in the step
+    uint64_t mask[4];
+    unsigned long long red[4];
+};
+
+template <typename T, int GEOM, int ACC>
+struct Sweep {
     static constexpr bool F64 = sizeof(T) == 8;
+    using Lds = SweepLds<T, GEOM>;
     using Lay = RecLayout<GEOM, F64>;
-    // chunks per block: three. With double-precision fields (degree-5 records) this leaves a few
-    // values that live through the whole kernel in scratch (36 bytes, reloaded once per particle);
-    // still faster than two chunks: 1124 against 1141 ms on 1e4 electrons of the precision workload
-    static constexpr int NB = 3;
-    Wave<T, GEOM, ACC> d;  // queue and drain (shared with the careful path)
-    double *pcl;           // LDS: o, px, py, g of the tile's pixels, [kTilePix + 1][4] (one padding row);
-                           // g: the pixel's next grid point above the arrival times scanned so far
-    uint64_t okmask[kPPL]; // pixels 64 h + l of the tile that take part (in the pass, geometry ok)
+    Lds &s;
+    const double *__restrict__ pt;  // the tile's rows of the pixel table
+    T *__restrict__ E;              // the tile's first trace row
+    const DepShape &sh;
+    DetAcc det;  // from the tile's first trace row
+    double cK, rb2, q;
+    int tid;
 
-    // Issue the loads of the records of chunks q .. q + NB - 1 (lane = sample) into R; valid[c]
-    // is false for samples past the last one and chunks past the last one (q + c >= nq), whose
-    // constant term the caller sets to -inf once the loads are in (mask_block), so that the loads
-    // can stay in flight meanwhile.
+    // a pixel's constants in the arrival time of MODE
     template <int MODE>
-    __device__ __forceinline__ void load_block(const double *rk, int q, int nq, double (*R)[ScanVals<GEOM, F64, MODE>::N],
-                                               bool *valid, bool use_first, const double (&first)[NB]) const
+    __device__ __forceinline__ PixC pixel(int p) const
     {
-        using SV = ScanVals<GEOM, F64, MODE>;
-        const int ns = (int)d.sh.n_samples;
+        if constexpr (MODE == kModeMixed) return pixc_row(pt + (size_t)p * kPT);
+        PixC P;
+        const double2 a = s.px[p][0];
+        P.o = a.x;
+        P.px = a.y;
+        P.py = s.px[p][1].x;
+        return P;
+    }
+    // arrival time of staged sample j at a pixel; v: its scan values
+    template <int MODE>
+    __device__ __forceinline__ double tau_at(const PixC &P, int j, double *v) const
+    {
 #pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            const int s = 63 * (q + c) + d.lane;
-            valid[c] = s < ns && q + c < nq;
-            const double *src = rk + (size_t)(valid[c] ? s : ns - 1) * Lay::W;
-            R[c][0] = use_first ? first[c] : src[0];
+        for (int c = 0; c < Lds::NP; ++c) {
+            if (2 * c >= ScanVals<GEOM, F64, MODE>::N) break;
+            const double2 d = s.rec[c][j];
+            v[2 * c] = d.x;
+            v[2 * c + 1] = d.y;
+        }
+        return tau_eval<GEOM, F64, MODE>(P, v, cK, rb2, sh.C);
+    }
+    template <int MODE>
+    __device__ __forceinline__ double tau_at(const PixC &P, int j) const
+    {
+        double v[2 * Lds::NP];
+        return tau_at<MODE>(P, j, v);
+    }
+    // field of staged sample j at pixel p
+    template <int MODE>
+    __device__ __forceinline__ void field_at(int p, int j, T &ex, T &ey, T &ez) const
+    {
+        constexpr int X = ScanVals<GEOM, F64, MODE>::X;
+        double v[2 * Lds::NP];
 #pragma unroll
-            for (int v = 1; v < SV::N; ++v) R[c][v] = src[v];
+        for (int c = X / 2; c <= (X + 2) / 2; ++c) {
+            const double2 d = s.rec[c][j];
+            v[2 * c] = d.x;
+            v[2 * c + 1] = d.y;
+        }
+        const double2 b01 = s.be[0][j], b23 = s.be[1][j];
+        const double2 g1 = s.px[p][1], g2 = s.px[p][2];
+        const double xm[3] = {g1.y, g2.x, g2.y};
+        PixGeo g;
+        g.nx = g1.y;
+        g.ny = g2.x;
+        g.nz = g2.y;
+        if constexpr (GEOM == LW_GEOM_FARFIELD) g.invD = s.px[p][3].x;
+        lw_field_ib<T, GEOM>(g, xm, v[X], v[X + 1], v[X + 2], b01.x, b01.y, b23.x, b23.y, s.acc[0][j], s.acc[1][j],
+                             s.acc[2][j], q, sh.fmask, ex, ey, ez);
+    }
+    __device__ __forceinline__ void add(int p, int64_t u, T w, const T *a, const T *b) const
+    {
+        const T w1 = (T)1 - w;
+        const size_t j = (size_t)p * 3 * (size_t)sh.n_obs + (size_t)u;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            put<ACC>(E, det, j + (size_t)c * (size_t)sh.n_obs, 3 * p + c, w1 * a[c] + w * b[c]);
+    }
+    __device__ __forceinline__ static T inverse(double dt)  // 1/(tau_i - tau_{i-1})
+    {
+        return F64 ? (T)(1.0 / dt) : (T)__builtin_amdgcn_rcpf((float)dt);
+    }
+
+    // Stage samples i0 .. i0 + n of a particle (rk: its records' scan values, bk, dk: its beta, beta_dot)
+    template <int MODE>
+    __device__ __forceinline__ void stage(const double *rk, const double *bk, const double *dk, int64_t i0, int n) const
+    {
+        if (tid > n) return;
+        const int64_t i = i0 + tid;
+        const double *src = rk + (size_t)i * Lay::W;
+#pragma unroll
+        for (int c = 0; c < Lds::NP; ++c)
+            if (2 * c < ScanVals<GEOM, F64, MODE>::N) s.rec[c][tid] = make_double2(src[2 * c], src[2 * c + 1]);
+        const double bx = bk[3 * i], by = bk[3 * i + 1], bz = bk[3 * i + 2];
+        s.be[0][tid] = make_double2(bx, by);
+        s.be[1][tid] = make_double2(bz, inv_beta<T>(bx, by, bz));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s.acc[c][tid] = (T)dk[3 * i + c];
+    }
+
+    // The step's (pixel, grid point) pairs, one per lane
+    template <int MODE>
+    __device__ __forceinline__ void deposit_points(int n, int tot0, int total) const
+    {
+        const double nob = (double)sh.n_obs;
+        const int q1 = n >> 2, q2 = n >> 1, q3 = (3 * n) >> 2;
+        for (int it = tid; it < total; it += kStep) {
+            int p = it >= tot0 ? 64 : 0;
+            const int r = it >= tot0 ? it - tot0 : it;
+#pragma unroll
+            for (int b = 32; b > 0; b >>= 1)
+                if (s.cum[p + b] <= r) p += b;
+            const PixC P = pixel<MODE>(p);
+            double ta = s.tl[p], tb = s.th[p];
+            const int u = (int)grid_count(ta, nob) + (r - s.cum[p]);
+            const double ud = (double)u;
+            // the quarter of the step that holds the crossing
+            int lo = 0, hi = n;
+            const double m2 = s.node[1][p];
+            const bool up = ud > m2;
+            const double m13 = s.node[up ? 2 : 0][p];
+            const int q13 = up ? q3 : q1;
+            if (up) {
+                lo = q2;
+                ta = m2;
+            } else {
+                hi = q2;
+                tb = m2;
+            }
+            if (ud > m13) {
+                lo = q13;
+                ta = m13;
+            } else {
+                hi = q13;
+                tb = m13;
+            }
+            float ya = (float)(ta - ud), yb = (float)(tb - ud);  // ya < 0 <= yb
+            int g = lo + (int)rintf((float)(hi - lo) * (-ya * __builtin_amdgcn_rcpf(yb - ya)));
+            for (int k = 0; hi - lo > 1; ++k) {
+                g = min(max(g, lo + 1), hi - 1);
+                const double tg = tau_at<MODE>(P, g);
+                const float yg = (float)(tg - ud), fl = (float)(g - lo), fr = (float)(hi - g);
+                // slope at g of the parabola through the bracket's ends and g
+                const float d = ((yg - ya) * fr * __builtin_amdgcn_rcpf(fl) + (yb - yg) * fl * __builtin_amdgcn_rcpf(fr)) *
+                                __builtin_amdgcn_rcpf(fl + fr);
+                const float x = (float)g - yg * __builtin_amdgcn_rcpf(d);
+                if (tg >= ud) {
+                    hi = g;
+                    tb = tg;
+                    yb = yg;
+                    g = (int)floorf(x);
+                } else {
+                    lo = g;
+                    ta = tg;
+                    ya = yg;
+                    g = (int)ceilf(x);
+                }
+                if (k >= 4) g = (lo + hi) >> 1;
+            }
+            T a[3], b[3];
+            field_at<MODE>(p, lo, a[0], a[1], a[2]);
+            field_at<MODE>(p, hi, b[0], b[1], b[2]);
+            add(p, u, (T)(ud - ta) * inverse(tb - ta), a, b);
         }
     }
-    // The first scan value of each record of chunks q .. q + NB - 1, loaded one block ahead: it
-    // brings the records' cache lines in while the current block is scanned (the rest of each
-    // record is loaded at the block's start, from the cache).
-    template <int MODE>
-    __device__ __forceinline__ void touch_block(const double *rk, int q, double (&first)[NB]) const
-    {
-        const int ns = (int)d.sh.n_samples;
-#pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            const int s = std::min(63 * (q + c) + d.lane, ns - 1);
-            first[c] = rk[(size_t)s * Lay::W];
-        }
-    }
-    template <int MODE>
-    __device__ __forceinline__ static void mask_block(double (*R)[ScanVals<GEOM, F64, MODE>::N], const bool *valid)
-    {
-#pragma unroll
-        for (int c = 0; c < NB; ++c)
-            if (!valid[c]) R[c][ScanVals<GEOM, F64, MODE>::LEAD] = -INFINITY;
-    }
 
-    // Crossings of pixel p (tile-local) in the chunks of a block that reached its next grid point:
-    // the intervals that hold grid points of the window are queued with their two arrival times
-    // (the field and the deposit follow in the drain, 64 intervals at a time).
-    __device__ __forceinline__ void crossings(int64_t k, int q0, int nq, int p, const double *t)
+    // Every pixel's intervals of the step, one pixel at a time
+    template <int MODE>
+    __device__ __forceinline__ void deposit_dense(int n) const
     {
-        const int ns = (int)d.sh.n_samples;
-        const double nob2 = (double)d.sh.n_obs - 2.0;
-        const uint32_t tag = ((uint32_t)(k - d.k0) << kPixBits) | (uint32_t)p;
-#pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            if (q0 + c >= nq) break;
-            const int s = 63 * (q0 + c) + d.lane;
-            const bool iv = d.lane >= 1 && s < ns;  // this lane ends an interval
-            const double tb = t[c];
-            const double ta = lane_shift_up(tb);
-            // arrival times increase on the fast path: the interval holds grid points iff the
-            // count of window grid points up to its end, clamp(floor(t) + 1, 0, n_obs), exceeds
-            // that up to its start; with ta <= tb that is floor(tb) > floor(ta), floor(tb) >= 0
-            // and floor(ta) <= n_obs - 2
-            const double fb = floor(tb), fa = lane_shift_up(fb);
-            const bool hit = iv && fb > fa && fb >= 0.0 && fa <= nob2;
-            const uint64_t mask = __ballot(hit);
-            if (mask) {
-                d.push(hit, mask, (uint32_t)s, tag, ta, tb);
-                d.pump();
+        const double nob = (double)sh.n_obs;
+        uint64_t left[2] = {s.live[0], s.live[1]};
+        while (left[0] | left[1]) {  // the same in every thread
+            const int h = left[0] ? 0 : 1, p = 64 * h + (int)__builtin_ctzll(left[h]);
+            left[h] &= left[h] - 1;
+            const int64_t u0 = grid_count(s.tl[p], nob), u1 = grid_count(s.th[p], nob);
+            __syncthreads();  // the previous pixel's fields are read
+            if (tid <= n) {
+                s.tau[tid] = tau_at<MODE>(pixel<MODE>(p), tid);
+                T x, y, z;
+                field_at<MODE>(p, tid, x, y, z);
+                s.e[0][tid] = x;
+                s.e[1][tid] = y;
+                s.e[2][tid] = z;
+            }
+            __syncthreads();
+            for (int64_t u = u0 + tid; u < u1; u += kStep) {
+                const double ud = (double)u;
+                int lo = 0, hi = n;
+                double ta = s.tau[0], tb = s.tau[n];
+                for (int k = 0; hi - lo > 1; ++k) {
+                    int g = lo + (int)((float)(hi - lo) * ((float)(ud - ta) * __builtin_amdgcn_rcpf((float)(tb - ta))));
+                    g = (k & 3) == 3 ? (lo + hi) >> 1 : min(max(g, lo + 1), hi - 1);
+                    const double tg = s.tau[g];
+                    if (tg >= ud) {
+                        hi = g;
+                        tb = tg;
+                    } else {
+                        lo = g;
+                        ta = tg;
+                    }
+                }
+                const T a[3] = {s.e[0][lo], s.e[1][lo], s.e[2][lo]}, b[3] = {s.e[0][hi], s.e[1][hi], s.e[2][hi]};
+                add(p, u, (T)(ud - ta) * inverse(tb - ta), a, b);
             }
         }
     }
 
-    // Scan of a fast-path particle over all its intervals (each pixel's next grid point is in pcl)
+    // One particle's steps [st0, st1) (the same in every thread): rk, bk, dk as in stage
     template <int MODE>
-    __device__ __forceinline__ void scan(int64_t k, const double *rk)
+    __device__ __forceinline__ void particle(const double *rk, const double *bk, const double *dk, int st0, int st1,
+                                             bool lane_ok) const
     {
-        using SV = ScanVals<GEOM, F64, MODE>;
-        constexpr int NV = SV::N;
-        const int ns = (int)d.sh.n_samples;
-        const int nq = (ns - 1 + 62) / 63;  // chunks (ns >= 2)
-        const double nob = (double)d.sh.n_obs;
-        double R[NB][NV], first[NB] = {};
-        bool vr[NB];
-        for (int q0 = 0; q0 < nq; q0 += NB) {
-            // this block's records, all in before the pixel loop, so that no wait inside it also
-            // waits for the drain's atomics; the next block's first values are loaded meanwhile
-            // (a whole prefetched block would take registers that cost a wavefront per SIMD)
-            load_block<MODE>(rk, q0, nq, R, vr, q0 > 0, first);
-            mask_block<MODE>(R, vr);
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-            if (q0 + NB < nq) touch_block<MODE>(rk, q0 + NB, first);
-            // the block's last sample: chunk c_last, lane l_last (uniform)
-            const int s_last = std::min(63 * (q0 + NB), ns - 1);
-            const int c_last = (s_last - 1) / 63 - q0;
-            const int l_last = s_last - 63 * (q0 + c_last);
-            // every pixel of the tile: one that takes no part (past the pass's last pixel, or its
-            // geometry not usable) has next grid point +inf, so its arrival times never reach it
+        const int ns = (int)sh.n_samples;
+        const double nob = (double)sh.n_obs;
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int p = tid & (kTilePix - 1);
+        for (int c0 = st0; c0 < st1; c0 += kSteps) {
+            // steps of this chunk with window grid points at some pixel: wavefronts 0, 1 (pixels) take
+            // the first half of the steps, 2, 3 the second
+            const int c1 = min(c0 + kSteps, st1), mid = c0 + (c1 - c0 + 1) / 2;
+            const int a = wv < 2 ? c0 : mid, b = wv < 2 ? mid : c1;
+            uint64_t mask = 0;
+            if (a < b) {
+                const PixC P = pixel<MODE>(p);
+                auto count = [&](int st) {  // window grid points up to the first sample of step st
+                    const int64_t i = min((int64_t)st * (kStep - 1), (int64_t)ns - 1);
+                    const cdptr src = uniform_ptr(rk + (size_t)i * Lay::W);
+                    double v[2 * Lds::NP];
 #pragma unroll
-            for (int h = 0; h < kPPL; ++h) {
-                cdptr row = uniform_ptr(d.pt + (size_t)(d.tile * kTilePix + 64 * h) * kPT);
-                // o, px, py, g of the next pixel, read from LDS one iteration ahead (the same address
-                // in every lane; one padding row past the tile's last pixel)
-                double no = pcl[4 * (64 * h)], npx = pcl[4 * (64 * h) + 1], npy = pcl[4 * (64 * h) + 2],
-                       ng = pcl[4 * (64 * h) + 3];
-#pragma unroll 2
-                for (int l = 0; l < 64; ++l, row += kPT) {
-                    const int p = 64 * h + l;
-                    PixC P;
-                    const double g = ng;
-                    if constexpr (MODE == kModeMixed) {
-                        P = pixc_row(row);  // the whole geometry, scalar loads
-                    } else {
-                        P.o = no;
-                        P.px = npx;
-                        P.py = npy;
-                        no = pcl[4 * (p + 1)];
-                        npx = pcl[4 * (p + 1) + 1];
-                        npy = pcl[4 * (p + 1) + 2];
-                    }
-                    ng = pcl[4 * (p + 1) + 3];
-                    double t[NB];
-                    tau_eval_block<GEOM, F64, MODE, NB>(P, R, d.cK, d.rb2, d.sh.C, t);
-                    uint64_t any = 0;
-#pragma unroll
-                    for (int c = 0; c < NB; ++c) any |= __ballot(t[c] >= g);
-                    if (__builtin_expect(any != 0, 0)) {  // rare: keep the scan's path straight
-                        crossings(k, q0, nq, p, t);
-                        double tl = t[0];
-#pragma unroll
-                        for (int c = 1; c < NB; ++c)
-                            if (c_last == c) tl = t[c];
-                        const double gn = next_grid(readlane_double(tl, l_last), nob);
-                        if (d.lane == 0) pcl[4 * p + 3] = gn;
+                    for (int c = 0; c < ScanVals<GEOM, F64, MODE>::N; ++c) v[c] = src[c];
+                    return grid_count(tau_eval<GEOM, F64, MODE>(P, v, cK, rb2, sh.C), nob);
+                };
+                int64_t prev = count(a);
+                if (__ballot(lane_ok && count(b) != prev) != 0) {
+                    for (int st = a; st < b; ++st) {
+                        const int64_t next = count(st + 1);
+                        if (__ballot(lane_ok && next != prev) != 0) mask |= 1ull << (st - c0);
+                        prev = next;
                     }
                 }
             }
-        }
-    }
-
-    // One fast-path particle: first and last arrival times per pixel (lanes over pixels), the
-    // culling test (LW_CULL), the scan, and the counters, which follow from the two end points.
-    template <int MODE, bool CULL>
-    __device__ __forceinline__ void particle(int64_t k, const bool *pix_in, unsigned long long &c1,
-                                             unsigned long long &c2, unsigned long long &c3)
-    {
-        using SV = ScanVals<GEOM, F64, MODE>;
-        constexpr int NV = SV::N;
-        const int ns = (int)d.sh.n_samples;
-        const double nob = (double)d.sh.n_obs;
-        const double *rk = d.rec + (size_t)k * d.sh.n_samples * Lay::W + SV::OFF;
-        double tau0[kPPL], taul[kPPL];
-        bool lane_ok[kPPL];
-        {
-            const cdptr a = uniform_ptr(rk), b = uniform_ptr(rk + (size_t)(ns - 1) * Lay::W);
-            double v0[NV], v1[NV];
+            __syncthreads();  // the previous chunk's masks are read
+            if (lane == 0) s.mask[wv] = mask;
+            __syncthreads();
+            mask = s.mask[0] | s.mask[1] | s.mask[2] | s.mask[3];
+            while (mask) {
+                const int st = c0 + (int)__builtin_ctzll(mask);
+                mask &= mask - 1;
+                const int64_t i0 = (int64_t)st * (kStep - 1);
+                const int n = (int)min((int64_t)(kStep - 1), (int64_t)ns - 1 - i0);  // intervals
+                stage<MODE>(rk, bk, dk, i0, n);
+                __syncthreads();
+                if (tid < kTilePix) {
+                    double tl = 0.0, th = 0.0;
+                    if (lane_ok) {
+                        const PixC P = pixel<MODE>(p);
+                        tl = tau_at<MODE>(P, 0);
+                        th = tau_at<MODE>(P, n);
+                    }
+                    s.tl[p] = tl;
+                    s.th[p] = th;
+                    // counts above 2^20 make the step dense, where they are not used
+                    const int cnt = (int)min(grid_count(th, nob) - grid_count(tl, nob), (int64_t)1 << 20);
+                    int sum = cnt;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                v0[v] = a[v];
-                v1[v] = b[v];
+                    for (int off = 1; off < 64; off <<= 1) {
+                        const int o = __shfl_up(sum, off);
+                        if (lane >= off) sum += o;
+                    }
+                    s.cum[p] = sum - cnt;
+                    const uint64_t live = __ballot(cnt > 0);
+                    if (lane == 63) {
+                        s.tot[wv] = sum;
+                        s.live[wv] = live;
+                    }
+                } else {
+                    const PixC P = pixel<MODE>(p);
+                    s.node[0][p] = tau_at<MODE>(P, n >> 2);
+                    s.node[1][p] = tau_at<MODE>(P, n >> 1);
+                    s.node[2][p] = tau_at<MODE>(P, (3 * n) >> 2);
+                }
+                __syncthreads();
+                const int tot0 = s.tot[0], total = tot0 + s.tot[1];
+                if ((float)total >= kDensePoints * (float)((__popcll(s.live[0]) + __popcll(s.live[1])) * n))
+                    deposit_dense<MODE>(n);
+                else
+                    deposit_points<MODE>(n, tot0, total);
+                __syncthreads();  // the step is read
             }
-            // this lane's pixel constants, read again per particle (not held through the scan)
-            const double *ptl = d.pt;
-            asm volatile("" : "+s"(ptl));
-#pragma unroll
-            for (int h = 0; h < kPPL; ++h) {
-                const PixC pc = pixc_row(ptl + (size_t)(d.tile * kTilePix + 64 * h + d.lane) * kPT);
-                lane_ok[h] = (okmask[h] >> d.lane) & 1ull;
-                tau0[h] = tau_eval<GEOM, F64, MODE>(pc, v0, d.cK, d.rb2, d.sh.C);
-                taul[h] = tau_eval<GEOM, F64, MODE>(pc, v1, d.cK, d.rb2, d.sh.C);
-            }
-        }
-        bool skip = false;
-        if (CULL) {
-            bool in = false;
-#pragma unroll
-            for (int h = 0; h < kPPL; ++h) in |= lane_ok[h] && grid_count(taul[h], nob) > grid_count(tau0[h], nob);
-            skip = __ballot(in) == 0;
-        }
-        // the counters (taken before the scan, so that the end points are not held through it)
-#pragma unroll
-        for (int h = 0; h < kPPL; ++h) {
-            if (lane_ok[h]) {
-                const int64_t inside = grid_count(taul[h], nob) - grid_count(tau0[h], nob);
-                c3 += (unsigned long long)inside;
-                c2 += (unsigned long long)((int64_t)(floor(taul[h]) - floor(tau0[h])) - inside);
-            } else if (pix_in[h]) {
-                c1 += (unsigned long long)(ns - 1);
-            }
-        }
-        if (!skip && ns >= 2) {
-#pragma unroll
-            for (int h = 0; h < kPPL; ++h) pcl[4 * (64 * h + d.lane) + 3] = lane_ok[h] ? next_grid(tau0[h], nob) : INFINITY;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            scan<MODE>(k, rk);
         }
     }
 };
 
-template <typename T, int GEOM, bool CULL, int ACC>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_scan(
-    const double *__restrict__ r, const double *__restrict__ beta, const double *__restrict__ beta_dot,
-    const double *__restrict__ charge, const double *__restrict__ x_det, const double *__restrict__ rec,
-    const double *__restrict__ pt, const int *__restrict__ pflag, const unsigned long long *__restrict__ rmax2,
-    const double *__restrict__ rbound2, T *__restrict__ E, unsigned long long *__restrict__ diag, DepShape sh, DetAcc det)
+// segments of the samples, in steps
+struct SweepShape {
+    int n_seg, per_seg, n_steps;
+};
+
+template <typename T, int GEOM, int ACC>
+__global__ __launch_bounds__(kStep) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 3))) void k_sweep(
+    const double *__restrict__ beta, const double *__restrict__ beta_dot, const double *__restrict__ charge,
+    const double *__restrict__ x_det, const double *__restrict__ rec, const double *__restrict__ pt,
+    const int *__restrict__ pflag, const unsigned long long *__restrict__ rmax2, const double *__restrict__ rbound2,
+    T *__restrict__ E, unsigned long long *__restrict__ diag, DepShape sh, SweepShape sw, DetAcc det)
 {
     constexpr bool kF64 = sizeof(T) == 8;
     constexpr int kRec = kF64 ? kModeRec5 : kModeRec3;
-    __shared__ uint2 q_all[kQCap];
-    __shared__ double2 qt_all[kQCap];
-    __shared__ double pcl_all[4 * (kTilePix + 1)];
-    __shared__ unsigned long long red[4];
-    const int lane = threadIdx.x & 63;
-    if (threadIdx.x < 4) red[threadIdx.x] = 0ull;
-    __syncthreads();
-
-    // block -> (particle group, tile); consecutive groups on one XCD share trajectory lines in L2
+    using Lay = RecLayout<GEOM, kF64>;
+    __shared__ SweepLds<T, GEOM> lds;
+    const int tid = threadIdx.x, p = tid & (kTilePix - 1);
+    // block -> (particle group and segment, tile); blocks go to the 8 XCDs round robin, and all tiles
+    // of a group run on one XCD at once, so that they share its records in that L2
     const int64_t b = blockIdx.x;
     const int64_t xcd = b & 7, slot = b >> 3;
-    const int64_t grp = (slot / sh.n_tiles) * 8 + xcd;
+    const int64_t unit = (slot / sh.n_tiles) * 8 + xcd;
     const int64_t tile = slot % sh.n_tiles;
-    const int64_t k0 = grp * sh.parts_per_group;
-    const int64_t k1 = grp < sh.n_groups ? std::min(k0 + sh.parts_per_group, sh.n_particles) : k0;
+    const int64_t grp = unit / sw.n_seg;
+    const int seg = (int)(unit - grp * sw.n_seg);
+    if (grp >= sh.n_groups) return;  // padding block
+    const int64_t k0 = grp * sh.parts_per_group, k1 = std::min(k0 + sh.parts_per_group, sh.n_particles);
+    const int st0 = seg * sw.per_seg, st1 = min(st0 + sw.per_seg, sw.n_steps);
 
-    ScanWave<T, GEOM, ACC> w;
-    Wave<T, GEOM, ACC> &d = w.d;
-    bool pix_in[kPPL];
-    double id2 = 0.0, s2 = 0.0;
+    if (tid < 4) lds.red[tid] = 0ull;
+    const int64_t m = tile * kTilePix + p;
+    const bool pix_in = m < sh.n_pix;
     const double Dref = pix_geo(x_det, 0).D;  // the records' pixel distance
-    bool far_off = false;                     // a pixel of this wavefront at another distance
-#pragma unroll
-    for (int h = 0; h < kPPL; ++h) {
-        const int p = 64 * h + lane;
-        const int64_t m = tile * kTilePix + p;
-        pix_in[h] = m < sh.n_pix;
+    bool lane_ok, far_off = false;
+    double id2 = 0.0, s2 = 0.0;
+    {
         // rows past the pass's last pixel are zero padding (not usable)
         const PixC pc = pixc_row(pt + m * kPT);
-        const bool ok = pix_in[h] && pc.g.ok;
-        w.okmask[h] = __ballot(ok);
-        pcl_all[4 * p] = pc.o;
-        pcl_all[4 * p + 1] = pc.px;
-        pcl_all[4 * p + 2] = pc.py;
-        pcl_all[4 * p + 3] = INFINITY;
-        if (p < 4) pcl_all[4 * kTilePix + p] = p == 3 ? INFINITY : 0.0;
-        if (ok) {
-            id2 = fmax(id2, pc.g.invD * pc.g.invD);
-            s2 = fmax(s2, 2.0 * (1.0 - pc.g.nz));
-            far_off |= !(fabs(pc.g.D - Dref) <= kSameDistance * Dref);
+        lane_ok = pix_in && pc.g.ok;
+        if (tid < kTilePix) {
+            double g0 = pc.g.nx, g1 = pc.g.ny, g2 = pc.g.nz;
+            if (GEOM == LW_GEOM_EXACT) {
+                g0 = pix_in ? x_det[3 * m] : 0.0;
+                g1 = pix_in ? x_det[3 * m + 1] : 0.0;
+                g2 = pix_in ? x_det[3 * m + 2] : 0.0;
+            }
+            lds.px[p][0] = make_double2(pc.o, pc.px);
+            lds.px[p][1] = make_double2(pc.py, g0);
+            lds.px[p][2] = make_double2(g1, g2);
+            if constexpr (GEOM == LW_GEOM_FARFIELD) lds.px[p][3] = make_double2(pc.g.invD, 0.0);
+        }
+        if (lane_ok) {
+            id2 = pc.g.invD * pc.g.invD;
+            s2 = fmax(0.0, 2.0 * (1.0 - pc.g.nz));
+            far_off = !(fabs(pc.g.D - Dref) <= kSameDistance * Dref);
         }
     }
+    // over the tile's pixels: its two halves are wavefronts 0, 1 (and again 2, 3)
     for (int off = 32; off > 0; off >>= 1) {
         id2 = fmax(id2, __shfl_xor(id2, off));
         s2 = fmax(s2, __shfl_xor(s2, off));
     }
-    const double invD2max = uniform_double(id2), s2max = uniform_double(s2);
-    const bool rec_ok = GEOM == LW_GEOM_EXACT && __ballot(far_off) == 0;
+    const uint64_t off_mask = __ballot(far_off);
+    if ((tid & 63) == 0) {
+        lds.tl[tid >> 6] = id2;
+        lds.th[tid >> 6] = s2;
+        lds.mask[tid >> 6] = off_mask;
+    }
+    __syncthreads();
+    const double invD2max = fmax(lds.tl[0], lds.tl[1]), s2max = fmax(lds.th[0], lds.th[1]);
+    const bool rec_ok = GEOM == LW_GEOM_EXACT && (lds.mask[0] | lds.mask[1]) == 0;
+
+    const size_t row0 = (size_t)(tile * kTilePix) * 3;
+    if constexpr (ACC != kAccFloat) {
+        det.hi += row0 * (size_t)sh.n_obs;
+        det.scale += row0;
+    }
+    Sweep<T, GEOM, ACC> w{lds, pt + (size_t)(tile * kTilePix) * kPT, E + row0 * (size_t)sh.n_obs, sh, det, 0.0, 0.0, 0.0, tid};
     {
         double c[6];
-        if (kF64)
-            tau_poly<5>(0.0, 0.0, 0.0, 0.0, sh.C, Dref, c);
-        else
-            tau_poly<3>(0.0, 0.0, 0.0, 0.0, sh.C, Dref, c);
-        d.cK = c[kF64 ? 5 : 3];
+        tau_poly<kF64 ? 5 : 3>(0.0, 0.0, 0.0, 0.0, sh.C, Dref, c);
+        w.cK = c[kF64 ? 5 : 3];
     }
-    w.pcl = pcl_all;
-    d.r = r;
-    d.beta = beta;
-    d.beta_dot = beta_dot;
-    d.charge = charge;
-    d.x_det = x_det;
-    d.rec = rec;
-    d.pt = pt;
-    d.E = E;
-    if constexpr (ACC != kAccFloat) d.det = det;
-    d.sh = sh;
-    d.lane = lane;
-    d.tile = tile;
-    d.k0 = k0;
-    d.q = q_all;
-    d.qt = qt_all;
-    d.qh = 0;
-    d.qn = 0;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-
+    const double nob = (double)sh.n_obs;
     unsigned long long c1 = 0, c2 = 0, c3 = 0;
     for (int64_t k = k0; k < k1; ++k) {
         if (pflag[k] != 0) continue;  // careful path: k_careful
         // series forms where |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory (the max over the
         // whole trajectory when given, else over the samples of this call), decided per pixel
-        d.rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
-        const bool all_ser = GEOM == LW_GEOM_EXACT && d.rb2 * invD2max <= kSeriesBound;
-        if (GEOM == LW_GEOM_FARFIELD)
-            w.template particle<kModeFar, CULL>(k, pix_in, c1, c2, c3);
-        else if (all_ser && rec_ok) {
-            if (tail_negligible<kF64>(d.rb2, s2max, sh.C, d.cK, Dref))
-                w.template particle<kModeRecLow, CULL>(k, pix_in, c1, c2, c3);
-            else
-                w.template particle<kRec, CULL>(k, pix_in, c1, c2, c3);
-        } else
-            w.template particle<kModeMixed, CULL>(k, pix_in, c1, c2, c3);
+        w.rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
+        w.q = charge ? charge[k] : -kQe;
+        const bool all_ser = GEOM == LW_GEOM_EXACT && w.rb2 * invD2max <= kSeriesBound;
+        const double *rk = rec + (size_t)k * sh.n_samples * Lay::W;
+        const double *bk = beta + (size_t)k * sh.n_samples * 3, *dk = beta_dot + (size_t)k * sh.n_samples * 3;
+        auto run = [&](auto mode) {
+            constexpr int MODE = decltype(mode)::value;
+            using SV = ScanVals<GEOM, kF64, MODE>;
+            const double *rm = rk + SV::OFF;
+            if (seg == 0 && tid < kTilePix) {
+                // the counters follow from the first and last arrival times
+                if (lane_ok) {
+                    const PixC P = w.template pixel<MODE>(p);
+                    const cdptr f = uniform_ptr(rm), l = uniform_ptr(rm + (size_t)(sh.n_samples - 1) * Lay::W);
+                    double v0[SV::N], v1[SV::N];
+#pragma unroll
+                    for (int v = 0; v < SV::N; ++v) {
+                        v0[v] = f[v];
+                        v1[v] = l[v];
+                    }
+                    const double t0 = tau_eval<GEOM, kF64, MODE>(P, v0, w.cK, w.rb2, sh.C);
+                    const double t1 = tau_eval<GEOM, kF64, MODE>(P, v1, w.cK, w.rb2, sh.C);
+                    const int64_t inside = grid_count(t1, nob) - grid_count(t0, nob);
+                    c3 += (unsigned long long)inside;
+                    c2 += (unsigned long long)((int64_t)(floor(t1) - floor(t0)) - inside);
+                } else if (pix_in) {
+                    c1 += (unsigned long long)(sh.n_samples - 1);
+                }
+            }
+            w.template particle<MODE>(rm, bk, dk, st0, st1, lane_ok);
+        };
+        if constexpr (GEOM == LW_GEOM_FARFIELD) {
+            run(std::integral_constant<int, kModeFar>{});
+        } else {
+            if (all_ser && rec_ok) {
+                if (tail_negligible<kF64>(w.rb2, s2max, sh.C, w.cK, Dref))
+                    run(std::integral_constant<int, kModeRecLow>{});
+                else
+                    run(std::integral_constant<int, kRec>{});
+            } else
+                run(std::integral_constant<int, kModeMixed>{});
+        }
     }
-    while (d.qn > 0) d.drain(d.qn < 64 ? d.qn : 64);
 
     // counters: block reduction in LDS, then one global atomic per counter
-    if (c1) atomicAdd(&red[1], c1);
-    if (c2) atomicAdd(&red[2], c2);
-    if (c3) atomicAdd(&red[3], c3);
+    if (c1) atomicAdd(&lds.red[1], c1);
+    if (c2) atomicAdd(&lds.red[2], c2);
+    if (c3) atomicAdd(&lds.red[3], c3);
     __syncthreads();
-    if (diag && threadIdx.x < 4 && red[threadIdx.x]) atomicAdd(diag + threadIdx.x, red[threadIdx.x]);
+    if (diag && tid < 4 && lds.red[tid]) atomicAdd(diag + tid, lds.red[tid]);
 }
 
 // Row scales of the fixed-point pass from the first pass's max |v| per element (bits of a
@@ -1154,14 +1247,14 @@ __global__ __launch_bounds__(256) void k_det_finish(double *__restrict__ E, cons
 
 template <int GEOM>
 void launch_prepass(bool f64, dim3 grid, hipStream_t s, const double *r, const double *b, const double *bd,
-                    const double *x_det, int64_t ns, int64_t sample0, double t_start, double dt, double t0,
+                    const double *x_det, int64_t ns, int chunk, int64_t sample0, double t_start, double dt, double t0,
                     double dt_obs, double C, const DepWs &w)
 {
     if (f64)
-        k_prepass<GEOM, 5><<<grid, 256, 0, s>>>(r, b, bd, x_det, ns, sample0, t_start, dt, t0, dt_obs, C, w.rec,
+        k_prepass<GEOM, 5><<<grid, 256, 0, s>>>(r, b, bd, x_det, ns, chunk, sample0, t_start, dt, t0, dt_obs, C, w.rec,
                                                w.pflag, w.rmax2);
     else
-        k_prepass<GEOM, 3><<<grid, 256, 0, s>>>(r, b, bd, x_det, ns, sample0, t_start, dt, t0, dt_obs, C, w.rec,
+        k_prepass<GEOM, 3><<<grid, 256, 0, s>>>(r, b, bd, x_det, ns, chunk, sample0, t_start, dt, t0, dt_obs, C, w.rec,
                                                w.pflag, w.rmax2);
 }
 
@@ -1258,14 +1351,19 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             sh.n_pix = npx;
             sh.n_obs = n_obs;
             sh.n_tiles = (npx + kTilePix - 1) / kTilePix;
-            int64_t groups = std::max<int64_t>(1, (kTargetWaves + sh.n_tiles - 1) / sh.n_tiles);
-            groups = std::max<int64_t>(groups, (np + kMaxPartsPerGroup - 1) / kMaxPartsPerGroup);
-            groups = std::max<int64_t>(1, std::min<int64_t>(groups, np));
-            sh.parts_per_group = std::max<int64_t>(1, (np + groups - 1) / groups);
+            sh.parts_per_group =
+                std::max<int64_t>(1, std::min<int64_t>(kMaxPartsPerGroup, np * sh.n_tiles / kTargetBlocks));
             sh.n_groups = (np + sh.parts_per_group - 1) / sh.parts_per_group;
+            SweepShape sw;
+            sw.n_steps = (int)((ns - 1 + kStep - 2) / (kStep - 1));
+            const int64_t units = sh.n_groups * sh.n_tiles;
+            const int64_t want = std::max<int64_t>(1, std::min<int64_t>(sw.n_steps, (kFillBlocks + units - 1) / units));
+            sw.per_seg = (int)((sw.n_steps + want - 1) / want);
+            sw.n_seg = sw.per_seg > 0 ? (sw.n_steps + sw.per_seg - 1) / sw.per_seg : 1;
             sh.fmask = fmask;
             sh.C = C;
-            const int64_t blocks = (sh.n_groups + 7) / 8 * 8 * sh.n_tiles;
+            const int64_t blocks = (sh.n_groups * sw.n_seg + 7) / 8 * 8 * sh.n_tiles;
+            const int64_t blocks_careful = (sh.n_groups + 7) / 8 * 8 * sh.n_tiles;
             if (sh.parts_per_group >= (int64_t(1) << (32 - kPixBits)))
                 return fail(LW_E_SHAPE, "lw_deposit_td: too many particles per pixel tile group");
             if (np > 0x7fffffff) return fail(LW_E_SHAPE, "lw_deposit_td: too many particles");
@@ -1282,21 +1380,23 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             const int fill_blocks = (int)std::min<int64_t>((np + 255) / 256, 65536);
             k_fill<int><<<fill_blocks, 256, 0, s>>>(w.pflag, np);
             k_fill<unsigned long long><<<fill_blocks, 256, 0, s>>>(w.rmax2, np);
-            const dim3 pgrid((unsigned)np, (unsigned)n_chunks_s);
+            int pchunk = kPrepassChunk;
+            while (pchunk > 256 && np * ((ns + pchunk - 1) / pchunk) < kPrepassBlocks) pchunk /= 2;
+            const dim3 pgrid((unsigned)np, (unsigned)((ns + pchunk - 1) / pchunk));
             if (geom == LW_GEOM_EXACT)
-                launch_prepass<LW_GEOM_EXACT>(f64, pgrid, s, r, b, bd, xd, ns, sample0, t->t_start, t->dt, gr->t0,
+                launch_prepass<LW_GEOM_EXACT>(f64, pgrid, s, r, b, bd, xd, ns, pchunk, sample0, t->t_start, t->dt, gr->t0,
                                               gr->dt_obs, C, w);
             else
-                launch_prepass<LW_GEOM_FARFIELD>(f64, pgrid, s, r, b, bd, xd, ns, sample0, t->t_start, t->dt, gr->t0,
+                launch_prepass<LW_GEOM_FARFIELD>(f64, pgrid, s, r, b, bd, xd, ns, pchunk, sample0, t->t_start, t->dt, gr->t0,
                                                  gr->dt_obs, C, w);
             unsigned long long *dg = (unsigned long long *)diag;
-            const dim3 grid((unsigned)blocks), block(kBlockThreads);
+            const dim3 grid((unsigned)blocks), grid_careful((unsigned)blocks_careful);
             if (acc_mode != kAccFloat) {
 #define LW_DET_LAUNCH(G, A)                                                                                          \
     do {                                                                                                             \
-        k_scan<double, G, false, A><<<grid, block, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,  \
-                                                           (double *)Ep, dg, sh, dp);                                \
-        k_careful<double, G, A><<<grid, block, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,      \
+        k_sweep<double, G, A><<<grid, kStep, 0, s>>>(b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2, (double *)Ep,   \
+                                                     dg, sh, sw, dp);                                                \
+        k_careful<double, G, A><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,      \
                                                        (double *)Ep, dg, sh, dp);                                    \
     } while (0)
                 if (geom == LW_GEOM_EXACT) {
@@ -1309,27 +1409,18 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
                 if (st != LW_OK) return st;
                 continue;
             }
-            // the fast path (timed as the deposit kernel), then the careful path; culling is a
-            // separate instantiation of the fast path, so the full evaluation carries none of its code
-#define LW_SCAN_LAUNCH(T, G, CU)                                                                                  \
-    k_scan<T, G, CU, kAccFloat><<<grid, block, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,      \
-                                                       (T *)Ep, dg, sh, DetAcc{nullptr, nullptr})
+            // the fast path (timed as the deposit kernel), then the careful path
+#define LW_SWEEP_LAUNCH(T, G)                                                                                    \
+    k_sweep<T, G, kAccFloat><<<grid, kStep, 0, s>>>(b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2, (T *)Ep, dg, \
+                                                    sh, sw, DetAcc{nullptr, nullptr})
 #define LW_CAREFUL_LAUNCH(T, G)                                                                                   \
-    k_careful<T, G, kAccFloat><<<grid, block, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,       \
+    k_careful<T, G, kAccFloat><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,       \
                                                       (T *)Ep, dg, sh, DetAcc{nullptr, nullptr})
             hipEvent_t ev = timing_begin(LW_KERNEL_DEPOSIT, s);
             if (f64) {
-                if (geom == LW_GEOM_EXACT) {
-                    if (cull) LW_SCAN_LAUNCH(double, LW_GEOM_EXACT, true); else LW_SCAN_LAUNCH(double, LW_GEOM_EXACT, false);
-                } else {
-                    if (cull) LW_SCAN_LAUNCH(double, LW_GEOM_FARFIELD, true); else LW_SCAN_LAUNCH(double, LW_GEOM_FARFIELD, false);
-                }
+                if (geom == LW_GEOM_EXACT) LW_SWEEP_LAUNCH(double, LW_GEOM_EXACT); else LW_SWEEP_LAUNCH(double, LW_GEOM_FARFIELD);
             } else {
-                if (geom == LW_GEOM_EXACT) {
-                    if (cull) LW_SCAN_LAUNCH(float, LW_GEOM_EXACT, true); else LW_SCAN_LAUNCH(float, LW_GEOM_EXACT, false);
-                } else {
-                    if (cull) LW_SCAN_LAUNCH(float, LW_GEOM_FARFIELD, true); else LW_SCAN_LAUNCH(float, LW_GEOM_FARFIELD, false);
-                }
+                if (geom == LW_GEOM_EXACT) LW_SWEEP_LAUNCH(float, LW_GEOM_EXACT); else LW_SWEEP_LAUNCH(float, LW_GEOM_FARFIELD);
             }
             timing_end(LW_KERNEL_DEPOSIT, ev, s);
             if (f64) {
@@ -1337,7 +1428,7 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             } else {
                 if (geom == LW_GEOM_EXACT) LW_CAREFUL_LAUNCH(float, LW_GEOM_EXACT); else LW_CAREFUL_LAUNCH(float, LW_GEOM_FARFIELD);
             }
-#undef LW_SCAN_LAUNCH
+#undef LW_SWEEP_LAUNCH
 #undef LW_CAREFUL_LAUNCH
             const lw_status st = check_launch("lw_deposit_td");
             if (st != LW_OK) return st;

@@ -251,15 +251,24 @@ __host__ __device__ __forceinline__ void tau_poly(double d, double x, double y, 
     c[1] += 1.0;
 }
 
+// 1/|beta| as the field takes it, 0 at rest.  Single-precision fields need one Newton step of the
+// reciprocal square roots (relative error ~1e-13, far below float rounding of n - beta and
+// kappa); double fields take two.
+template <typename T>
+__device__ __forceinline__ double inv_beta(double bx, double by, double bz)
+{
+    const double b2 = bx * bx + by * by + bz * bz;
+    return b2 > 0.0 ? rsqrt_nr<sizeof(T) == 4 ? 1 : 2>(b2) : 0.0;
+}
+
 // Lienard-Wiechert field of one sample at one pixel.  Geometry (n, R, n - beta, kappa) in
 // double; the field arithmetic in T.  kappa = 1 - n.b is formed as (1-b^2)/(1+|b|) + |b||n - b^|^2/2.
+// ib: the sample's inv_beta.
 template <typename T, int GEOM>
-__device__ __forceinline__ void lw_field(const PixGeo &g, const double *xm, double rx, double ry, double rz,
-                                         double bx, double by, double bz, double ax, double ay, double az, double q,
-                                         int fmask, T &Ex, T &Ey, T &Ez, double *kappa_out = nullptr)
+__device__ __forceinline__ void lw_field_ib(const PixGeo &g, const double *xm, double rx, double ry, double rz,
+                                            double bx, double by, double bz, double ib, T tax, T tay, T taz, double q,
+                                            int fmask, T &Ex, T &Ey, T &Ez, double *kappa_out = nullptr)
 {
-    // single-precision fields need one Newton step of the reciprocal square roots (relative
-    // error ~1e-13, far below float rounding of n - beta and kappa); double fields take two
     constexpr int kNR = sizeof(T) == 4 ? 1 : 2;
     double nx, ny, nz, iR;
     if (GEOM == LW_GEOM_EXACT) {
@@ -279,7 +288,7 @@ __device__ __forceinline__ void lw_field(const PixGeo &g, const double *xm, doub
     if (b2 > 0.0) {
         // 1 - n.b = (1 - |b|) + |b| |n - b/|b||^2 / 2 for a unit n, with no cancellation of
         // the O(1/gamma^2) result against O(1) terms
-        const double ib = rsqrt_nr<kNR>(b2), bn = b2 * ib;
+        const double bn = b2 * ib;
         double dx = nx - bx * ib, dy = ny - by * ib, dz = nz - bz * ib;
         kappa = (1.0 - bn) + 0.5 * bn * (dx * dx + dy * dy + dz * dz);
     }
@@ -307,7 +316,6 @@ __device__ __forceinline__ void lw_field(const PixGeo &g, const double *xm, doub
         Ez += f * mz;
     }
     if (fmask & LW_FIELD_ACCEL) {
-        T tax = (T)ax, tay = (T)ay, taz = (T)az;
         // w = (n - b) x bd ; v = n x w
         T wx = my * taz - mz * tay, wy = mz * tax - mx * taz, wz = mx * tay - my * tax;
         T vx = tny * wz - tnz * wy, vy = tnz * wx - tnx * wz, vz = tnx * wy - tny * wx;
@@ -316,6 +324,15 @@ __device__ __forceinline__ void lw_field(const PixGeo &g, const double *xm, doub
         Ey += f * vy;
         Ez += f * vz;
     }
+}
+
+template <typename T, int GEOM>
+__device__ __forceinline__ void lw_field(const PixGeo &g, const double *xm, double rx, double ry, double rz,
+                                         double bx, double by, double bz, double ax, double ay, double az, double q,
+                                         int fmask, T &Ex, T &Ey, T &Ez, double *kappa_out = nullptr)
+{
+    lw_field_ib<T, GEOM>(g, xm, rx, ry, rz, bx, by, bz, inv_beta<T>(bx, by, bz), (T)ax, (T)ay, (T)az, q, fmask, Ex, Ey,
+                         Ez, kappa_out);
 }
 
 // Vector-Jacobian product of lw_field (double): given g = dJ/dE at one (sample, pixel), adds

@@ -1,0 +1,60 @@
+"""The fast path of lw_deposit_td at the edges of its steps (256 samples that share their boundary
+sample), of its 128-pixel tiles and their halves, of its sample segments, and on both sides of the
+rule that takes a step point by point or interval by interval, against the FP64 oracle.
+
+Tolerances as in test_gpu_deposit.py: FP64 1e-9 max|E|, mixed 2e-5 max|E|; counters exact."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from cases import synthetic
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+TOL = {"fp64": 1e-9, "mixed": 2e-5}
+
+
+def check(c, prec, geom):
+    from paper_2206_03015_amd import lw
+    t = {k: torch.as_tensor(np.ascontiguousarray(c[k]), device=DEV) for k in ("r", "beta", "beta_dot", "x_det", "charge")}
+    E, diag = lw.deposit_td(t["r"], t["beta"], t["beta_dot"], c["t_start"], c["dt"], t["x_det"], c["t0"], c["dt_obs"],
+                            c["n_obs"], prec=prec, field_mask=3, geom=geom, charge=t["charge"])
+    Eo, do = oracle.deposit_td(c["t_start"], c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"], c["t0"], c["dt_obs"],
+                               c["n_obs"], charge=c["charge"], field_mask=3,
+                               geom=oracle.GEOM_EXACT if geom == "exact" else oracle.GEOM_FARFIELD)
+    torch.cuda.synchronize()
+    assert diag.cpu().tolist() == list(do) and do[3] > 0
+    assert np.max(np.abs(E.double().cpu().numpy() - Eo)) <= TOL[prec] * np.max(np.abs(Eo))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("geom", ["exact", "farfield"])
+@pytest.mark.parametrize("n_samples, n_pix", [(2, 1), (3, 64), (4, 65), (255, 127), (256, 128), (257, 129), (511, 3),
+                                              (512, 70), (16321, 2), (16600, 5)])
+def test_step_and_tile_edges(n_samples, n_pix, prec, geom):
+    """n_samples - 1 intervals: one step short, exact, one over; 64 steps (one mask) and one more."""
+    check(synthetic(n_p=3, n_samples=n_samples, n_pix=n_pix, n_obs=max(16, n_samples // 7), seed=n_samples,
+                    dt=2e-18 * 700 / max(n_samples, 200)), prec, geom)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("per_interval", [0.02, 0.4, 0.59, 0.61, 1.0, 3.0])
+def test_sparse_and_dense_steps(per_interval, prec):
+    """Grid points per sample interval around the rule's line (0.6)."""
+    n_samples = 600
+    check(synthetic(n_p=3, n_samples=n_samples, n_pix=9, n_obs=int(0.7 * per_interval * n_samples), seed=2), prec, "exact")
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_pixels_at_several_distances(prec):
+    """Pixels off the records' distance, some inside the series bound and some outside it: every
+    pixel takes its own arrival-time form."""
+    c = synthetic(n_p=3, n_samples=300, n_pix=40, n_obs=200, seed=4)
+    c["x_det"] = c["x_det"] * np.linspace(0.5, 3.0, 40)[:, None]
+    check(c, prec, "exact")
+    c["x_det"] = c["x_det"] * 1e-3  # |r| up to 0.18 um against 0.5 to 3 mm
+    tau, _, _ = oracle.eval_samples(0.0, c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"], 0.0, 1.0)
+    c["dt_obs"] = float(np.ptp(tau)) / 140
+    c["t0"] = float(np.median(tau)) - 100 * c["dt_obs"]
+    check(c, prec, "exact")
