@@ -243,7 +243,7 @@ def headline(torch, dev, args):
     torch.cuda.synchronize()
     push_ms = e0.elapsed_time(e1)
     traj_bytes = 72 * W.n_p * W.n_samples
-    stream_rec = {"kernel": "k_boris (lw_trajectory_boris)", "bytes_written": traj_bytes, "ms": push_ms,
+    stream_rec = {"kernel": "k_push (lw_trajectory_boris)", "bytes_written": traj_bytes, "ms": push_ms,
                   "GBs": traj_bytes / (push_ms / 1e3) / 1e9, "frac_of_hbm_peak":
                   traj_bytes / (push_ms / 1e3) / 1e9 / PEAK_HBM_GBS}
     log(f"[bench] Boris trajectories {W.n_p} x {W.n_samples}: {push_ms:.0f} ms, {stream_rec['GBs']:.0f} GB/s")

@@ -1,8 +1,7 @@
 // FP64 Boris trajectories of electrons in the laser pulse (the trajectory source of
 // the time-domain method; the paper integrates the equations of motion with the
 // Boris method), and their forward-mode tangents with respect to the initial phase
-// space and the laser amplitude a0.  One lane per particle; samples are
-// r, beta, beta_dot [n_particles][n_samples][3].
+// space and the laser amplitude a0.  Samples are r, beta, beta_dot [n_particles][n_samples][3].
 #include "lw_internal.h"
 
 #include <algorithm>
@@ -287,101 +286,282 @@ __device__ __forceinline__ void push_particle(const LaserDev &L, R a0, const R *
     }
 }
 
-__global__ __launch_bounds__(256) void k_boris(const double *__restrict__ init, int64_t n_particles,
-                                               int64_t n_samples, double t_start, double dt, LaserDev L,
-                                               double *__restrict__ r, double *__restrict__ beta,
-                                               double *__restrict__ beta_dot)
+constexpr int kStateDoubles = 9;  // of the pusher, carried between spans
+
+// ---------------------------------------------------------------------------------------------
+// The pusher.  A particle's steps are one serial chain, and a wavefront of it issues one FP64
+// instruction in four cycles whether the chip is full or not, so its time is the instructions per
+// step of one wavefront until there are enough wavefronts for every SIMD: 4000 particles x 20001
+// samples took 17.3 ms with one lane per particle and everything in the chain (~440 VALU
+// instructions per step).  The chain here carries only what the next step needs:
+//   * the samples' beta, beta_dot and the stores are another wavefront's work: a block is one wavefront
+//     of the chain and one that turns its states, handed over through LDS kPushSteps steps at a
+//     time, into samples (lanes over particles and steps, so that a particle's steps are stored
+//     next to each other);
+//   * a particle has two lanes, which take the pulse's two sine/cosine pairs (carrier and envelope) in
+//     one call and exchange them; everything else both lanes do alike.  Only worth it while the
+//     wavefronts of paired particles find a SIMD each (kPairParticles);
+//   * quotients by constants are a product with the rounded reciprocal and one residual correction
+//     (Markstein: the correctly rounded quotient), the other quotients and the square roots
+//     Newton/Goldschmidt iterations without the range scaling that arguments of this size do not
+//     need.
+// All of these round as the plain expressions do, so the samples keep their bits.  ~250 instructions
+// per step inside the pulse, 0.51 us: 17.0 -> 10.3 ms for 4000 particles x 20001 samples.  What
+// is left is the latency of that dependent chain.
+constexpr int kPushSteps = 8;                  // steps per hand-over of a paired block (32 particles)
+constexpr int64_t kPairParticles = 32 * 1024;  // 1024 SIMDs
+
+// x / c for a constant c with rc = 1/c rounded
+__device__ __forceinline__ double div_const(double x, double c, double rc)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_particles) return;
-    double in[6];
-    for (int c = 0; c < 6; ++c) in[c] = init[6 * k + c];
-    push_particle<double>(L, L.a0, in, n_samples, t_start, dt,
-                          [&](int64_t i, const double *rr, const double *bb, const double *aa) {
-                              const size_t o = (size_t)(k * n_samples + i) * 3;
-                              for (int c = 0; c < 3; ++c) {
-                                  r[o + c] = rr[c];
-                                  beta[o + c] = bb[c];
-                                  beta_dot[o + c] = aa[c];
-                              }
-                          });
+    const double q = x * rc;
+    return __builtin_amdgcn_div_fixup(fma(fma(-q, c, x), rc, q), c, x);
+}
+// a / b for b of moderate size
+__device__ __forceinline__ double div_plain(double a, double b)
+{
+    double y = __builtin_amdgcn_rcp(b);
+    y = fma(fma(-b, y, 1.0), y, y);
+    y = fma(fma(-b, y, 1.0), y, y);
+    const double q = a * y;
+    return __builtin_amdgcn_div_fixup(fma(fma(-b, q, a), y, q), b, a);
+}
+// sqrt(x) for x >= 1
+__device__ __forceinline__ double sqrt_plain(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    return x < 1e300 ? g : x;  // infinite (or not a number)
 }
 
-// max_i |r_i|^2 over every sample of each particle's trajectory (nothing stored; the sum in the
-// order of the deposit's pre-pass, z^2 + (y^2 + x^2) with fused multiply-adds), so that
-// choices made per particle over its whole trajectory agree between the spans of a deposit
-// and its adjoint and with those of the stored samples
-__global__ __launch_bounds__(256) void k_boris_rmax2(const double *__restrict__ init, int64_t n_particles,
-                                                     int64_t n_samples, double t_start, double dt, LaserDev L,
-                                                     double *__restrict__ rmax2)
+// the quotients' constants
+struct PushConst {
+    double rc_c, nc2, rnc2, rnc, w02, rw02;
+};
+__device__ __forceinline__ PushConst push_const(const LaserDev &L)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_particles) return;
-    double in[6];
-    for (int c = 0; c < 6; ++c) in[c] = init[6 * k + c];
-    PushState<double> S;
-    push_start(L, L.a0, in, t_start, dt, S);
-    double mx = fma(S.z, S.z, fma(S.y, S.y, S.x * S.x));
-    for (int64_t i = 1; i < n_samples; ++i) {
-        push_step(L, L.a0, t_start + (double)i * dt, dt, S);
-        mx = fmax(mx, fma(S.z, S.z, fma(S.y, S.y, S.x * S.x)));
-    }
-    rmax2[k] = mx;
+    PushConst K;
+    K.rc_c = 1.0 / kC;
+    K.nc2 = 2.0 * L.nc;
+    K.rnc2 = 1.0 / K.nc2;
+    K.rnc = 1.0 / L.nc;
+    K.w02 = L.w0 * L.w0;
+    K.rw02 = 1.0 / K.w02;
+    return K;
 }
 
-// Samples s0 .. s0 + n_span - 1 of each particle into r, beta, beta_dot [n_particles][n_span][3].
-// The pusher starts from init (s0 = 0) or from the state saved by the previous span, which ends
-// at sample s0 (spans share their boundary sample), and saves its state at the last sample it
-// writes: x, y, z, u at the sample and u half a step later, [n_particles][9].
-constexpr int kStateDoubles = 9;
-
-__global__ __launch_bounds__(256) void k_boris_span(const double *__restrict__ init, int64_t n_particles,
-                                                    int64_t s0, int64_t n_span, double t_start, double dt,
-                                                    LaserDev L, double *__restrict__ state, double *__restrict__ r,
-                                                    double *__restrict__ beta, double *__restrict__ beta_dot)
+// value of the pair's even (ODD = 0) or odd lane
+template <int ODD>
+__device__ __forceinline__ double pair_lane(double v)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_particles) return;
-    PushState<double> S;
-    double *st = state + kStateDoubles * k;
-    if (s0 == 0) {
-        double in[6];
-        for (int c = 0; c < 6; ++c) in[c] = init[6 * k + c];
-        push_start(L, L.a0, in, t_start, dt, S);
+    constexpr int kCtrl = ODD ? 0xf5 /* quad_perm 1,1,3,3 */ : 0xa0 /* quad_perm 0,0,2,2 */;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// laser_eb's field E_x (B_y = -E_x / c)
+template <bool PAIR>
+__device__ __forceinline__ double laser_ex(const LaserDev &L, const PushConst &K, double x, double y, double z, double t,
+                                           bool odd)
+{
+    const double phi = L.wl * (t + div_const(z, kC, K.rc_c));
+    if (!(fabs(phi) < kPi * L.nc)) return 0.0;
+    const double half = div_const(phi, K.nc2, K.rnc2);
+    double sh, ch, sp, cp;
+    if constexpr (PAIR) {
+        double sn, cs;
+        ::sincos(odd ? phi : half, &sn, &cs);
+        sh = pair_lane<0>(sn);
+        ch = pair_lane<0>(cs);
+        sp = pair_lane<1>(sn);
+        cp = pair_lane<1>(cs);
     } else {
-        S.x = st[0];
-        S.y = st[1];
-        S.z = st[2];
-        S.usx = st[3];
-        S.usy = st[4];
-        S.usz = st[5];
-        S.uhx = st[6];
-        S.uhy = st[7];
-        S.uhz = st[8];
-        // the same arguments as the step that reached sample s0: the same field
-        laser_eb(L, L.a0, S.x, S.y, S.z, t_start + (double)s0 * dt, S.Ex, S.By);
+        ::sincos(half, &sh, &ch);
+        ::sincos(phi, &sp, &cp);
     }
-    for (int64_t j = 0; j < n_span; ++j) {
-        double rr[3], bb[3], aa[3];
-        push_sample(S, rr, bb, aa);
-        const size_t o = (size_t)(k * n_span + j) * 3;
-        for (int c = 0; c < 3; ++c) {
-            r[o + c] = rr[c];
-            beta[o + c] = bb[c];
-            beta_dot[o + c] = aa[c];
+    const double g = ch * ch;
+    const double gp = -div_const(sh * ch, L.nc, K.rnc);
+    const double dS = gp * sp + g * cp;
+    double T = 1.0;
+    if (L.w0 > 0.0) T = ::exp(-div_const(x * x + y * y, K.w02, K.rw02));
+    return -(L.e0_per_a0 * (L.a0 * T * dS));
+}
+
+// kick, with the quotients and the square root of this kernel
+__device__ __forceinline__ void kick_plain(double &ux, double &uy, double &uz, double Ex, double By, double h)
+{
+    const double q = -kQe, m = kMe;
+    const double a = q * h / (2.0 * m * kC);
+    const double mx = ux + a * Ex, my = uy, mz = uz;
+    const double gm = sqrt_plain(1.0 + (mx * mx + my * my + mz * mz));
+    const double ty = div_plain((q * h / (2.0 * m)) * By, gm);
+    const double sy = div_plain(2.0 * ty, 1.0 + ty * ty);
+    const double px = mx - mz * ty, pz = mz + mx * ty;
+    const double nx = mx - pz * sy, nz = mz + px * sy;
+    ux = nx + a * Ex;
+    uy = my;
+    uz = nz;
+}
+
+// state of one sample in the hand-over buffer: x, y, z, E_x, u (4 doubles with padding)
+template <int P, int S>
+struct PushLds {
+    double2 st[2][P][4 * S + 1];  // one pad entry: the particles' entries start in different banks
+};
+
+// Samples s0 .. s0 + n_span - 1 of each particle: stored in r, beta, beta_dot [n_particles][n_span][3] (OUT),
+// and their max |r|^2 in rmax2 if given (fma order z^2 + (y^2 + x^2), that of the deposit's pre-pass).
+// The pusher starts from init (s0 = 0) or from the state [n_particles][9] that the span ending at
+// sample s0 left (spans share their boundary sample): x, y, z, u at the sample and u half a step
+// later.  The field at sample s0 is that of the step that reached it (same arguments, same bits).
+// The state at the last sample is left in `state` if given.
+template <bool PAIR, bool OUT>
+__global__ __launch_bounds__(128) void k_push(const double *__restrict__ init, int64_t n_particles, int64_t s0,
+                                              int64_t n_span, double t_start, double dt, LaserDev L,
+                                              double *__restrict__ state, double *__restrict__ r,
+                                              double *__restrict__ beta, double *__restrict__ beta_dot,
+                                              double *__restrict__ rmax2)
+{
+    constexpr int P = PAIR ? 32 : 64, S = PAIR ? kPushSteps : kPushSteps / 2;
+    __shared__ PushLds<P, S> lds;
+    const int lane = threadIdx.x & 63;
+    // the chain is the first wavefront of a block, or the second in every other 512 blocks: where
+    // several blocks share a compute unit their chains then sit on different SIMDs
+    const bool chain = (__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) ^ (int)((blockIdx.x >> 9) & 1)) == 0;
+    const int64_t kb = (int64_t)blockIdx.x * P;
+    const PushConst K = push_const(L);
+    const int64_t nb = (n_span + S - 1) / S;
+    if (chain) {
+        const int p = PAIR ? lane >> 1 : lane;
+        const bool odd = PAIR && (lane & 1);
+        const bool in = kb + p < n_particles;
+        const int64_t k = in ? kb + p : n_particles - 1;
+        double x, y, z, usx, usy, usz, uhx, uhy, uhz, Ex;
+        double *st = state ? state + kStateDoubles * k : nullptr;
+        if (s0 == 0) {
+            const double *in0 = init + 6 * k;
+            x = in0[0];
+            y = in0[1];
+            z = in0[2];
+            uhx = usx = in0[3];
+            uhy = usy = in0[4];
+            uhz = usz = in0[5];
+            Ex = laser_ex<PAIR>(L, K, x, y, z, t_start, odd);
+            kick_plain(uhx, uhy, uhz, Ex, -div_const(Ex, kC, K.rc_c), 0.5 * dt);
+        } else {
+            x = st[0];
+            y = st[1];
+            z = st[2];
+            usx = st[3];
+            usy = st[4];
+            usz = st[5];
+            uhx = st[6];
+            uhy = st[7];
+            uhz = st[8];
+            Ex = laser_ex<PAIR>(L, K, x, y, z, t_start + (double)s0 * dt, odd);
         }
-        if (j + 1 == n_span) break;
-        push_step(L, L.a0, t_start + (double)(s0 + j + 1) * dt, dt, S);
+        double at = (double)s0;  // index of the sample the state stands at
+        for (int64_t b = 0; b < nb; ++b) {
+            const int n = (int)std::min<int64_t>(S, n_span - b * S);
+            const bool last = b + 1 == nb;
+            double2 *row = lds.st[b & 1][p];
+            for (int j = 0; j < n; ++j) {
+                if constexpr (PAIR) {
+                    row[4 * j + (odd ? 2 : 0)] = odd ? make_double2(usx, usy) : make_double2(x, y);
+                    row[4 * j + (odd ? 3 : 1)] = odd ? make_double2(usz, 0.0) : make_double2(z, Ex);
+                } else {
+                    row[4 * j] = make_double2(x, y);
+                    row[4 * j + 1] = make_double2(z, Ex);
+                    row[4 * j + 2] = make_double2(usx, usy);
+                    row[4 * j + 3] = make_double2(usz, 0.0);
+                }
+                if (last && j + 1 == n) break;
+                at += 1.0;
+                const double gh = sqrt_plain(1.0 + (uhx * uhx + uhy * uhy + uhz * uhz));
+                const double cg = div_plain(kC * dt, gh);
+                x = x + cg * uhx;
+                y = y + cg * uhy;
+                z = z + cg * uhz;
+                double nx = uhx, ny = uhy, nz = uhz;
+                Ex = laser_ex<PAIR>(L, K, x, y, z, t_start + at * dt, odd);
+                kick_plain(nx, ny, nz, Ex, -div_const(Ex, kC, K.rc_c), dt);
+                usx = 0.5 * (uhx + nx);
+                usy = 0.5 * (uhy + ny);
+                usz = 0.5 * (uhz + nz);
+                uhx = nx;
+                uhy = ny;
+                uhz = nz;
+            }
+            __syncthreads();  // batch b is written, batch b - 1 read
+        }
+        if (st && in && !odd) {
+            st[0] = x;
+            st[1] = y;
+            st[2] = z;
+            st[3] = usx;
+            st[4] = usy;
+            st[5] = usz;
+            st[6] = uhx;
+            st[7] = uhy;
+            st[8] = uhz;
+        }
+    } else {
+        // lane -> (particle of a group of 64 / S, step): a particle's S steps on neighbouring lanes
+        constexpr int G = 64 / S;
+        const int j = lane & (S - 1), pg = lane / S;
+        double mx[P / G];
+#pragma unroll
+        for (int g = 0; g < P / G; ++g) mx[g] = 0.0;
+        for (int64_t b = 0; b < nb; ++b) {
+            __syncthreads();  // batch b is written
+            const int64_t i = b * S + j;
+            if (i >= n_span) continue;
+#pragma unroll
+            for (int g = 0; g < P / G; ++g) {
+                const int p = g * G + pg;
+                const double2 *row = lds.st[b & 1][p] + 4 * j;
+                const double2 xy = row[0], ze = row[1];
+                mx[g] = fmax(mx[g], fma(ze.x, ze.x, fma(xy.y, xy.y, xy.x * xy.x)));
+                if constexpr (OUT) {
+                    if (kb + p >= n_particles) continue;
+                    const double2 uv = row[2], w0 = row[3];
+                    PushState<double> Q;
+                    Q.x = xy.x;
+                    Q.y = xy.y;
+                    Q.z = ze.x;
+                    Q.Ex = ze.y;
+                    Q.By = -div_const(ze.y, kC, K.rc_c);
+                    Q.usx = uv.x;
+                    Q.usy = uv.y;
+                    Q.usz = w0.x;
+                    double rr[3], bb[3], aa[3];
+                    push_sample(Q, rr, bb, aa);
+                    const size_t o = (size_t)((kb + p) * n_span + i) * 3;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        r[o + c] = rr[c];
+                        beta[o + c] = bb[c];
+                        beta_dot[o + c] = aa[c];
+                    }
+                }
+            }
+        }
+        if (rmax2) {
+#pragma unroll
+            for (int g = 0; g < P / G; ++g) {
+                double m = mx[g];
+                for (int off = S / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+                const int64_t k = kb + g * G + pg;
+                if (j == 0 && k < n_particles) rmax2[k] = m;
+            }
+        }
     }
-    st[0] = S.x;
-    st[1] = S.y;
-    st[2] = S.z;
-    st[3] = S.usx;
-    st[4] = S.usy;
-    st[5] = S.usz;
-    st[6] = S.uhx;
-    st[7] = S.uhy;
-    st[8] = S.uhz;
 }
 
 // Gradient through the pusher by forward-mode tangents: lane l handles particle k = l / 7
@@ -520,34 +700,34 @@ LaserDev laser_dev(const lw_laser_t &l)
 
 }  // namespace
 
+// samples s0 .. s0 + n_span - 1 (r given) and / or max |r|^2 over them (rmax2 given)
+static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, double *state, double *r, double *beta,
+                             double *beta_dot, double *rmax2, hipStream_t s, const char *what)
+{
+    if (t->n_particles == 0 || n_span == 0) return LW_OK;
+    const LaserDev L = laser_dev(t->laser);
+    const bool pair = t->n_particles <= kPairParticles;
+    const unsigned blocks = (unsigned)((t->n_particles + (pair ? 31 : 63)) / (pair ? 32 : 64));
+    auto *k = pair ? (r ? k_push<true, true> : k_push<true, false>) : (r ? k_push<false, true> : k_push<false, false>);
+    k<<<blocks, 128, 0, s>>>(t->init, t->n_particles, s0, n_span, t->t_start, t->dt, L, state, r, beta, beta_dot, rmax2);
+    return check_launch(what);
+}
+
 lw_status launch_boris(const lw_traj_t *t, double *r, double *beta, double *beta_dot, hipStream_t s)
 {
-    if (t->n_particles == 0) return LW_OK;
-    const LaserDev L = laser_dev(t->laser);
-    const int64_t blocks = (t->n_particles + 63) / 64;
-    k_boris<<<(unsigned)blocks, 64, 0, s>>>(t->init, t->n_particles, t->n_samples, t->t_start, t->dt, L, r, beta,
-                                           beta_dot);
-    return check_launch("lw_trajectory_boris");
+    return launch_push(t, 0, t->n_samples, nullptr, r, beta, beta_dot, nullptr, s, "lw_trajectory_boris");
 }
 
 lw_status launch_boris_rmax2(const lw_traj_t *t, double *rmax2, hipStream_t s)
 {
-    if (t->n_particles == 0) return LW_OK;
-    const LaserDev L = laser_dev(t->laser);
-    const int64_t blocks = (t->n_particles + 63) / 64;
-    k_boris_rmax2<<<(unsigned)blocks, 64, 0, s>>>(t->init, t->n_particles, t->n_samples, t->t_start, t->dt, L, rmax2);
-    return check_launch("max |r|^2 of the pushed trajectories");
+    return launch_push(t, 0, t->n_samples, nullptr, nullptr, nullptr, nullptr, rmax2, s,
+                       "max |r|^2 of the pushed trajectories");
 }
 
 lw_status launch_boris_span(const lw_traj_t *t, int64_t s0, int64_t n_span, double *state, double *r, double *beta,
-                            double *beta_dot, hipStream_t s)
+                            double *beta_dot, double *rmax2, hipStream_t s)
 {
-    if (t->n_particles == 0 || n_span == 0) return LW_OK;
-    const LaserDev L = laser_dev(t->laser);
-    const int64_t blocks = (t->n_particles + 63) / 64;
-    k_boris_span<<<(unsigned)blocks, 64, 0, s>>>(t->init, t->n_particles, s0, n_span, t->t_start, t->dt, L, state, r,
-                                                beta, beta_dot);
-    return check_launch("lw_deposit_td (pusher span)");
+    return launch_push(t, s0, n_span, state, r, beta, beta_dot, rmax2, s, "lw_deposit_td (pusher span)");
 }
 
 lw_status launch_boris_bwd_span(const lw_traj_t *t, int64_t s0, int64_t n_span, double *tstate, const double *g_r,

@@ -144,12 +144,14 @@ lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec
         lw_traj_t push = *t;
         push.n_particles = nb;
         push.init = t->init + 6 * b0;
-        // max |r|^2 over each whole trajectory: every span takes the same arrival-time forms
-        lw_status st = launch_boris_rmax2(&push, rb2, s);
+        // max |r|^2 over each whole trajectory, so that every span takes the same arrival-time forms:
+        // from the push itself where one span is the whole trajectory, else from a push of its own
+        const bool whole = P.span >= ns;
+        lw_status st = whole ? LW_OK : launch_boris_rmax2(&push, rb2, s);
         if (st != LW_OK) return st;
         for (int64_t s0 = 0;;) {
             const int64_t n_span = std::min<int64_t>(P.span, ns - s0);
-            st = launch_boris_span(&push, s0, n_span, state, r, b, bd, s);
+            st = launch_boris_span(&push, s0, n_span, state, r, b, bd, whole ? rb2 : nullptr, s);
             if (st != LW_OK) return st;
             lw_traj_t sub = *t;
             sub.kind = LW_TRAJ_SAMPLES;
@@ -198,13 +200,14 @@ lw_status launch_deposit_bwd_boris(const lw_traj_t *t, const lw_grid_t *gr, int 
         lw_traj_t push = *t;
         push.n_particles = nb;
         push.init = t->init + 6 * b0;
-        lw_status st = launch_boris_rmax2(&push, rb2, s);
+        const bool whole = P.span >= ns;  // max |r|^2 as in launch_deposit_boris
+        lw_status st = whole ? LW_OK : launch_boris_rmax2(&push, rb2, s);
         if (st != LW_OK) return st;
         for (int64_t s0 = 0;;) {
             const int64_t n_span = std::min<int64_t>(P.span, ns - s0);
             // the span's samples, the deposit adjoint over its intervals (dJ/d samples), then
             // the tangents of the same span contracted with them
-            st = launch_boris_span(&push, s0, n_span, pstate, r, b, bd, s);
+            st = launch_boris_span(&push, s0, n_span, pstate, r, b, bd, whole ? rb2 : nullptr, s);
             if (st != LW_OK) return st;
             const int64_t nz = nb * n_span * 3;
             for (double *z : {gr_, gb, ga})

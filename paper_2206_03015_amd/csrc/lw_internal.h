@@ -470,9 +470,10 @@ lw_status launch_boris(const lw_traj_t *traj, double *r, double *beta, double *b
 // max |r|^2 over every sample of each trajectory of traj (LW_TRAJ_BORIS), [n_particles]
 lw_status launch_boris_rmax2(const lw_traj_t *traj, double *rmax2, hipStream_t s);
 // samples s0 .. s0 + n_span - 1 of every particle of traj (LW_TRAJ_BORIS), starting from init
-// (s0 = 0) or from the pusher state [n_particles][9] left by the span that ended at sample s0
+// (s0 = 0) or from the pusher state [n_particles][9] left by the span that ended at sample s0;
+// rmax2 (or nullptr): max |r|^2 over the span's samples
 lw_status launch_boris_span(const lw_traj_t *traj, int64_t s0, int64_t n_span, double *state, double *r,
-                            double *beta, double *beta_dot, hipStream_t s);
+                            double *beta, double *beta_dot, double *rmax2, hipStream_t s);
 lw_status launch_boris_bwd(const lw_traj_t *traj, const double *g_r, const double *g_beta,
                            const double *g_beta_dot, double *grad_init, double *grad_a0, hipStream_t s);
 // the pusher's tangents over samples s0 .. s0 + n_span - 1 (gradients g_* [n_particles][n_span][3]),
