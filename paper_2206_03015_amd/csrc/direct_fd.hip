@@ -1,14 +1,14 @@
 // Direct frequency-domain sum (Eq. inty_dft, Algorithm 1), the comparison path.
 //
-// FP64 (k_direct_fd): a wavefront owns one pixel and 64 frequencies (one per lane) and a
-// group of particles.  Per chunk of 64 samples every lane evaluates one sample (arrival
-// time and E*kappa, the integrand of Eq. const_phase_drop) into LDS; then every lane sweeps
-// the 64 staged samples for its own frequency, forming the phase w*(t_a - t0) in double per
-// term and reducing it to one revolution before sin/cos.
+// A block of threads owns one pixel, a tile of frequencies and a range of chunks of samples.  Per chunk every
+// thread evaluates one sample (arrival time t_a - t0 and E*kappa, the integrand of Eq. const_phase_drop) into
+// LDS; then the block sums the chunk for its frequencies.
 //
-// Mixed (k_direct_fd_mixed): lane l owns K consecutive frequencies (8, or fewer for short
-// frequency lists).  Per chunk and
-// lane the phase of the lane's first frequency at a reference arrival time of the chunk is
+// FP64 (k_direct_fd): the phase w (t_a - t0) is formed in double and reduced to one revolution before
+// sin/cos; for equally spaced frequencies the sums are matrix products, otherwise one sin/cos pair per term.
+//
+// Mixed (k_direct_fd_mixed): lane l owns K consecutive frequencies (8, or fewer for short frequency lists).
+// Per 64 samples and lane the phase of the lane's first frequency at a reference arrival time is
 // formed in double (reduced to one revolution); per sample one float FMA adds nu*(t_a -
 // t_ref), a few revolutions at most, and the hardware sin/cos (arguments in revolutions)
 // give the first phasor.  When the wavefront's frequencies are equally spaced by dw (checked
@@ -16,9 +16,9 @@
 // phasor e^{i dw t_a} formed once per sample at staging (phase in double, reduced, then
 // float sin/cos), p_1 = p_0 e^{i dw t} and p_{j+1} = 2 cos(dw t) p_j - p_{j-1}, two FMAs per
 // further frequency instead of a sin/cos pair.  Otherwise every phasor gets its own sin/cos.
-// Terms are summed in float over a chunk, chunks in double.
+// Terms are summed in float over 64 samples, those sums in double.
 //
-// Partial sums of a wavefront go to a double workspace with atomics; a final kernel forms
+// Partial sums of a block go to a double workspace with atomics; a final kernel forms
 // S = (dt^2/2pi) sum_c |F_c|^2.
 #include "lw_internal.h"
 
@@ -26,8 +26,6 @@
 
 namespace lw {
 namespace {
-
-constexpr int kWavesPerBlock = 4;
 
 // value of lane src (wavefront-uniform src) of a double register
 __device__ __forceinline__ double readlane_f64(double v, int src)
@@ -40,15 +38,14 @@ __device__ __forceinline__ double readlane_f64(double v, int src)
 
 struct FdShape {
     int64_t n_particles, n_samples, n_pix, n_omega;
-    int64_t n_wblocks, n_groups, parts_per_group;
+    int64_t n_wblocks;               // frequency tiles
+    int64_t n_groups, parts_per_group;  // groups of chunks of samples, chunks per group
     double t_start, dt, t0, inv_cdt, cdt;
     int fmask;
 };
 
-// most frequencies per lane of the mixed kernel (fewer when there are few frequencies, so
-// that the lanes stay busy), and how equal the spacing of a wavefront's frequencies must be
-// (relative) for the recurrence over frequency
-constexpr int kFdFreq = 8;
+// how equal the spacing of a mixed wavefront's frequencies must be (relative) for the recurrence over
+// frequency
 constexpr double kFdEqualTol = 1e-13;
 
 // Arrival time relative to t0 (s) and E*kappa of sample i of particle k at pixel g; zeros for
@@ -82,105 +79,277 @@ __device__ __forceinline__ void stage_sample(const double *__restrict__ r, const
     }
 }
 
-template <int GEOM>
-__global__ __launch_bounds__(256) void k_direct_fd(const double *__restrict__ r, const double *__restrict__ beta,
-                                                   const double *__restrict__ beta_dot,
-                                                   const double *__restrict__ charge, const double *__restrict__ x_det,
-                                                   const double *__restrict__ omega, double *__restrict__ acc,
-                                                   FdShape sh)
+// ---------------------------------------------------------------------------------------------
+// FP64 sums
+//
+// Equally spaced frequencies (kFdBlk of them to a block, block centre w_A, offsets +-h dw with
+// h = 1/2, 3/2 ... 31/2): e^{i (w_A +- h dw) t} = e^{i w_A t} (cos h dw t +- i sin h dw t), so the sums are
+// one matrix product over the samples,
+//   [A_c cos w_A t, A_c sin w_A t] (6 rows per block)  x  [cos h dw t, sin h dw t] (32 columns),
+// whose 192 elements per block are 32 frequencies x 3 components x (re, im): six multiply-adds a term, on
+// the matrix cores, and 1/32 + 1/64 sine/cosine pairs a term instead of one.  Other lists take one sine/cosine
+// pair per term as they come.  The rule is decided per block of threads from the frequencies themselves.
+// 20 x 2001 samples, 9 pixels, 1024 frequencies: 997 us with a sine/cosine pair per term -> 202 us (57 us of it
+// the matrix product at this card's FP64 rate, the rest the phasors and the exchange through LDS).
+constexpr int kFdBlk = 32;
+constexpr double kFdTol64 = 1e-15;  // a few roundings of a frequency: what the phase product's rounding is
+constexpr double kInv2Pi = 0.15915494309189535, kInv2PiLo = -9.839338337591243e-18;
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// centre of frequency block A
+__device__ __forceinline__ double fd_centre(const double *__restrict__ omega, int64_t n, int64_t A, double dw)
 {
-    __shared__ double s_ta[kWavesPerBlock][64];
-    __shared__ double s_ek[kWavesPerBlock][3][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + wv;
-    const int64_t per_pix = sh.n_wblocks * sh.n_groups;
-    const int64_t m = wave / per_pix;
-    if (m >= sh.n_pix) return;  // whole wavefront idle; no block-level sync below
-    const int64_t rem = wave - m * per_pix;
-    const int64_t wb = rem / sh.n_groups, grp = rem - wb * sh.n_groups;
-    const int64_t w = wb * 64 + lane;
-    const bool w_ok = w < sh.n_omega;
-    const double nu = w_ok ? omega[w] / (2.0 * kPi) : 0.0;  // cycles per second
-    const int64_t k0 = grp * sh.parts_per_group, k1 = std::min(k0 + sh.parts_per_group, sh.n_particles);
-    PixGeo g = pix_geo(x_det, m);
-    const double *xm = x_det + 3 * m;
-    double a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0;  // Re/Im of F_x, F_y, F_z
-    const int64_t ns = sh.n_samples;
-    for (int64_t k = k0; k < k1; ++k) {
-        const double q = charge ? charge[k] : -kQe;
-        for (int64_t i0 = 0; i0 < ns; i0 += 64) {
-            // stage: lane -> sample i0 + lane
-            {
-                double ta = 0.0, ex = 0, ey = 0, ez = 0;
-                stage_sample<double, GEOM>(r, beta, beta_dot, g, xm, q, k, i0 + lane, sh, ta, ex, ey, ez);
-                s_ta[wv][lane] = ta;
-                s_ek[wv][0][lane] = ex;
-                s_ek[wv][1][lane] = ey;
-                s_ek[wv][2][lane] = ez;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int cnt = (int)std::min<int64_t>(64, ns - i0);
-            double b0 = 0, b1 = 0, b2 = 0, b3 = 0, b4 = 0, b5 = 0;
-            for (int j = 0; j < cnt; ++j) {
-                const double x = nu * s_ta[wv][j];
-                const double fr = x - floor(x);  // revolutions in [0, 1)
-                double sn, c;
-                sincospi(2.0 * fr, &sn, &c);
-                const double e0 = s_ek[wv][0][j], e1 = s_ek[wv][1][j], e2 = s_ek[wv][2][j];
-                b0 += e0 * c;
-                b1 += e0 * sn;
-                b2 += e1 * c;
-                b3 += e1 * sn;
-                b4 += e2 * c;
-                b5 += e2 * sn;
-            }
-            a0 += b0;
-            a1 += b1;
-            a2 += b2;
-            a3 += b3;
-            a4 += b4;
-            a5 += b5;
-            __builtin_amdgcn_wave_barrier();
-        }
+    const int64_t j0 = A * kFdBlk;
+    return j0 + kFdBlk <= n ? 0.5 * omega[j0] + 0.5 * omega[j0 + kFdBlk - 1]
+                            : fma(0.5 * (kFdBlk - 1), dw, omega[j0]);
+}
+__device__ __forceinline__ double fd_step(const double *__restrict__ omega, int64_t n)
+{
+    return n > 1 ? (omega[n - 1] - omega[0]) / (double)(n - 1) : 0.0;
+}
+// whether the whole list is equally spaced (by the whole block of threads)
+__device__ __forceinline__ bool fd_equal(const double *__restrict__ omega, int64_t n, double dw)
+{
+    bool ok = true;
+    for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
+        const double c = fd_centre(omega, n, j / kFdBlk, dw);
+        const double pred = fma((double)(j % kFdBlk) - 0.5 * (kFdBlk - 1), dw, c);
+        ok &= fabs(omega[j] - pred) <= kFdTol64 * fmax(fabs(omega[j]), fabs(c));
     }
-    if (w_ok && k1 > k0) {
+    return __syncthreads_and(ok) != 0;
+}
+// frequency in cycles per second, as an unevaluated sum
+__device__ __forceinline__ double2 fd_cycles(double w)
+{
+    const double hi = w * kInv2Pi;
+    return make_double2(hi, fma(w, kInv2PiLo, fma(w, kInv2Pi, -hi)));
+}
+// cos and sin of the phase nu t (nu in cycles per second)
+__device__ __forceinline__ void fd_phasor(double2 nu, double t, double &c, double &s)
+{
+    const double x = nu.x * t;
+    const double fr = (x - floor(x)) + fma(nu.y, t, fma(nu.x, t, -x));
+    sincospi(2.0 * fr, &s, &c);
+}
+
+// A block of 256 threads owns one pixel, a tile of 256 W frequencies (W = 1, 2, 4) and a range of chunks of
+// kFdChunk samples.  Equal spacing: per kSub samples the two factors are formed in LDS, then wavefront
+// v takes the 8 frequency blocks v mod W (48 x 32 accumulators) and every (4 / W)-th group of samples.
+// Two blocks per compute unit: one forms phasors on the vector pipe while the other multiplies.
+constexpr int kFdChunk = 256;
+template <int W>
+struct alignas(16) Fd64Lds {
+    static constexpr int kSub = W == 1 ? 64 : 32;
+    static constexpr int kRows = 48 * W, kPitch = kRows + 16;  // pitch = 16 mod 32 doubles: a 4-sample operand
+    static constexpr int kPitchR = 48;                         // column read falls in distinct banks
+    double ta[kFdChunk], e[3][kFdChunk];
+    double2 nu[8 * W];
+    union {
+        struct {
+            double l[kSub][kPitch], r[kSub][kPitchR];
+        };
+        double sum[kRows][kFdBlk];
+    };
+};
+
+template <int GEOM, int W>
+__global__ __launch_bounds__(256, 2) void k_direct_fd(const double *__restrict__ r, const double *__restrict__ beta,
+                                                      const double *__restrict__ beta_dot,
+                                                      const double *__restrict__ charge,
+                                                      const double *__restrict__ x_det,
+                                                      const double *__restrict__ omega, double *__restrict__ acc,
+                                                      FdShape sh)
+{
+    using Lds = Fd64Lds<W>;
+    __shared__ Lds s;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t per_pix = sh.n_wblocks * sh.n_groups;
+    const int64_t m = blockIdx.x / per_pix, rem = blockIdx.x - m * per_pix;
+    const int64_t wb = rem / sh.n_groups, grp = rem - wb * sh.n_groups;
+    const int64_t w0 = wb * 256 * W;
+    const int64_t upp = (sh.n_samples + kFdChunk - 1) / kFdChunk;  // chunks per particle
+    const int64_t u0 = grp * sh.parts_per_group, u1 = std::min(u0 + sh.parts_per_group, upp * sh.n_particles);
+    const PixGeo g = pix_geo(x_det, m);
+    const double *xm = x_det + 3 * m;
+    const int64_t left = sh.n_omega - w0;  // frequencies of the tile
+    const double dw = fd_step(omega, sh.n_omega);
+    // stage chunk u: arrival times and E kappa; returns its number of samples
+    auto stage = [&](int64_t u) {
+        const int64_t k = u / upp, i0 = (u - k * upp) * kFdChunk;
+        double ta, ex, ey, ez;
+        stage_sample<double, GEOM>(r, beta, beta_dot, g, xm, charge ? charge[k] : -kQe, k, i0 + tid, sh, ta, ex, ey, ez);
+        s.ta[tid] = ta;
+        s.e[0][tid] = ex;
+        s.e[1][tid] = ey;
+        s.e[2][tid] = ez;
+        return (int)std::min<int64_t>(kFdChunk, sh.n_samples - i0);
+    };
+    if (fd_equal(omega, sh.n_omega, dw)) {
+        const int na = (int)std::min<int64_t>(8 * W, (left + kFdBlk - 1) / kFdBlk);
+        if (tid < 8 * W) s.nu[tid] = tid < na ? fd_cycles(fd_centre(omega, sh.n_omega, w0 / kFdBlk + tid, dw)) : make_double2(0.0, 0.0);
+        const double dnu = dw * kInv2Pi;
+        const int fw = wv % W, sw = wv / W;
+        const bool mine = 8 * fw < na;
+        v4d d[3][2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) d[i][0] = d[i][1] = v4d{0.0, 0.0, 0.0, 0.0};
+        for (int64_t u = u0; u < u1; ++u) {
+            const int n = stage(u);
+            __syncthreads();
+            for (int q0 = 0; q0 < n; q0 += Lds::kSub) {
+                // the factors of samples q0 .. q0 + kSub (past the chunk's end their field is zero)
+                for (int it = tid; it < Lds::kSub * 2 * W; it += 256) {
+                    const int q = it % Lds::kSub, a0 = it / Lds::kSub * 4;
+                    const double t = s.ta[q0 + q], e0 = s.e[0][q0 + q], e1 = s.e[1][q0 + q], e2 = s.e[2][q0 + q];
+#pragma unroll
+                    for (int a = a0; a < a0 + 4; ++a) {
+                        double c = 0.0, sn = 0.0;
+                        if (a < na) fd_phasor(s.nu[a], t, c, sn);
+                        double2 *o = (double2 *)&s.l[q][6 * a];
+                        o[0] = make_double2(e0 * c, e0 * sn);
+                        o[1] = make_double2(e1 * c, e1 * sn);
+                        o[2] = make_double2(e2 * c, e2 * sn);
+                    }
+                }
+                for (int it = tid; it < Lds::kSub * 16; it += 256) {
+                    const int q = it % Lds::kSub, h = it / Lds::kSub;
+                    const double x = ((double)h + 0.5) * dnu * s.ta[q0 + q];
+                    double c, sn;
+                    sincospi(2.0 * (x - floor(x)), &sn, &c);
+                    s.r[q][h] = c;
+                    s.r[q][16 + h] = sn;
+                }
+                __syncthreads();
+                if (mine) {
+#pragma unroll
+                    for (int q = 0; q < Lds::kSub / (4 / W); q += 4) {
+                        const int k = sw * (Lds::kSub / (4 / W)) + q + (lane >> 4);
+                        const double b0 = s.r[k][lane & 15], b1 = s.r[k][16 + (lane & 15)];
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            const double a = s.l[k][48 * fw + 16 * i + (lane & 15)];
+                            d[i][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b0, d[i][0], 0, 0, 0);
+                            d[i][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b1, d[i][1], 0, 0, 0);
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        // rows (block, component, re / im) x (cos h, sin h), summed over the wavefronts that share them
+        for (int it = tid; it < Lds::kRows * kFdBlk; it += 256) ((double *)s.sum)[it] = 0.0;
+        __syncthreads();
+        if (mine) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    double *o = s.sum[48 * fw + 16 * i + (lane >> 4) + 4 * v] + (lane & 15);
+                    atomicAdd(o, d[i][0][v]);
+                    atomicAdd(o + 16, d[i][1][v]);
+                }
+        }
+        __syncthreads();
+        for (int it = tid; it < (int)std::min<int64_t>(left, 256 * W) * 3; it += 256) {
+            const int j = it / 3, c = it - 3 * j, b = j % kFdBlk;
+            const double *re = s.sum[j / kFdBlk * 6 + 2 * c], *im = s.sum[j / kFdBlk * 6 + 2 * c + 1];
+            const int h = b >= 16 ? b - 16 : 15 - b;
+            const double sg = b >= 16 ? 1.0 : -1.0;
+            double *o = acc + ((size_t)m * sh.n_omega + w0 + j) * 6 + 2 * c;
+            atomic_add(o, fma(-sg, im[16 + h], re[h]));
+            atomic_add(o + 1, fma(sg, re[16 + h], im[h]));
+        }
+        return;
+    }
+    // any frequencies: wavefront v takes the tile's frequencies 64 (v + 4 f) + lane, f < W
+    double nu[W], a[W][6];
+#pragma unroll
+    for (int f = 0; f < W; ++f) {
+        const int64_t w = w0 + 64 * (wv + 4 * f) + lane;
+        nu[f] = w < sh.n_omega ? omega[w] / (2.0 * kPi) : 0.0;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) a[f][c] = 0.0;
+    }
+    for (int64_t u = u0; u < u1; ++u) {
+        const int n = stage(u);
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < W; ++f) {
+            if (64 * (wv + 4 * f) >= left) continue;
+            for (int q0 = 0; q0 < n; q0 += 64) {
+                double b0 = 0, b1 = 0, b2 = 0, b3 = 0, b4 = 0, b5 = 0;
+                for (int q = q0; q < std::min(q0 + 64, n); ++q) {
+                    const double x = nu[f] * s.ta[q];
+                    double sn, c;
+                    sincospi(2.0 * (x - floor(x)), &sn, &c);
+                    const double e0 = s.e[0][q], e1 = s.e[1][q], e2 = s.e[2][q];
+                    b0 += e0 * c;
+                    b1 += e0 * sn;
+                    b2 += e1 * c;
+                    b3 += e1 * sn;
+                    b4 += e2 * c;
+                    b5 += e2 * sn;
+                }
+                a[f][0] += b0;
+                a[f][1] += b1;
+                a[f][2] += b2;
+                a[f][3] += b3;
+                a[f][4] += b4;
+                a[f][5] += b5;
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int f = 0; f < W; ++f) {
+        const int64_t w = w0 + 64 * (wv + 4 * f) + lane;
+        if (w >= sh.n_omega) continue;
         double *o = acc + ((size_t)m * sh.n_omega + w) * 6;
-        atomicAdd(o + 0, a0);
-        atomicAdd(o + 1, a1);
-        atomicAdd(o + 2, a2);
-        atomicAdd(o + 3, a3);
-        atomicAdd(o + 4, a4);
-        atomicAdd(o + 5, a5);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) atomic_add(o + c, a[f][c]);
     }
 }
 
-template <int GEOM, int K>
-__global__ __launch_bounds__(256) void k_direct_fd_mixed(const double *__restrict__ r,
-                                                         const double *__restrict__ beta,
-                                                         const double *__restrict__ beta_dot,
-                                                         const double *__restrict__ charge,
-                                                         const double *__restrict__ x_det,
-                                                         const double *__restrict__ omega, double *__restrict__ acc,
-                                                         FdShape sh)
+// ---------------------------------------------------------------------------------------------
+// Mixed sums.  A block of W wavefronts owns one pixel, W x 64 K frequencies and a range of chunks of 64 W
+// samples.  The samples are staged once for the W wavefronts (the field and the arrival time are ~150 FP64
+// instructions a sample); the sums run on the matrix cores: a 4x4x1 product holds 16 blocks of 4 columns, so
+// that with the sample's (E_x, E_y, E_z, 0) in every block's rows and the lane's phasor in its column it is
+// the three multiply-adds of 64 lanes, each rounded as fmaf rounds, in two passes instead of three.  The vector
+// pipe is left with the phasors.  The two kinds of instruction don't overlap (measured: 10.5 cycles a 4x4x1 product,
+// 4.4 a vector FMA, ~8 for each change from one to the other), so they come in batches of kFdBatch samples.
+// 25 x 20001 samples, 64 pixels, 4096 frequencies: 34.0 ms (six vector FMAs a term, every wavefront staging for
+// itself) -> 25.6 ms; a batch of one sample 26.1, four 25.4, instructions mixed by the compiler 31.9.
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int kFdBatch = 2;
+
+template <int GEOM, int K, int W>
+__global__ __launch_bounds__(64 * W, 2) void k_direct_fd_mixed(const double *__restrict__ r,
+                                                               const double *__restrict__ beta,
+                                                               const double *__restrict__ beta_dot,
+                                                               const double *__restrict__ charge,
+                                                               const double *__restrict__ x_det,
+                                                               const double *__restrict__ omega,
+                                                               double *__restrict__ acc, FdShape sh)
 {
-    __shared__ double s_tref[kWavesPerBlock];
-    __shared__ float s_dtf[kWavesPerBlock][64];     // t_a - t_ref (s)
-    __shared__ float2 s_step[kWavesPerBlock][64];   // e^{i dw t_a}
-    __shared__ float s_ek[kWavesPerBlock][3][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+    constexpr int NS = 64 * W;
+    __shared__ float4 s_t[W][NS];  // per wavefront's frequencies: t_a - t_ref (s), e^{i dw t_a}
+    __shared__ float s_e[NS][4];   // E kappa
+    __shared__ double s_tref[W], s_dnu[W];
+    __shared__ int s_eq[W];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t per_pix = sh.n_wblocks * sh.n_groups;
-    const int64_t m = wave / per_pix;
-    if (m >= sh.n_pix) return;  // whole wavefront idle; no block-level sync below
-    const int64_t rem = wave - m * per_pix;
+    const int64_t m = blockIdx.x / per_pix, rem = blockIdx.x - m * per_pix;
     const int64_t wb = rem / sh.n_groups, grp = rem - wb * sh.n_groups;
-    const int64_t wfirst = wb * 64 * K, wl = wfirst + (int64_t)lane * K;
+    const int64_t wfirst = (wb * W + wv) * 64 * K, wl = wfirst + (int64_t)lane * K;
+    const int64_t ns = sh.n_samples, upp = (ns + NS - 1) / NS;  // chunks per particle
+    const int64_t u0 = grp * sh.parts_per_group, u1 = std::min(u0 + sh.parts_per_group, upp * sh.n_particles);
+    const bool mine = wfirst < sh.n_omega;
     // frequencies in cycles per second; the wavefront's spacing from its first two
     double nu[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) nu[j] = wl + j < sh.n_omega ? omega[wl + j] / (2.0 * kPi) : 0.0;
-    const double nu_a = omega[wfirst] / (2.0 * kPi);
+    const double nu_a = mine ? omega[wfirst] / (2.0 * kPi) : 0.0;
     const double dnu = wfirst + 1 < sh.n_omega ? omega[wfirst + 1] / (2.0 * kPi) - nu_a : 0.0;
     bool lane_eq = true;
 #pragma unroll
@@ -189,82 +358,93 @@ __global__ __launch_bounds__(256) void k_direct_fd_mixed(const double *__restric
         if (wl + j < sh.n_omega) lane_eq &= fabs(nu[j] - pred) <= kFdEqualTol * fabs(nu[j]);
     }
     const bool equal = __ballot(!lane_eq) == 0;  // wavefront-uniform
-    const int64_t k0 = grp * sh.parts_per_group, k1 = std::min(k0 + sh.parts_per_group, sh.n_particles);
-    PixGeo g = pix_geo(x_det, m);
+    if (lane == 0) {
+        s_dnu[wv] = dnu;
+        s_eq[wv] = equal && mine;
+    }
+    __syncthreads();
+    const PixGeo g = pix_geo(x_det, m);
     const double *xm = x_det + 3 * m;
     double a[K][6];
 #pragma unroll
     for (int j = 0; j < K; ++j)
 #pragma unroll
         for (int c = 0; c < 6; ++c) a[j][c] = 0.0;
-    const int64_t ns = sh.n_samples;
-    for (int64_t k = k0; k < k1; ++k) {
-        const double q = charge ? charge[k] : -kQe;
-        for (int64_t i0 = 0; i0 < ns; i0 += 64) {
-            // stage: lane -> sample i0 + lane
-            {
-                double ta = 0.0;
-                float ex = 0, ey = 0, ez = 0;
-                stage_sample<float, GEOM>(r, beta, beta_dot, g, xm, q, k, i0 + lane, sh, ta, ex, ey, ez);
-                const bool live = ex != 0.0f || ey != 0.0f || ez != 0.0f;
-                // reference arrival time: the first lane with a contribution
-                const uint64_t lm = __ballot(live);
-                const double tref = lm ? readlane_f64(ta, (int)__builtin_ctzll(lm)) : 0.0;
-                s_dtf[wv][lane] = live ? (float)(ta - tref) : 0.0f;
-                if (lane == 0) s_tref[wv] = tref;
+    for (int64_t u = u0; u < u1; ++u) {
+        const int64_t k = u / upp, i0 = (u - k * upp) * NS;
+        {
+            double ta = 0.0;
+            float ex = 0, ey = 0, ez = 0;
+            stage_sample<float, GEOM>(r, beta, beta_dot, g, xm, charge ? charge[k] : -kQe, k, i0 + tid, sh, ta, ex, ey, ez);
+            const bool live = ex != 0.0f || ey != 0.0f || ez != 0.0f;
+            // reference arrival time of 64 samples: the first with a contribution
+            const uint64_t lm = __ballot(live);
+            const double tref = lm ? readlane_f64(ta, (int)__builtin_ctzll(lm)) : 0.0;
+            if (lane == 0) s_tref[wv] = tref;
+            const float dt = live ? (float)(ta - tref) : 0.0f;
+#pragma unroll
+            for (int v = 0; v < W; ++v) {
                 float2 st = make_float2(1.0f, 0.0f);
-                if (equal && live) {
-                    const double x = dnu * ta;
+                if (s_eq[v] && live) {
+                    const double x = s_dnu[v] * ta;
                     const float fr = (float)(x - floor(x));  // revolutions in [0, 1)
                     st = make_float2(__builtin_amdgcn_cosf(fr), __builtin_amdgcn_sinf(fr));
                 }
-                s_step[wv][lane] = st;
-                s_ek[wv][0][lane] = ex;
-                s_ek[wv][1][lane] = ey;
-                s_ek[wv][2][lane] = ez;
+                s_t[v][tid] = make_float4(dt, st.x, st.y, 0.0f);
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int cnt = (int)std::min<int64_t>(64, ns - i0);
-            const double tref = s_tref[wv];
-            float b[K][6];
+            *(float4 *)s_e[tid] = make_float4(ex, ey, ez, 0.0f);
+        }
+        __syncthreads();
+        for (int ch = 0; ch < W && mine; ++ch) {
+            // staged samples past the end have a zero field
+            const int cnt = ((int)std::min<int64_t>(64, ns - i0 - 64 * ch) + 3) & ~3;
+            if (cnt <= 0) break;
+            const double tref = s_tref[ch];
+            const float4 *st4 = s_t[wv] + 64 * ch;
+            const float *ep = &s_e[64 * ch][lane & 3];
+            v4f b[K][2];
 #pragma unroll
-            for (int j = 0; j < K; ++j)
-#pragma unroll
-                for (int c = 0; c < 6; ++c) b[j][c] = 0.0f;
+            for (int j = 0; j < K; ++j) b[j][0] = b[j][1] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
             if (equal) {
                 const double x = nu[0] * tref;
                 const float base = (float)(x - floor(x));  // revolutions in [0, 1)
                 const float nuf = (float)nu[0];
-                for (int s = 0; s < cnt; ++s) {
-                    const float ph = fmaf(nuf, s_dtf[wv][s], base);
-                    // phasors p_j = e^{i(w_0 + j dw)t}: p_1 = p_0 e^{i dw t}, then the two-term
-                    // recurrence p_{j+1} = 2 cos(dw t) p_j - p_{j-1} (two FMAs per frequency)
-                    float c = __builtin_amdgcn_cosf(ph), sn = __builtin_amdgcn_sinf(ph);
-                    const float e0 = s_ek[wv][0][s], e1 = s_ek[wv][1][s], e2 = s_ek[wv][2][s];
-                    const float2 st = s_step[wv][s];
-                    const float tc = st.x + st.x;
-                    float cp = 0.0f, sp = 0.0f;
+                // phasors p_j = e^{i(w_0 + j dw)t}: p_1 = p_0 e^{i dw t}, then the two-term recurrence
+                // p_{j+1} = 2 cos(dw t) p_j - p_{j-1} (two FMAs per frequency)
+                auto phasors = [&](const float4 q, float *pc, float *ps) {
+                    const float ph = fmaf(nuf, q.x, base);
+                    pc[0] = __builtin_amdgcn_cosf(ph);
+                    ps[0] = __builtin_amdgcn_sinf(ph);
+                    const float tc = q.y + q.y;
+                    if constexpr (K > 1) {
+                        pc[1] = fmaf(pc[0], q.y, -ps[0] * q.z);
+                        ps[1] = fmaf(pc[0], q.z, ps[0] * q.y);
+                    }
 #pragma unroll
-                    for (int j = 0; j < K; ++j) {
-                        b[j][0] = fmaf(e0, c, b[j][0]);
-                        b[j][1] = fmaf(e0, sn, b[j][1]);
-                        b[j][2] = fmaf(e1, c, b[j][2]);
-                        b[j][3] = fmaf(e1, sn, b[j][3]);
-                        b[j][4] = fmaf(e2, c, b[j][4]);
-                        b[j][5] = fmaf(e2, sn, b[j][5]);
-                        if (j == 0 && K > 1) {
-                            cp = c;
-                            sp = sn;
-                            c = fmaf(cp, st.x, -sp * st.y);
-                            sn = fmaf(cp, st.y, sp * st.x);
-                        } else if (j + 1 < K) {
-                            const float cn = fmaf(tc, c, -cp), sn2 = fmaf(tc, sn, -sp);
-                            cp = c;
-                            sp = sn;
-                            c = cn;
-                            sn = sn2;
+                    for (int j = 2; j < K; ++j) {
+                        pc[j] = fmaf(tc, pc[j - 1], -pc[j - 2]);
+                        ps[j] = fmaf(tc, ps[j - 1], -ps[j - 2]);
+                    }
+                };
+                // matrix and vector instructions in turn cost ~8 cycles a change: batches of kFdBatch samples each
+                for (int s = 0; s < cnt; s += 4) {
+#pragma unroll
+                    for (int v0 = 0; v0 < 4; v0 += kFdBatch) {
+                        float pc[kFdBatch][K], ps[kFdBatch][K], e[kFdBatch];
+#pragma unroll
+                        for (int v = 0; v < kFdBatch; ++v) {
+                            e[v] = ep[4 * (s + v0 + v)];
+                            phasors(st4[s + v0 + v], pc[v], ps[v]);
                         }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int v = 0; v < kFdBatch; ++v)
+#pragma unroll
+                            for (int j = 0; j < K; ++j) {
+                                b[j][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(e[v], pc[v][j], b[j][0], 0, 0, 0);
+                                b[j][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(e[v], ps[v][j], b[j][1], 0, 0, 0);
+                            }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             } else {
@@ -276,36 +456,31 @@ __global__ __launch_bounds__(256) void k_direct_fd_mixed(const double *__restric
                     nuf[j] = (float)nu[j];
                 }
                 for (int s = 0; s < cnt; ++s) {
-                    const float dtf = s_dtf[wv][s];
-                    const float e0 = s_ek[wv][0][s], e1 = s_ek[wv][1][s], e2 = s_ek[wv][2][s];
+                    const float dtf = st4[s].x, e = ep[4 * s];
 #pragma unroll
                     for (int j = 0; j < K; ++j) {
                         const float ph = fmaf(nuf[j], dtf, base[j]);
-                        const float c = __builtin_amdgcn_cosf(ph), sn = __builtin_amdgcn_sinf(ph);
-                        b[j][0] = fmaf(e0, c, b[j][0]);
-                        b[j][1] = fmaf(e0, sn, b[j][1]);
-                        b[j][2] = fmaf(e1, c, b[j][2]);
-                        b[j][3] = fmaf(e1, sn, b[j][3]);
-                        b[j][4] = fmaf(e2, c, b[j][4]);
-                        b[j][5] = fmaf(e2, sn, b[j][5]);
+                        b[j][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(e, __builtin_amdgcn_cosf(ph), b[j][0], 0, 0, 0);
+                        b[j][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(e, __builtin_amdgcn_sinf(ph), b[j][1], 0, 0, 0);
                     }
                 }
             }
 #pragma unroll
             for (int j = 0; j < K; ++j)
 #pragma unroll
-                for (int c = 0; c < 6; ++c) a[j][c] += (double)b[j][c];
-            __builtin_amdgcn_wave_barrier();
+                for (int c = 0; c < 3; ++c) {
+                    a[j][2 * c] += (double)b[j][0][c];
+                    a[j][2 * c + 1] += (double)b[j][1][c];
+                }
         }
+        __syncthreads();
     }
-    if (k1 > k0) {
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-            if (wl + j >= sh.n_omega) continue;
-            double *o = acc + ((size_t)m * sh.n_omega + wl + j) * 6;
+    for (int j = 0; j < K; ++j) {
+        if (wl + j >= sh.n_omega) continue;
+        double *o = acc + ((size_t)m * sh.n_omega + wl + j) * 6;
 #pragma unroll
-            for (int c = 0; c < 6; ++c) atomicAdd(o + c, a[j][c]);
-        }
+        for (int c = 0; c < 6; ++c) atomic_add(o + c, a[j][c]);
     }
 }
 
@@ -328,44 +503,66 @@ __global__ void k_fd_finish(const double *__restrict__ acc, double *__restrict__
 //   dJ/dA_c = 2f sum_w dS(w) (R_c cos wt + I_c sin wt),
 //   dJ/dt   = 2f sum_w dS(w) w sum_c A_c (I_c cos wt - R_c sin wt),       f = dt^2 / 2pi,
 // then dJ/dE = kappa dJ/dA, dJ/dkappa = E.dJ/dA through lw_field_vjp, and dt/dr = -n/c.
-// A wavefront owns 64 consecutive samples of one particle (one per lane) and loops over every
-// pixel; the frequencies are staged 64 at a time in LDS.  Each sample is owned by one lane, so
-// the gradient is added without atomics.
+//
+// A block owns 64 consecutive samples of one particle and loops over the pixels, four at a time: wavefront
+// v takes the field, arrival time and Jacobian of pixel 4 n + v (lanes over samples), all four the sums of
+// each pixel.  With C = dS F (and w dS F for dJ/dt) the sums are the real (imaginary) parts of
+// sum_w C(w) e^{-iwt}; for equally spaced frequencies (blocks and offsets as in the forward sums)
+//   sum_w C e^{-iwt} = sum_A e^{-i w_A t} sum_h [cos h dw t (C+ + C-) - i sin h dw t (C+ - C-)]_A,
+// the inner sum a matrix product over the 32 cosines and sines of a sample, 12 columns (6 quantities, re and
+// im) per block of 32 frequencies, four blocks (48 columns) at a time: 12 multiply-adds a term on the matrix
+// cores and 1/32 sine/cosine pair.  Each sample is owned by one block: no atomics on the gradient.
+// 20 x 2001 samples, 9 pixels, 1024 frequencies: 2071 us with a sine/cosine pair per term -> 444 us (112 us of it
+// the matrix product).
+struct alignas(16) FdBwdLds {
+    double nu[4][64], ta[4][64];  // any-frequency path: staged frequencies; arrival times of four pixels
+    double g[4][6][64];           // G_c, K_c of four pixels
+    union {
+        struct {
+            double w[32][48];    // coefficients of the four blocks
+            double p[4][64][2];  // cos, sin of w_A t
+        };
+        double row[4][64][8];  // any-frequency path: dS, w dS, R_x, I_x, R_y, I_y, R_z, I_z
+        double red[4][9][64];  // the wavefronts' gradients
+    };
+};
+
 template <int GEOM>
-__global__ __launch_bounds__(256) void k_direct_fd_bwd(const double *__restrict__ r, const double *__restrict__ beta,
-                                                       const double *__restrict__ beta_dot,
-                                                       const double *__restrict__ charge,
-                                                       const double *__restrict__ x_det,
-                                                       const double *__restrict__ omega,
-                                                       const double *__restrict__ acc, const double *__restrict__ dS,
-                                                       double *__restrict__ d_r, double *__restrict__ d_beta,
-                                                       double *__restrict__ d_beta_dot, FdShape sh, double two_f)
+__global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restrict__ r, const double *__restrict__ beta,
+                                                          const double *__restrict__ beta_dot,
+                                                          const double *__restrict__ charge,
+                                                          const double *__restrict__ x_det,
+                                                          const double *__restrict__ omega,
+                                                          const double *__restrict__ acc, const double *__restrict__ dS,
+                                                          double *__restrict__ d_r, double *__restrict__ d_beta,
+                                                          double *__restrict__ d_beta_dot, FdShape sh, double two_f)
 {
-    __shared__ double s_w[kWavesPerBlock][64][8];  // dS, w dS, R_x, I_x, R_y, I_y, R_z, I_z
-    __shared__ double s_nu[kWavesPerBlock][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+    __shared__ FdBwdLds s;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n_chunks = (sh.n_samples + 63) / 64;
-    const int64_t k = wave / n_chunks;
-    if (k >= sh.n_particles) return;  // whole wavefront idle; no block-level sync below
-    const int64_t i = (wave - k * n_chunks) * 64 + lane;
+    const int64_t k = blockIdx.x / n_chunks;
+    const int64_t i = (blockIdx.x - k * n_chunks) * 64 + lane;
     const bool in = i < sh.n_samples;
-    const size_t s = (size_t)(k * sh.n_samples + (in ? i : 0)) * 3;
+    const size_t so = (size_t)(k * sh.n_samples + (in ? i : 0)) * 3;
     double rs[3], bs[3], as[3];
     for (int c = 0; c < 3; ++c) {
-        rs[c] = r[s + c];
-        bs[c] = beta[s + c];
-        as[c] = beta_dot[s + c];
+        rs[c] = r[so + c];
+        bs[c] = beta[so + c];
+        as[c] = beta_dot[so + c];
     }
     const bool usable = in && sample_usable(rs, bs, as);
     const double q = charge ? charge[k] : -kQe;
     const double u = sh.cdt / kC;
     const double d = arrival_base(sh.t_start, sh.dt, (double)i, sh.t0, u, rs[2]);
     double gr[3] = {0, 0, 0}, gb[3] = {0, 0, 0}, ga[3] = {0, 0, 0};
-    for (int64_t m = 0; m < sh.n_pix; ++m) {
-        const PixGeo g = pix_geo(x_det, m);
-        const double *xm = x_det + 3 * m;
-        bool ok = usable && g.ok;
+    const int64_t n_w = sh.n_omega;
+    const double dw = fd_step(omega, n_w), dnu = dw * kInv2Pi;
+    const bool equal = fd_equal(omega, n_w, dw);
+    for (int64_t m0 = 0; m0 < sh.n_pix; m0 += 4) {
+        const int64_t m = m0 + wv;
+        PixGeo g = pix_geo(x_det, m < sh.n_pix ? m : 0);
+        const double *xm = x_det + 3 * (m < sh.n_pix ? m : 0);
+        bool ok = usable && g.ok && m < sh.n_pix;
         double ta = 0.0, kap = 0.0, E[3] = {0, 0, 0}, A[3] = {0, 0, 0};
         if (ok) {
             lw_field<double, GEOM>(g, xm, rs[0], rs[1], rs[2], bs[0], bs[1], bs[2], as[0], as[1], as[2], q, sh.fmask,
@@ -374,48 +571,133 @@ __global__ __launch_bounds__(256) void k_direct_fd_bwd(const double *__restrict_
             for (int c = 0; c < 3; ++c) A[c] = E[c] * kap;
             ok = isfinite(ta) && isfinite(A[0]) && isfinite(A[1]) && isfinite(A[2]);
         }
-        double G[3] = {0, 0, 0}, K[3] = {0, 0, 0};
-        for (int64_t w0 = 0; w0 < sh.n_omega; w0 += 64) {
-            {
-                const int64_t w = w0 + lane;
-                double *row = s_w[wv][lane];
-                if (w < sh.n_omega) {
-                    const double *f = acc + ((size_t)m * sh.n_omega + w) * 6;
-                    const double d = dS[(size_t)m * sh.n_omega + w];
-                    s_nu[wv][lane] = omega[w] / (2.0 * kPi);
-                    row[0] = d;
-                    row[1] = d * omega[w];
-                    for (int c = 0; c < 6; ++c) row[2 + c] = f[c];
-                } else {
-                    s_nu[wv][lane] = 0.0;
-                    for (int c = 0; c < 8; ++c) row[c] = 0.0;
+        s.ta[wv][lane] = ok ? ta : 0.0;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) s.g[wv][c][lane] = 0.0;
+        __syncthreads();
+        const int np = (int)std::min<int64_t>(4, sh.n_pix - m0);
+        for (int p = 0; p < np; ++p) {
+            const double *fs = acc + (size_t)(m0 + p) * n_w * 6, *ds = dS + (size_t)(m0 + p) * n_w;
+            if (equal) {
+                // this lane's operand: cos / sin of h dw t of sample 16 wv + lane % 16, h - 1/2 = lane / 16 + 4 j
+                const double tl = s.ta[p][16 * wv + (lane & 15)];
+                double av[8];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double x = ((double)(4 * j + (lane >> 4)) + 0.5) * dnu * tl;
+                    sincospi(2.0 * (x - floor(x)), &av[4 + j], &av[j]);
                 }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int cnt = (int)std::min<int64_t>(64, sh.n_omega - w0);
-            if (ok) {
-                for (int j = 0; j < cnt; ++j) {
-                    const double x = s_nu[wv][j] * ta;
-                    double sn, cs;
-                    sincospi(2.0 * (x - floor(x)), &sn, &cs);
-                    const double *row = s_w[wv][j];
-                    for (int c = 0; c < 3; ++c) {
-                        const double Rc = row[2 + 2 * c], Ic = row[3 + 2 * c];
-                        G[c] = fma(row[0], fma(Rc, cs, Ic * sn), G[c]);
-                        K[c] = fma(row[1], fma(Ic, cs, -Rc * sn), K[c]);
+                double sum[3][4];
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) sum[t][v] = 0.0;
+                for (int64_t w0 = 0; w0 < n_w; w0 += 4 * kFdBlk) {
+                    if (tid < 192) {  // block a, offset h, component c
+                        const int c = tid % 3, h = tid / 3 % 16, a = tid / 48;
+                        const int64_t jp = w0 + kFdBlk * a + 16 + h, jm = w0 + kFdBlk * a + 15 - h;
+                        double cp[2] = {0, 0}, cm[2] = {0, 0}, wp = 0.0, wm = 0.0;
+                        if (jp < n_w) {
+                            cp[0] = ds[jp] * fs[jp * 6 + 2 * c];
+                            cp[1] = ds[jp] * fs[jp * 6 + 2 * c + 1];
+                            wp = omega[jp];
+                        }
+                        if (jm < n_w) {
+                            cm[0] = ds[jm] * fs[jm * 6 + 2 * c];
+                            cm[1] = ds[jm] * fs[jm * 6 + 2 * c + 1];
+                            wm = omega[jm];
+                        }
+#pragma unroll
+                        for (int z = 0; z < 2; ++z) {  // C, then w C
+                            double *o = &s.w[h][12 * a + 6 * z + 2 * c], *o2 = &s.w[16 + h][12 * a + 6 * z + 2 * c];
+                            o[0] = cp[0] + cm[0];
+                            o[1] = cp[1] + cm[1];
+                            o2[0] = cp[1] - cm[1];
+                            o2[1] = cm[0] - cp[0];
+#pragma unroll
+                            for (int e = 0; e < 2; ++e) {
+                                cp[e] *= wp;
+                                cm[e] *= wm;
+                            }
+                        }
                     }
+                    {  // block wv's phase at sample `lane`
+                        double cs = 0.0, sn = 0.0;
+                        if (w0 + kFdBlk * wv < n_w)
+                            fd_phasor(fd_cycles(fd_centre(omega, n_w, w0 / kFdBlk + wv, dw)), s.ta[p][lane], cs, sn);
+                        *(double2 *)s.p[wv][lane] = make_double2(cs, sn);
+                    }
+                    __syncthreads();
+                    v4d t3[3];
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) t3[t] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+#pragma unroll
+                        for (int t = 0; t < 3; ++t)
+                            t3[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[j], s.w[4 * j + (lane >> 4)][16 * t + (lane & 15)],
+                                                                         t3[t], 0, 0, 0);
+                    // column -> block a, quantity z (< 3: real part wanted, else imaginary), re / im: the part of
+                    // (cos - i sin) (re + i im) it feeds (the sign of K's -sin re is applied at the end)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        const int col = 16 * t + (lane & 15), a = col / 12, z = col % 12 / 2, ri = col & 1;
+                        const double *pp = &s.p[a][16 * wv + (lane >> 4)][z < 3 ? ri : 1 - ri];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sum[t][v] = fma(t3[t][v], pp[8 * v], sum[t][v]);
+                    }
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    const int col = 16 * t + (lane & 15), z = col % 12 / 2, ri = col & 1;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        atomicAdd(&s.g[p][z][16 * wv + (lane >> 4) + 4 * v], z >= 3 && ri == 0 ? -sum[t][v] : sum[t][v]);
+                }
+            } else {
+                // any frequencies: lanes over samples, wavefront v takes every fourth 64 frequencies
+                const double tl = s.ta[p][lane];
+                double G[3] = {0, 0, 0}, K[3] = {0, 0, 0};
+                for (int64_t w0 = 64 * wv; w0 < n_w; w0 += 256) {
+                    const int64_t w = w0 + lane;
+                    double *row = s.row[wv][lane];
+                    const double dv = w < n_w ? ds[w] : 0.0, ov = w < n_w ? omega[w] : 0.0;
+                    s.nu[wv][lane] = ov / (2.0 * kPi);
+                    row[0] = dv;
+                    row[1] = dv * ov;
+                    for (int c = 0; c < 6; ++c) row[2 + c] = w < n_w ? fs[w * 6 + c] : 0.0;
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    const int cnt = (int)std::min<int64_t>(64, n_w - w0);
+                    for (int j = 0; j < cnt; ++j) {
+                        const double x = s.nu[wv][j] * tl;
+                        double sn, cs;
+                        sincospi(2.0 * (x - floor(x)), &sn, &cs);
+                        const double *rj = s.row[wv][j];
+                        for (int c = 0; c < 3; ++c) {
+                            const double Rc = rj[2 + 2 * c], Ic = rj[3 + 2 * c];
+                            G[c] = fma(rj[0], fma(Rc, cs, Ic * sn), G[c]);
+                            K[c] = fma(rj[1], fma(Ic, cs, -Rc * sn), K[c]);
+                        }
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                }
+                for (int c = 0; c < 3; ++c) {
+                    atomicAdd(&s.g[p][c][lane], G[c]);
+                    atomicAdd(&s.g[p][3 + c][lane], K[c]);
                 }
             }
-            __builtin_amdgcn_wave_barrier();
         }
+        __syncthreads();
         if (ok) {
-            double gE[3], gk = 0.0, H = 0.0;
+            double G[3], gE[3], gk = 0.0, H = 0.0;
             for (int c = 0; c < 3; ++c) {
-                G[c] *= two_f;
+                G[c] = two_f * s.g[wv][c][lane];
                 gE[c] = kap * G[c];
                 gk = fma(E[c], G[c], gk);
-                H = fma(A[c], two_f * K[c], H);
+                H = fma(A[c], two_f * s.g[wv][3 + c][lane], H);
             }
             lw_field_vjp<GEOM>(g, xm, rs, bs, as, q, sh.fmask, gE, gr, gb, ga, gk);
             // t = t_i + (|x - r| - |x|)/c - t0 (exact) or t_i - n.r/c - t0 (far field): dt/dr = -n/c
@@ -430,11 +712,20 @@ __global__ __launch_bounds__(256) void k_direct_fd_bwd(const double *__restrict_
             for (int c = 0; c < 3; ++c) gr[c] -= H * n[c] / kC;
         }
     }
-    if (in) {
+    // the wavefronts' gradients, summed in their order
+    __syncthreads();
+    for (int c = 0; c < 3; ++c) {
+        s.red[wv][c][lane] = gr[c];
+        s.red[wv][3 + c][lane] = gb[c];
+        s.red[wv][6 + c][lane] = ga[c];
+    }
+    __syncthreads();
+    if (in && wv < 3) {
+        double *out = wv == 0 ? d_r : wv == 1 ? d_beta : d_beta_dot;
         for (int c = 0; c < 3; ++c) {
-            d_r[s + c] += gr[c];
-            d_beta[s + c] += gb[c];
-            d_beta_dot[s + c] += ga[c];
+            double v = s.red[0][3 * wv + c][lane];
+            for (int w = 1; w < 4; ++w) v += s.red[w][3 * wv + c][lane];
+            out[so + c] += v;
         }
     }
 }
@@ -446,65 +737,105 @@ size_t direct_fd_ws_bytes(int64_t n_pix, int64_t n_omega)
     return (size_t)std::max<int64_t>(n_pix * n_omega, 1) * 6 * sizeof(double);
 }
 
-lw_status launch_direct_fd(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, int64_t n_omega, int prec,
-                           int fmask, int geom, double *S, void *ws, size_t ws_bytes, hipStream_t s)
+namespace {
+
+FdShape fd_shape(const lw_traj_t *t, const lw_grid_t *gr, int64_t n_omega, int fmask)
 {
-    const int64_t n_pix = gr->n_pix;
-    const int64_t nS = n_pix * n_omega;
-    if (nS == 0) return LW_OK;
-    double *acc = (double *)ws;
-    k_fd_zero<<<(int)std::min<int64_t>((6 * nS + 255) / 256, 65536), 256, 0, s>>>(acc, 6 * nS);
     FdShape sh;
     sh.n_particles = t->n_particles;
     sh.n_samples = t->n_samples;
-    sh.n_pix = n_pix;
+    sh.n_pix = gr->n_pix;
     sh.n_omega = n_omega;
-    // frequencies per lane (mixed): the largest power of two <= kFdFreq that still fills a wavefront
-    int K = 1;
-    while (K < kFdFreq && 64 * 2 * K <= n_omega) K *= 2;
-    const int64_t per_wave = prec == LW_PREC_FP64 ? 64 : 64 * K;  // frequencies per wavefront
-    sh.n_wblocks = (n_omega + per_wave - 1) / per_wave;
-    const int64_t base = n_pix * sh.n_wblocks;
-    int64_t groups = std::max<int64_t>(1, (8192 + base - 1) / base);
-    groups = std::min<int64_t>(groups, std::max<int64_t>(t->n_particles, 1));
-    sh.parts_per_group = (std::max<int64_t>(t->n_particles, 1) + groups - 1) / groups;
-    sh.n_groups = (std::max<int64_t>(t->n_particles, 1) + sh.parts_per_group - 1) / sh.parts_per_group;
+    sh.n_wblocks = sh.n_groups = sh.parts_per_group = 0;
     sh.t_start = t->t_start;
     sh.dt = t->dt;
     sh.t0 = gr->t0;
     // any positive grid step gives the same arrival times; use dt (the grid of this call is irrelevant)
-    const double dts = t->dt;
-    sh.cdt = kC * dts;
+    sh.cdt = kC * t->dt;
     sh.inv_cdt = 1.0 / sh.cdt;
     sh.fmask = fmask;
-    if (t->n_particles > 0) {
-        const int64_t waves = base * sh.n_groups;
-        const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-        if (blocks > 0x7fffffff) return fail(LW_E_SHAPE, "lw_direct_fd: problem too large for one launch");
-        if (prec == LW_PREC_FP64) {
-            if (geom == LW_GEOM_EXACT)
-                k_direct_fd<LW_GEOM_EXACT><<<(unsigned)blocks, 256, 0, s>>>(
-                    t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
-            else
-                k_direct_fd<LW_GEOM_FARFIELD><<<(unsigned)blocks, 256, 0, s>>>(
-                    t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
-        } else {
-#define LW_FD_MIXED(G, KK)                                                                                        \
-    k_direct_fd_mixed<G, KK><<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, \
-                                                               acc, sh)
-            if (geom == LW_GEOM_EXACT) {
-                if (K == 8) LW_FD_MIXED(LW_GEOM_EXACT, 8);
-                else if (K == 4) LW_FD_MIXED(LW_GEOM_EXACT, 4);
-                else if (K == 2) LW_FD_MIXED(LW_GEOM_EXACT, 2);
-                else LW_FD_MIXED(LW_GEOM_EXACT, 1);
-            } else {
-                if (K == 8) LW_FD_MIXED(LW_GEOM_FARFIELD, 8);
-                else if (K == 4) LW_FD_MIXED(LW_GEOM_FARFIELD, 4);
-                else if (K == 2) LW_FD_MIXED(LW_GEOM_FARFIELD, 2);
-                else LW_FD_MIXED(LW_GEOM_FARFIELD, 1);
-            }
-#undef LW_FD_MIXED
-        }
+    return sh;
+}
+
+// chunks of samples per group, so that about `rounds` times `resident` blocks run; returns the blocks (0: too many)
+int64_t fd_groups(FdShape &sh, int64_t chunk, int64_t resident, int64_t rounds)
+{
+    const int64_t base = sh.n_pix * sh.n_wblocks;
+    const int64_t units = std::max<int64_t>(1, sh.n_particles * ((sh.n_samples + chunk - 1) / chunk));
+    const int64_t groups = std::max<int64_t>(1, std::min(units, resident * rounds / base));
+    sh.parts_per_group = (units + groups - 1) / groups;
+    sh.n_groups = (units + sh.parts_per_group - 1) / sh.parts_per_group;
+    const int64_t blocks = base * sh.n_groups;
+    return blocks > 0x7fffffff ? 0 : blocks;
+}
+
+// FP64 sums F_c(w), added into acc
+lw_status launch_sums64(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, FdShape sh, int geom, double *acc,
+                        hipStream_t s, const char *what)
+{
+    // frequencies per block: one tile of 256, 512 or 1024
+    const int W = sh.n_omega > 512 ? 4 : sh.n_omega > 256 ? 2 : 1;
+    sh.n_wblocks = (sh.n_omega + 256 * W - 1) / (256 * W);
+    // two blocks per compute unit; more rounds of them once each has eight chunks (every block adds its sums
+    // with 6 atomics per frequency)
+    const int64_t units = sh.n_particles * ((sh.n_samples + kFdChunk - 1) / kFdChunk);
+    const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(4, units * sh.n_pix * sh.n_wblocks / (512 * 8)));
+    const int64_t blocks = fd_groups(sh, kFdChunk, 512, rounds);
+    if (!blocks) return fail(LW_E_SHAPE, "%s: problem too large for one launch", what);
+    auto go = [&](auto *k) {
+        k<<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
+    };
+    if (geom == LW_GEOM_EXACT)
+        W == 4 ? go(k_direct_fd<LW_GEOM_EXACT, 4>) : W == 2 ? go(k_direct_fd<LW_GEOM_EXACT, 2>) : go(k_direct_fd<LW_GEOM_EXACT, 1>);
+    else
+        W == 4 ? go(k_direct_fd<LW_GEOM_FARFIELD, 4>) : W == 2 ? go(k_direct_fd<LW_GEOM_FARFIELD, 2>) : go(k_direct_fd<LW_GEOM_FARFIELD, 1>);
+    return LW_OK;
+}
+
+template <int GEOM, int K>
+lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, FdShape sh, double *acc, hipStream_t s)
+{
+    // wavefronts per block: four where they all have frequencies (or nearly), else two or one
+    const int64_t waves = (sh.n_omega + 64 * K - 1) / (64 * K);
+    const int W = waves >= 8 || waves % 4 == 0 ? 4 : waves % 2 == 0 ? 2 : 1;
+    sh.n_wblocks = (waves + W - 1) / W;
+    // eight rounds of the resident blocks (two wavefronts per SIMD)
+    const int64_t blocks = fd_groups(sh, 64 * W, 2048 / W, 8);
+    if (!blocks) return fail(LW_E_SHAPE, "lw_direct_fd: problem too large for one launch");
+    auto go = [&](auto *k) {
+        k<<<(unsigned)blocks, 64 * W, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
+    };
+    W == 4 ? go(k_direct_fd_mixed<GEOM, K, 4>) : W == 2 ? go(k_direct_fd_mixed<GEOM, K, 2>) : go(k_direct_fd_mixed<GEOM, K, 1>);
+    return LW_OK;
+}
+
+template <int GEOM>
+lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, const FdShape &sh, double *acc,
+                       hipStream_t s)
+{
+    // frequencies per lane: the largest power of two <= 8 that still fills a wavefront
+    if (sh.n_omega >= 64 * 8) return launch_mixed<GEOM, 8>(t, gr, omega, sh, acc, s);
+    if (sh.n_omega >= 64 * 4) return launch_mixed<GEOM, 4>(t, gr, omega, sh, acc, s);
+    if (sh.n_omega >= 64 * 2) return launch_mixed<GEOM, 2>(t, gr, omega, sh, acc, s);
+    return launch_mixed<GEOM, 1>(t, gr, omega, sh, acc, s);
+}
+
+}  // namespace
+
+lw_status launch_direct_fd(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, int64_t n_omega, int prec,
+                           int fmask, int geom, double *S, void *ws, size_t ws_bytes, hipStream_t s)
+{
+    const int64_t nS = gr->n_pix * n_omega;
+    if (nS == 0) return LW_OK;
+    double *acc = (double *)ws;
+    k_fd_zero<<<(int)std::min<int64_t>((6 * nS + 255) / 256, 65536), 256, 0, s>>>(acc, 6 * nS);
+    if (t->n_particles > 0 && t->n_samples > 0) {
+        const FdShape sh = fd_shape(t, gr, n_omega, fmask);
+        const lw_status st = prec == LW_PREC_FP64 ? launch_sums64(t, gr, omega, sh, geom, acc, s, "lw_direct_fd")
+                             : geom == LW_GEOM_EXACT
+                                 ? launch_mixed<LW_GEOM_EXACT>(t, gr, omega, sh, acc, s)
+                                 : launch_mixed<LW_GEOM_FARFIELD>(t, gr, omega, sh, acc, s);
+        if (st != LW_OK) return st;
     }
     const double f = t->dt * t->dt / (2.0 * kPi);
     k_fd_finish<<<(int)std::min<int64_t>((nS + 255) / 256, 65536), 256, 0, s>>>(acc, S, nS, f);
@@ -515,54 +846,20 @@ lw_status launch_direct_fd_bwd(const lw_traj_t *t, const lw_grid_t *gr, const do
                                int fmask, int geom, const double *dS, double *d_r, double *d_beta, double *d_beta_dot,
                                void *ws, size_t ws_bytes, hipStream_t s)
 {
-    const int64_t n_pix = gr->n_pix;
-    if (n_pix == 0 || n_omega == 0 || t->n_particles == 0) return LW_OK;
+    if (gr->n_pix == 0 || n_omega == 0 || t->n_particles == 0 || t->n_samples == 0) return LW_OK;
     // forward sums F_c(w) in FP64 into the workspace (the |F|^2 pass is not needed)
     double *acc = (double *)ws;
-    const int64_t nS = n_pix * n_omega;
+    const int64_t nS = gr->n_pix * n_omega;
     k_fd_zero<<<(int)std::min<int64_t>((6 * nS + 255) / 256, 65536), 256, 0, s>>>(acc, 6 * nS);
-    FdShape sh;
-    sh.n_particles = t->n_particles;
-    sh.n_samples = t->n_samples;
-    sh.n_pix = n_pix;
-    sh.n_omega = n_omega;
-    sh.n_wblocks = (n_omega + 63) / 64;
-    const int64_t base = n_pix * sh.n_wblocks;
-    int64_t groups = std::max<int64_t>(1, (8192 + base - 1) / base);
-    groups = std::min<int64_t>(groups, t->n_particles);
-    sh.parts_per_group = (t->n_particles + groups - 1) / groups;
-    sh.n_groups = (t->n_particles + sh.parts_per_group - 1) / sh.parts_per_group;
-    sh.t_start = t->t_start;
-    sh.dt = t->dt;
-    sh.t0 = gr->t0;
-    sh.cdt = kC * t->dt;
-    sh.inv_cdt = 1.0 / sh.cdt;
-    sh.fmask = fmask;
-    {
-        const int64_t waves = base * sh.n_groups;
-        const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-        if (blocks > 0x7fffffff) return fail(LW_E_SHAPE, "lw_direct_fd_bwd: problem too large for one launch");
-        if (geom == LW_GEOM_EXACT)
-            k_direct_fd<LW_GEOM_EXACT><<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge,
-                                                                              gr->x_det, omega, acc, sh);
-        else
-            k_direct_fd<LW_GEOM_FARFIELD><<<(unsigned)blocks, 256, 0, s>>>(
-                t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
-    }
-    {
-        const int64_t waves = t->n_particles * ((t->n_samples + 63) / 64);
-        const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-        if (blocks > 0x7fffffff) return fail(LW_E_SHAPE, "lw_direct_fd_bwd: problem too large for one launch");
-        const double two_f = 2.0 * t->dt * t->dt / (2.0 * kPi);
-        if (geom == LW_GEOM_EXACT)
-            k_direct_fd_bwd<LW_GEOM_EXACT><<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge,
-                                                                         gr->x_det, omega, acc, dS, d_r, d_beta,
-                                                                         d_beta_dot, sh, two_f);
-        else
-            k_direct_fd_bwd<LW_GEOM_FARFIELD><<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge,
-                                                                            gr->x_det, omega, acc, dS, d_r, d_beta,
-                                                                            d_beta_dot, sh, two_f);
-    }
+    const FdShape sh = fd_shape(t, gr, n_omega, fmask);
+    const lw_status st = launch_sums64(t, gr, omega, sh, geom, acc, s, "lw_direct_fd_bwd");
+    if (st != LW_OK) return st;
+    const int64_t blocks = t->n_particles * ((t->n_samples + 63) / 64);
+    if (blocks > 0x7fffffff) return fail(LW_E_SHAPE, "lw_direct_fd_bwd: problem too large for one launch");
+    const double two_f = 2.0 * t->dt * t->dt / (2.0 * kPi);
+    auto *k = geom == LW_GEOM_EXACT ? k_direct_fd_bwd<LW_GEOM_EXACT> : k_direct_fd_bwd<LW_GEOM_FARFIELD>;
+    k<<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, dS, d_r, d_beta,
+                                       d_beta_dot, sh, two_f);
     return check_launch("lw_direct_fd_bwd");
 }
 
