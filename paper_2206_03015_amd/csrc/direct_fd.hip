@@ -310,6 +310,15 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd(const double *__restrict__
     }
 }
 
+// The mixed sums' place of frequency j of lane l of a wavefront with R of its 64 K frequencies, in a plane per
+// component: the wavefront's atomics fall on neighbouring elements (lanes own consecutive frequencies; with a
+// frequency's six sums side by side each lane's atomics fell on lines of their own, and 400 groups' adding took
+// 1.3 ms of a call)
+__host__ __device__ __forceinline__ int64_t fd_place(int64_t R, int K, int j, int64_t l)
+{
+    return j * (R / K) + (j < R % K ? j : R % K) + l;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Mixed sums.  A block of W wavefronts owns one pixel, W x 64 K frequencies and a range of chunks of 64 W
 // samples.  The samples are staged once for the W wavefronts (the field and the arrival time are ~150 FP64
@@ -478,9 +487,10 @@ __global__ __launch_bounds__(64 * W, 2) void k_direct_fd_mixed(const double *__r
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         if (wl + j >= sh.n_omega) continue;
-        double *o = acc + ((size_t)m * sh.n_omega + wl + j) * 6;
+        double *o = acc + (size_t)m * 6 * sh.n_omega + wfirst +
+                    fd_place(std::min<int64_t>(64 * K, sh.n_omega - wfirst), K, j, lane);
 #pragma unroll
-        for (int c = 0; c < 6; ++c) atomic_add(o + c, a[j][c]);
+        for (int c = 0; c < 6; ++c) atomic_add(o + c * sh.n_omega, a[j][c]);
     }
 }
 
@@ -490,10 +500,19 @@ __global__ void k_fd_zero(double *__restrict__ p, int64_t n)
         p[j] = 0.0;
 }
 
-__global__ void k_fd_finish(const double *__restrict__ acc, double *__restrict__ S, int64_t n, double f)
+// K = 0: acc [n_pix][n_omega][6]; else [n_pix][6][n_omega], placed by fd_place
+__global__ void k_fd_finish(const double *__restrict__ acc, double *__restrict__ S, int64_t n, int64_t n_omega, int K, double f)
 {
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
-        const double *a = acc + 6 * j;
+        double a[6];
+        if (K == 0) {
+            for (int c = 0; c < 6; ++c) a[c] = acc[6 * j + c];
+        } else {
+            const int64_t m = j / n_omega, w = j - m * n_omega, w0 = w / (64 * K) * (64 * K);
+            const int64_t R = n_omega - w0 < 64 * K ? n_omega - w0 : 64 * K;
+            const double *p = acc + m * 6 * n_omega + w0 + fd_place(R, K, (int)((w - w0) % K), (w - w0) / K);
+            for (int c = 0; c < 6; ++c) a[c] = p[c * n_omega];
+        }
         S[j] = f * (a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3] + a[4] * a[4] + a[5] * a[5]);
     }
 }
@@ -799,8 +818,10 @@ lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *om
     const int64_t waves = (sh.n_omega + 64 * K - 1) / (64 * K);
     const int W = waves >= 8 || waves % 4 == 0 ? 4 : waves % 2 == 0 ? 2 : 1;
     sh.n_wblocks = (waves + W - 1) / W;
-    // eight rounds of the resident blocks (two wavefronts per SIMD)
-    const int64_t blocks = fd_groups(sh, 64 * W, 2048 / W, 8);
+    // up to eight rounds of the resident blocks (two wavefronts per SIMD), of at least eight chunks each
+    const int64_t units = sh.n_particles * ((sh.n_samples + 64 * W - 1) / (64 * W)), resident = 2048 / W;
+    const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(8, units * sh.n_pix * sh.n_wblocks / (resident * 8)));
+    const int64_t blocks = fd_groups(sh, 64 * W, resident, rounds);
     if (!blocks) return fail(LW_E_SHAPE, "lw_direct_fd: problem too large for one launch");
     auto go = [&](auto *k) {
         k<<<(unsigned)blocks, 64 * W, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
@@ -809,15 +830,19 @@ lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *om
     return LW_OK;
 }
 
+// frequencies per lane: the largest power of two <= 8 that still fills a wavefront
+int fd_per_lane(int64_t n_omega) { return n_omega >= 64 * 8 ? 8 : n_omega >= 64 * 4 ? 4 : n_omega >= 64 * 2 ? 2 : 1; }
+
 template <int GEOM>
 lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, const FdShape &sh, double *acc,
                        hipStream_t s)
 {
-    // frequencies per lane: the largest power of two <= 8 that still fills a wavefront
-    if (sh.n_omega >= 64 * 8) return launch_mixed<GEOM, 8>(t, gr, omega, sh, acc, s);
-    if (sh.n_omega >= 64 * 4) return launch_mixed<GEOM, 4>(t, gr, omega, sh, acc, s);
-    if (sh.n_omega >= 64 * 2) return launch_mixed<GEOM, 2>(t, gr, omega, sh, acc, s);
-    return launch_mixed<GEOM, 1>(t, gr, omega, sh, acc, s);
+    switch (fd_per_lane(sh.n_omega)) {
+    case 8: return launch_mixed<GEOM, 8>(t, gr, omega, sh, acc, s);
+    case 4: return launch_mixed<GEOM, 4>(t, gr, omega, sh, acc, s);
+    case 2: return launch_mixed<GEOM, 2>(t, gr, omega, sh, acc, s);
+    default: return launch_mixed<GEOM, 1>(t, gr, omega, sh, acc, s);
+    }
 }
 
 }  // namespace
@@ -838,7 +863,8 @@ lw_status launch_direct_fd(const lw_traj_t *t, const lw_grid_t *gr, const double
         if (st != LW_OK) return st;
     }
     const double f = t->dt * t->dt / (2.0 * kPi);
-    k_fd_finish<<<(int)std::min<int64_t>((nS + 255) / 256, 65536), 256, 0, s>>>(acc, S, nS, f);
+    k_fd_finish<<<(int)std::min<int64_t>((nS + 255) / 256, 65536), 256, 0, s>>>(acc, S, nS, n_omega,
+                                                                              prec == LW_PREC_FP64 ? 0 : fd_per_lane(n_omega), f);
     return check_launch("lw_direct_fd");
 }
 
