@@ -227,13 +227,11 @@ __device__ __forceinline__ void push_start(const LaserDev &L, R a0, const R *ini
     kick(S.uhx, S.uhy, S.uhz, S.Ex, S.By, 0.5 * dt);
 }
 
-// r, beta and beta_dot of the sample the state stands at
+// r, beta and beta_dot of the sample the state stands at; ig: 1/gamma there
 template <typename R>
-__device__ __forceinline__ void push_sample(const PushState<R> &S, R *rr, R *bb, R *aa)
+__device__ __forceinline__ void push_sample(const PushState<R> &S, R ig, R *rr, R *bb, R *aa)
 {
     const double q = -kQe, m = kMe;
-    const R g = sqrt(1.0 + (S.usx * S.usx + S.usy * S.usy + S.usz * S.usz));
-    const R ig = 1.0 / g;  // one division for the four quotients by gamma
     const R bx = S.usx * ig, by = S.usy * ig, bz = S.usz * ig;
     // d beta/dt = q/(gamma m c) [E + c beta x B - beta (beta.E)],  E = (Ex,0,0), B = (0,By,0)
     const R f = (q / (m * kC)) * ig;
@@ -247,6 +245,12 @@ __device__ __forceinline__ void push_sample(const PushState<R> &S, R *rr, R *bb,
     aa[0] = f * (S.Ex - kC * (bz * S.By) - bx * be);
     aa[1] = f * (-(by * be));
     aa[2] = f * (kC * (bx * S.By) - bz * be);
+}
+template <typename R>
+__device__ __forceinline__ void push_sample(const PushState<R> &S, R *rr, R *bb, R *aa)
+{
+    const R g = sqrt(1.0 + (S.usx * S.usx + S.usy * S.usy + S.usz * S.usz));
+    push_sample(S, 1.0 / g, rr, bb, aa);  // one division for the four quotients by gamma
 }
 
 // one Boris step from sample i to sample i + 1 (t_next = t_start + (i + 1) dt)
@@ -289,25 +293,29 @@ __device__ __forceinline__ void push_particle(const LaserDev &L, R a0, const R *
 constexpr int kStateDoubles = 9;  // of the pusher, carried between spans
 
 // ---------------------------------------------------------------------------------------------
-// The pusher.  A particle's steps are one serial chain, and a wavefront of it issues one FP64
-// instruction in four cycles whether the chip is full or not, so its time is the instructions per
-// step of one wavefront until there are enough wavefronts for every SIMD: 4000 particles x 20001
-// samples took 17.3 ms with one lane per particle and everything in the chain (~440 VALU
-// instructions per step).  The chain here carries only what the next step needs:
-//   * the samples' beta, beta_dot and the stores are another wavefront's work: a block is one wavefront
-//     of the chain and one that turns its states, handed over through LDS kPushSteps steps at a
+// The pusher.  A particle's steps are one serial chain, so its time is one wavefront's instructions per step and
+// their dependent latency until there are enough wavefronts for every SIMD: 4000 particles x 20001
+// samples took 17.3 ms with one lane per particle and everything in the chain (~440 VALU instructions per
+// step).  The chain here carries only what the next step needs:
+//   * the samples' beta, beta_dot and the stores are other wavefronts' work: a block is one wavefront
+//     of the chain and two or four that turn its states, handed over through LDS kPushSteps steps at a
 //     time, into samples (lanes over particles and steps, so that a particle's steps are stored
 //     next to each other);
 //   * a particle has two lanes, which take the pulse's two sine/cosine pairs (carrier and envelope) in
 //     one call and exchange them; everything else both lanes do alike.  Only worth it while the
 //     wavefronts of paired particles find a SIMD each (kPairParticles);
+//   * where no particle of the wavefront can reach the pulse within a batch of steps, the kick changes nothing and
+//     the batch is three multiply-adds a step; a particle of the bunch workload is inside the pulse for a third of
+//     its steps, and blocks take the particles in the order in which they meet the pulse, so that this
+//     holds for most of a block's steps (67 % of them had some of 32 particles inside in the given order);
+//   * inside the pulse a step has no branches (push_fast), so that its dependent sequences overlap;
 //   * quotients by constants are a product with the rounded reciprocal and one residual correction
 //     (Markstein: the correctly rounded quotient), the other quotients and the square roots
 //     Newton/Goldschmidt iterations without the range scaling that arguments of this size do not
-//     need.
-// All of these round as the plain expressions do, so the samples keep their bits.  ~250 instructions
-// per step inside the pulse, 0.51 us: 17.0 -> 10.3 ms for 4000 particles x 20001 samples.  What
-// is left is the latency of that dependent chain.
+//     need, and a root's reciprocal comes from the root's own iteration.
+// All of these round as the plain expressions do, so the samples keep their bits.  A step takes 0.47 us
+// inside the pulse and 0.08 us outside: 17.0 ms at first, 10.4 with the second wavefront and the paired
+// lanes, 5.0 now for 4000 particles x 20001 samples.  What is left is the latency of the dependent chain.
 constexpr int kPushSteps = 8;                  // steps per hand-over of a paired block (32 particles)
 constexpr int64_t kPairParticles = 32 * 1024;  // 1024 SIMDs
 
@@ -350,7 +358,7 @@ __device__ __forceinline__ PushConst push_const(const LaserDev &L)
     K.nc2 = 2.0 * L.nc;
     K.rnc2 = 1.0 / K.nc2;
     K.rnc = 1.0 / L.nc;
-    K.w02 = L.w0 * L.w0;
+    K.w02 = L.w0 > 0.0 ? L.w0 * L.w0 : 1.0;
     K.rw02 = 1.0 / K.w02;
     return K;
 }
@@ -365,12 +373,18 @@ __device__ __forceinline__ double pair_lane(double v)
     return __hiloint2double(hi, lo);
 }
 
+// the pulse's phase at (z, t)
+__device__ __forceinline__ double laser_phase(const LaserDev &L, const PushConst &K, double z, double t)
+{
+    return L.wl * (t + div_const(z, kC, K.rc_c));
+}
+
 // laser_eb's field E_x (B_y = -E_x / c)
 template <bool PAIR>
 __device__ __forceinline__ double laser_ex(const LaserDev &L, const PushConst &K, double x, double y, double z, double t,
                                            bool odd)
 {
-    const double phi = L.wl * (t + div_const(z, kC, K.rc_c));
+    const double phi = laser_phase(L, K, z, t);
     if (!(fabs(phi) < kPi * L.nc)) return 0.0;
     const double half = div_const(phi, K.nc2, K.rnc2);
     double sh, ch, sp, cp;
@@ -409,11 +423,214 @@ __device__ __forceinline__ void kick_plain(double &ux, double &uy, double &uz, d
     uz = nz;
 }
 
-// state of one sample in the hand-over buffer: x, y, z, E_x, u (4 doubles with padding)
+// sqrt(x) for x >= 1 and finite, as sqrt_plain, and 1/sqrt(x) from the same iteration
+__device__ __forceinline__ void sqrt_rcp(double x, double &g, double &y)
+{
+    const double y0 = __builtin_amdgcn_rsq(x);
+    double h = 0.5 * y0;
+    g = x * y0;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    y = h + h;
+    y = fma(fma(-g, y, 1.0), y, y);
+}
+// a / b with y = 1/b; a / c for a constant c: without the fix-up of quotients that are not finite numbers
+__device__ __forceinline__ double div_by(double a, double b, double y)
+{
+    const double q = a * y;
+    return fma(fma(-b, q, a), y, q);
+}
+
+// One step of the pusher (push_step's arithmetic and rounding) where u, the phase and the field are of
+// moderate size: nothing here branches, so that the chain's dependent sequences (the field's sines, cosines and
+// exponential, the roots and quotients) overlap as far as they can.  Returns u at the sample.
+template <bool PAIR>
+__device__ __forceinline__ void push_fast(const LaserDev &L, const PushConst &K, double t_next, double dt, bool odd, double &x,
+                                          double &y, double &z, double &uhx, double &uhy, double &uhz, double &Ex,
+                                          double &usx, double &usy, double &usz)
+{
+    double gh, ig;
+    sqrt_rcp(1.0 + (uhx * uhx + uhy * uhy + uhz * uhz), gh, ig);
+    const double cg = div_by(kC * dt, gh, ig);
+    x = x + cg * uhx;
+    y = y + cg * uhy;
+    z = z + cg * uhz;
+    const double phi = L.wl * (t_next + div_by(z, kC, K.rc_c));
+    const double half = div_by(phi, K.nc2, K.rnc2);
+    const double rho2 = L.w0 > 0.0 ? x * x + y * y : 0.0;
+    const double T = ::exp(-div_by(rho2, K.w02, K.rw02));
+    double sh, ch, sp, cp;
+    // below 2^30 sincos needs no reduction of large arguments (the bound in its own terms: that branch goes)
+    if constexpr (PAIR) {
+        const double arg = odd ? phi : half;
+        if (!(fabs(arg) < 0x1p30)) __builtin_unreachable();
+        double sn, cs;
+        ::sincos(arg, &sn, &cs);
+        sh = pair_lane<0>(sn);
+        ch = pair_lane<0>(cs);
+        sp = pair_lane<1>(sn);
+        cp = pair_lane<1>(cs);
+    } else {
+        if (!(fabs(phi) < 0x1p30) || !(fabs(half) < 0x1p30)) __builtin_unreachable();
+        ::sincos(half, &sh, &ch);
+        ::sincos(phi, &sp, &cp);
+    }
+    const double gp = -div_by(sh * ch, L.nc, K.rnc);
+    const double g = ch * ch, dS = gp * sp + g * cp;
+    Ex = fabs(phi) < kPi * L.nc ? -(L.e0_per_a0 * (L.a0 * T * dS)) : 0.0;
+    const double By = -div_by(Ex, kC, K.rc_c);
+    const double q = -kQe, m = kMe, a = q * dt / (2.0 * m * kC);
+    const double mx = uhx + a * Ex, mz = uhz;
+    double gm, igm;
+    sqrt_rcp(1.0 + (mx * mx + uhy * uhy + mz * mz), gm, igm);
+    const double ty = div_by((q * dt / (2.0 * m)) * By, gm, igm);
+    const double d = 1.0 + ty * ty;
+    double yd = __builtin_amdgcn_rcp(d);
+    yd = fma(fma(-d, yd, 1.0), yd, yd);
+    yd = fma(fma(-d, yd, 1.0), yd, yd);
+    const double sy = div_by(2.0 * ty, d, yd);
+    const double px = mx - mz * ty, pz = mz + mx * ty;
+    const double nx = (mx - pz * sy) + a * Ex, nz = mz + px * sy;
+    usx = 0.5 * (uhx + nx);
+    usy = 0.5 * (uhy + uhy);
+    usz = 0.5 * (uhz + nz);
+    uhx = nx;
+    uhz = nz;
+}
+
+// push_sample, with sqrt_rcp where u is of moderate size
+__device__ __forceinline__ void push_sample_fast(const PushState<double> &S, double *rr, double *bb, double *aa)
+{
+    const double g2 = 1.0 + (S.usx * S.usx + S.usy * S.usy + S.usz * S.usz);
+    double g, ig;
+    sqrt_rcp(g2, g, ig);
+    ig = div_by(1.0, g, ig);
+    if (!(g2 < 1e200)) ig = 1.0 / sqrt(g2);
+    push_sample(S, ig, rr, bb, aa);
+}
+
+// state of one sample in the hand-over buffer: x, y, z, E_x, u (an odd pitch: the particles' entries
+// start in different banks)
 template <int P, int S>
 struct PushLds {
-    double2 st[2][P][4 * S + 1];  // one pad entry: the particles' entries start in different banks
+    static constexpr int kPitch = 8 * S + 1;
+    double st[2][P * kPitch];
 };
+
+// Which particles a block pushes: those of ranks kb .. kb + P - 1 by the time at which they meet the pulse, so
+// that a block's particles are inside it together.  Every block ranks all particles for itself: a histogram of
+// kPushBins bins over the keys, then the candidates of its bins by (bin, index).  Keys that crowd into one bin
+// (particles that meet the pulse together, or an outlier that stretches the range) are left in their
+// order, by the same rule in every block.
+constexpr int kPushBins = 2048, kPushCand = 512, kPushMaxBin = 240;
+struct PushSort {
+    int hist[kPushBins];
+    int cand[kPushCand], bin[kPushCand];
+    int part[4], n_cand, max_bin;
+    float lo[8], hi[8];
+};
+
+__device__ __forceinline__ float pulse_time(const double *__restrict__ init, int64_t k, float early)
+{
+    const double *p = init + 6 * k;
+    const float ux = (float)p[3], uy = (float)p[4], uz = (float)p[5];
+    const float t = (early - (float)(p[2] * (1.0 / kC))) / (1.0f + uz / sqrtf(1.0f + ux * ux + uy * uy + uz * uz));
+    return t > -1e30f ? fminf(t, 1e30f) : -1e30f;  // NaN among the earliest
+}
+
+// idx[p], p < P: the block's particles (-1: none).  All threads of the block; ends with a barrier.
+template <int P, int NT>
+__device__ void push_select(const double *__restrict__ init, int64_t n_particles, int64_t kb, float early, PushSort &q, int *idx)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = (int)n_particles;
+    float lo = 3e38f, hi = -3e38f;
+#pragma unroll 4
+    for (int k = tid; k < n; k += NT) {
+        const float t = pulse_time(init, k, early);
+        lo = fminf(lo, t);
+        hi = fmaxf(hi, t);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, off));
+        hi = fmaxf(hi, __shfl_xor(hi, off));
+    }
+    if (lane == 0) {
+        q.lo[wv] = lo;
+        q.hi[wv] = hi;
+    }
+    for (int j = tid; j < kPushBins; j += NT) q.hist[j] = 0;
+    if (tid == 0) q.n_cand = q.max_bin = 0;
+    __syncthreads();
+    for (int v = 0; v < NT / 64; ++v) {
+        lo = fminf(lo, q.lo[v]);
+        hi = fmaxf(hi, q.hi[v]);
+    }
+    const float scale = hi > lo ? ((float)kPushBins - 0.5f) / (hi - lo) : 0.0f;
+    auto bin_of = [&](int k) { return min((int)((pulse_time(init, k, early) - lo) * scale), kPushBins - 1); };
+#pragma unroll 4
+    for (int k = tid; k < n; k += NT) atomicAdd(&q.hist[bin_of(k)], 1);
+    __syncthreads();
+    // exclusive ranks of the bins' first particles (the first 128 threads, 16 bins each)
+    constexpr int kPer = kPushBins / 128;
+    int sum = 0, before = 0;
+    if (tid < 128) {
+        int mx = 0;
+        for (int j = 0; j < kPer; ++j) {
+            const int h = q.hist[kPer * tid + j];
+            sum += h;
+            mx = max(mx, h);
+        }
+        atomicMax(&q.max_bin, mx);
+        before = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(before, off);
+            if (lane >= off) before += o;
+        }
+        if (lane == 63) q.part[wv] = before;
+        before -= sum;
+    }
+    __syncthreads();
+    if (tid < 128) {
+        if (wv == 1) before += q.part[0];
+        for (int j = 0; j < kPer; ++j) {
+            const int h = q.hist[kPer * tid + j];
+            q.hist[kPer * tid + j] = before;
+            before += h;
+        }
+    }
+    __syncthreads();
+    const int r0 = (int)kb, r1 = min(r0 + P, n);
+    if (q.max_bin > kPushMaxBin) {
+        if (tid < P) idx[tid] = r0 + tid < n ? r0 + tid : -1;
+        __syncthreads();
+        return;
+    }
+    // candidates: bins that hold some of the ranks r0 .. r1 - 1 (fewer than P + 2 kPushMaxBin particles)
+    static_assert(P + 2 * kPushMaxBin <= kPushCand, "candidates fit");
+    for (int k = tid; k < n; k += NT) {
+        const int b = bin_of(k), f = q.hist[b], e = b + 1 < kPushBins ? q.hist[b + 1] : n;
+        if (f < r1 && e > r0) {
+            const int c = atomicAdd(&q.n_cand, 1);
+            if (c < kPushCand) {
+                q.cand[c] = k;
+                q.bin[c] = b;
+            }
+        }
+    }
+    if (tid < P) idx[tid] = -1;
+    __syncthreads();
+    const int nc = min(q.n_cand, kPushCand);
+    for (int c = tid; c < nc; c += NT) {
+        const int k = q.cand[c], b = q.bin[c];
+        int rank = q.hist[b];
+        for (int o = 0; o < nc; ++o) rank += q.bin[o] == b && q.cand[o] < k ? 1 : 0;
+        if (rank >= r0 && rank < r1) idx[rank - r0] = k;
+    }
+    __syncthreads();
+}
 
 // Samples s0 .. s0 + n_span - 1 of each particle: stored in r, beta, beta_dot [n_particles][n_span][3] (OUT),
 // and their max |r|^2 in rmax2 if given (fma order z^2 + (y^2 + x^2), that of the deposit's pre-pass).
@@ -421,27 +638,39 @@ struct PushLds {
 // sample s0 left (spans share their boundary sample): x, y, z, u at the sample and u half a step
 // later.  The field at sample s0 is that of the step that reached it (same arguments, same bits).
 // The state at the last sample is left in `state` if given.
-template <bool PAIR, bool OUT>
-__global__ __launch_bounds__(128) void k_push(const double *__restrict__ init, int64_t n_particles, int64_t s0,
-                                              int64_t n_span, double t_start, double dt, LaserDev L,
-                                              double *__restrict__ state, double *__restrict__ r,
-                                              double *__restrict__ beta, double *__restrict__ beta_dot,
-                                              double *__restrict__ rmax2)
+template <bool PAIR, bool OUT, int NC>
+__global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict__ init, int64_t n_particles, int64_t s0,
+                                                       int64_t n_span, double t_start, double dt, LaserDev L, int sorted,
+                                                       double *__restrict__ state, double *__restrict__ r,
+                                                       double *__restrict__ beta, double *__restrict__ beta_dot,
+                                                       double *__restrict__ rmax2)
 {
     constexpr int P = PAIR ? 32 : 64, S = PAIR ? kPushSteps : kPushSteps / 2;
-    __shared__ PushLds<P, S> lds;
-    const int lane = threadIdx.x & 63;
-    // the chain is the first wavefront of a block, or the second in every other 512 blocks: where
-    // several blocks share a compute unit their chains then sit on different SIMDs
-    const bool chain = (__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) ^ (int)((blockIdx.x >> 9) & 1)) == 0;
+    using Lds = PushLds<P, S>;
+    __shared__ union {
+        Lds b;
+        PushSort q;
+    } lds;
+    __shared__ int idx[P];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t kb = (int64_t)blockIdx.x * P;
+    bool ranked = false;
+    if constexpr (PAIR) {
+        ranked = sorted != 0;
+        if (ranked)
+            push_select<P, 64 * (1 + NC)>(init, n_particles, kb, (float)(-kPi * L.nc / L.wl - t_start), lds.q, idx);
+    }
+    if (!ranked) {
+        if (threadIdx.x < P) idx[threadIdx.x] = kb + threadIdx.x < n_particles ? (int)(kb + threadIdx.x) : -1;
+        __syncthreads();
+    }
     const PushConst K = push_const(L);
     const int64_t nb = (n_span + S - 1) / S;
-    if (chain) {
+    if (wv == 0) {
         const int p = PAIR ? lane >> 1 : lane;
         const bool odd = PAIR && (lane & 1);
-        const bool in = kb + p < n_particles;
-        const int64_t k = in ? kb + p : n_particles - 1;
+        const bool in = idx[p] >= 0;
+        const int64_t k = in ? idx[p] : idx[0];
         double x, y, z, usx, usy, usz, uhx, uhy, uhz, Ex;
         double *st = state ? state + kStateDoubles * k : nullptr;
         if (s0 == 0) {
@@ -466,83 +695,121 @@ __global__ __launch_bounds__(128) void k_push(const double *__restrict__ init, i
             uhz = st[8];
             Ex = laser_ex<PAIR>(L, K, x, y, z, t_start + (double)s0 * dt, odd);
         }
+        double *row = lds.b.st[0] + p * Lds::kPitch;
+        // both lanes of a pair write the same values
+        auto put = [&](double ux, double uy, double uz, double e) {
+            row[0] = x;
+            row[1] = y;
+            row[2] = z;
+            row[3] = e;
+            if constexpr (OUT) {
+                row[4] = ux;
+                row[5] = uy;
+                row[6] = uz;
+            }
+        };
+        put(usx, usy, usz, Ex);
         double at = (double)s0;  // index of the sample the state stands at
+        double cg = 0.0;         // c dt / gamma at the half step, where known
+        bool have_cg = false;
+        // the pulse, and how far a batch of steps can take the phase (|dz| <= c dt)
+        const double lim = kPi * L.nc, far = lim + 2.01 * S * fabs(L.wl * dt) + 1e-6;
+        const bool moderate = far < 1e9 && fabs(L.e0_per_a0 * L.a0) < 1e100;
         for (int64_t b = 0; b < nb; ++b) {
             const int n = (int)std::min<int64_t>(S, n_span - b * S);
-            const bool last = b + 1 == nb;
-            double2 *row = lds.st[b & 1][p];
-            for (int j = 0; j < n; ++j) {
-                if constexpr (PAIR) {
-                    row[4 * j + (odd ? 2 : 0)] = odd ? make_double2(usx, usy) : make_double2(x, y);
-                    row[4 * j + (odd ? 3 : 1)] = odd ? make_double2(usz, 0.0) : make_double2(z, Ex);
+            row = lds.b.st[b & 1] + p * Lds::kPitch - (b == 0 ? 0 : 8);
+            const int j0 = b == 0 ? 1 : 0;
+            // one kind of step for the whole batch and wavefront
+            const double phi0 = fabs(L.wl * fma(z, K.rc_c, t_start + at * dt));
+            const double u2 = uhx * uhx + uhy * uhy + uhz * uhz;
+            if (__builtin_amdgcn_ballot_w64(!(phi0 > far) || !(have_cg || u2 < 1e200)) == 0) {
+                // no field on the way: the kick changes nothing, u at the sample is u half a step later
+                if (!have_cg) cg = div_plain(kC * dt, sqrt_plain(1.0 + u2));
+                have_cg = true;
+                auto coast = [&] {
+                    x = x + cg * uhx;
+                    y = y + cg * uhy;
+                    z = z + cg * uhz;
+                    row += 8;
+                    put(uhx, uhy, uhz, 0.0);
+                };
+                at += (double)(n - j0);
+                if (n - j0 == S) {
+#pragma unroll
+                    for (int j = 0; j < S; ++j) coast();
                 } else {
-                    row[4 * j] = make_double2(x, y);
-                    row[4 * j + 1] = make_double2(z, Ex);
-                    row[4 * j + 2] = make_double2(usx, usy);
-                    row[4 * j + 3] = make_double2(usz, 0.0);
+                    for (int j = j0; j < n; ++j) coast();
                 }
-                if (last && j + 1 == n) break;
-                at += 1.0;
-                const double gh = sqrt_plain(1.0 + (uhx * uhx + uhy * uhy + uhz * uhz));
-                const double cg = div_plain(kC * dt, gh);
-                x = x + cg * uhx;
-                y = y + cg * uhy;
-                z = z + cg * uhz;
-                double nx = uhx, ny = uhy, nz = uhz;
-                Ex = laser_ex<PAIR>(L, K, x, y, z, t_start + at * dt, odd);
-                kick_plain(nx, ny, nz, Ex, -div_const(Ex, kC, K.rc_c), dt);
-                usx = 0.5 * (uhx + nx);
-                usy = 0.5 * (uhy + ny);
-                usz = 0.5 * (uhz + nz);
-                uhx = nx;
-                uhy = ny;
-                uhz = nz;
+            } else if (moderate && __builtin_amdgcn_ballot_w64(!(phi0 < 1e9) || !(u2 < 1e200)) == 0) {
+                have_cg = false;
+                for (int j = j0; j < n; ++j) {
+                    at += 1.0;
+                    push_fast<PAIR>(L, K, t_start + at * dt, dt, odd, x, y, z, uhx, uhy, uhz, Ex, usx, usy, usz);
+                    row += 8;
+                    put(usx, usy, usz, Ex);
+                }
+            } else {
+                have_cg = false;
+                for (int j = j0; j < n; ++j) {
+                    at += 1.0;
+                    cg = div_plain(kC * dt, sqrt_plain(1.0 + (uhx * uhx + uhy * uhy + uhz * uhz)));
+                    x = x + cg * uhx;
+                    y = y + cg * uhy;
+                    z = z + cg * uhz;
+                    double nx = uhx, ny = uhy, nz = uhz;
+                    Ex = laser_ex<PAIR>(L, K, x, y, z, t_start + at * dt, odd);
+                    kick_plain(nx, ny, nz, Ex, -div_const(Ex, kC, K.rc_c), dt);
+                    row += 8;
+                    put(0.5 * (uhx + nx), 0.5 * (uhy + ny), 0.5 * (uhz + nz), Ex);
+                    uhx = nx;
+                    uhy = ny;
+                    uhz = nz;
+                }
             }
             __syncthreads();  // batch b is written, batch b - 1 read
         }
-        if (st && in && !odd) {
+        if (OUT && st && in && !odd) {
             st[0] = x;
             st[1] = y;
             st[2] = z;
-            st[3] = usx;
-            st[4] = usy;
-            st[5] = usz;
+            st[3] = row[4];
+            st[4] = row[5];
+            st[5] = row[6];
             st[6] = uhx;
             st[7] = uhy;
             st[8] = uhz;
         }
     } else {
-        // lane -> (particle of a group of 64 / S, step): a particle's S steps on neighbouring lanes
-        constexpr int G = 64 / S;
-        const int j = lane & (S - 1), pg = lane / S;
-        double mx[P / G];
+        // lane -> (particle of a group of 64 / S, step): a particle's S steps on neighbouring lanes; the
+        // P S / 64 groups are split between the NC wavefronts
+        constexpr int G = 64 / S, NG = P / G / NC;
+        const int j = lane & (S - 1), p0 = (wv - 1) * NG * G + lane / S;
+        double mx[NG];
 #pragma unroll
-        for (int g = 0; g < P / G; ++g) mx[g] = 0.0;
+        for (int g = 0; g < NG; ++g) mx[g] = 0.0;
         for (int64_t b = 0; b < nb; ++b) {
             __syncthreads();  // batch b is written
             const int64_t i = b * S + j;
             if (i >= n_span) continue;
 #pragma unroll
-            for (int g = 0; g < P / G; ++g) {
-                const int p = g * G + pg;
-                const double2 *row = lds.st[b & 1][p] + 4 * j;
-                const double2 xy = row[0], ze = row[1];
-                mx[g] = fmax(mx[g], fma(ze.x, ze.x, fma(xy.y, xy.y, xy.x * xy.x)));
+            for (int g = 0; g < NG; ++g) {
+                const int p = p0 + g * G;
+                const double *row = lds.b.st[b & 1] + p * Lds::kPitch + 8 * j;
+                PushState<double> Q;
+                Q.x = row[0];
+                Q.y = row[1];
+                Q.z = row[2];
+                mx[g] = fmax(mx[g], fma(Q.z, Q.z, fma(Q.y, Q.y, Q.x * Q.x)));
                 if constexpr (OUT) {
-                    if (kb + p >= n_particles) continue;
-                    const double2 uv = row[2], w0 = row[3];
-                    PushState<double> Q;
-                    Q.x = xy.x;
-                    Q.y = xy.y;
-                    Q.z = ze.x;
-                    Q.Ex = ze.y;
-                    Q.By = -div_const(ze.y, kC, K.rc_c);
-                    Q.usx = uv.x;
-                    Q.usy = uv.y;
-                    Q.usz = w0.x;
+                    if (idx[p] < 0) continue;
+                    Q.Ex = row[3];
+                    Q.By = -div_const(Q.Ex, kC, K.rc_c);
+                    Q.usx = row[4];
+                    Q.usy = row[5];
+                    Q.usz = row[6];
                     double rr[3], bb[3], aa[3];
-                    push_sample(Q, rr, bb, aa);
-                    const size_t o = (size_t)((kb + p) * n_span + i) * 3;
+                    push_sample_fast(Q, rr, bb, aa);
+                    const size_t o = ((size_t)idx[p] * n_span + i) * 3;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         r[o + c] = rr[c];
@@ -554,11 +821,11 @@ __global__ __launch_bounds__(128) void k_push(const double *__restrict__ init, i
         }
         if (rmax2) {
 #pragma unroll
-            for (int g = 0; g < P / G; ++g) {
+            for (int g = 0; g < NG; ++g) {
                 double m = mx[g];
                 for (int off = S / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-                const int64_t k = kb + g * G + pg;
-                if (j == 0 && k < n_particles) rmax2[k] = m;
+                const int k = idx[p0 + g * G];
+                if (j == 0 && k >= 0) rmax2[k] = m;
             }
         }
     }
@@ -708,8 +975,21 @@ static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, dou
     const LaserDev L = laser_dev(t->laser);
     const bool pair = t->n_particles <= kPairParticles;
     const unsigned blocks = (unsigned)((t->n_particles + (pair ? 31 : 63)) / (pair ? 32 : 64));
-    auto *k = pair ? (r ? k_push<true, true> : k_push<true, false>) : (r ? k_push<false, true> : k_push<false, false>);
-    k<<<blocks, 128, 0, s>>>(t->init, t->n_particles, s0, n_span, t->t_start, t->dt, L, state, r, beta, beta_dot, rmax2);
+    // ranking costs a block three passes over the initial conditions (~1 us per 128 particles, L2), a step inside
+    // the pulse ~0.4 us more than one outside
+    const int sorted = pair && t->n_particles > 32 && n_span >= 256 && n_span * 16 >= t->n_particles;
+    // wavefronts that form and store samples: four per block where every block has a compute unit for itself,
+    // else two (10000 particles, 313 blocks: 7.6 ms with four, whose chains share SIMDs, 4.6 with two)
+    auto go = [&](auto *k, int nc) {
+        k<<<blocks, 64 * (1 + nc), 0, s>>>(t->init, t->n_particles, s0, n_span, t->t_start, t->dt, L, sorted, state, r, beta,
+                                          beta_dot, rmax2);
+    };
+    if (pair && blocks <= 256)
+        r ? go(k_push<true, true, 4>, 4) : go(k_push<true, false, 4>, 4);
+    else if (pair)
+        r ? go(k_push<true, true, 2>, 2) : go(k_push<true, false, 2>, 2);
+    else
+        r ? go(k_push<false, true, 2>, 2) : go(k_push<false, false, 2>, 2);
     return check_launch(what);
 }
 

@@ -45,3 +45,33 @@ def test_layouts_give_the_same_bits(n_samples):
         part = lw.trajectory_boris(it[lo:hi].contiguous(), *args)
         for a, b in zip(whole, part):
             assert torch.equal(a[lo:hi], b)
+
+
+@pytest.mark.parametrize("n_p, n_samples, keys", [(33, 256, "bunch"), (63, 300, "bunch"), (97, 1025, "bunch"),
+                                                  (1000, 640, "bunch"), (700, 300, "crowd"), (300, 300, "outlier"),
+                                                  (300, 300, "nan")])
+def test_ranked_blocks_and_coasting_give_the_same_bits(n_p, n_samples, keys):
+    """Particles that meet the pulse at different times (blocks take them in that order, and coast before and after
+    it) have the bits of pushes of 32 particles in their own order; the keys of "crowd" and
+    "outlier" fall into one bin, those of "nan" are partly undefined.  One particle against the oracle."""
+    from paper_2206_03015_amd import lw
+    W = inputs.workload("bunch").scaled(n_p=n_p, n_steps=n_samples - 1)
+    L = W.laser
+    init = inputs.bunch_init(W)
+    if keys == "crowd":
+        init[:, 2:] = init[0, 2:]
+    elif keys == "outlier":
+        init[7, 2] = -1e6
+    elif keys == "nan":
+        init[5, 2] = init[9, 3] = np.nan
+        init[11, 5] = np.inf
+    args = (W.n_samples, W.t_start, W.dt, L.a0, L.lam, L.w0, L.n_cycles)
+    it = torch.as_tensor(init, device=DEV)
+    whole = lw.trajectory_boris(it, *args)
+    for lo in range(0, n_p, 32):
+        part = lw.trajectory_boris(it[lo:lo + 32].contiguous(), *args)
+        for a, b in zip(whole, part):
+            assert torch.equal(torch.nan_to_num(a[lo:lo + 32], nan=7.0), torch.nan_to_num(b, nan=7.0))
+    ref = oracle.boris(init[:3], *args)
+    for g, o, tol in zip(whole, ref, (1e-12, 1e-12, 1e-9)):
+        assert np.max(np.abs(g[:3].cpu().numpy() - o)) <= tol * np.max(np.abs(o))
