@@ -274,22 +274,6 @@ __device__ __forceinline__ void push_step(const LaserDev &L, R a0, double t_next
     S.uhz = nz;
 }
 
-// Runs the pusher of one particle and calls emit(i, r[3], beta[3], beta_dot[3]) per sample.
-template <typename R, typename Emit>
-__device__ __forceinline__ void push_particle(const LaserDev &L, R a0, const R *init, int64_t n_samples,
-                                              double t_start, double dt, Emit emit)
-{
-    PushState<R> S;
-    push_start(L, a0, init, t_start, dt, S);
-    for (int64_t i = 0; i < n_samples; ++i) {
-        R rr[3], bb[3], aa[3];
-        push_sample(S, rr, bb, aa);
-        emit(i, rr, bb, aa);
-        if (i + 1 == n_samples) break;
-        push_step(L, a0, t_start + (double)(i + 1) * dt, dt, S);
-    }
-}
-
 constexpr int kStateDoubles = 9;  // of the pusher, carried between spans
 
 // ---------------------------------------------------------------------------------------------
@@ -637,13 +621,15 @@ __device__ void push_select(const double *__restrict__ init, int64_t n_particles
 // The pusher starts from init (s0 = 0) or from the state [n_particles][9] that the span ending at
 // sample s0 left (spans share their boundary sample): x, y, z, u at the sample and u half a step
 // later.  The field at sample s0 is that of the step that reached it (same arguments, same bits).
-// The state at the last sample is left in `state` if given.
+// The state at the last sample is left in `state` if given, and x, y, z and u half a step later of the samples
+// seg - 1, 2 seg - 1 ... (seg a multiple of kPushSteps) in ck [n_particles][ck_stride] if given.
 template <bool PAIR, bool OUT, int NC>
 __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict__ init, int64_t n_particles, int64_t s0,
                                                        int64_t n_span, double t_start, double dt, LaserDev L, int sorted,
                                                        double *__restrict__ state, double *__restrict__ r,
                                                        double *__restrict__ beta, double *__restrict__ beta_dot,
-                                                       double *__restrict__ rmax2)
+                                                       double *__restrict__ rmax2, double *__restrict__ ck,
+                                                       int64_t ck_stride, int64_t seg)
 {
     constexpr int P = PAIR ? 32 : 64, S = PAIR ? kPushSteps : kPushSteps / 2;
     using Lds = PushLds<P, S>;
@@ -714,6 +700,8 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
         bool have_cg = false;
         // the pulse, and how far a batch of steps can take the phase (|dz| <= c dt)
         const double lim = kPi * L.nc, far = lim + 2.01 * S * fabs(L.wl * dt) + 1e-6;
+        double *ck_at = ck ? ck + k * ck_stride : nullptr;
+        int64_t ck_next = seg / S - 1;  // the batch after which the next checkpoint falls
         const bool moderate = far < 1e9 && fabs(L.e0_per_a0 * L.a0) < 1e100;
         for (int64_t b = 0; b < nb; ++b) {
             const int n = (int)std::min<int64_t>(S, n_span - b * S);
@@ -765,6 +753,15 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                     uhy = ny;
                     uhz = nz;
                 }
+            }
+            if (OUT && ck && b == ck_next && b + 1 < nb) {
+                if (in && !odd) {
+                    const double v[6] = {x, y, z, uhx, uhy, uhz};
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) ck_at[c] = v[c];
+                }
+                ck_at += 6;
+                ck_next += seg / S;
             }
             __syncthreads();  // batch b is written, batch b - 1 read
         }
@@ -838,6 +835,276 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
 // tangents per particle are the whole gradient.
 constexpr int kParams = 7;
 
+// ---------------------------------------------------------------------------------------------
+// The tangents over samples s0 .. s0 + n_span - 1, in segments.  A lane's chain of steps is serial (1000 particles x
+// 10001 samples: 110 wavefronts, 13.0 ms), but the tangents are linear: a segment that starts from the
+// state the pusher left on its way takes the unit tangents of that state (x, y, z, u half a step later)
+// and that of a0, seven lanes again, and k_tangent_join puts the segments together,
+//   d(state)/dp after a segment = sum_j [d(state)/d(start_j)] d(start_j)/dp (+ the a0 lane's for p = a0),
+// and likewise the segment's sums g.d(samples).  The first segment of a span starts from the parameters' own
+// tangents, those of the initial conditions or those the previous span left.  The number of segments fills
+// one wavefront per SIMD (1024), which is where the chains stop being latency-bound: 1000 x 10001 in 9 segments,
+// 13.0 -> 1.1 ms (with the step of push_fast).  28086 particles (three wavefronts per SIMD) keep one segment.
+// Two or four tangents per lane measured slower on the large workload's adjoint (444 and 448 against 326 ms): their
+// registers leave fewer wavefronts.
+// Workspace per particle (tstate): the state's nine values, their derivatives [7][9], the checkpoints.
+constexpr int kTanCk = 9 * (1 + kParams);                // offset of the checkpoints
+constexpr int kTanStateDoubles = 7 * 18;                 // per particle
+constexpr int kTanSegments = 1 + (kTanStateDoubles - kTanCk) / 6;
+constexpr int kTanRes = 10;                              // results per lane: nine derivatives, the sum
+struct TanSegments {
+    int64_t n, len;
+};
+TanSegments tangent_segments(int64_t n_particles, int64_t n_span)
+{
+    const int64_t waves = (n_particles * kParams + 63) / 64;
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>({kTanSegments, 1024 / waves, n_span / 64}));
+    TanSegments g;
+    g.len = ((n_span + want - 1) / want + kPushSteps - 1) / kPushSteps * kPushSteps;
+    g.n = (n_span + g.len - 1) / g.len;
+    return g;
+}
+
+// push_fast in dual numbers (values as there; derivatives through the reciprocals at hand); da0: derivative of a0
+__device__ __forceinline__ void tangent_step(const LaserDev &L, const PushConst &K, double da0, double t_next, double dt,
+                                             PushState<Dual<1>> &S)
+{
+    using D = Dual<1>;
+    const D ux = S.uhx, uy = S.uhy, uz = S.uhz;
+    double gh, ig;
+    sqrt_rcp(1.0 + (ux.v * ux.v + uy.v * uy.v + uz.v * uz.v), gh, ig);
+    const double cg = div_by(kC * dt, gh, ig);
+    const double dcg = -cg * (ux.v * ux.d[0] + uy.v * uy.d[0] + uz.v * uz.d[0]) * (ig * ig);
+    S.x.v = S.x.v + cg * ux.v;
+    S.y.v = S.y.v + cg * uy.v;
+    S.z.v = S.z.v + cg * uz.v;
+    S.x.d[0] += fma(cg, ux.d[0], dcg * ux.v);
+    S.y.d[0] += fma(cg, uy.d[0], dcg * uy.v);
+    S.z.d[0] += fma(cg, uz.d[0], dcg * uz.v);
+    const double x = S.x.v, y = S.y.v;
+    const double phi = L.wl * (t_next + div_by(S.z.v, kC, K.rc_c)), dphi = (L.wl * K.rc_c) * S.z.d[0];
+    const double half = div_by(phi, K.nc2, K.rnc2);
+    const bool wide = L.w0 > 0.0;
+    const double T = ::exp(-div_by(wide ? x * x + y * y : 0.0, K.w02, K.rw02));
+    const double dT = wide ? -2.0 * (x * S.x.d[0] + y * S.y.d[0]) * K.rw02 * T : 0.0;
+    double sh, ch, sp, cp;
+    if (!(fabs(phi) < 0x1p30) || !(fabs(half) < 0x1p30)) __builtin_unreachable();
+    ::sincos(half, &sh, &ch);
+    ::sincos(phi, &sp, &cp);
+    const double gp = -div_by(sh * ch, L.nc, K.rnc);
+    const double g = ch * ch, dS = gp * sp + g * cp;
+    // d(dS)/dphi: g' = gp, gp' = -(ch^2 - sh^2) / (2 nc^2)
+    const double dSp = fma(2.0 * gp, cp, -sp * fma(ch * ch - sh * sh, K.rnc * K.rnc2, g));
+    const bool inside = fabs(phi) < kPi * L.nc;
+    S.Ex.v = inside ? -(L.e0_per_a0 * (L.a0 * T * dS)) : 0.0;
+    S.Ex.d[0] = inside ? -(L.e0_per_a0 * (fma(da0, T, L.a0 * dT) * dS + L.a0 * T * dSp * dphi)) : 0.0;
+    S.By.v = -div_by(S.Ex.v, kC, K.rc_c);
+    S.By.d[0] = -S.Ex.d[0] * K.rc_c;
+    const double q = -kQe, m = kMe, a = q * dt / (2.0 * m * kC), b = q * dt / (2.0 * m);
+    const double mx = ux.v + a * S.Ex.v, dmx = fma(a, S.Ex.d[0], ux.d[0]), mz = uz.v, dmz = uz.d[0];
+    double gm, igm;
+    sqrt_rcp(1.0 + (mx * mx + uy.v * uy.v + mz * mz), gm, igm);
+    const double dgm = (mx * dmx + uy.v * uy.d[0] + mz * dmz) * igm;
+    const double ty = div_by(b * S.By.v, gm, igm), dty = (b * S.By.d[0] - ty * dgm) * igm;
+    const double d = 1.0 + ty * ty;
+    double yd = __builtin_amdgcn_rcp(d);
+    yd = fma(fma(-d, yd, 1.0), yd, yd);
+    yd = fma(fma(-d, yd, 1.0), yd, yd);
+    const double sy = div_by(2.0 * ty, d, yd), dsy = 2.0 * dty * fma(-sy, ty, 1.0) * yd;
+    const double px = mx - mz * ty, pz = mz + mx * ty;
+    const double dpx = dmx - (dmz * ty + mz * dty), dpz = dmz + (dmx * ty + mx * dty);
+    D nx, nz;
+    nx.v = (mx - pz * sy) + a * S.Ex.v;
+    nx.d[0] = dmx - (dpz * sy + pz * dsy) + a * S.Ex.d[0];
+    nz.v = mz + px * sy;
+    nz.d[0] = dmz + (dpx * sy + px * dsy);
+    S.usx = 0.5 * (ux + nx);
+    S.usy = uy;
+    S.usz = 0.5 * (uz + nz);
+    S.uhx = nx;
+    S.uhz = nz;
+}
+
+// g.d(sample) of the sample the state stands at (push_sample in dual numbers)
+__device__ __forceinline__ double tangent_sample(const PushState<Dual<1>> &S, const double *g_r, const double *g_b,
+                                                 const double *g_a, double acc)
+{
+    const double q = -kQe, m = kMe;
+    const double ux = S.usx.v, uy = S.usy.v, uz = S.usz.v, Ex = S.Ex.v, By = S.By.v, dEx = S.Ex.d[0], dBy = S.By.d[0];
+    double g, ig;
+    sqrt_rcp(1.0 + (ux * ux + uy * uy + uz * uz), g, ig);
+    const double dig = -(ux * S.usx.d[0] + uy * S.usy.d[0] + uz * S.usz.d[0]) * (ig * ig * ig);
+    const double bx = ux * ig, by = uy * ig, bz = uz * ig;
+    const double dbx = fma(S.usx.d[0], ig, ux * dig), dby = fma(S.usy.d[0], ig, uy * dig), dbz = fma(S.usz.d[0], ig, uz * dig);
+    const double f = (q / (m * kC)) * ig, df = (q / (m * kC)) * dig;
+    const double be = bx * Ex, dbe = fma(dbx, Ex, bx * dEx);
+    const double ax = Ex - kC * (bz * By) - bx * be, ay = -(by * be), az = kC * (bx * By) - bz * be;
+    const double dax = dEx - kC * fma(dbz, By, bz * dBy) - fma(dbx, be, bx * dbe);
+    const double day = -fma(dby, be, by * dbe);
+    const double daz = kC * fma(dbx, By, bx * dBy) - fma(dbz, be, bz * dbe);
+    acc += g_r[0] * S.x.d[0] + g_b[0] * dbx + g_a[0] * fma(df, ax, f * dax);
+    acc += g_r[1] * S.y.d[0] + g_b[1] * dby + g_a[1] * fma(df, ay, f * day);
+    acc += g_r[2] * S.z.d[0] + g_b[2] * dbz + g_a[2] * fma(df, az, f * daz);
+    return acc;
+}
+
+// sum of g.d(sample) over samples i0 .. i1 - 1 (of the span whose first sample is sample s0 of the trajectory): from
+// the state at sample i0 (`at`), or from that at sample i0 - 1
+__device__ __forceinline__ double tangent_run(const LaserDev &L, const PushConst &K, Dual<1> a0, int64_t s0, int64_t i0,
+                                              int64_t i1, bool at, double t_start, double dt, PushState<Dual<1>> &S,
+                                              const double *__restrict__ g_r, const double *__restrict__ g_b,
+                                              const double *__restrict__ g_a)
+{
+    using D = Dual<1>;
+    double acc = 0.0;
+    const bool tame = S.uhx.v * S.uhx.v + S.uhy.v * S.uhy.v + S.uhz.v * S.uhz.v < 1e200 &&
+                      S.usx.v * S.usx.v + S.usy.v * S.usy.v + S.usz.v * S.usz.v < 1e200 &&
+                      fabs(laser_phase(L, K, S.z.v, t_start + (double)(s0 + i0) * dt)) < 1e8 &&
+                      2.01 * fabs(L.wl * dt) * (double)(i1 - i0) + kPi * L.nc < 1e8 && fabs(L.e0_per_a0 * L.a0) < 1e100;
+    if (__ballot(!tame) == 0) {
+        // the gradients of kAhead samples are on their way while the kAhead before them are used: a step takes
+        // less than a miss of their lines
+        constexpr int kAhead = 4;
+        double g[2][kAhead][9];
+        auto load = [&](double (*o)[9], int64_t from) {
+#pragma unroll
+            for (int v = 0; v < kAhead; ++v) {
+                const int64_t j = 3 * std::min(from + v, i1 - 1);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    o[v][c] = g_r[j + c];
+                    o[v][3 + c] = g_b[j + c];
+                    o[v][6 + c] = g_a[j + c];
+                }
+            }
+        };
+        int64_t i = i0;
+        if (at) {
+            acc = tangent_sample(S, g_r + 3 * i, g_b + 3 * i, g_a + 3 * i, acc);
+            ++i;
+        }
+        if (i >= i1) return acc;
+        load(g[0], i);
+        for (; i < i1; i += kAhead) {
+            load(g[1], i + kAhead);
+#pragma unroll
+            for (int v = 0; v < kAhead; ++v) {
+                if (i + v >= i1) break;
+                tangent_step(L, K, a0.d[0], t_start + (double)(s0 + i + v) * dt, dt, S);
+                acc = tangent_sample(S, g[0][v], g[0][v] + 3, g[0][v] + 6, acc);
+            }
+#pragma unroll
+            for (int v = 0; v < kAhead; ++v)
+#pragma unroll
+                for (int c = 0; c < 9; ++c) g[0][v][c] = g[1][v][c];
+        }
+        return acc;
+    }
+    for (int64_t i = i0; i < i1; ++i) {
+        if (i > i0 || !at) push_step(L, a0, t_start + (double)(s0 + i) * dt, dt, S);
+        D rr[3], bb[3], aa[3];
+        push_sample(S, rr, bb, aa);
+        for (int c = 0; c < 3; ++c)
+            acc += g_r[3 * i + c] * rr[c].d[0] + g_b[3 * i + c] * bb[c].d[0] + g_a[3 * i + c] * aa[c].d[0];
+    }
+    return acc;
+}
+
+// lane -> (segment, particle, seed): results [segment][kTanRes][n_particles][7] in res.  Gradients g_* [n_particles][n_span][3].  Spans share their boundary sample; the
+// gradients of a boundary sample are split between the two spans' deposit adjoints (each gathers its own
+// intervals), so the two contractions add up to the whole.
+__global__ __launch_bounds__(64) void k_tangent_segment(const double *__restrict__ init, int64_t n_particles, int64_t s0,
+                                                        int64_t n_span, int64_t n_seg, int64_t seg_len, double t_start,
+                                                        double dt, LaserDev L, double *tstate,
+                                                        const double *__restrict__ g_r, const double *__restrict__ g_b,
+                                                        const double *__restrict__ g_a, double *__restrict__ res)
+{
+    using D = Dual<1>;
+    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t per = n_particles * kParams, seg = l / per;
+    const int64_t i0 = seg * seg_len, i1 = std::min(i0 + seg_len, n_span);
+    if (i0 >= n_span) return;
+    const int64_t kp = l - seg * per, k = kp / kParams;
+    const int p = (int)(kp - k * kParams);
+    const PushConst K = push_const(L);
+    D a0(L.a0);
+    a0.d[0] = p == 6 ? 1.0 : 0.0;
+    PushState<D> S;
+    double *st = tstate + kTanStateDoubles * k;
+    if (seg > 0) {
+        const double *c = st + kTanCk + 6 * (seg - 1);
+        D *f[6] = {&S.x, &S.y, &S.z, &S.uhx, &S.uhy, &S.uhz};
+        for (int j = 0; j < 6; ++j) {
+            f[j]->v = c[j];
+            f[j]->d[0] = j == p ? 1.0 : 0.0;
+        }
+        S.usx = S.uhx;
+        S.usy = S.uhy;
+        S.usz = S.uhz;
+        S.Ex = S.By = 0.0;
+    } else if (s0 == 0) {
+        D in[6];
+        for (int c = 0; c < 6; ++c) {
+            in[c] = D(init[6 * k + c]);
+            in[c].d[0] = c == p ? 1.0 : 0.0;
+        }
+        push_start(L, a0, in, t_start, dt, S);
+    } else {
+        D *f[9] = {&S.x, &S.y, &S.z, &S.usx, &S.usy, &S.usz, &S.uhx, &S.uhy, &S.uhz};
+        for (int c = 0; c < 9; ++c) {
+            f[c]->v = st[c];
+            f[c]->d[0] = st[9 + 9 * p + c];
+        }
+        // the same arguments as the step that reached sample s0: the same field and derivative
+        laser_eb(L, a0, S.x, S.y, S.z, t_start + (double)s0 * dt, S.Ex, S.By);
+    }
+    const size_t o = (size_t)(k * n_span) * 3;
+    const double acc = tangent_run(L, K, a0, s0, i0, i1, seg == 0, t_start, dt, S, g_r + o, g_b + o, g_a + o);
+    const D *f[9] = {&S.x, &S.y, &S.z, &S.uhx, &S.uhy, &S.uhz, &S.usx, &S.usy, &S.usz};
+    // one segment: straight to the state (each lane has read its own), the sum to the checkpoints' place
+    double *out = n_seg > 1 ? res + seg * kTanRes * per + kp : st + 9 + 9 * p;
+    const int64_t step = n_seg > 1 ? per : 1;
+    for (int c = 0; c < 9; ++c) out[(n_seg > 1 || c < 3 ? c : c < 6 ? c + 3 : c - 3) * step] = f[c]->d[0];
+    *(n_seg > 1 ? out + 9 * per : st + kTanCk + p) = acc;
+}
+
+// thread -> (particle, parameter): the segments in order; the first span (s0 = 0) writes grad_init, grad_a0,
+// later ones add to them; the pusher's state at the span's last sample and its derivatives go to tstate
+__global__ __launch_bounds__(256) void k_tangent_join(int64_t n_particles, int64_t n_seg, const double *__restrict__ res,
+                                                      const double *__restrict__ state, double *__restrict__ tstate, bool first,
+                                                      double *__restrict__ grad_init, double *__restrict__ grad_a0)
+{
+    const int64_t per = n_particles * kParams, l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (l >= per) return;
+    const int64_t k = l / kParams;
+    const int p = (int)(l - k * kParams);
+    double *st = tstate + kTanStateDoubles * k;
+    double cur[9];  // d(x, y, z, u half a step later, u)/dp
+    double acc = n_seg > 1 ? res[9 * per + l] : st[kTanCk + p];
+    for (int c = 0; c < 9 && n_seg > 1; ++c) cur[c] = res[c * per + l];
+    for (int64_t s = 1; s < n_seg; ++s) {
+        const double *q = res + s * kTanRes * per + k * kParams;
+        double nxt[kTanRes];
+        for (int c = 0; c < kTanRes; ++c) {
+            nxt[c] = p == 6 ? q[c * per + 6] : 0.0;
+            for (int j = 0; j < 6; ++j) nxt[c] = fma(q[c * per + j], cur[j], nxt[c]);
+        }
+        for (int c = 0; c < 9; ++c) cur[c] = nxt[c];
+        acc += nxt[9];
+    }
+    double *d = st + 9 + 9 * p;  // x, y, z, u, u half a step later
+    for (int c = 0; c < 3 && n_seg > 1; ++c) {
+        d[c] = cur[c];
+        d[3 + c] = cur[6 + c];
+        d[6 + c] = cur[3 + c];
+    }
+    if (p == 0)
+        for (int c = 0; c < 9; ++c) st[c] = state[kStateDoubles * k + c];
+    double *out = p < 6 ? grad_init + 6 * k + p : grad_a0 + k;
+    *out = first ? acc : *out + acc;
+}
+
+// whole trajectories in one segment, without a workspace
 __global__ __launch_bounds__(64) void k_boris_tangent(const double *__restrict__ init, int64_t n_particles,
                                                       int64_t n_samples, double t_start, double dt, LaserDev L,
                                                       const double *__restrict__ g_r, const double *__restrict__ g_b,
@@ -852,106 +1119,18 @@ __global__ __launch_bounds__(64) void k_boris_tangent(const double *__restrict__
     D in[6];
     for (int c = 0; c < 6; ++c) {
         in[c] = D(init[6 * k + c]);
-        in[c].d[0] = (c == p) ? 1.0 : 0.0;
+        in[c].d[0] = c == p ? 1.0 : 0.0;
     }
     D a0(L.a0);
-    a0.d[0] = (p == 6) ? 1.0 : 0.0;
-    double acc = 0.0;
-    push_particle<D>(L, a0, in, n_samples, t_start, dt, [&](int64_t i, const D *rr, const D *bb, const D *aa) {
-        const size_t o = (size_t)(k * n_samples + i) * 3;
-        for (int c = 0; c < 3; ++c) acc += g_r[o + c] * rr[c].d[0] + g_b[o + c] * bb[c].d[0] + g_a[o + c] * aa[c].d[0];
-    });
+    a0.d[0] = p == 6 ? 1.0 : 0.0;
+    PushState<D> S;
+    push_start(L, a0, in, t_start, dt, S);
+    const size_t o = (size_t)(k * n_samples) * 3;
+    const double acc = tangent_run(L, push_const(L), a0, 0, 0, n_samples, true, t_start, dt, S, g_r + o, g_b + o, g_a + o);
     if (p < 6)
         grad_init[6 * k + p] = acc;
     else
         grad_a0[k] = acc;
-}
-
-// The tangents over samples s0 .. s0 + n_span - 1 only, kTanND of the seven per lane: lane l
-// takes particle k = l / G and parameters p = kTanND (l % G) + j (j < kTanND, p < 7), G =
-// ceil(7 / kTanND) lanes per particle, so each lane runs the pusher's values once for kTanND
-// tangents (the laser's sin, cos and exp serve them all).  Each lane starts from its seeded
-// initial state (s0 = 0) or from the dual-number state the previous span left at sample s0
-// ([lane][9 (1 + kTanND)]: the 9 state values, then their derivatives), contracts the span's
-// gradients g_* [n_particles][n_span][3], saves its state at the span's last sample, and writes
-// (s0 = 0) or adds its sums.  Spans share their boundary sample; the gradients of a boundary
-// sample are split between the two spans' deposit adjoints (each gathers its own intervals), so
-// the two contractions add up to the whole.
-// One tangent per lane: two or four per lane (values computed once for them) measured slower on
-// the large workload's adjoint (444 and 448 against 326 ms): their registers (221, 324) leave
-// fewer wavefronts to hide the pusher's serial chain of steps.
-constexpr int kTanND = 1;
-constexpr int kTanLanes = (kParams + kTanND - 1) / kTanND;          // lanes per particle
-constexpr int kTanStateDoubles = 9 * (1 + kTanND);                  // per lane
-static_assert(kTanLanes * kTanStateDoubles <= 7 * 18, "the workspace holds 126 doubles of state per particle");
-
-__global__ __launch_bounds__(64) void k_boris_tangent_span(const double *__restrict__ init, int64_t n_particles,
-                                                           int64_t s0, int64_t n_span, double t_start, double dt,
-                                                           LaserDev L, double *__restrict__ tstate,
-                                                           const double *__restrict__ g_r,
-                                                           const double *__restrict__ g_b,
-                                                           const double *__restrict__ g_a,
-                                                           double *__restrict__ grad_init,
-                                                           double *__restrict__ grad_a0)
-{
-    using D = Dual<kTanND>;
-    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= n_particles * kTanLanes) return;
-    const int64_t k = l / kTanLanes;
-    const int p0 = (int)(l - k * kTanLanes) * kTanND;  // parameters p0 .. p0 + kTanND - 1
-    D a0(L.a0);
-#pragma unroll
-    for (int j = 0; j < kTanND; ++j) a0.d[j] = (p0 + j == 6) ? 1.0 : 0.0;
-    PushState<D> S;
-    double *st = tstate + kTanStateDoubles * l;
-    if (s0 == 0) {
-        D in[6];
-        for (int c = 0; c < 6; ++c) {
-            in[c] = D(init[6 * k + c]);
-#pragma unroll
-            for (int j = 0; j < kTanND; ++j) in[c].d[j] = (c == p0 + j) ? 1.0 : 0.0;
-        }
-        push_start(L, a0, in, t_start, dt, S);
-    } else {
-        D *f[9] = {&S.x, &S.y, &S.z, &S.usx, &S.usy, &S.usz, &S.uhx, &S.uhy, &S.uhz};
-        for (int c = 0; c < 9; ++c) {
-            f[c]->v = st[c];
-#pragma unroll
-            for (int j = 0; j < kTanND; ++j) f[c]->d[j] = st[9 + 9 * j + c];
-        }
-        // the same arguments as the step that reached sample s0: the same field and derivative
-        laser_eb(L, a0, S.x, S.y, S.z, t_start + (double)s0 * dt, S.Ex, S.By);
-    }
-    double acc[kTanND];
-#pragma unroll
-    for (int j = 0; j < kTanND; ++j) acc[j] = 0.0;
-    for (int64_t i = 0; i < n_span; ++i) {
-        D rr[3], bb[3], aa[3];
-        push_sample(S, rr, bb, aa);
-        const size_t o = (size_t)(k * n_span + i) * 3;
-        for (int c = 0; c < 3; ++c) {
-            const double gr = g_r[o + c], gb = g_b[o + c], ga = g_a[o + c];
-#pragma unroll
-            for (int j = 0; j < kTanND; ++j) acc[j] += gr * rr[c].d[j] + gb * bb[c].d[j] + ga * aa[c].d[j];
-        }
-        if (i + 1 == n_span) break;
-        push_step(L, a0, t_start + (double)(s0 + i + 1) * dt, dt, S);
-    }
-    {
-        const D *f[9] = {&S.x, &S.y, &S.z, &S.usx, &S.usy, &S.usz, &S.uhx, &S.uhy, &S.uhz};
-        for (int c = 0; c < 9; ++c) {
-            st[c] = f[c]->v;
-#pragma unroll
-            for (int j = 0; j < kTanND; ++j) st[9 + 9 * j + c] = f[c]->d[j];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < kTanND; ++j) {
-        const int p = p0 + j;
-        if (p >= kParams) break;
-        double *out = p < 6 ? grad_init + 6 * k + p : grad_a0 + k;
-        *out = s0 == 0 ? acc[j] : *out + acc[j];
-    }
 }
 
 LaserDev laser_dev(const lw_laser_t &l)
@@ -969,7 +1148,8 @@ LaserDev laser_dev(const lw_laser_t &l)
 
 // samples s0 .. s0 + n_span - 1 (r given) and / or max |r|^2 over them (rmax2 given)
 static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, double *state, double *r, double *beta,
-                             double *beta_dot, double *rmax2, hipStream_t s, const char *what)
+                             double *beta_dot, double *rmax2, hipStream_t s, const char *what, double *ck = nullptr,
+                             int64_t seg = kPushSteps)
 {
     if (t->n_particles == 0 || n_span == 0) return LW_OK;
     const LaserDev L = laser_dev(t->laser);
@@ -982,7 +1162,7 @@ static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, dou
     // else two (10000 particles, 313 blocks: 7.6 ms with four, whose chains share SIMDs, 4.6 with two)
     auto go = [&](auto *k, int nc) {
         k<<<blocks, 64 * (1 + nc), 0, s>>>(t->init, t->n_particles, s0, n_span, t->t_start, t->dt, L, sorted, state, r, beta,
-                                          beta_dot, rmax2);
+                                          beta_dot, rmax2, ck, kTanStateDoubles, seg);
     };
     if (pair && blocks <= 256)
         r ? go(k_push<true, true, 4>, 4) : go(k_push<true, false, 4>, 4);
@@ -1005,23 +1185,27 @@ lw_status launch_boris_rmax2(const lw_traj_t *t, double *rmax2, hipStream_t s)
 }
 
 lw_status launch_boris_span(const lw_traj_t *t, int64_t s0, int64_t n_span, double *state, double *r, double *beta,
-                            double *beta_dot, double *rmax2, hipStream_t s)
+                            double *beta_dot, double *rmax2, hipStream_t s, double *tstate)
 {
-    return launch_push(t, s0, n_span, state, r, beta, beta_dot, rmax2, s, "lw_deposit_td (pusher span)");
+    const TanSegments g = tangent_segments(t->n_particles, n_span);
+    return launch_push(t, s0, n_span, state, r, beta, beta_dot, rmax2, s, "lw_deposit_td (pusher span)",
+                       tstate && g.n > 1 ? tstate + kTanCk : nullptr, g.len);
 }
 
-lw_status launch_boris_bwd_span(const lw_traj_t *t, int64_t s0, int64_t n_span, double *tstate, const double *g_r,
-                                const double *g_beta, const double *g_beta_dot, double *grad_init, double *grad_a0,
-                                hipStream_t s)
+lw_status launch_boris_bwd_span(const lw_traj_t *t, int64_t s0, int64_t n_span, const double *state, double *tstate,
+                                double *res, const double *g_r, const double *g_beta, const double *g_beta_dot,
+                                double *grad_init, double *grad_a0, hipStream_t s)
 {
     if (t->n_particles == 0 || n_span == 0) return LW_OK;
     const LaserDev L = laser_dev(t->laser);
-    const int64_t lanes = t->n_particles * kTanLanes;
-    const int64_t blocks = (lanes + 63) / 64;
+    const TanSegments g = tangent_segments(t->n_particles, n_span);
+    const int64_t lanes = t->n_particles * kParams;
     hipEvent_t ev = timing_begin(LW_KERNEL_BORIS_TANGENT, s);
-    k_boris_tangent_span<<<(unsigned)blocks, 64, 0, s>>>(t->init, t->n_particles, s0, n_span, t->t_start, t->dt, L,
-                                                        tstate, g_r, g_beta, g_beta_dot, grad_init, grad_a0);
+    k_tangent_segment<<<(unsigned)((lanes * g.n + 63) / 64), 64, 0, s>>>(t->init, t->n_particles, s0, n_span, g.n, g.len,
+                                                                        t->t_start, t->dt, L, tstate, g_r, g_beta, g_beta_dot, res);
     timing_end(LW_KERNEL_BORIS_TANGENT, ev, s);
+    k_tangent_join<<<(unsigned)((lanes + 255) / 256), 256, 0, s>>>(t->n_particles, g.n, res, state, tstate, s0 == 0, grad_init,
+                                                                   grad_a0);
     return check_launch("lw_deposit_td_bwd_boris (tangent span)");
 }
 

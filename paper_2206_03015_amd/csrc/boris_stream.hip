@@ -207,7 +207,7 @@ lw_status launch_deposit_bwd_boris(const lw_traj_t *t, const lw_grid_t *gr, int 
             const int64_t n_span = std::min<int64_t>(P.span, ns - s0);
             // the span's samples, the deposit adjoint over its intervals (dJ/d samples), then
             // the tangents of the same span contracted with them
-            st = launch_boris_span(&push, s0, n_span, pstate, r, b, bd, whole ? rb2 : nullptr, s);
+            st = launch_boris_span(&push, s0, n_span, pstate, r, b, bd, whole ? rb2 : nullptr, s, tstate);
             if (st != LW_OK) return st;
             const int64_t nz = nb * n_span * 3;
             for (double *z : {gr_, gb, ga})
@@ -224,7 +224,8 @@ lw_status launch_deposit_bwd_boris(const lw_traj_t *t, const lw_grid_t *gr, int 
             sub.charge = t->charge ? t->charge + b0 : nullptr;
             st = launch_deposit_bwd(&sub, gr, fmask, geom, dE, gr_, gb, ga, nullptr, 0, s, s0, rb2);
             if (st != LW_OK) return st;
-            st = launch_boris_bwd_span(&push, s0, n_span, tstate, gr_, gb, ga, grad_init + 6 * b0, grad_a0 + b0, s);
+            // (the span's samples are read: their space takes the segments' results)
+            st = launch_boris_bwd_span(&push, s0, n_span, pstate, tstate, r, gr_, gb, ga, grad_init + 6 * b0, grad_a0 + b0, s);
             if (st != LW_OK) return st;
             if (s0 + n_span >= ns) break;
             s0 += n_span - 1;  // the next span starts at this span's last sample

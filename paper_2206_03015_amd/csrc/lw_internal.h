@@ -471,17 +471,19 @@ lw_status launch_boris(const lw_traj_t *traj, double *r, double *beta, double *b
 lw_status launch_boris_rmax2(const lw_traj_t *traj, double *rmax2, hipStream_t s);
 // samples s0 .. s0 + n_span - 1 of every particle of traj (LW_TRAJ_BORIS), starting from init
 // (s0 = 0) or from the pusher state [n_particles][9] left by the span that ended at sample s0;
-// rmax2 (or nullptr): max |r|^2 over the span's samples
+// rmax2 (or nullptr): max |r|^2 over the span's samples; tstate (or nullptr): the tangents' state, which takes
+// the pusher's state at the starts of their segments
 lw_status launch_boris_span(const lw_traj_t *traj, int64_t s0, int64_t n_span, double *state, double *r,
-                            double *beta, double *beta_dot, double *rmax2, hipStream_t s);
+                            double *beta, double *beta_dot, double *rmax2, hipStream_t s, double *tstate = nullptr);
 lw_status launch_boris_bwd(const lw_traj_t *traj, const double *g_r, const double *g_beta,
                            const double *g_beta_dot, double *grad_init, double *grad_a0, hipStream_t s);
 // the pusher's tangents over samples s0 .. s0 + n_span - 1 (gradients g_* [n_particles][n_span][3]),
-// their state [n_particles][7][18] carried between spans; the first span (s0 = 0) writes
+// their state [n_particles][7][18] carried between spans; state: the pusher's after the same span; res:
+// the segments' results, at most 9 doubles per (particle, sample); the first span (s0 = 0) writes
 // grad_init, grad_a0, later ones add to them
-lw_status launch_boris_bwd_span(const lw_traj_t *traj, int64_t s0, int64_t n_span, double *tstate,
-                                const double *g_r, const double *g_beta, const double *g_beta_dot, double *grad_init,
-                                double *grad_a0, hipStream_t s);
+lw_status launch_boris_bwd_span(const lw_traj_t *traj, int64_t s0, int64_t n_span, const double *state, double *tstate,
+                                double *res, const double *g_r, const double *g_beta, const double *g_beta_dot,
+                                double *grad_init, double *grad_a0, hipStream_t s);
 // adjoint of the deposit; rbound2 as for launch_deposit (nullptr: computed from the samples into
 // ws, which then needs deposit_bwd_ws_bytes(n_particles) bytes)
 lw_status launch_deposit_bwd(const lw_traj_t *traj, const lw_grid_t *grid, int field_mask, int geom, const double *dE,

@@ -75,3 +75,28 @@ def test_ranked_blocks_and_coasting_give_the_same_bits(n_p, n_samples, keys):
     ref = oracle.boris(init[:3], *args)
     for g, o, tol in zip(whole, ref, (1e-12, 1e-12, 1e-9)):
         assert np.max(np.abs(g[:3].cpu().numpy() - o)) <= tol * np.max(np.abs(o))
+
+
+@pytest.mark.parametrize("n_p, n_samples", [(1, 127), (1, 128), (5, 129), (10, 641), (40, 700)])
+def test_tangent_segments_equal_one_segment(n_p, n_samples):
+    """The streamed adjoint takes the tangents in segments of at least 64 samples (one below 128 samples); the adjoint
+    of the stored trajectories runs each in one.  Same sums in another order: 1e-12 of the largest gradient."""
+    from paper_2206_03015_amd import lw
+    W = inputs.workload("bunch").scaled(n_p=n_p, n_steps=n_samples - 1, n_side=2, n_obs=512)
+    L = W.laser
+    init = inputs.bunch_init(W)
+    init[:, 2] = np.random.default_rng(n_p).uniform(-2e-6, 2e-6, n_p)
+    init = torch.as_tensor(init, device=DEV)
+    args = (n_samples, -1e-15, W.dt, L.a0, L.lam, L.w0, L.n_cycles)
+    x = torch.as_tensor(inputs.pixel_positions(W.n_side, W.theta_max, W.D), device=DEV)
+    r, b, bd = lw.trajectory_boris(init, *args)
+    t0 = -1e-15 - float(r[:, 0, 2].max()) / inputs.C_LIGHT
+    dt_obs = (n_samples - 1) * W.dt / (2 * W.gamma ** 2) / 256
+    grid = (x, t0, dt_obs, 512)
+    dE = torch.randn((4, 3, 512), dtype=torch.float64, device=DEV, generator=torch.Generator(DEV).manual_seed(1))
+    g = lw.deposit_td_bwd(r, b, bd, args[1], W.dt, *grid, dE)
+    assert float(g[0].abs().max()) > 0
+    want = lw.trajectory_boris_bwd(init, *args, *g)
+    got = lw.deposit_td_bwd_boris(init, *args, *grid, dE)
+    for a, o in zip(got, want):
+        assert float((a - o).abs().max()) <= 1e-12 * float(o.abs().max())
