@@ -36,7 +36,7 @@ constexpr int kTanStateBytes = 7 * 18 * sizeof(double);
 
 inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
-// workspace of a plan.  Forward: deposit scratch (records of the span), pusher states, the
+// workspace of a plan.  Forward: deposit scratch (arrival bases of the span), pusher states, the
 // particles' max |r|^2, r, beta, beta_dot of the span.  Adjoint (bwd): tangent states, pusher
 // states, the particles' max |r|^2, the span's samples and their gradients.
 size_t plan_bytes(int64_t B, int64_t L, int prec, bool bwd)
@@ -44,18 +44,18 @@ size_t plan_bytes(int64_t B, int64_t L, int prec, bool bwd)
     const size_t arr = align256((size_t)B * (size_t)L * 3 * sizeof(double));
     const size_t rb = align256((size_t)B * sizeof(double));
     if (bwd) return align256((size_t)B * kTanStateBytes) + align256((size_t)B * kStateBytes) + rb + 6 * arr;
-    return align256(deposit_ws_bytes(B, L, prec)) + align256((size_t)B * kStateBytes) + rb + 3 * arr;
+    return align256(deposit_ws_bytes(B, L)) + align256((size_t)B * kStateBytes) + rb + 3 * arr;
 }
 
-// bytes per (particle, sample) of a plan: samples (72), records (forward) or gradients (adjoint)
-size_t per_sample_bytes(int prec, bool bwd) { return bwd ? 144 : 72 + (prec == LW_PREC_FP64 ? 80 : 64); }
+// bytes per (particle, sample) of a plan: samples (72), arrival bases (forward) or gradients (adjoint)
+size_t per_sample_bytes(bool bwd) { return bwd ? 144 : 80; }
 
 // longest span (<= lmax) of B particles within `bytes` (0 if not even one sample fits)
 int64_t fit_span(int64_t B, int64_t lmax, size_t bytes, int prec, bool bwd)
 {
     const size_t fixed = plan_bytes(B, 1, prec, bwd);
     if (fixed > bytes) return 0;
-    const size_t per_sample = (size_t)B * per_sample_bytes(prec, bwd);
+    const size_t per_sample = (size_t)B * per_sample_bytes(bwd);
     int64_t L = std::min<int64_t>(lmax, 1 + (int64_t)((bytes - fixed) / per_sample));
     while (L > 1 && plan_bytes(B, L, prec, bwd) > bytes) --L;
     return L;
@@ -66,7 +66,7 @@ int64_t fit_batch(int64_t bmax, int64_t L, size_t bytes, int prec, bool bwd)
 {
     const size_t fixed = plan_bytes(1, L, prec, bwd);
     if (fixed > bytes) return 0;
-    const size_t per_particle_bytes = (size_t)L * per_sample_bytes(prec, bwd) + kStateBytes + 3 * sizeof(double) +
+    const size_t per_particle_bytes = (size_t)L * per_sample_bytes(bwd) + kStateBytes + 3 * sizeof(double) +
                                       (bwd ? kTanStateBytes : 0);
     int64_t B = std::min<int64_t>(bmax, 1 + (int64_t)((bytes - fixed) / per_particle_bytes));
     while (B > 1 && plan_bytes(B, L, prec, bwd) > bytes) --B;
@@ -131,7 +131,7 @@ lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec
     }
     const BorisPlan P = boris_plan_fit(n_p, ns, t->span, ws_bytes, prec);
     if (P.batch < 1 || (ns > 1 && P.span < 2)) return fail(LW_E_WORKSPACE, "lw_deposit_td: workspace holds no span");
-    const size_t dep_bytes = align256(deposit_ws_bytes(P.batch, P.span, prec));
+    const size_t dep_bytes = align256(deposit_ws_bytes(P.batch, P.span));
     char *p = (char *)ws + dep_bytes;
     double *state = (double *)p;
     p += align256((size_t)P.batch * kStateBytes);

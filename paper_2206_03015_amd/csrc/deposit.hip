@@ -2,17 +2,13 @@
 // Sec. "Interpolation"), forward pass.
 //
 // Work decomposition (one GPU's share of the paper's detector decomposition):
-//   * a pre-pass writes, for every (particle, sample), a record: the sample's arrival base d
+//   * a pre-pass writes, for every (particle, sample), the sample's arrival base d
 //     (the two large, cancelling terms of the arrival time, carried in double-double and
-//     rounded once) and, for the exact geometry with the path term in series form, the
-//     coefficients of the arrival time as a polynomial in the pixel variable b
-//     (tau = sum_j c_j b^j, b = C((1 - n_z) z - n_x x - n_y y): one fused multiply-add per
-//     degree and pixel, at a lower degree where kModeRecLow applies); it also flags particles
-//     whose arrival times are not provably increasing and finds each particle's max |r|^2; a pixel
-//     table holds each pixel's constants;
+//     rounded once), flags particles whose arrival times are not provably increasing and finds
+//     each particle's max |r|^2; a pixel table holds each pixel's constants;
 //   * fast path (k_sweep, particles whose arrival times provably increase): for each pixel the grid
 //     points of the window are looked up among the samples, not the samples among the grid points.
-//     A block takes a particle in steps of 256 samples, finds from the arrival times at the steps'
+//     A block takes a particle in steps of 256 samples (128 in FP64), finds from the arrival times at the steps'
 //     ends which steps hold window grid points for its 128 pixels, stages those steps' samples in
 //     LDS and gives every lane one (pixel, grid point) pair: the lane finds the sample interval of
 //     its grid point, evaluates the field at the interval's two ends and adds the interpolated
@@ -87,24 +83,12 @@ constexpr int kModeMixed = 6;
 // fields, 3 of 5 with double ones) where tail_negligible holds for the particle and the tile
 constexpr int kModeRecLow = 7;
 
-// Record of one sample (doubles):
-//   far field:          d, x, y, z
-//   exact, degree 3:    c_0, c_1, c_2, x, y, z, d, (pad)
-//   exact, degree 5:    c_0, c_1, c_2, c_3, c_4, x, y, z, d, (pad)
-// (the leading coefficient c_DEG is the same for every sample and is not stored)
+// Degrees of the arrival time as a polynomial in the pixel variable (exact geometry), and the lower one of kModeRecLow
 template <int GEOM, bool F64>
 struct RecLayout {
     static constexpr int DEG = GEOM == LW_GEOM_FARFIELD ? 0 : (F64 ? 5 : 3);
-    static constexpr int LOW = GEOM == LW_GEOM_FARFIELD ? 0 : (F64 ? 3 : 2);  // degree of kModeRecLow
-    static constexpr int X = GEOM == LW_GEOM_FARFIELD ? 1 : DEG;      // x, y, z at X, X + 1, X + 2
-    static constexpr int D = GEOM == LW_GEOM_FARFIELD ? 0 : DEG + 3;  // d
-    static constexpr int W = GEOM == LW_GEOM_FARFIELD ? 4 : DEG + 5;  // width
+    static constexpr int LOW = GEOM == LW_GEOM_FARFIELD ? 0 : (F64 ? 3 : 2);
 };
-__host__ __device__ constexpr int rec_width(int geom, bool f64)
-{
-    return geom == LW_GEOM_FARFIELD ? RecLayout<LW_GEOM_FARFIELD, false>::W
-                                    : (f64 ? RecLayout<LW_GEOM_EXACT, true>::W : RecLayout<LW_GEOM_EXACT, false>::W);
-}
 
 // number of window grid points <= tau: clamp(floor(tau) + 1, 0, n_obs)
 __device__ __forceinline__ int64_t grid_count(double tau, double n_obs)
@@ -196,21 +180,38 @@ __device__ __forceinline__ PixC pixc_row(P row)
     return p;
 }
 
-// The part of a record a scan mode reads: offset OFF and count N of doubles; X: offset of the
-// position within them; LEAD: the value (c_0 or d) that carries the arrival time's constant term
-// (-inf there makes the arrival time -inf: no crossing)
+// The values of a sample that a scan mode's arrival time takes (N of them; X: offset of the position):
+//   far field:             d, x, y, z
+//   polynomial records:    c_0 .. c_{DEG-1}, x, y, z (the leading coefficient is the same for every sample)
+//   kModeMixed:            x, y, z, d
 template <int GEOM, bool F64, int MODE>
 struct ScanVals {
     using L = RecLayout<GEOM, F64>;
-    static constexpr bool kRecMode = MODE == kModeRec3 || MODE == kModeRec5 || MODE == kModeRecLow;
-    static constexpr int OFF = MODE == kModeMixed ? L::X : 0;
     static constexpr int N = (MODE == kModeFar || MODE == kModeMixed) ? 4 : L::DEG + 3;
     static constexpr int X = MODE == kModeFar ? 1 : (MODE == kModeMixed ? 0 : L::DEG);
-    static constexpr int LEAD = MODE == kModeMixed ? 3 : 0;
 };
+template <int GEOM, bool F64, int MODE>
+__device__ __forceinline__ void scan_vals(double d, double x, double y, double z, double C, double Dref, double *v)
+{
+    using V = ScanVals<GEOM, F64, MODE>;
+    v[V::X] = x;
+    v[V::X + 1] = y;
+    v[V::X + 2] = z;
+    if constexpr (MODE == kModeFar) {
+        v[0] = d;
+    } else if constexpr (MODE == kModeMixed) {
+        v[3] = d;
+    } else {
+        constexpr int DEG = RecLayout<GEOM, F64>::DEG, LOW = RecLayout<GEOM, F64>::LOW;
+        double c[DEG + 1];
+        tau_poly<DEG>(d, x, y, z, C, Dref, c);
+#pragma unroll
+        for (int j = 0; j < DEG; ++j) v[j] = MODE == kModeRecLow && j > LOW ? 0.0 : c[j];
+    }
+}
 
-// Arrival time of one (sample, pixel) in scan mode MODE from the record values v and the pixel
-// constants P: far field tau = d + b; polynomial records tau = sum_j c_j b^j (c_DEG = cK; up to
+// Arrival time of one (sample, pixel) in scan mode MODE from the sample's values v (scan_vals) and the
+// pixel constants P: far field tau = d + b; polynomial records tau = sum_j c_j b^j (c_DEG = cK; up to
 // j = LOW in kModeRecLow); else
 // arrival_tau in the pixel's form (series where rb2 |x_m|^-2 <= kSeriesBound).  A (sample, pixel)
 // gets the same bits wherever it is evaluated.
@@ -247,17 +248,17 @@ struct DepWs {
     double *pt;                 // [kPixTabMax][kPT] pixel table of the current pass
     int *pflag;                 // [n_p] 0 = fast path
     unsigned long long *rmax2;  // [n_p] bits of max_i |r_i|^2 (non-negative doubles order as integers)
-    double *rec;                // [n_p][n_s][rec_width] records
+    double *d;                  // [n_p][n_s] arrival bases
 };
 
 constexpr size_t kPixTabBytes = (size_t)kPixTabMax * kPT * sizeof(double);
 
-// pixel table, flags, bounds and records (one record more than the samples: padding)
-size_t ws_bytes_for(int64_t n_p, int64_t ns, int rw)
+// pixel table, flags, bounds and arrival bases
+size_t ws_bytes_for(int64_t n_p, int64_t ns)
 {
     const size_t np = (size_t)std::max<int64_t>(n_p, 1), nsz = (size_t)std::max<int64_t>(ns, 1);
     return kPixTabBytes + align_up(np * sizeof(int), 256) + align_up(np * sizeof(unsigned long long), 256) +
-           align_up((np * nsz + 1) * (size_t)rw * sizeof(double), 256);
+           align_up(np * nsz * sizeof(double), 256);
 }
 
 DepWs carve(void *ws, int64_t n_p)
@@ -270,29 +271,27 @@ DepWs carve(void *ws, int64_t n_p)
     p += align_up((size_t)std::max<int64_t>(n_p, 1) * sizeof(int), 256);
     w.rmax2 = (unsigned long long *)p;
     p += align_up((size_t)std::max<int64_t>(n_p, 1) * sizeof(unsigned long long), 256);
-    w.rec = (double *)p;
+    w.d = (double *)p;
     return w;
 }
 
 // ---------------------------------------------------------------------------------------------
-// pre-pass: one block per (particle, chunk of samples): records, per-particle max |r|^2 and the
-// fast-path flag
-template <int GEOM, int DEG>
+// pre-pass: one block per (particle, chunk of samples): arrival bases, per-particle max |r|^2 and the
+// fast-path flag.  Bound by memory: 72 bytes of a sample read, 8 written (with the polynomial's coefficients
+// and the position stored beside the base, 64 or 80 written, the pre-pass of 2000 x 20001 samples took
+// 1.75 ms; the coefficients are formed where a step's samples are staged instead)
 __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, const double *__restrict__ beta,
-                                                 const double *__restrict__ beta_dot,
-                                                 const double *__restrict__ x_det, int64_t n_samples, int chunk,
+                                                 const double *__restrict__ beta_dot, int64_t n_samples, int chunk,
                                                  int64_t sample0, double t_start, double dt, double t0,
-                                                 double dt_obs, double C, double *__restrict__ rec,
+                                                 double dt_obs, double C, double *__restrict__ base,
                                                  int *__restrict__ pflag, unsigned long long *__restrict__ rmax2)
 {
-    using L = RecLayout<GEOM, DEG == 5>;
     __shared__ unsigned long long s_max[4];
     __shared__ int s_bad[4];
     const int64_t k = blockIdx.x;
     const int64_t i_begin = (int64_t)blockIdx.y * chunk;
     const int64_t i_end = std::min<int64_t>(i_begin + chunk, n_samples);
     const double cdt_step = kC * dt;
-    const double Dref = pix_geo(x_det, 0).D;  // the records' pixel distance
     double mx = 0.0;
     int bad = 0;
     for (int64_t i = i_begin + threadIdx.x; i < i_end; i += blockDim.x) {
@@ -301,18 +300,7 @@ __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, c
         const double x = ri[0], y = ri[1], z = ri[2];
         // sample i of the arrays is sample sample0 + i of the trajectory (spans of a longer one)
         const double d = arrival_base(t_start, dt, (double)(sample0 + i), t0, dt_obs, z);
-        double *o = rec + (size_t)s * L::W;
-        o[L::D] = d;
-        o[L::X] = x;
-        o[L::X + 1] = y;
-        o[L::X + 2] = z;
-        if (GEOM == LW_GEOM_EXACT) {
-            double c[DEG + 1];
-            tau_poly<DEG>(d, x, y, z, C, Dref, c);
-#pragma unroll
-            for (int j = 0; j < DEG; ++j) o[j] = c[j];
-            o[L::W - 1] = 0.0;
-        }
+        base[s] = d;
         const double rr = sq3(x, y, z);
         bool b = !sample_usable(ri, bi, di);
         if (!b) {
@@ -402,12 +390,13 @@ struct Wave {
     const double *__restrict__ beta_dot;
     const double *__restrict__ charge;
     const double *__restrict__ x_det;
-    const double *__restrict__ rec;
-    const double *__restrict__ pt;  // pixel table of this pass
+    const double *__restrict__ base;  // arrival bases
+    const double *__restrict__ pt;    // pixel table of this pass
     T *__restrict__ E;
     DepShape sh;
-    double cK;  // leading coefficient of the polynomial records
-    double rb2; // the current particle's bound of |r|^2 over its whole trajectory
+    double cK;   // leading coefficient of the polynomial records
+    double Dref; // the records' pixel distance
+    double rb2;  // the current particle's bound of |r|^2 over its whole trajectory
     int lane;
     int64_t tile, k0;
     uint2 *q;          // queue ring in LDS: {sample index, (particle - k0) << kPixBits | pixel in tile}
@@ -417,19 +406,6 @@ struct Wave {
     DetAcc det;        // high words and row scales (ACC == kAccFixed)
 
     __device__ __forceinline__ static uint32_t qwrap(uint32_t v) { return v >= kQCap ? v - kQCap : v; }
-
-    using Lay = RecLayout<GEOM, sizeof(T) == 8>;
-    // the part of a record a scan mode reads: offset and count of doubles
-    template <int MODE>
-    static constexpr int scan_off()
-    {
-        return MODE == kModeMixed ? Lay::X : 0;
-    }
-    template <int MODE>
-    static constexpr int scan_n()
-    {
-        return MODE == kModeFar || MODE == kModeMixed ? 4 : Lay::DEG + 3;
-    }
 
     // Arrival time of pixel h from the scan values v of a sample's record (wavefront-uniform)
     template <int MODE>
@@ -442,9 +418,8 @@ struct Wave {
     template <int MODE>
     __device__ __forceinline__ void load_scan(int64_t k, int64_t i, double *v) const
     {
-        const double *src = rec + ((size_t)k * sh.n_samples + i) * Lay::W + scan_off<MODE>();
-#pragma unroll
-        for (int c = 0; c < scan_n<MODE>(); ++c) v[c] = src[c];
+        const size_t s = (size_t)k * sh.n_samples + i;
+        scan_vals<GEOM, sizeof(T) == 8, MODE>(base[s], r[3 * s], r[3 * s + 1], r[3 * s + 2], sh.C, Dref, v);
     }
 
     // Evaluate the cnt oldest queued crossings (lane j takes entry j).
@@ -553,7 +528,7 @@ struct Wave {
                                                      unsigned long long &c0, unsigned long long &c1,
                                                      unsigned long long &c2, unsigned long long &c3)
     {
-        constexpr int NV = scan_n<MODE>();
+        constexpr int NV = ScanVals<GEOM, sizeof(T) == 8, MODE>::N;
         const int64_t ns = sh.n_samples;
         const double nob = (double)sh.n_obs;
         const double q = charge ? charge[k] : -kQe;
@@ -614,7 +589,7 @@ struct Wave {
 template <typename T, int GEOM, int ACC>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_careful(
     const double *__restrict__ r, const double *__restrict__ beta, const double *__restrict__ beta_dot,
-    const double *__restrict__ charge, const double *__restrict__ x_det, const double *__restrict__ rec,
+    const double *__restrict__ charge, const double *__restrict__ x_det, const double *__restrict__ base,
     const double *__restrict__ pt, const int *__restrict__ pflag, const unsigned long long *__restrict__ rmax2,
     const double *__restrict__ rbound2, T *__restrict__ E, unsigned long long *__restrict__ diag, DepShape sh, DetAcc det)
 {
@@ -677,7 +652,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
     w.beta_dot = beta_dot;
     w.charge = charge;
     w.x_det = x_det;
-    w.rec = rec;
+    w.base = base;
+    w.Dref = Dref;
     w.pt = pt;
     w.E = E;
     if constexpr (ACC != kAccFloat) w.det = det;
@@ -721,13 +697,12 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 // ---------------------------------------------------------------------------------------------
 // Fast path.  A block owns a tile of kTilePix pixels and a group of particles (and, where there are
 // few of those, a segment of the samples).  For each particle:
-//   * a mask of the steps (kStep samples, kStep - 1 intervals; neighbouring steps share a sample)
-//     that hold window grid points for some pixel of the tile, from the arrival times at the steps'
-//     boundaries alone, lanes over pixels (arrival times increase on this path);
-//   * per such step the samples are staged in LDS (the record's scan values, beta, 1/|beta|,
-//     beta_dot) and every pixel's grid points in the step counted;
-//   * sparse steps (deposit_points): lanes over the step's (pixel, grid point) pairs.  A lane finds
-//     the interval of its grid point (bracket from the pixel's arrival times at five samples, then
+//   * a mask of the steps (H intervals) that hold window grid points for some pixel of the tile, from the
+//     arrival times at the steps' boundaries alone, lanes over pixels (arrival times increase on this path);
+//   * per such step the samples are staged in LDS (scan values, beta, 1/|beta|, beta_dot), in a ring that holds this
+//     step's and the one's before, and every pixel's grid points counted;
+//   * sparse steps (deposit_points): lanes over (pixel, grid point) pairs.  A lane finds
+//     the interval of its grid point (bracket from the pixel's arrival times at five samples of the step, then
 //     three-point interpolation), evaluates the field at its two ends and adds the interpolated
 //     value to the trace;
 //   * dense steps (deposit_dense; at least kDensePoints grid points per interval): per pixel, lanes
@@ -735,44 +710,58 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 //     points interpolate.
 // The interval found is the one with tau_{i-1} < u <= tau_i whichever way it is found, and the
 // contribution's arithmetic is the same in both, so a contribution has the same bits.
-constexpr int kStep = 256;      // samples per step, one per thread of the block
+//
+// The traces' atomics set the time: they leave the chip's L2 as requests of at most 64 bytes, and the memory side takes
+// 18-20 billion of those a second whatever they hold (285 G floats/s in aligned groups of 16, 98 G/s in runs of 8
+// at any place).  A step of the bunch workload has 12 grid points a pixel, 7.1 to a request; so the last points of
+// a step wait for the next one where that completes their 64 bytes, which is what the second half of the ring is
+// for: 12.8 to a request.  2000 x 20001 samples, 4096 pixels, mixed: 51.3 -> 34.8 ms.
+template <typename T>
+struct SweepCfg {
+    static constexpr int NT = sizeof(T) == 8 ? 128 : 256;  // samples of a step, neighbouring steps sharing one
+    static constexpr int H = NT - 1;                       // intervals of a step
+    static constexpr int R = 2 * NT;                       // ring
+    static constexpr int kThreads = 2 * NT;
+    static constexpr int G = 64 / (int)sizeof(T);  // elements per request
+    static constexpr int kDensePix = sizeof(T) == 8 ? 1 : 2;  // pixels of a dense step at a time
+};
 constexpr int kSteps = 64;      // steps per mask
 // grid points per interval of the step's live pixels from which a step is dense
 constexpr float kDensePoints = 0.6f;
 
 template <typename T, int GEOM>
 struct SweepLds {
-    using Lay = RecLayout<GEOM, sizeof(T) == 8>;
-    static constexpr int NP = GEOM == LW_GEOM_FARFIELD ? 2 : (Lay::DEG + 3) / 2;  // pairs of scan values
+    using Cfg = SweepCfg<T>;
+    static constexpr int NP = GEOM == LW_GEOM_FARFIELD ? 2 : (RecLayout<GEOM, sizeof(T) == 8>::DEG + 3) / 2;  // pairs of scan values
     static constexpr int PX = GEOM == LW_GEOM_FARFIELD ? 8 : 6;  // doubles per pixel: o, px, py, then x_m or n, 1/|x_m|
-    double2 rec[NP][kStep];
-    double2 be[2][kStep];  // beta_x, beta_y; beta_z, 1/|beta| (0 at rest)
-    T acc[3][kStep];       // beta_dot
+    double2 rec[NP][Cfg::R];  // sample i at i mod R
+    double2 be[2][Cfg::R];    // beta_x, beta_y; beta_z, 1/|beta| (0 at rest)
+    T acc[3][Cfg::R];         // beta_dot
     double2 px[kTilePix][PX / 2];
-    double tl[kTilePix], th[kTilePix];  // a pixel's arrival times at the step's first and last sample
-    union {
-        double node[3][kTilePix];  // and at a quarter, half and three quarters of it
-        T e[3][kStep];             // dense steps: one pixel's fields
-    };
-    double tau[kStep];  // dense steps: one pixel's arrival times
-    int cum[kTilePix];  // grid points of the tile half's pixels before this one
-    int tot[2];
+    // a pixel's arrival times at the first sample of a step, a quarter, half and three quarters of it and the last,
+    // of this step (its parity) and the one before
+    double node[2][5][kTilePix];
+    double tau[Cfg::kDensePix][Cfg::NT];  // dense steps: the current pixels' arrival times
+    T e[Cfg::kDensePix][3][Cfg::NT];      // and fields
+    int ulo[kTilePix];       // a pixel's first grid point to deposit
+    int cum[2][kTilePix];    // grid points of the tile half's pixels before this one: sparse, held back before a dense step
+    int tot[2][2], fresh[2];
     uint64_t live[2];  // pixels with grid points in the step
-    uint64_t mask[4];
+    uint64_t mask[Cfg::kThreads / 64];
     unsigned long long red[4];
 };
 
 template <typename T, int GEOM, int ACC>
 struct Sweep {
     static constexpr bool F64 = sizeof(T) == 8;
+    using Cfg = SweepCfg<T>;
     using Lds = SweepLds<T, GEOM>;
-    using Lay = RecLayout<GEOM, F64>;
     Lds &s;
     const double *__restrict__ pt;  // the tile's rows of the pixel table
     T *__restrict__ E;              // the tile's first trace row
     const DepShape &sh;
     DetAcc det;  // from the tile's first trace row
-    double cK, rb2, q;
+    double cK, Dref, rb2, q;
     int tid;
 
     // a pixel's constants in the arrival time of MODE
@@ -787,10 +776,12 @@ struct Sweep {
         P.py = s.px[p][1].x;
         return P;
     }
-    // arrival time of staged sample j at a pixel; v: its scan values
+    // arrival time of staged sample i at a pixel
     template <int MODE>
-    __device__ __forceinline__ double tau_at(const PixC &P, int j, double *v) const
+    __device__ __forceinline__ double tau_at(const PixC &P, int i) const
     {
+        const int j = i & (Cfg::R - 1);
+        double v[2 * Lds::NP];
 #pragma unroll
         for (int c = 0; c < Lds::NP; ++c) {
             if (2 * c >= ScanVals<GEOM, F64, MODE>::N) break;
@@ -800,17 +791,12 @@ struct Sweep {
         }
         return tau_eval<GEOM, F64, MODE>(P, v, cK, rb2, sh.C);
     }
+    // field of staged sample i at pixel p
     template <int MODE>
-    __device__ __forceinline__ double tau_at(const PixC &P, int j) const
-    {
-        double v[2 * Lds::NP];
-        return tau_at<MODE>(P, j, v);
-    }
-    // field of staged sample j at pixel p
-    template <int MODE>
-    __device__ __forceinline__ void field_at(int p, int j, T &ex, T &ey, T &ez) const
+    __device__ __forceinline__ void field_at(int p, int i, T &ex, T &ey, T &ez) const
     {
         constexpr int X = ScanVals<GEOM, F64, MODE>::X;
+        const int j = i & (Cfg::R - 1);
         double v[2 * Lds::NP];
 #pragma unroll
         for (int c = X / 2; c <= (X + 2) / 2; ++c) {
@@ -841,45 +827,64 @@ struct Sweep {
     {
         return F64 ? (T)(1.0 / dt) : (T)__builtin_amdgcn_rcpf((float)dt);
     }
-
-    // Stage samples i0 .. i0 + n of a particle (rk: its records' scan values, bk, dk: its beta, beta_dot)
-    template <int MODE>
-    __device__ __forceinline__ void stage(const double *rk, const double *bk, const double *dk, int64_t i0, int n) const
+    // the last grid point <= u whose element starts a request (of the pixel's first component; the tile's first
+    // element does, 3 kTilePix rows being a multiple of G)
+    __device__ __forceinline__ int64_t request_start(int p, int64_t u) const
     {
-        if (tid > n) return;
-        const int64_t i = i0 + tid;
-        const double *src = rk + (size_t)i * Lay::W;
-#pragma unroll
-        for (int c = 0; c < Lds::NP; ++c)
-            if (2 * c < ScanVals<GEOM, F64, MODE>::N) s.rec[c][tid] = make_double2(src[2 * c], src[2 * c + 1]);
-        const double bx = bk[3 * i], by = bk[3 * i + 1], bz = bk[3 * i + 2];
-        s.be[0][tid] = make_double2(bx, by);
-        s.be[1][tid] = make_double2(bz, inv_beta<T>(bx, by, bz));
-#pragma unroll
-        for (int c = 0; c < 3; ++c) s.acc[c][tid] = (T)dk[3 * i + c];
+        const int64_t off = (int64_t)(((uint64_t)p * 3 * (uint64_t)sh.n_obs) & (Cfg::G - 1));
+        return ((u + off) & ~(int64_t)(Cfg::G - 1)) - off;
     }
 
-    // The step's (pixel, grid point) pairs, one per lane
+    // Stage samples i0 + 1 .. i0 + n of a particle, and i0 unless the ring holds it (base, rk, bk, dk: its arrival
+    // bases, r, beta, beta_dot)
     template <int MODE>
-    __device__ __forceinline__ void deposit_points(int n, int tot0, int total) const
+    __device__ __forceinline__ void stage(const double *base, const double *rk, const double *bk, const double *dk, int i0, int n,
+                                          bool prev) const
     {
-        const double nob = (double)sh.n_obs;
-        const int q1 = n >> 2, q2 = n >> 1, q3 = (3 * n) >> 2;
-        for (int it = tid; it < total; it += kStep) {
+        const int t = tid & (Cfg::NT - 1);
+        if (t > n || (t == 0 && prev)) return;
+        const int64_t i = i0 + t;
+        const int j = (int)i & (Cfg::R - 1);
+        if (tid < Cfg::NT) {
+            double v[2 * Lds::NP];
+            scan_vals<GEOM, F64, MODE>(base[i], rk[3 * i], rk[3 * i + 1], rk[3 * i + 2], sh.C, Dref, v);
+#pragma unroll
+            for (int c = 0; c < Lds::NP; ++c)
+                if (2 * c < ScanVals<GEOM, F64, MODE>::N) s.rec[c][j] = make_double2(v[2 * c], v[2 * c + 1]);
+        } else {
+            const double bx = bk[3 * i], by = bk[3 * i + 1], bz = bk[3 * i + 2];
+            s.be[0][j] = make_double2(bx, by);
+            s.be[1][j] = make_double2(bz, inv_beta<T>(bx, by, bz));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s.acc[c][j] = (T)dk[3 * i + c];
+        }
+    }
+
+    // (pixel, grid point) pairs, one per lane: `total` of them, tot0 at the tile's first half of the pixels, pixel p's
+    // from ulo[p] on.  The step's samples are i0 .. i0 + n; those of the step before hold the points held back.
+    template <int MODE>
+    __device__ __forceinline__ void deposit_points(const int *cum, int i0, int n, bool prev, int par, int tot0, int total) const
+    {
+        for (int it = tid; it < total; it += Cfg::kThreads) {
             int p = it >= tot0 ? 64 : 0;
             const int r = it >= tot0 ? it - tot0 : it;
 #pragma unroll
             for (int b = 32; b > 0; b >>= 1)
-                if (s.cum[p + b] <= r) p += b;
+                if (cum[p + b] <= r) p += b;
             const PixC P = pixel<MODE>(p);
-            double ta = s.tl[p], tb = s.th[p];
-            const int u = (int)grid_count(ta, nob) + (r - s.cum[p]);
+            const int u = s.ulo[p] + (r - cum[p]);
             const double ud = (double)u;
-            // the quarter of the step that holds the crossing
-            int lo = 0, hi = n;
-            const double m2 = s.node[1][p];
+            // the step and the quarter of it that hold the crossing
+            const bool old = prev && !(ud > s.node[par][0][p]);
+            const double (*nd)[kTilePix] = s.node[old ? par ^ 1 : par];
+            int lo = old ? i0 - Cfg::H : i0;
+            const int len = old ? Cfg::H : n;
+            int hi = lo + len;
+            const int q1 = lo + (len >> 2), q2 = lo + (len >> 1), q3 = lo + ((3 * len) >> 2);
+            double ta = nd[0][p], tb = nd[4][p];
+            const double m2 = nd[2][p];
             const bool up = ud > m2;
-            const double m13 = s.node[up ? 2 : 0][p];
+            const double m13 = nd[up ? 3 : 1][p];
             const int q13 = up ? q3 : q1;
             if (up) {
                 lo = q2;
@@ -904,17 +909,17 @@ struct Sweep {
                 // slope at g of the parabola through the bracket's ends and g
                 const float d = ((yg - ya) * fr * __builtin_amdgcn_rcpf(fl) + (yb - yg) * fl * __builtin_amdgcn_rcpf(fr)) *
                                 __builtin_amdgcn_rcpf(fl + fr);
-                const float x = (float)g - yg * __builtin_amdgcn_rcpf(d);
+                const float x = __builtin_amdgcn_fmed3f(-yg * __builtin_amdgcn_rcpf(d), -1e3f, 1e3f);  // from g
                 if (tg >= ud) {
                     hi = g;
                     tb = tg;
                     yb = yg;
-                    g = (int)floorf(x);
+                    g += (int)floorf(x);
                 } else {
                     lo = g;
                     ta = tg;
                     ya = yg;
-                    g = (int)ceilf(x);
+                    g += (int)ceilf(x);
                 }
                 if (k >= 4) g = (lo + hi) >> 1;
             }
@@ -925,34 +930,49 @@ struct Sweep {
         }
     }
 
-    // Every pixel's intervals of the step, one pixel at a time
+    // Every pixel's intervals of the step, kDensePix pixels at a time
     template <int MODE>
-    __device__ __forceinline__ void deposit_dense(int n) const
+    __device__ __forceinline__ void deposit_dense(int i0, int n, int par) const
     {
         const double nob = (double)sh.n_obs;
+        constexpr int kShare = Cfg::kThreads / Cfg::kDensePix;
+        const int hb = tid / kShare, t = tid % kShare;
         uint64_t left[2] = {s.live[0], s.live[1]};
-        while (left[0] | left[1]) {  // the same in every thread
-            const int h = left[0] ? 0 : 1, p = 64 * h + (int)__builtin_ctzll(left[h]);
+        auto pop = [&]() {
+            const int h = left[0] ? 0 : 1;
+            if (!left[h]) return -1;
+            const int p = 64 * h + (int)__builtin_ctzll(left[h]);
             left[h] &= left[h] - 1;
-            const int64_t u0 = grid_count(s.tl[p], nob), u1 = grid_count(s.th[p], nob);
-            __syncthreads();  // the previous pixel's fields are read
-            if (tid <= n) {
-                s.tau[tid] = tau_at<MODE>(pixel<MODE>(p), tid);
+            return p;
+        };
+        while (left[0] | left[1]) {  // the same in every thread
+            int p = pop();
+            if constexpr (Cfg::kDensePix == 2) {
+                const int pb = pop();
+                if (hb) p = pb;
+            }
+            __syncthreads();  // the previous pixels' fields are read
+            if (p >= 0 && t <= n) {
+                s.tau[hb][t] = tau_at<MODE>(pixel<MODE>(p), i0 + t);
                 T x, y, z;
-                field_at<MODE>(p, tid, x, y, z);
-                s.e[0][tid] = x;
-                s.e[1][tid] = y;
-                s.e[2][tid] = z;
+                field_at<MODE>(p, i0 + t, x, y, z);
+                s.e[hb][0][t] = x;
+                s.e[hb][1][t] = y;
+                s.e[hb][2][t] = z;
             }
             __syncthreads();
-            for (int64_t u = u0 + tid; u < u1; u += kStep) {
+            if (p < 0) continue;
+            const int64_t u0 = grid_count(s.node[par][0][p], nob), u1 = grid_count(s.node[par][4][p], nob);
+            const double *tau = s.tau[hb];
+            for (int64_t u = request_start(p, u0) + t; u < u1; u += kShare) {
+                if (u < u0) continue;
                 const double ud = (double)u;
                 int lo = 0, hi = n;
-                double ta = s.tau[0], tb = s.tau[n];
+                double ta = tau[0], tb = tau[n];
                 for (int k = 0; hi - lo > 1; ++k) {
                     int g = lo + (int)((float)(hi - lo) * ((float)(ud - ta) * __builtin_amdgcn_rcpf((float)(tb - ta))));
                     g = (k & 3) == 3 ? (lo + hi) >> 1 : min(max(g, lo + 1), hi - 1);
-                    const double tg = s.tau[g];
+                    const double tg = tau[g];
                     if (tg >= ud) {
                         hi = g;
                         tb = tg;
@@ -961,35 +981,38 @@ struct Sweep {
                         ta = tg;
                     }
                 }
-                const T a[3] = {s.e[0][lo], s.e[1][lo], s.e[2][lo]}, b[3] = {s.e[0][hi], s.e[1][hi], s.e[2][hi]};
+                const T a[3] = {s.e[hb][0][lo], s.e[hb][1][lo], s.e[hb][2][lo]};
+                const T b[3] = {s.e[hb][0][hi], s.e[hb][1][hi], s.e[hb][2][hi]};
                 add(p, u, (T)(ud - ta) * inverse(tb - ta), a, b);
             }
         }
     }
 
-    // One particle's steps [st0, st1) (the same in every thread): rk, bk, dk as in stage
+    // One particle's steps [st0, st1) (the same in every thread): base, rk, bk, dk as in stage
     template <int MODE>
-    __device__ __forceinline__ void particle(const double *rk, const double *bk, const double *dk, int st0, int st1,
-                                             bool lane_ok) const
+    __device__ __forceinline__ void particle(const double *base, const double *rk, const double *bk, const double *dk, int st0,
+                                             int st1, bool lane_ok) const
     {
+        constexpr int kWaves = Cfg::kThreads / 64;
         const int ns = (int)sh.n_samples;
         const double nob = (double)sh.n_obs;
         const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int p = tid & (kTilePix - 1);
+        int last = -2;        // the step staged last
+        int64_t unext = 0;    // thread p < kTilePix: pixel p's first grid point not yet deposited
         for (int c0 = st0; c0 < st1; c0 += kSteps) {
-            // steps of this chunk with window grid points at some pixel: wavefronts 0, 1 (pixels) take
-            // the first half of the steps, 2, 3 the second
-            const int c1 = min(c0 + kSteps, st1), mid = c0 + (c1 - c0 + 1) / 2;
-            const int a = wv < 2 ? c0 : mid, b = wv < 2 ? mid : c1;
+            // steps of this chunk with window grid points at some pixel: pairs of wavefronts (pixels) take
+            // equal shares of the steps
+            const int c1 = min(c0 + kSteps, st1), share = (c1 - c0 + kWaves / 2 - 1) / (kWaves / 2);
+            const int a = min(c0 + (wv >> 1) * share, c1), b = min(a + share, c1);
             uint64_t mask = 0;
             if (a < b) {
                 const PixC P = pixel<MODE>(p);
                 auto count = [&](int st) {  // window grid points up to the first sample of step st
-                    const int64_t i = min((int64_t)st * (kStep - 1), (int64_t)ns - 1);
-                    const cdptr src = uniform_ptr(rk + (size_t)i * Lay::W);
+                    const int64_t i = min((int64_t)st * Cfg::H, (int64_t)ns - 1);
+                    const cdptr sd = uniform_ptr(base + i), sr = uniform_ptr(rk + 3 * i);
                     double v[2 * Lds::NP];
-#pragma unroll
-                    for (int c = 0; c < ScanVals<GEOM, F64, MODE>::N; ++c) v[c] = src[c];
+                    scan_vals<GEOM, F64, MODE>(sd[0], sr[0], sr[1], sr[2], sh.C, Dref, v);
                     return grid_count(tau_eval<GEOM, F64, MODE>(P, v, cK, rb2, sh.C), nob);
                 };
                 int64_t prev = count(a);
@@ -1004,49 +1027,69 @@ struct Sweep {
             __syncthreads();  // the previous chunk's masks are read
             if (lane == 0) s.mask[wv] = mask;
             __syncthreads();
-            mask = s.mask[0] | s.mask[1] | s.mask[2] | s.mask[3];
+            mask = 0;
+#pragma unroll
+            for (int v = 0; v < kWaves; ++v) mask |= s.mask[v];
             while (mask) {
                 const int st = c0 + (int)__builtin_ctzll(mask);
                 mask &= mask - 1;
-                const int64_t i0 = (int64_t)st * (kStep - 1);
-                const int n = (int)min((int64_t)(kStep - 1), (int64_t)ns - 1 - i0);  // intervals
-                stage<MODE>(rk, bk, dk, i0, n);
+                const bool prev = last == st - 1;
+                const bool more = st + 1 < c1 && ((mask >> (st + 1 - c0)) & 1);  // the next step follows
+                const int par = st & 1, i0 = st * Cfg::H;
+                const int n = min(Cfg::H, ns - 1 - i0);  // intervals
+                stage<MODE>(base, rk, bk, dk, i0, n, prev);
                 __syncthreads();
                 if (tid < kTilePix) {
                     double tl = 0.0, th = 0.0;
                     if (lane_ok) {
                         const PixC P = pixel<MODE>(p);
-                        tl = tau_at<MODE>(P, 0);
-                        th = tau_at<MODE>(P, n);
+                        tl = tau_at<MODE>(P, i0);
+                        th = tau_at<MODE>(P, i0 + n);
                     }
-                    s.tl[p] = tl;
-                    s.th[p] = th;
+                    s.node[par][0][p] = tl;
+                    s.node[par][4][p] = th;
+                    const int64_t cl = grid_count(tl, nob), ch = grid_count(th, nob);
+                    const int64_t u0 = prev ? unext : cl;
+                    // points from the last request's start on wait for the next step, if all of them are this step's
+                    const int64_t cut = request_start(p, ch);
+                    const int64_t u1 = more && cut >= cl ? cut : ch;
+                    s.ulo[p] = (int)u0;
                     // counts above 2^20 make the step dense, where they are not used
-                    const int cnt = (int)min(grid_count(th, nob) - grid_count(tl, nob), (int64_t)1 << 20);
-                    int sum = cnt;
+                    const int fresh = (int)min(ch - cl, (int64_t)1 << 20), held = (int)(cl - u0);
+                    const int cnt = (int)min(u1 - u0, (int64_t)1 << 20);
+                    int sum = cnt, sumh = held, sumf = fresh;
 #pragma unroll
                     for (int off = 1; off < 64; off <<= 1) {
-                        const int o = __shfl_up(sum, off);
-                        if (lane >= off) sum += o;
+                        const int o = __shfl_up(sum, off), oh = __shfl_up(sumh, off), of = __shfl_up(sumf, off);
+                        if (lane >= off) {
+                            sum += o;
+                            sumh += oh;
+                            sumf += of;
+                        }
                     }
-                    s.cum[p] = sum - cnt;
-                    const uint64_t live = __ballot(cnt > 0);
+                    s.cum[0][p] = sum - cnt;
+                    s.cum[1][p] = sumh - held;
+                    const uint64_t live = __ballot(fresh > 0);
                     if (lane == 63) {
-                        s.tot[wv] = sum;
+                        s.tot[0][wv] = sum;
+                        s.tot[1][wv] = sumh;
+                        s.fresh[wv] = sumf;
                         s.live[wv] = live;
                     }
-                } else {
-                    const PixC P = pixel<MODE>(p);
-                    s.node[0][p] = tau_at<MODE>(P, n >> 2);
-                    s.node[1][p] = tau_at<MODE>(P, n >> 1);
-                    s.node[2][p] = tau_at<MODE>(P, (3 * n) >> 2);
+                    unext = u1;
                 }
+                for (int c = tid / kTilePix; c >= 1 && c <= 3; c += Cfg::kThreads / kTilePix - 1)
+                    s.node[par][c][p] = lane_ok ? tau_at<MODE>(pixel<MODE>(p), i0 + ((c * n) >> 2)) : 0.0;
                 __syncthreads();
-                const int tot0 = s.tot[0], total = tot0 + s.tot[1];
-                if ((float)total >= kDensePoints * (float)((__popcll(s.live[0]) + __popcll(s.live[1])) * n))
-                    deposit_dense<MODE>(n);
-                else
-                    deposit_points<MODE>(n, tot0, total);
+                const bool dense = (float)(s.fresh[0] + s.fresh[1]) >=
+                                   kDensePoints * (float)((__popcll(s.live[0]) + __popcll(s.live[1])) * n);
+                const int d = dense ? 1 : 0, tot0 = s.tot[d][0], total = tot0 + s.tot[d][1];
+                deposit_points<MODE>(s.cum[d], i0, n, prev, par, tot0, total);
+                if (dense) {
+                    if (tid < kTilePix) unext = grid_count(s.node[par][4][p], nob);
+                    deposit_dense<MODE>(i0, n, par);
+                }
+                last = st;
                 __syncthreads();  // the step is read
             }
         }
@@ -1059,19 +1102,19 @@ struct SweepShape {
 };
 
 template <typename T, int GEOM, int ACC>
-__global__ __launch_bounds__(kStep) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 3))) void k_sweep(
-    const double *__restrict__ beta, const double *__restrict__ beta_dot, const double *__restrict__ charge,
-    const double *__restrict__ x_det, const double *__restrict__ rec, const double *__restrict__ pt,
-    const int *__restrict__ pflag, const unsigned long long *__restrict__ rmax2, const double *__restrict__ rbound2,
-    T *__restrict__ E, unsigned long long *__restrict__ diag, DepShape sh, SweepShape sw, DetAcc det)
+__global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 3))) void k_sweep(
+    const double *__restrict__ r, const double *__restrict__ beta, const double *__restrict__ beta_dot,
+    const double *__restrict__ charge, const double *__restrict__ x_det, const double *__restrict__ base,
+    const double *__restrict__ pt, const int *__restrict__ pflag, const unsigned long long *__restrict__ rmax2,
+    const double *__restrict__ rbound2, T *__restrict__ E, unsigned long long *__restrict__ diag, DepShape sh, SweepShape sw,
+    DetAcc det)
 {
     constexpr bool kF64 = sizeof(T) == 8;
     constexpr int kRec = kF64 ? kModeRec5 : kModeRec3;
-    using Lay = RecLayout<GEOM, kF64>;
     __shared__ SweepLds<T, GEOM> lds;
     const int tid = threadIdx.x, p = tid & (kTilePix - 1);
     // block -> (particle group and segment, tile); blocks go to the 8 XCDs round robin, and all tiles
-    // of a group run on one XCD at once, so that they share its records in that L2
+    // of a group run on one XCD at once, so that they share its samples in that L2
     const int64_t b = blockIdx.x;
     const int64_t xcd = b & 7, slot = b >> 3;
     const int64_t unit = (slot / sh.n_tiles) * 8 + xcd;
@@ -1110,19 +1153,19 @@ __global__ __launch_bounds__(kStep) __attribute__((amdgpu_waves_per_eu(sizeof(T)
             far_off = !(fabs(pc.g.D - Dref) <= kSameDistance * Dref);
         }
     }
-    // over the tile's pixels: its two halves are wavefronts 0, 1 (and again 2, 3)
+    // over the tile's pixels: its two halves are wavefronts 0, 1 (and again the later ones)
     for (int off = 32; off > 0; off >>= 1) {
         id2 = fmax(id2, __shfl_xor(id2, off));
         s2 = fmax(s2, __shfl_xor(s2, off));
     }
     const uint64_t off_mask = __ballot(far_off);
-    if ((tid & 63) == 0) {
-        lds.tl[tid >> 6] = id2;
-        lds.th[tid >> 6] = s2;
+    if ((tid & 63) == 0 && tid < kTilePix) {
+        lds.node[0][0][tid >> 6] = id2;
+        lds.node[0][1][tid >> 6] = s2;
         lds.mask[tid >> 6] = off_mask;
     }
     __syncthreads();
-    const double invD2max = fmax(lds.tl[0], lds.tl[1]), s2max = fmax(lds.th[0], lds.th[1]);
+    const double invD2max = fmax(lds.node[0][0][0], lds.node[0][0][1]), s2max = fmax(lds.node[0][1][0], lds.node[0][1][1]);
     const bool rec_ok = GEOM == LW_GEOM_EXACT && (lds.mask[0] | lds.mask[1]) == 0;
 
     const size_t row0 = (size_t)(tile * kTilePix) * 3;
@@ -1130,7 +1173,7 @@ __global__ __launch_bounds__(kStep) __attribute__((amdgpu_waves_per_eu(sizeof(T)
         det.hi += row0 * (size_t)sh.n_obs;
         det.scale += row0;
     }
-    Sweep<T, GEOM, ACC> w{lds, pt + (size_t)(tile * kTilePix) * kPT, E + row0 * (size_t)sh.n_obs, sh, det, 0.0, 0.0, 0.0, tid};
+    Sweep<T, GEOM, ACC> w{lds, pt + (size_t)(tile * kTilePix) * kPT, E + row0 * (size_t)sh.n_obs, sh, det, 0.0, Dref, 0.0, 0.0, tid};
     {
         double c[6];
         tau_poly<kF64 ? 5 : 3>(0.0, 0.0, 0.0, 0.0, sh.C, Dref, c);
@@ -1145,25 +1188,21 @@ __global__ __launch_bounds__(kStep) __attribute__((amdgpu_waves_per_eu(sizeof(T)
         w.rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
         w.q = charge ? charge[k] : -kQe;
         const bool all_ser = GEOM == LW_GEOM_EXACT && w.rb2 * invD2max <= kSeriesBound;
-        const double *rk = rec + (size_t)k * sh.n_samples * Lay::W;
-        const double *bk = beta + (size_t)k * sh.n_samples * 3, *dk = beta_dot + (size_t)k * sh.n_samples * 3;
+        const size_t s0 = (size_t)k * sh.n_samples;
+        const double *dk = base + s0, *rk = r + 3 * s0;
         auto run = [&](auto mode) {
             constexpr int MODE = decltype(mode)::value;
-            using SV = ScanVals<GEOM, kF64, MODE>;
-            const double *rm = rk + SV::OFF;
             if (seg == 0 && tid < kTilePix) {
                 // the counters follow from the first and last arrival times
                 if (lane_ok) {
                     const PixC P = w.template pixel<MODE>(p);
-                    const cdptr f = uniform_ptr(rm), l = uniform_ptr(rm + (size_t)(sh.n_samples - 1) * Lay::W);
-                    double v0[SV::N], v1[SV::N];
-#pragma unroll
-                    for (int v = 0; v < SV::N; ++v) {
-                        v0[v] = f[v];
-                        v1[v] = l[v];
-                    }
-                    const double t0 = tau_eval<GEOM, kF64, MODE>(P, v0, w.cK, w.rb2, sh.C);
-                    const double t1 = tau_eval<GEOM, kF64, MODE>(P, v1, w.cK, w.rb2, sh.C);
+                    auto tau = [&](int64_t i) {
+                        const cdptr sd = uniform_ptr(dk + i), sr = uniform_ptr(rk + 3 * i);
+                        double v[ScanVals<GEOM, kF64, MODE>::N];
+                        scan_vals<GEOM, kF64, MODE>(sd[0], sr[0], sr[1], sr[2], sh.C, Dref, v);
+                        return tau_eval<GEOM, kF64, MODE>(P, v, w.cK, w.rb2, sh.C);
+                    };
+                    const double t0 = tau(0), t1 = tau(sh.n_samples - 1);
                     const int64_t inside = grid_count(t1, nob) - grid_count(t0, nob);
                     c3 += (unsigned long long)inside;
                     c2 += (unsigned long long)((int64_t)(floor(t1) - floor(t0)) - inside);
@@ -1171,7 +1210,7 @@ __global__ __launch_bounds__(kStep) __attribute__((amdgpu_waves_per_eu(sizeof(T)
                     c1 += (unsigned long long)(sh.n_samples - 1);
                 }
             }
-            w.template particle<MODE>(rm, bk, dk, st0, st1, lane_ok);
+            w.template particle<MODE>(dk, rk, beta + 3 * s0, beta_dot + 3 * s0, st0, st1, lane_ok);
         };
         if constexpr (GEOM == LW_GEOM_FARFIELD) {
             run(std::integral_constant<int, kModeFar>{});
@@ -1245,19 +1284,6 @@ __global__ __launch_bounds__(256) void k_det_finish(double *__restrict__ E, cons
     }
 }
 
-template <int GEOM>
-void launch_prepass(bool f64, dim3 grid, hipStream_t s, const double *r, const double *b, const double *bd,
-                    const double *x_det, int64_t ns, int chunk, int64_t sample0, double t_start, double dt, double t0,
-                    double dt_obs, double C, const DepWs &w)
-{
-    if (f64)
-        k_prepass<GEOM, 5><<<grid, 256, 0, s>>>(r, b, bd, x_det, ns, chunk, sample0, t_start, dt, t0, dt_obs, C, w.rec,
-                                               w.pflag, w.rmax2);
-    else
-        k_prepass<GEOM, 3><<<grid, 256, 0, s>>>(r, b, bd, x_det, ns, chunk, sample0, t_start, dt, t0, dt_obs, C, w.rec,
-                                               w.pflag, w.rmax2);
-}
-
 }  // namespace
 
 size_t det_acc_bytes(int64_t n_pix, int64_t n_obs)
@@ -1294,9 +1320,9 @@ lw_status launch_deposit_det(const lw_traj_t *t, const lw_grid_t *gr, int fmask,
     return check_launch("lw_deposit_td_det");
 }
 
-size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples, int prec)
+size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples)
 {
-    return ws_bytes_for(n_particles, n_samples, rec_width(LW_GEOM_EXACT, prec == LW_PREC_FP64));
+    return ws_bytes_for(n_particles, n_samples);
 }
 
 lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int fmask, int geom, bool accumulate,
@@ -1323,13 +1349,12 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
         if (diag) k_fill<unsigned long long><<<1, 64, 0, s>>>((unsigned long long *)diag, 4);
     }
     if (n_p == 0 || n_pix == 0 || ns == 0) return check_launch("deposit fill");
-    const int rw = rec_width(geom, f64);
-    // particles per launch: all of them, or as many as the workspace holds records for
+    // particles per launch: all of them, or as many as the workspace holds arrival bases for
     int64_t chunk = n_p;
-    while (chunk > 1 && ws_bytes_for(chunk, ns, rw) > ws_bytes) chunk = std::max<int64_t>(1, chunk / 2);
-    if (ws_bytes_for(chunk, ns, rw) > ws_bytes)
+    while (chunk > 1 && ws_bytes_for(chunk, ns) > ws_bytes) chunk = std::max<int64_t>(1, chunk / 2);
+    if (ws_bytes_for(chunk, ns) > ws_bytes)
         return fail(LW_E_WORKSPACE, "lw_deposit_td: workspace of %zu bytes holds no particle (%zu needed)", ws_bytes,
-                    ws_bytes_for(1, ns, rw));
+                    ws_bytes_for(1, ns));
     const double C = 1.0 / (kC * gr->dt_obs);
     const int64_t n_chunks_s = (ns + kPrepassChunk - 1) / kPrepassChunk;
     if (n_chunks_s > 65535) return fail(LW_E_SHAPE, "lw_deposit_td: too many samples");
@@ -1355,7 +1380,8 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
                 std::max<int64_t>(1, std::min<int64_t>(kMaxPartsPerGroup, np * sh.n_tiles / kTargetBlocks));
             sh.n_groups = (np + sh.parts_per_group - 1) / sh.parts_per_group;
             SweepShape sw;
-            sw.n_steps = (int)((ns - 1 + kStep - 2) / (kStep - 1));
+            const int step = f64 ? SweepCfg<double>::H : SweepCfg<float>::H;
+            sw.n_steps = (int)((ns - 1 + step - 1) / step);
             const int64_t units = sh.n_groups * sh.n_tiles;
             const int64_t want = std::max<int64_t>(1, std::min<int64_t>(sw.n_steps, (kFillBlocks + units - 1) / units));
             sw.per_seg = (int)((sw.n_steps + want - 1) / want);
@@ -1383,20 +1409,16 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             int pchunk = kPrepassChunk;
             while (pchunk > 256 && np * ((ns + pchunk - 1) / pchunk) < kPrepassBlocks) pchunk /= 2;
             const dim3 pgrid((unsigned)np, (unsigned)((ns + pchunk - 1) / pchunk));
-            if (geom == LW_GEOM_EXACT)
-                launch_prepass<LW_GEOM_EXACT>(f64, pgrid, s, r, b, bd, xd, ns, pchunk, sample0, t->t_start, t->dt, gr->t0,
-                                              gr->dt_obs, C, w);
-            else
-                launch_prepass<LW_GEOM_FARFIELD>(f64, pgrid, s, r, b, bd, xd, ns, pchunk, sample0, t->t_start, t->dt, gr->t0,
-                                                 gr->dt_obs, C, w);
+            k_prepass<<<pgrid, 256, 0, s>>>(r, b, bd, ns, pchunk, sample0, t->t_start, t->dt, gr->t0, gr->dt_obs, C, w.d,
+                                            w.pflag, w.rmax2);
             unsigned long long *dg = (unsigned long long *)diag;
             const dim3 grid((unsigned)blocks), grid_careful((unsigned)blocks_careful);
             if (acc_mode != kAccFloat) {
 #define LW_DET_LAUNCH(G, A)                                                                                          \
     do {                                                                                                             \
-        k_sweep<double, G, A><<<grid, kStep, 0, s>>>(b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2, (double *)Ep,   \
+        k_sweep<double, G, A><<<grid, SweepCfg<double>::kThreads, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2, (double *)Ep,   \
                                                      dg, sh, sw, dp);                                                \
-        k_careful<double, G, A><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,      \
+        k_careful<double, G, A><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2,        \
                                                        (double *)Ep, dg, sh, dp);                                    \
     } while (0)
                 if (geom == LW_GEOM_EXACT) {
@@ -1411,10 +1433,10 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             }
             // the fast path (timed as the deposit kernel), then the careful path
 #define LW_SWEEP_LAUNCH(T, G)                                                                                    \
-    k_sweep<T, G, kAccFloat><<<grid, kStep, 0, s>>>(b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2, (T *)Ep, dg, \
+    k_sweep<T, G, kAccFloat><<<grid, SweepCfg<T>::kThreads, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2, (T *)Ep, dg, \
                                                     sh, sw, DetAcc{nullptr, nullptr})
 #define LW_CAREFUL_LAUNCH(T, G)                                                                                   \
-    k_careful<T, G, kAccFloat><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.rec, w.pt, w.pflag, w.rmax2, rb2,       \
+    k_careful<T, G, kAccFloat><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2,         \
                                                       (T *)Ep, dg, sh, DetAcc{nullptr, nullptr})
             hipEvent_t ev = timing_begin(LW_KERNEL_DEPOSIT, s);
             if (f64) {

@@ -208,7 +208,7 @@ size_t lw_workspace_bytes(int which, int64_t n_a, int64_t n_b, int prec)
 {
     switch (which) {
     case LW_WS_DEPOSIT:
-        return deposit_ws_bytes(n_a, n_b, prec);
+        return deposit_ws_bytes(n_a, n_b);
     case LW_WS_DEPOSIT_BWD:
         return deposit_bwd_ws_bytes(n_a);
     case LW_WS_FFT:
@@ -271,7 +271,7 @@ static lw_status deposit_entry(const char *fn, const lw_traj_t *traj, const lw_g
     }
     // any workspace that holds one particle's records is accepted (the particles are then taken
     // in chunks); lw_workspace_bytes gives the size that takes them all at once
-    const size_t need = deposit_ws_bytes(1, traj->n_samples, prec);
+    const size_t need = deposit_ws_bytes(1, traj->n_samples);
     if (traj->n_particles > 0 && grid->n_pix > 0 && (!ws || ws_bytes < need))
         return fail(LW_E_WORKSPACE, "%s: workspace of %zu bytes < %zu needed", fn, ws_bytes, need);
     if (det) return launch_deposit_det(traj, grid, field_mask, g, (double *)E, diag, acc, ws, ws_bytes, stream);

@@ -450,7 +450,7 @@ lw_status launch_deposit_det(const lw_traj_t *traj, const lw_grid_t *grid, int f
 size_t det_acc_bytes(int64_t n_pix, int64_t n_obs);
 // workspace of a deposit launch that holds the records of all its particles (a smaller one makes
 // it process the particles in chunks)
-size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples, int prec);
+size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples);
 lw_status launch_fft(const void *E, int64_t n_pix, int64_t n_obs, double dt_obs, int prec, void *S, void *ws,
                      size_t ws_bytes, hipStream_t s);
 size_t fft_ws_bytes(int64_t n_pix, int64_t n_obs, int prec);

@@ -58,3 +58,18 @@ def test_pixels_at_several_distances(prec):
     c["dt_obs"] = float(np.ptp(tau)) / 140
     c["t0"] = float(np.median(tau)) - 100 * c["dt_obs"]
     check(c, prec, "exact")
+
+
+@pytest.mark.parametrize("prec, n_samples", [("fp64", 128), ("fp64", 129), ("fp64", 255), ("fp64", 382), ("mixed", 256),
+                                             ("mixed", 510), ("mixed", 511), ("mixed", 1300)])
+@pytest.mark.parametrize("n_obs", [37, 64, 125, 333])
+def test_points_held_back_for_a_full_request(prec, n_samples, n_obs):
+    """Steps of a few to many grid points per pixel, in rows that start on a request (64) and that don't: a step's
+    last points wait for the next one, in the step's last interval, over a whole step, or not at all."""
+    c = synthetic(n_p=4, n_samples=n_samples, n_pix=67, n_obs=n_obs, seed=n_samples + n_obs,
+                  dt=2e-18 * 700 / max(n_samples, 200))
+    check(c, prec, "exact")
+    # unusable samples leave a particle to the careful path beside the others
+    c["beta"] = c["beta"].copy()
+    c["beta"][2, n_samples // 2, 0] = np.nan
+    check(c, prec, "farfield")
