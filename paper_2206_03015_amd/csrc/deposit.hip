@@ -58,12 +58,18 @@ constexpr int kBlockThreads = 64;
 constexpr uint32_t kQCap = 128;
 // intervals with more grid points than this are deposited by the whole wavefront
 constexpr int kLongRun = 8;
-// particles per block of the fast path: one until there are kTargetBlocks blocks (16 rounds of the
-// 1024 resident ones), then up to kMaxPartsPerGroup; with fewer than kFillBlocks blocks each
-// particle's samples are split into segments
+// Fast path: a particle's samples are split into segments of at most kSegIntervals intervals, into more of them
+// where that leaves fewer than kFillBlocks blocks; particles per block: one until there are kTargetBlocks
+// blocks (some 20 to 30 rounds of the resident ones), then up to kMaxPartsPerGroup.  Few of a bunch's particles may
+// pass the window (1 in 70 of the precision workload, whose (particle, tile) units took 2.8 ms each, a quarter of the
+// sweep with most of the chip idle at its end): a block looks its particles through first, and a unit is
+// short.  Precision cut 35.8 -> 29.1 ms, 1000-electron bunch FP64 3.42 -> 2.68 ms (4096 intervals: 3.2).
+constexpr int64_t kSegIntervals = 4096, kSegIntervals64 = 2048;
 constexpr int64_t kTargetBlocks = 16384;
-constexpr int kMaxPartsPerGroup = 4;
+constexpr int kMaxPartsPerGroup = 64;
 constexpr int64_t kFillBlocks = 2048;
+// particles per block of the careful path
+constexpr int kMaxPartsCareful = 4;
 // samples per block of the pre-pass: at most kPrepassChunk, less where that leaves fewer than
 // kPrepassBlocks blocks (one electron of 20001 samples: 65 us in 3 blocks)
 constexpr int kPrepassChunk = 8192;
@@ -715,7 +721,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 // 18-20 billion of those a second whatever they hold (285 G floats/s in aligned groups of 16, 98 G/s in runs of 8
 // at any place).  A step of the bunch workload has 12 grid points a pixel, 7.1 to a request; so the last points of
 // a step wait for the next one where that completes their 64 bytes, which is what the second half of the ring is
-// for: 12.8 to a request.  2000 x 20001 samples, 4096 pixels, mixed: 51.3 -> 34.8 ms.
+// for: 12.8 to a request.  2000 x 20001 samples, 4096 pixels, mixed: 51.3 -> 34.5 ms,
+// 6.4e8 requests; with whole requests per wavefront (lanes idle where a step starts or ends inside one) the same.
 template <typename T>
 struct SweepCfg {
     static constexpr int NT = sizeof(T) == 8 ? 128 : 256;  // samples of a step, neighbouring steps sharing one
@@ -744,8 +751,11 @@ struct SweepLds {
     double tau[Cfg::kDensePix][Cfg::NT];  // dense steps: the current pixels' arrival times
     T e[Cfg::kDensePix][3][Cfg::NT];      // and fields
     int ulo[kTilePix];       // a pixel's first grid point to deposit
-    int cum[2][kTilePix];    // grid points of the tile half's pixels before this one: sparse, held back before a dense step
+    // of the tile half's pixels before this one: grid points to deposit, those held back by the step before
+    int cum[2][kTilePix];
     int tot[2][2], fresh[2];
+    int hit[kMaxPartsPerGroup];  // scan mode + 1 of the group's particles that the segment deposits
+    uint64_t okm[2];             // usable pixels
     uint64_t live[2];  // pixels with grid points in the step
     uint64_t mask[Cfg::kThreads / 64];
     unsigned long long red[4];
@@ -871,36 +881,19 @@ struct Sweep {
 #pragma unroll
             for (int b = 32; b > 0; b >>= 1)
                 if (cum[p + b] <= r) p += b;
-            const PixC P = pixel<MODE>(p);
             const int u = s.ulo[p] + (r - cum[p]);
+            const PixC P = pixel<MODE>(p);
             const double ud = (double)u;
             // the step and the quarter of it that hold the crossing
             const bool old = prev && !(ud > s.node[par][0][p]);
             const double (*nd)[kTilePix] = s.node[old ? par ^ 1 : par];
-            int lo = old ? i0 - Cfg::H : i0;
-            const int len = old ? Cfg::H : n;
-            int hi = lo + len;
-            const int q1 = lo + (len >> 2), q2 = lo + (len >> 1), q3 = lo + ((3 * len) >> 2);
-            double ta = nd[0][p], tb = nd[4][p];
-            const double m2 = nd[2][p];
-            const bool up = ud > m2;
-            const double m13 = nd[up ? 3 : 1][p];
-            const int q13 = up ? q3 : q1;
-            if (up) {
-                lo = q2;
-                ta = m2;
-            } else {
-                hi = q2;
-                tb = m2;
-            }
-            if (ud > m13) {
-                lo = q13;
-                ta = m13;
-            } else {
-                hi = q13;
-                tb = m13;
-            }
+            const int lo0 = old ? i0 - Cfg::H : i0, len = old ? Cfg::H : n;
+            int j = ud > nd[2][p] ? 2 : 0;
+            j += ud > nd[j + 1][p] ? 1 : 0;
+            int lo = lo0 + ((j * len) >> 2), hi = lo0 + (((j + 1) * len) >> 2);
+            double ta = nd[j][p], tb = nd[j + 1][p];
             float ya = (float)(ta - ud), yb = (float)(tb - ud);  // ya < 0 <= yb
+            // (a first guess that is a parabola through the node beyond as well saved no arrival time)
             int g = lo + (int)rintf((float)(hi - lo) * (-ya * __builtin_amdgcn_rcpf(yb - ya)));
             for (int k = 0; hi - lo > 1; ++k) {
                 g = min(max(g, lo + 1), hi - 1);
@@ -1158,11 +1151,12 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
         id2 = fmax(id2, __shfl_xor(id2, off));
         s2 = fmax(s2, __shfl_xor(s2, off));
     }
-    const uint64_t off_mask = __ballot(far_off);
+    const uint64_t off_mask = __ballot(far_off), ok_mask = __ballot(lane_ok);
     if ((tid & 63) == 0 && tid < kTilePix) {
         lds.node[0][0][tid >> 6] = id2;
         lds.node[0][1][tid >> 6] = s2;
         lds.mask[tid >> 6] = off_mask;
+        lds.okm[tid >> 6] = ok_mask;
     }
     __syncthreads();
     const double invD2max = fmax(lds.node[0][0][0], lds.node[0][0][1]), s2max = fmax(lds.node[0][1][0], lds.node[0][1][1]);
@@ -1181,48 +1175,75 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     }
     const double nob = (double)sh.n_obs;
     unsigned long long c1 = 0, c2 = 0, c3 = 0;
-    for (int64_t k = k0; k < k1; ++k) {
-        if (pflag[k] != 0) continue;  // careful path: k_careful
+    // the particle's constants, then f with its scan mode
+    auto with_mode = [&](int64_t k, auto f) {
         // series forms where |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory (the max over the
         // whole trajectory when given, else over the samples of this call), decided per pixel
         w.rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
         w.q = charge ? charge[k] : -kQe;
-        const bool all_ser = GEOM == LW_GEOM_EXACT && w.rb2 * invD2max <= kSeriesBound;
-        const size_t s0 = (size_t)k * sh.n_samples;
-        const double *dk = base + s0, *rk = r + 3 * s0;
-        auto run = [&](auto mode) {
-            constexpr int MODE = decltype(mode)::value;
-            if (seg == 0 && tid < kTilePix) {
-                // the counters follow from the first and last arrival times
-                if (lane_ok) {
-                    const PixC P = w.template pixel<MODE>(p);
-                    auto tau = [&](int64_t i) {
-                        const cdptr sd = uniform_ptr(dk + i), sr = uniform_ptr(rk + 3 * i);
-                        double v[ScanVals<GEOM, kF64, MODE>::N];
-                        scan_vals<GEOM, kF64, MODE>(sd[0], sr[0], sr[1], sr[2], sh.C, Dref, v);
-                        return tau_eval<GEOM, kF64, MODE>(P, v, w.cK, w.rb2, sh.C);
-                    };
-                    const double t0 = tau(0), t1 = tau(sh.n_samples - 1);
-                    const int64_t inside = grid_count(t1, nob) - grid_count(t0, nob);
-                    c3 += (unsigned long long)inside;
-                    c2 += (unsigned long long)((int64_t)(floor(t1) - floor(t0)) - inside);
-                } else if (pix_in) {
-                    c1 += (unsigned long long)(sh.n_samples - 1);
-                }
-            }
-            w.template particle<MODE>(dk, rk, beta + 3 * s0, beta_dot + 3 * s0, st0, st1, lane_ok);
-        };
         if constexpr (GEOM == LW_GEOM_FARFIELD) {
-            run(std::integral_constant<int, kModeFar>{});
+            f(std::integral_constant<int, kModeFar>{});
         } else {
+            const bool all_ser = w.rb2 * invD2max <= kSeriesBound;
             if (all_ser && rec_ok) {
                 if (tail_negligible<kF64>(w.rb2, s2max, sh.C, w.cK, Dref))
-                    run(std::integral_constant<int, kModeRecLow>{});
+                    f(std::integral_constant<int, kModeRecLow>{});
                 else
-                    run(std::integral_constant<int, kRec>{});
+                    f(std::integral_constant<int, kRec>{});
             } else
-                run(std::integral_constant<int, kModeMixed>{});
+                f(std::integral_constant<int, kModeMixed>{});
         }
+    };
+    // the group's particles whose arrival times pass window grid points within the segment, at some pixel: a
+    // wavefront per particle, lanes over pixels; and the counters, which follow from the first and last arrival times
+    const int nk = (int)(k1 - k0), lane = tid & 63;
+    for (int kk = __builtin_amdgcn_readfirstlane(tid >> 6); kk < nk; kk += SweepCfg<T>::kThreads / 64) {
+        const int64_t k = k0 + kk;
+        int hit = 0;
+        if (pflag[k] == 0) {  // else careful path: k_careful
+            const size_t s0 = (size_t)k * sh.n_samples;
+            with_mode(k, [&](auto mode) {
+                constexpr int MODE = decltype(mode)::value;
+                const int64_t ie[3] = {std::min<int64_t>((int64_t)st0 * SweepCfg<T>::H, sh.n_samples - 1),
+                                       std::min<int64_t>((int64_t)st1 * SweepCfg<T>::H, sh.n_samples - 1), sh.n_samples - 1};
+                const int ne = seg == 0 && ie[1] < ie[2] ? 3 : 2;
+                double v[3][ScanVals<GEOM, kF64, MODE>::N];
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    if (e >= ne) break;
+                    const cdptr sd = uniform_ptr(base + s0 + ie[e]), sr = uniform_ptr(r + 3 * (s0 + ie[e]));
+                    scan_vals<GEOM, kF64, MODE>(sd[0], sr[0], sr[1], sr[2], sh.C, Dref, v[e]);
+                }
+                bool any = false;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bool in = tile * kTilePix + 64 * h + lane < sh.n_pix, ok = (lds.okm[h] >> lane) & 1;
+                    const PixC P = w.template pixel<MODE>(64 * h + lane);
+                    const double t0 = tau_eval<GEOM, kF64, MODE>(P, v[0], w.cK, w.rb2, sh.C);
+                    const double t1 = tau_eval<GEOM, kF64, MODE>(P, v[1], w.cK, w.rb2, sh.C);
+                    any |= ok && grid_count(t1, nob) != grid_count(t0, nob);
+                    if (seg == 0 && ok) {
+                        const double te = ne == 3 ? tau_eval<GEOM, kF64, MODE>(P, v[2], w.cK, w.rb2, sh.C) : t1;
+                        const int64_t inside = grid_count(te, nob) - grid_count(t0, nob);
+                        c3 += (unsigned long long)inside;
+                        c2 += (unsigned long long)((int64_t)(floor(te) - floor(t0)) - inside);
+                    } else if (seg == 0 && in) {
+                        c1 += (unsigned long long)(sh.n_samples - 1);
+                    }
+                }
+                hit = __ballot(any) != 0 ? MODE + 1 : 0;
+            });
+        }
+        if (lane == 0) lds.hit[kk] = hit;
+    }
+    __syncthreads();
+    for (int kk = 0; kk < nk; ++kk) {
+        if (!lds.hit[kk]) continue;
+        const int64_t k = k0 + kk;
+        const size_t s0 = (size_t)k * sh.n_samples;
+        with_mode(k, [&](auto mode) {
+            w.template particle<decltype(mode)::value>(base + s0, r + 3 * s0, beta + 3 * s0, beta_dot + 3 * s0, st0, st1, lane_ok);
+        });
     }
 
     // counters: block reduction in LDS, then one global atomic per counter
@@ -1376,24 +1397,27 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             sh.n_pix = npx;
             sh.n_obs = n_obs;
             sh.n_tiles = (npx + kTilePix - 1) / kTilePix;
-            sh.parts_per_group =
-                std::max<int64_t>(1, std::min<int64_t>(kMaxPartsPerGroup, np * sh.n_tiles / kTargetBlocks));
-            sh.n_groups = (np + sh.parts_per_group - 1) / sh.parts_per_group;
-            SweepShape sw;
             const int step = f64 ? SweepCfg<double>::H : SweepCfg<float>::H;
+            SweepShape sw;
             sw.n_steps = (int)((ns - 1 + step - 1) / step);
-            const int64_t units = sh.n_groups * sh.n_tiles;
-            const int64_t want = std::max<int64_t>(1, std::min<int64_t>(sw.n_steps, (kFillBlocks + units - 1) / units));
+            const int64_t seg_len = f64 ? kSegIntervals64 : kSegIntervals;
+            const int64_t units = np * sh.n_tiles, least = (ns + seg_len - 1) / seg_len;
+            const int64_t want = std::max<int64_t>({1, least, std::min<int64_t>(sw.n_steps, (kFillBlocks + units - 1) / units)});
             sw.per_seg = (int)((sw.n_steps + want - 1) / want);
             sw.n_seg = sw.per_seg > 0 ? (sw.n_steps + sw.per_seg - 1) / sw.per_seg : 1;
+            sh.parts_per_group =
+                std::max<int64_t>(1, std::min<int64_t>(kMaxPartsPerGroup, units * sw.n_seg / kTargetBlocks));
+            sh.n_groups = (np + sh.parts_per_group - 1) / sh.parts_per_group;
             sh.fmask = fmask;
             sh.C = C;
             const int64_t blocks = (sh.n_groups * sw.n_seg + 7) / 8 * 8 * sh.n_tiles;
-            const int64_t blocks_careful = (sh.n_groups + 7) / 8 * 8 * sh.n_tiles;
-            if (sh.parts_per_group >= (int64_t(1) << (32 - kPixBits)))
-                return fail(LW_E_SHAPE, "lw_deposit_td: too many particles per pixel tile group");
+            DepShape shc = sh;
+            shc.parts_per_group = std::max<int64_t>(1, std::min<int64_t>(kMaxPartsCareful, units / kTargetBlocks));
+            shc.n_groups = (np + shc.parts_per_group - 1) / shc.parts_per_group;
+            const int64_t blocks_careful = (shc.n_groups + 7) / 8 * 8 * sh.n_tiles;
             if (np > 0x7fffffff) return fail(LW_E_SHAPE, "lw_deposit_td: too many particles");
-            if (blocks > 0x7fffffff) return fail(LW_E_SHAPE, "lw_deposit_td: problem too large for one launch");
+            if (std::max(blocks, blocks_careful) > 0x7fffffff)
+                return fail(LW_E_SHAPE, "lw_deposit_td: problem too large for one launch");
             const DepWs w = carve(ws, np);
             if (p0 == 0) {
                 const int64_t rows = sh.n_tiles * kTilePix;  // <= kPixTabMax
@@ -1419,7 +1443,7 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
         k_sweep<double, G, A><<<grid, SweepCfg<double>::kThreads, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2, (double *)Ep,   \
                                                      dg, sh, sw, dp);                                                \
         k_careful<double, G, A><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2,        \
-                                                       (double *)Ep, dg, sh, dp);                                    \
+                                                       (double *)Ep, dg, shc, dp);                                   \
     } while (0)
                 if (geom == LW_GEOM_EXACT) {
                     if (acc_mode == kAccMaxAbs) LW_DET_LAUNCH(LW_GEOM_EXACT, kAccMaxAbs); else LW_DET_LAUNCH(LW_GEOM_EXACT, kAccFixed);
@@ -1437,7 +1461,7 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
                                                     sh, sw, DetAcc{nullptr, nullptr})
 #define LW_CAREFUL_LAUNCH(T, G)                                                                                   \
     k_careful<T, G, kAccFloat><<<grid_careful, kBlockThreads, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2,         \
-                                                      (T *)Ep, dg, sh, DetAcc{nullptr, nullptr})
+                                                      (T *)Ep, dg, shc, DetAcc{nullptr, nullptr})
             hipEvent_t ev = timing_begin(LW_KERNEL_DEPOSIT, s);
             if (f64) {
                 if (geom == LW_GEOM_EXACT) LW_SWEEP_LAUNCH(double, LW_GEOM_EXACT); else LW_SWEEP_LAUNCH(double, LW_GEOM_FARFIELD);
