@@ -1182,6 +1182,175 @@ __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type
     }
 }
 
+// The adjoint's passes at the forward path's shapes (N1 of ET to 2^kFastColsMaxLg1 points: rows of L): pass A is the
+// forward one (k_fwd_cols_fast), then
+//
+// pass B' (k_bwd_rows_fast): a row pair (k1, N1 - k1) of the three packed transforms per block, in place: the
+// forward row passes leave the pair's outputs in registers with their partners (as in pass B), the product with
+// h dS is formed there, and since a thread holds elements u + NT m of a row it is the input of the inverse
+// passes' first one.  The pair's L values of dS per pixel serve all three transforms.
+// pass C (k_bwd_cols_fast): the columns back, real and imaginary parts to the two packed components.
+//
+// Three reads and three writes of the traces' size, with nothing in LDS but a row: 256 pixels of 2^16 points in FP64
+// 1022 us with two LDS buffers, radix 4 and a sine/cosine pair per element of every pass -> 515 us.
+template <typename T>
+__global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_waves_per_eu(FastCfg<T>::kRowWaves))) void k_bwd_rows_fast(
+    typename C2<T>::type *__restrict__ Y, const T *__restrict__ dS, FwdShape sh, T scale)
+{
+    using T2 = typename C2<T>::type;
+    using Cfg = FastCfg<T>;
+    constexpr int LGL = Cfg::kLgL, L = 1 << LGL, LGR = Cfg::kLgR, R = 1 << LGR;
+    constexpr int REM = LGL % LGR;
+    constexpr int NT = L / R;
+    __shared__ T2 buf[L + L / R];
+    __shared__ T2 tab[tab_slots(tab_entries_rows<T>())];
+    const int tid = threadIdx.x;
+    const int N1 = 1 << sh.lg1;
+    const int64_t N = (int64_t)1 << sh.lg, ldS = N / 2 + 1;
+    // block -> (row pair, pixel pair) as in pass B: the row pairs of one pixel pair read the lines of its dS together
+    const int64_t b = blockIdx.x, xcd = b & 7, slot = b >> 3;
+    const int nrp = N1 / 2 + 1;
+    const int rp = (int)(slot % nrp);
+    const int64_t pl = (slot / nrp) * 8 + xcd;
+    if (pl >= sh.nbatch) return;  // padding block (whole block)
+    const int64_t p = sh.pair0 + pl, m0 = 2 * p, m1 = m0 + 1;
+    const bool has1 = m1 < sh.n_pix;
+    const int ka = rp, kb = (N1 - rp) & (N1 - 1);
+    const bool two = ka != kb, row0 = ka == 0;
+    const int rho = row0 ? ((NT - tid) & (NT - 1)) : NT - 1 - tid;
+    for (int q = tid; q < tab_entries_rows<T>(); q += NT) tab[tabi(q)] = twiddle<T2>(q, L);
+    __syncthreads();
+    const T2 wa = tab[tabi(tid)], wb = row0 && tid == 0 ? twiddle<T2>(1, R) : tab[tabi(rho)];
+    const AtRow<LGR> at;
+    // scale h dS of output tid + NT q of row ka and its partner
+    T d0[R], d1[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int64_t j = ka + ((int64_t)(tid + NT * q) << sh.lg1), js = j < N - j ? j : N - j;
+        const T h = (js == 0 || js == N / 2) ? scale : (T)0.5 * scale;
+        d0[q] = h * dS[m0 * ldS + js];
+        d1[q] = has1 ? h * dS[m1 * ldS + js] : (T)0;
+    }
+    // inverse twiddles W_N^{-n2 k} of a row, n2 = tid + NT r: the conjugate of base step^r
+    const double inv_n = ldexp(1.0, -sh.lg);
+    const T2 base_a = phasor_mod<T2>((int64_t)tid * ka, N, inv_n), step_a = phasor_mod<T2>((int64_t)NT * ka, N, inv_n);
+    const T2 base_b = phasor_mod<T2>((int64_t)tid * kb, N, inv_n), step_b = phasor_mod<T2>((int64_t)NT * kb, N, inv_n);
+    auto store_row = [&](T2 *dst, const T2 *O, T2 base, T2 step) {  // conjugates of O times the forward twiddles
+        // opaque: the powers are formed per transform, not held in registers through the others
+        asm volatile("" : "+v"(step.x), "+v"(step.y));
+        T2 sp[R];
+        powers<R>(step, sp);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            T2 v = cmul(O[r], r ? cmul(base, sp[r < 1 ? 1 : r]) : base);
+            v.y = -v.y;
+            dst[tid + NT * r] = v;
+        }
+    };
+    const int nt = has1 ? 3 : 2;
+    auto row_ptr = [&](int tt, bool second) {
+        const int t = (!has1 && tt == 1) ? 2 : tt;
+        return Y + (pl * 3 + t) * N + (int64_t)(second ? kb : ka) * L;
+    };
+    T2 X[R];
+    auto passes = [&](const T2 *in, int j0, const T2 *next) {  // next: the row to load into X meanwhile, or null
+        __syncthreads();  // the previous row's last pass has read the buffer
+        first_pass<R, 1, 1>(in, buf, at, j0);
+        if (next) load_row_lanes<R, NT>(X, next, tid);
+        __syncthreads();
+        if constexpr (REM > 0) mid_pass<REM, LGL, LGR, (L >> REM) / NT, NT, LGL>(buf, at, tid, tab);
+        mid_passes<LGR, LGL, LGR + REM, LGL - LGR, LGL>(buf, at, tid, tab);
+    };
+    load_row_lanes<R, NT>(X, row_ptr(0, false), tid);
+#pragma unroll 1
+    for (int tt = 0; tt < nt; ++tt) {
+        const int t = (!has1 && tt == 1) ? 2 : tt;
+        const T2 *after = tt + 1 < nt ? row_ptr(tt + 1, false) : nullptr;
+        // opaque per transform: keeps their powers and the addresses from being held through the loop
+        T2 w0 = wa, w1 = wb;
+        int u = tid, v = rho;
+        asm volatile("" : "+v"(w0.x), "+v"(w0.y), "+v"(w1.x), "+v"(w1.y), "+v"(u), "+v"(v));
+        T2 A[R], B[R];
+        passes(X, u, two ? row_ptr(tt, true) : nullptr);
+        last_pass_w<LGR, LGL>(buf, at, u, w0, A);
+        if (two) passes(X, u, nullptr);
+        last_pass_w<LGR, LGL>(buf, at, v, w1, B);
+        // conj(G) of the outputs (Z0, Z1: d Z; Z2: sp Z + sm conj(partner)); partners: A[q] and B[R - 1 - q]
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const T2 za = A[q], zb = B[R - 1 - q];
+            const T a = t == 0 ? d0[q] : t == 1 ? d1[q] : (T)0.5 * (d0[q] + d1[q]);
+            const T c = t == 2 ? (T)0.5 * (d0[q] - d1[q]) : (T)0;
+            A[q].x = a * za.x + c * zb.x;
+            A[q].y = c * zb.y - a * za.y;
+            B[R - 1 - q].x = a * zb.x + c * za.x;
+            B[R - 1 - q].y = c * za.y - a * zb.y;
+        }
+        T2 O[R];
+        passes(A, u, two ? nullptr : after);
+        asm volatile("" : "+v"(w0.x), "+v"(w0.y));
+        last_pass_w<LGR, LGL>(buf, at, u, w0, O);
+        store_row(Y + (pl * 3 + t) * N + (int64_t)ka * L, O, base_a, step_a);
+        if (two) {
+            passes(B, v, after);
+            asm volatile("" : "+v"(w0.x), "+v"(w0.y));
+            last_pass_w<LGR, LGL>(buf, at, u, w0, O);
+            store_row(Y + (pl * 3 + t) * N + (int64_t)kb * L, O, base_b, step_b);
+        }
+    }
+}
+
+// pass C: C = 2^LGC adjacent columns of one packed transform of one pixel pair per block
+template <typename T, int LG1>
+__global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::type *__restrict__ Y, T *__restrict__ dE, FwdShape sh)
+{
+    using T2 = typename C2<T>::type;
+    constexpr int LGET = FwdCfg<T>::kLgRadix, ET = 1 << LGET;
+    constexpr int LGTAB = FastCfg<T>::kLgL;
+    constexpr int LGC = 8 + LGET - LG1, C = 1 << LGC, TPC = 1 << (LG1 - LGET);
+    static_assert(LG1 >= LGET && LGC >= 0, "columns of ET to 256 ET points");
+    constexpr int LGR0 = LG1 % LGET ? LG1 % LGET : LGET, NB0 = ET >> LGR0;
+    constexpr bool kLds = LG1 > LGET;
+    __shared__ T2 buf[kLds ? (C << LG1) : 1];
+    __shared__ T2 tab[tab_slots(tab_entries_cols<T>())];
+    const int tid = threadIdx.x, c = tid & (C - 1), g = tid >> LGC;
+    const int t = blockIdx.y;
+    const int64_t pl = blockIdx.z, p = sh.pair0 + pl;
+    const int64_t N = (int64_t)1 << sh.lg;
+    const T *re0, *im0;
+    pair_pointers(dE, sh.n_pix, p, t, N, re0, im0);
+    if (!re0) return;  // transform of a missing pixel
+    T *re = const_cast<T *>(re0), *im = const_cast<T *>(im0);
+    const int n2 = blockIdx.x * C + c;
+    if constexpr (kLds) {
+        for (int q = tid; q < tab_entries_cols<T>(); q += 256) tab[tabi(q)] = twiddle<T2>(q, 1 << LGTAB);
+    }
+    const T2 *Yt = Y + (pl * 3 + t) * N;
+    T2 X[ET], O[ET];
+#pragma unroll
+    for (int m = 0; m < ET; ++m) {
+        X[m] = Yt[((g + TPC * m) << sh.lg2) + n2];
+        X[m].y = -X[m].y;
+    }
+    if constexpr (!kLds) {
+#pragma unroll
+        for (int r = 0; r < ET; ++r) O[r] = X[r];
+        dftR<ET>(O);
+    } else {
+        const AtCol<LGC> at{c};
+        first_pass<1 << LGR0, NB0, TPC>(X, buf, at, g);
+        __syncthreads();
+        mid_passes<LGET, LG1, LGR0, LG1 - LGET, LGTAB>(buf, at, g, tab);
+        last_pass<LGET, LG1, LGTAB>(buf, at, g, tab, O);
+    }
+#pragma unroll
+    for (int r = 0; r < ET; ++r) {
+        const int n = ((g + TPC * r) << sh.lg2) + n2;
+        re[n] = O[r].x;
+        if (im) im[n] = -O[r].y;
+    }
+}
+
 int ilog2(int64_t v)
 {
     int l = 0;
@@ -1210,6 +1379,17 @@ ColsKernel<T> pick_cols_fast(int lg1)
         return nullptr;
     else
         return lg1 == LG1 ? k_fwd_cols_fast<T, LG1> : pick_cols_fast<T, LG1 + 1>(lg1);
+}
+
+template <typename T>
+using ColsBwdKernel = void (*)(const typename C2<T>::type *, T *, FwdShape);
+template <typename T, int LG1>
+ColsBwdKernel<T> pick_cols_bwd(int lg1)
+{
+    if constexpr (LG1 > kFastColsMaxLg1)
+        return nullptr;
+    else
+        return lg1 == LG1 ? k_bwd_cols_fast<T, LG1> : pick_cols_bwd<T, LG1 + 1>(lg1);
 }
 
 template <typename T>
@@ -1262,7 +1442,32 @@ lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, dou
                       size_t ws_bytes, hipStream_t s)
 {
     using T2 = typename C2<T>::type;
+    using Cfg = FwdCfg<T>;
     const int lg = ilog2(n_obs);
+    // the forward path's shapes, where its columns have a compile-time pass
+    if (const ColsBwdKernel<T> inv = pick_cols_bwd<T, Cfg::kLgRadix>(lg - Cfg::kLgRow)) {
+        FwdShape f;
+        f.n_pix = n_pix;
+        f.lg = lg;
+        f.lg2 = Cfg::kLgRow;
+        f.lg1 = lg - f.lg2;
+        f.lgC = 8 + Cfg::kLgRadix - f.lg1;
+        const ColsKernel<T> cols = pick_cols_fast<T, Cfg::kLgRadix>(f.lg1);
+        const unsigned gx_c = 1u << (f.lg2 - f.lgC), gx_r = (unsigned)((1 << f.lg1) / 2 + 1);
+        const int64_t pairs = (n_pix + 1) / 2;
+        const int64_t batch = std::min<int64_t>({pairs, (int64_t)(ws_bytes / per_pair_bytes<T>(n_obs)), kMaxGridYZ});
+        T2 *Y = (T2 *)ws;
+        for (int64_t p0 = 0; p0 < pairs; p0 += batch) {
+            const int64_t nb = std::min(batch, pairs - p0);
+            f.pair0 = p0;
+            f.nbatch = nb;
+            cols<<<dim3(gx_c, 3, (unsigned)nb), 256, 0, s>>>(E, Y, f, (T)1);
+            k_bwd_rows_fast<T><<<(unsigned)((nb + 7) / 8 * 8 * gx_r), FastCfg<T>::kRowThreads, 0, s>>>(
+                Y, dS, f, (T)(dt_obs * dt_obs / kPi));
+            inv<<<dim3(gx_c, 3, (unsigned)nb), 256, 0, s>>>(Y, dE, f);
+        }
+        return check_launch("lw_spectrum_fft_bwd");
+    }
     FftShape sh;
     sh.n_pix = n_pix;
     sh.lg2 = lg / 2;

@@ -274,3 +274,22 @@ def test_direct_fd_bwd(geom, n_omega):
         d_gpu = np.sum(gr * w[0]) + np.sum(gb * w[1]) + np.sum(ga * w[2])
         print(f"{geom} {name}: gpu-adjoint {d_gpu:.9e} gpu-fd {fd:.9e}")
         assert fd == pytest.approx(d_gpu, rel=1e-6, abs=0)
+
+
+@pytest.mark.parametrize("prec, n_obs", [("fp64", 1 << 14), ("fp64", 1 << 15), ("fp64", 1 << 17), ("fp64", 1 << 19),
+                                         ("mixed", 1 << 16), ("mixed", 1 << 17), ("mixed", 1 << 18), ("mixed", 1 << 20)])
+@pytest.mark.parametrize("n_pix", [1, 4, 5])
+def test_spectrum_bwd_at_the_fixed_shapes(prec, n_obs, n_pix):
+    """Columns of the compile-time passes (8 to 256 points in FP64, 16 to 256 in FP32) behind rows of 2048 and 4096:
+    rows paired with each other and with themselves, a pixel pair and a single pixel.  Against the formula in FP64
+    (2^20 points: 60 roundings of 2^-53, of 2^-24 in single precision, well within the bounds)."""
+    from paper_2206_03015_amd import lw
+    rng = np.random.default_rng(n_obs + n_pix)
+    dtype = torch.float64 if prec == "fp64" else torch.float32
+    Et = torch.as_tensor(rng.normal(size=(n_pix, 3, n_obs)) * 1e5, dtype=dtype, device=DEV)
+    dSt = torch.as_tensor(rng.normal(size=(n_pix, n_obs // 2 + 1)), dtype=dtype, device=DEV)
+    dE = lw.spectrum_fft_bwd(Et, dSt, 2.3e-20, prec).double().cpu().numpy()
+    ref = og.spectrum_vjp(Et.double().cpu().numpy(), dSt.double().cpu().numpy(), 2.3e-20)
+    err = np.max(np.abs(dE - ref)) / np.max(np.abs(ref))
+    print(f"spectrum bwd {prec} n_obs={n_obs} n_pix={n_pix}: rel err {err:.2e}")
+    assert err <= (1e-11 if prec == "fp64" else 3e-5)
