@@ -827,6 +827,14 @@ __device__ __forceinline__ double2 phasor_mod<double2>(int64_t q, int64_t N, dou
     return unit_phasor(-(double)q2 * inv_n);
 }
 
+// lg of a thread's elements of a column: those of a radix pass, or the whole column where it is shorter (101 pixels of
+// 2^13 points in FP64, columns of 4: 12.5 us in the runtime-shaped pass -> 8.8 us)
+template <typename T>
+constexpr int cols_lget(int lg1)
+{
+    return lg1 < FwdCfg<T>::kLgRadix ? lg1 : FwdCfg<T>::kLgRadix;
+}
+
 // pass A: C = 2^LGC adjacent columns (of N1 = 2^LG1 points) of one packed transform of one pixel
 // pair per block
 template <typename T, int LG1>
@@ -834,10 +842,10 @@ __global__ __launch_bounds__(256) void k_fwd_cols_fast(const T *__restrict__ E, 
                                                        FwdShape sh, T sc)
 {
     using T2 = typename C2<T>::type;
-    constexpr int LGET = FwdCfg<T>::kLgRadix, ET = 1 << LGET;  // elements per thread
+    constexpr int LGET = cols_lget<T>(LG1), ET = 1 << LGET;  // elements per thread
     constexpr int LGTAB = FastCfg<T>::kLgL;
     constexpr int LGC = 8 + LGET - LG1, C = 1 << LGC, TPC = 1 << (LG1 - LGET);
-    static_assert(LG1 >= LGET && LGC >= 0, "columns of ET to 256 ET points");
+    static_assert(LGC >= 0, "columns of up to 256 ET points");
     constexpr int LGR0 = LG1 % LGET ? LG1 % LGET : LGET, NB0 = ET >> LGR0;
     constexpr bool kLds = LG1 > LGET;
     __shared__ T2 buf[kLds ? (C << LG1) : 1];
@@ -903,6 +911,24 @@ __device__ __forceinline__ void load_row_lanes(T2 *X, const T2 *row, int u)
     }
 }
 
+// block -> (row pair, pixel pair): all row-pair blocks of one pixel pair run on one XCD
+// (blocks go to the 8 XCDs round robin), so the partial lines of its spectrum, written at a
+// stride of N1 elements, merge in that XCD's L2.  With fewer pixel pairs than XCDs that would leave XCDs idle: then the
+// blocks of a pair go round them (one pixel of 2^20 points, FP32: 43.5 us on one XCD, 19.3 on all).
+__device__ __forceinline__ bool row_pair(const FwdShape &sh, int &rp, int64_t &pl)
+{
+    const int64_t b = blockIdx.x, nrp = (1 << sh.lg1) / 2 + 1;
+    if (sh.nbatch < 8) {
+        rp = (int)(b % nrp);
+        pl = b / nrp;
+    } else {
+        const int64_t slot = b >> 3;
+        rp = (int)(slot % nrp);
+        pl = (slot / nrp) * 8 + (b & 7);
+    }
+    return pl < sh.nbatch;
+}
+
 // pass B: row pair (k1, N1 - k1) of the three packed transforms of one pixel pair per block, then S
 template <typename T>
 __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_waves_per_eu(FastCfg<T>::kRowWaves))) void k_fwd_rows_fast(
@@ -919,14 +945,9 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     const int tid = threadIdx.x;
     const int N1 = 1 << sh.lg1;
     const int64_t N = (int64_t)1 << sh.lg, ldS = N / 2 + 1;
-    // block -> (row pair, pixel pair): all row-pair blocks of one pixel pair run on one XCD
-    // (blocks go to the 8 XCDs round robin), so the partial lines of its spectrum, written at a
-    // stride of N1 elements, merge in that XCD's L2
-    const int64_t b = blockIdx.x, xcd = b & 7, slot = b >> 3;
-    const int nrp = N1 / 2 + 1;
-    const int rp = (int)(slot % nrp);
-    const int64_t pl = (slot / nrp) * 8 + xcd;
-    if (pl >= sh.nbatch) return;  // padding block (whole block)
+    int rp;
+    int64_t pl;
+    if (!row_pair(sh, rp, pl)) return;  // padding block (whole block)
     const int64_t p = sh.pair0 + pl, m0 = 2 * p, m1 = m0 + 1;
     const bool has1 = m1 < sh.n_pix;
     const int ka = rp, kb = (N1 - rp) & (N1 - 1);
@@ -1182,7 +1203,7 @@ __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type
     }
 }
 
-// The adjoint's passes at the forward path's shapes (N1 of ET to 2^kFastColsMaxLg1 points: rows of L): pass A is the
+// The adjoint's passes at the forward path's shapes (N1 of 2 to 2^kFastColsMaxLg1 points: rows of L): pass A is the
 // forward one (k_fwd_cols_fast), then
 //
 // pass B' (k_bwd_rows_fast): a row pair (k1, N1 - k1) of the three packed transforms per block, in place: the
@@ -1207,12 +1228,9 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     const int tid = threadIdx.x;
     const int N1 = 1 << sh.lg1;
     const int64_t N = (int64_t)1 << sh.lg, ldS = N / 2 + 1;
-    // block -> (row pair, pixel pair) as in pass B: the row pairs of one pixel pair read the lines of its dS together
-    const int64_t b = blockIdx.x, xcd = b & 7, slot = b >> 3;
-    const int nrp = N1 / 2 + 1;
-    const int rp = (int)(slot % nrp);
-    const int64_t pl = (slot / nrp) * 8 + xcd;
-    if (pl >= sh.nbatch) return;  // padding block (whole block)
+    int rp;  // as in pass B: the row pairs of one pixel pair read the lines of its dS together
+    int64_t pl;
+    if (!row_pair(sh, rp, pl)) return;  // padding block (whole block)
     const int64_t p = sh.pair0 + pl, m0 = 2 * p, m1 = m0 + 1;
     const bool has1 = m1 < sh.n_pix;
     const int ka = rp, kb = (N1 - rp) & (N1 - 1);
@@ -1305,10 +1323,10 @@ template <typename T, int LG1>
 __global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::type *__restrict__ Y, T *__restrict__ dE, FwdShape sh)
 {
     using T2 = typename C2<T>::type;
-    constexpr int LGET = FwdCfg<T>::kLgRadix, ET = 1 << LGET;
+    constexpr int LGET = cols_lget<T>(LG1), ET = 1 << LGET;
     constexpr int LGTAB = FastCfg<T>::kLgL;
     constexpr int LGC = 8 + LGET - LG1, C = 1 << LGC, TPC = 1 << (LG1 - LGET);
-    static_assert(LG1 >= LGET && LGC >= 0, "columns of ET to 256 ET points");
+    static_assert(LGC >= 0, "columns of up to 256 ET points");
     constexpr int LGR0 = LG1 % LGET ? LG1 % LGET : LGET, NB0 = ET >> LGR0;
     constexpr bool kLds = LG1 > LGET;
     __shared__ T2 buf[kLds ? (C << LG1) : 1];
@@ -1419,9 +1437,9 @@ lw_status run_fft(const T *E, int64_t n_pix, int64_t n_obs, double dt_obs, T *S,
     }
     const int64_t batch = std::min<int64_t>({pairs, (int64_t)(ws_bytes / per_pair_bytes<T>(n_obs)), kMaxGridYZ});
     T2 *Y = (T2 *)ws;
-    // N > L: the compile-time passes (pass A for columns of ET to 2^kFastColsMaxLg1 points)
-    const ColsKernel<T> cols = pick_cols_fast<T, Cfg::kLgRadix>(sh.lg1);
-    const int lgC_fast = 8 + Cfg::kLgRadix - sh.lg1;
+    // N > L: the compile-time passes (pass A for columns of up to 2^kFastColsMaxLg1 points)
+    const ColsKernel<T> cols = pick_cols_fast<T, 1>(sh.lg1);
+    const int lgC_fast = 8 + cols_lget<T>(sh.lg1) - sh.lg1;
     const unsigned gx_a = (unsigned)(1u << (sh.lg2 - (cols ? lgC_fast : sh.lgC))), gx_b = (unsigned)((1 << sh.lg1) / 2 + 1);
     for (int64_t p0 = 0; p0 < pairs; p0 += batch) {
         const int64_t nb = std::min(batch, pairs - p0);
@@ -1445,14 +1463,14 @@ lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, dou
     using Cfg = FwdCfg<T>;
     const int lg = ilog2(n_obs);
     // the forward path's shapes, where its columns have a compile-time pass
-    if (const ColsBwdKernel<T> inv = pick_cols_bwd<T, Cfg::kLgRadix>(lg - Cfg::kLgRow)) {
+    if (const ColsBwdKernel<T> inv = pick_cols_bwd<T, 1>(lg - Cfg::kLgRow)) {
         FwdShape f;
         f.n_pix = n_pix;
         f.lg = lg;
         f.lg2 = Cfg::kLgRow;
         f.lg1 = lg - f.lg2;
-        f.lgC = 8 + Cfg::kLgRadix - f.lg1;
-        const ColsKernel<T> cols = pick_cols_fast<T, Cfg::kLgRadix>(f.lg1);
+        f.lgC = 8 + cols_lget<T>(f.lg1) - f.lg1;
+        const ColsKernel<T> cols = pick_cols_fast<T, 1>(f.lg1);
         const unsigned gx_c = 1u << (f.lg2 - f.lgC), gx_r = (unsigned)((1 << f.lg1) / 2 + 1);
         const int64_t pairs = (n_pix + 1) / 2;
         const int64_t batch = std::min<int64_t>({pairs, (int64_t)(ws_bytes / per_pair_bytes<T>(n_obs)), kMaxGridYZ});
