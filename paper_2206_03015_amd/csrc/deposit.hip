@@ -142,31 +142,46 @@ __device__ __forceinline__ cdptr uniform_ptr(const double *p)
 // ---------------------------------------------------------------------------------------------
 // Pixel table and the arrival time
 
-// rows [0, n_rows): the pixels [0, n_pix), then padding rows (all zero, not usable) up to the end
-// of the last tile, whose arrival times stay finite
-__global__ void k_pixtab(const double *__restrict__ x_det, int64_t n_pix, int64_t n_rows, double C,
-                         double *__restrict__ pt)
+// What a launch starts from, in one kernel (six launches of their own were 15 of one electron's 57 us): zeros in the
+// trace (n_trace 16-byte elements and n_tail 4-byte ones behind them), the counters, the particles' flags and bounds
+// (n_p), and the pixel table's rows [0, n_rows): the pixels [0, n_pix), then padding rows (all zero, not usable) up to
+// the end of the last tile, whose arrival times stay finite.
+struct SetupShape {
+    int64_t n_trace, n_tail, n_p, n_pix, n_rows;
+    double C;
+};
+__global__ __launch_bounds__(256) void k_setup(uint4 *__restrict__ trace, unsigned long long *__restrict__ diag,
+                                               int *__restrict__ pflag, unsigned long long *__restrict__ rmax2,
+                                               const double *__restrict__ x_det, double *__restrict__ pt, SetupShape sh)
 {
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n_rows) return;
-    double *o = pt + m * kPT;
-    if (m >= n_pix) {
-#pragma unroll
-        for (int j = 0; j < kPT; ++j) o[j] = 0.0;
-        return;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t j = t; j < sh.n_trace; j += step) trace[j] = make_uint4(0, 0, 0, 0);
+    if (t < sh.n_tail) ((uint32_t *)(trace + sh.n_trace))[t] = 0;
+    if (diag && t < 4) diag[t] = 0;
+    for (int64_t j = t; j < sh.n_p; j += step) {
+        pflag[j] = 0;
+        rmax2[j] = 0;
     }
-    const PixC p = pix_const(x_det, m, C);
-    o[0] = p.o;
-    o[1] = p.px;
-    o[2] = p.py;
-    o[3] = p.g.ok ? 1.0 : 0.0;
-    o[4] = p.g.nx;
-    o[5] = p.g.ny;
-    o[6] = p.g.nz;
-    o[7] = p.g.D;
-    o[8] = p.g.invD;
+    for (int64_t m = t; m < sh.n_rows; m += step) {
+        double *o = pt + m * kPT;
+        if (m >= sh.n_pix) {
 #pragma unroll
-    for (int j = 9; j < kPT; ++j) o[j] = 0.0;
+            for (int j = 0; j < kPT; ++j) o[j] = 0.0;
+            continue;
+        }
+        const PixC p = pix_const(x_det, m, sh.C);
+        o[0] = p.o;
+        o[1] = p.px;
+        o[2] = p.py;
+        o[3] = p.g.ok ? 1.0 : 0.0;
+        o[4] = p.g.nx;
+        o[5] = p.g.ny;
+        o[6] = p.g.nz;
+        o[7] = p.g.D;
+        o[8] = p.g.invD;
+#pragma unroll
+        for (int j = 9; j < kPT; ++j) o[j] = 0.0;
+    }
 }
 
 // a pixel's constants from its table row (per lane, or wavefront-uniform through scalar loads)
@@ -999,7 +1014,9 @@ struct Sweep {
             const int c1 = min(c0 + kSteps, st1), share = (c1 - c0 + kWaves / 2 - 1) / (kWaves / 2);
             const int a = min(c0 + (wv >> 1) * share, c1), b = min(a + share, c1);
             uint64_t mask = 0;
-            if (a < b) {
+            if (c1 == c0 + 1 && st1 == st0 + 1) {
+                mask = 1;  // one step: the look through the particles has told
+            } else if (a < b) {
                 const PixC P = pixel<MODE>(p);
                 auto count = [&](int st) {  // window grid points up to the first sample of step st
                     const int64_t i = min((int64_t)st * Cfg::H, (int64_t)ns - 1);
@@ -1359,24 +1376,33 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
         return fail(LW_E_UNSUPPORTED, "lw_deposit_td_det: FP64 without culling only");
     if (n_obs > 0x7fffffff) return fail(LW_E_SHAPE, "lw_deposit_td: n_obs must be below 2^31");
     if (ns > 0x7fffffff) return fail(LW_E_SHAPE, "lw_deposit_td: too many samples");
+    const double C = 1.0 / (kC * gr->dt_obs);
+    // the trace's and counters' zeros (accumulate: none), with the setup of the first launch
+    SetupShape su{0, 0, 0, 0, 0, C};
+    unsigned long long *diag0 = nullptr;
     if (!accumulate) {
-        if (trace_elems) {
-            const int blocks = (int)std::min<size_t>((trace_elems + 255) / 256, 65536);
-            if (f64)
-                k_fill<double><<<blocks, 256, 0, s>>>((double *)E, (int64_t)trace_elems);
-            else
-                k_fill<float><<<blocks, 256, 0, s>>>((float *)E, (int64_t)trace_elems);
-        }
-        if (diag) k_fill<unsigned long long><<<1, 64, 0, s>>>((unsigned long long *)diag, 4);
+        const size_t words = trace_elems * (f64 ? 2 : 1);
+        su.n_trace = (int64_t)(words / 4);
+        su.n_tail = (int64_t)(words % 4);
+        diag0 = (unsigned long long *)diag;
     }
-    if (n_p == 0 || n_pix == 0 || ns == 0) return check_launch("deposit fill");
+    auto setup = [&](const DepWs *w, const double *xd) {
+        const int64_t most = std::max({su.n_trace, su.n_p, su.n_rows, (int64_t)1});
+        k_setup<<<(unsigned)std::min<int64_t>((most + 255) / 256, 16384), 256, 0, s>>>(
+            (uint4 *)E, diag0, w ? w->pflag : nullptr, w ? w->rmax2 : nullptr, xd, w ? w->pt : nullptr, su);
+        su.n_trace = su.n_tail = 0;
+        diag0 = nullptr;
+    };
+    if (n_p == 0 || n_pix == 0 || ns == 0) {
+        if (!accumulate) setup(nullptr, nullptr);
+        return check_launch("deposit fill");
+    }
     // particles per launch: all of them, or as many as the workspace holds arrival bases for
     int64_t chunk = n_p;
     while (chunk > 1 && ws_bytes_for(chunk, ns) > ws_bytes) chunk = std::max<int64_t>(1, chunk / 2);
     if (ws_bytes_for(chunk, ns) > ws_bytes)
         return fail(LW_E_WORKSPACE, "lw_deposit_td: workspace of %zu bytes holds no particle (%zu needed)", ws_bytes,
                     ws_bytes_for(1, ns));
-    const double C = 1.0 / (kC * gr->dt_obs);
     const int64_t n_chunks_s = (ns + kPrepassChunk - 1) / kPrepassChunk;
     if (n_chunks_s > 65535) return fail(LW_E_SHAPE, "lw_deposit_td: too many samples");
     // pixel passes of at most kPixTabMax pixels (the pixel table's share of the workspace); each
@@ -1419,17 +1445,14 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             if (std::max(blocks, blocks_careful) > 0x7fffffff)
                 return fail(LW_E_SHAPE, "lw_deposit_td: problem too large for one launch");
             const DepWs w = carve(ws, np);
-            if (p0 == 0) {
-                const int64_t rows = sh.n_tiles * kTilePix;  // <= kPixTabMax
-                k_pixtab<<<(unsigned)((rows + 255) / 256), 256, 0, s>>>(xd, npx, rows, C, w.pt);
-            }
+            su.n_p = np;
+            su.n_pix = npx;
+            su.n_rows = p0 == 0 ? sh.n_tiles * kTilePix : 0;  // <= kPixTabMax
+            setup(&w, xd);
             const double *r = t->r + (size_t)p0 * ns * 3, *b = t->beta + (size_t)p0 * ns * 3,
                          *bd = t->beta_dot + (size_t)p0 * ns * 3;
             const double *charge = t->charge ? t->charge + p0 : nullptr;
             const double *rb2 = rbound2 ? rbound2 + p0 : nullptr;
-            const int fill_blocks = (int)std::min<int64_t>((np + 255) / 256, 65536);
-            k_fill<int><<<fill_blocks, 256, 0, s>>>(w.pflag, np);
-            k_fill<unsigned long long><<<fill_blocks, 256, 0, s>>>(w.rmax2, np);
             int pchunk = kPrepassChunk;
             while (pchunk > 256 && np * ((ns + pchunk - 1) / pchunk) < kPrepassBlocks) pchunk /= 2;
             const dim3 pgrid((unsigned)np, (unsigned)((ns + pchunk - 1) / pchunk));

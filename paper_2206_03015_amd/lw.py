@@ -188,7 +188,7 @@ def deposit_td(r, beta, beta_dot, t_start, dt, x_det, t0, dt_obs, n_obs, prec="m
         out = torch.empty((gr.n_pix, 3, int(n_obs)), dtype=dtype, device=r.device)
     _need(out, dtype, (gr.n_pix, 3, int(n_obs)), "E")
     if diag is None:
-        diag = torch.zeros(4, dtype=torch.int64, device=r.device)
+        diag = (torch.zeros if accumulate else torch.empty)(4, dtype=torch.int64, device=r.device)
     need = workspace_bytes(WS_DEPOSIT, tr.n_particles, tr.n_samples, prec)
     if ws is None:
         ws = _workspace(need, r.device)
@@ -204,7 +204,7 @@ def _deposit_det(tr, gr, device, ws_need, field_mask, geom, out, diag, ws, acc):
         out = torch.empty((gr.n_pix, 3, gr.n_obs), dtype=torch.float64, device=device)
     _need(out, torch.float64, (gr.n_pix, 3, gr.n_obs), "E")
     if diag is None:
-        diag = torch.zeros(4, dtype=torch.int64, device=device)
+        diag = torch.empty(4, dtype=torch.int64, device=device)
     if ws is None:
         ws = _workspace(ws_need, device)
     if acc is None:
@@ -413,7 +413,7 @@ def deposit_td_boris(init, n_samples, t_start, dt, a0, lam, w0, n_cycles, x_det,
         out = torch.empty((gr.n_pix, 3, int(n_obs)), dtype=dtype, device=init.device)
     _need(out, dtype, (gr.n_pix, 3, int(n_obs)), "E")
     if diag is None:
-        diag = torch.zeros(4, dtype=torch.int64, device=init.device)
+        diag = (torch.zeros if accumulate else torch.empty)(4, dtype=torch.int64, device=init.device)
     if ws is None:
         ws = _workspace(workspace_bytes(WS_DEPOSIT_BORIS, tr.n_particles, tr.n_samples, prec), init.device)
     flags = GEOM[geom] | (ACCUMULATE if accumulate else 0) | (CULL if cull else 0)
