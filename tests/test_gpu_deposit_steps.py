@@ -73,3 +73,31 @@ def test_points_held_back_for_a_full_request(prec, n_samples, n_obs):
     c["beta"] = c["beta"].copy()
     c["beta"][2, n_samples // 2, 0] = np.nan
     check(c, prec, "farfield")
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("geom", ["exact", "farfield"])
+@pytest.mark.parametrize("n_samples, n_pix, n_obs", [(2, 1, 4000), (3, 130, 700), (100, 2, 513), (255, 3, 1025),
+                                                     (256, 1, 2049), (257, 5, 4096), (1024, 2, 5000), (1025, 2, 5000)])
+def test_short_trajectories_on_a_fine_grid(n_samples, n_pix, n_obs, prec, geom):
+    """At least one grid point per interval of at most 1024 samples: windows of grid points gather what the particles
+    bring (passes of 255 intervals, ragged windows); one sample more takes the other path.  With an unusable sample and
+    a particle whose arrival times crowd into a few grid points beside the dense ones; and added to a trace."""
+    from paper_2206_03015_amd import lw
+    c = synthetic(n_p=5, n_samples=n_samples, n_pix=n_pix, n_obs=n_obs, seed=n_samples, dt=2e-18 * 700 / max(n_samples, 200))
+    check(c, prec, geom)
+    t = {k: torch.as_tensor(np.ascontiguousarray(c[k]), device=DEV) for k in ("r", "beta", "beta_dot", "x_det", "charge")}
+    args = (t["r"], t["beta"], t["beta_dot"], c["t_start"], c["dt"], t["x_det"], c["t0"], c["dt_obs"], c["n_obs"])
+    E, d = lw.deposit_td(*args, prec=prec, geom=geom, charge=t["charge"])
+    E2, d2 = lw.deposit_td(*args, prec=prec, geom=geom, charge=t["charge"], out=E.clone(), accumulate=True, diag=d.clone())
+    assert d2.tolist() == [2 * v for v in d.tolist()]
+    assert float((E2 - 2 * E).abs().max()) <= TOL[prec] * float(E.abs().max())
+    if n_samples > 3:
+        c["beta"] = c["beta"].copy()
+        c["beta"][1, n_samples // 2, 1] = np.nan
+        # particle 3 nearly follows its light: arrival times n_samples times closer
+        s = np.arange(n_samples)[:, None] * c["dt"] * 299792458.0
+        c["beta"][3] = np.array([0.0, 0.0, 1.0 - 1e-4 / n_samples])
+        c["r"] = c["r"].copy()
+        c["r"][3] = c["r"][3, :1] + s * c["beta"][3]
+        check(c, prec, geom)
