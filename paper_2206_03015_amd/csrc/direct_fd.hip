@@ -89,7 +89,7 @@ __device__ __forceinline__ void stage_sample(const double *__restrict__ r, const
 // whose 192 elements per block are 32 frequencies x 3 components x (re, im): six multiply-adds a term, on
 // the matrix cores, and 1/32 + 1/64 sine/cosine pairs a term instead of one.  Other lists take one sine/cosine
 // pair per term as they come.  The rule is decided per block of threads from the frequencies themselves.
-// 20 x 2001 samples, 9 pixels, 1024 frequencies: 997 us with a sine/cosine pair per term -> 202 us (57 us of it
+// 20 x 2001 samples, 9 pixels, 1024 frequencies: 997 us with a sine/cosine pair per term -> 156 us (57 us of it
 // the matrix product at this card's FP64 rate, the rest the phasors and the exchange through LDS).
 constexpr int kFdBlk = 32;
 constexpr double kFdTol64 = 1e-15;  // a few roundings of a frequency: what the phase product's rounding is
@@ -140,8 +140,11 @@ constexpr int kFdChunk = 256;
 template <int W>
 struct alignas(16) Fd64Lds {
     static constexpr int kSub = W == 1 ? 64 : 32;
-    static constexpr int kRows = 48 * W, kPitch = kRows + 16;  // pitch = 16 mod 32 doubles: a 4-sample operand
-    static constexpr int kPitchR = 48;                         // column read falls in distinct banks
+    // pitches: a half wavefront's operand read is two rows of 16 doubles, its writes one column of 32 rows; 18 mod 32
+    // doubles (16-byte writes) and 49 put nearly all of either in distinct banks (16 mod 32: reads without
+    // conflicts but 16 writes on one bank, 202 us instead of 156 at the size above)
+    static constexpr int kRows = 48 * W, kPitch = kRows + (kRows % 32 ? 2 : 18);
+    static constexpr int kPitchR = 49;
     double ta[kFdChunk], e[3][kFdChunk];
     double2 nu[8 * W];
     union {
@@ -530,15 +533,19 @@ __global__ void k_fd_finish(const double *__restrict__ acc, double *__restrict__
 //   sum_w C e^{-iwt} = sum_A e^{-i w_A t} sum_h [cos h dw t (C+ + C-) - i sin h dw t (C+ - C-)]_A,
 // the inner sum a matrix product over the 32 cosines and sines of a sample, 12 columns (6 quantities, re and
 // im) per block of 32 frequencies, four blocks (48 columns) at a time: 12 multiply-adds a term on the matrix
-// cores and 1/32 sine/cosine pair.  Each sample is owned by one block: no atomics on the gradient.
-// 20 x 2001 samples, 9 pixels, 1024 frequencies: 2071 us with a sine/cosine pair per term -> 444 us (112 us of it
+// cores and 1/32 sine/cosine pair.  The pixels are shared out over blocks until there are kFdBwdBlocks of them (a block's
+// chain of pixels and frequency blocks is its time, and two fit a compute unit).
+// 20 x 2001 samples, 9 pixels, 1024 frequencies: 2071 us with a sine/cosine pair per term -> 350 us (112 us of it
 // the matrix product).
+constexpr int64_t kFdBwdBlocks = 2048;
+constexpr int kFdNu = 128;  // frequency blocks whose centres are kept
 struct alignas(16) FdBwdLds {
+    double2 nua[kFdNu];
     double nu[4][64], ta[4][64];  // any-frequency path: staged frequencies; arrival times of four pixels
     double g[4][6][64];           // G_c, K_c of four pixels
     union {
         struct {
-            double w[32][48];    // coefficients of the four blocks
+            double w[32][50];    // coefficients of the four blocks (pitch as in Fd64Lds)
             double p[4][64][2];  // cos, sin of w_A t
         };
         double row[4][64][8];  // any-frequency path: dS, w dS, R_x, I_x, R_y, I_y, R_z, I_z
@@ -577,11 +584,16 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
     const int64_t n_w = sh.n_omega;
     const double dw = fd_step(omega, n_w), dnu = dw * kInv2Pi;
     const bool equal = fd_equal(omega, n_w, dw);
-    for (int64_t m0 = 0; m0 < sh.n_pix; m0 += 4) {
+    const int64_t na = (n_w + kFdBlk - 1) / kFdBlk;
+    for (int64_t A = tid; A < std::min<int64_t>(na, kFdNu); A += 256) s.nua[A] = fd_cycles(fd_centre(omega, n_w, A, dw));
+    // this block's share of the pixels
+    const int64_t mb = std::min<int64_t>((int64_t)blockIdx.y * sh.parts_per_group, sh.n_pix);
+    const int64_t me = std::min<int64_t>(mb + sh.parts_per_group, sh.n_pix);
+    for (int64_t m0 = mb; m0 < me; m0 += 4) {
         const int64_t m = m0 + wv;
-        PixGeo g = pix_geo(x_det, m < sh.n_pix ? m : 0);
-        const double *xm = x_det + 3 * (m < sh.n_pix ? m : 0);
-        bool ok = usable && g.ok && m < sh.n_pix;
+        PixGeo g = pix_geo(x_det, m < me ? m : mb);
+        const double *xm = x_det + 3 * (m < me ? m : mb);
+        bool ok = usable && g.ok && m < me;
         double ta = 0.0, kap = 0.0, E[3] = {0, 0, 0}, A[3] = {0, 0, 0};
         if (ok) {
             lw_field<double, GEOM>(g, xm, rs[0], rs[1], rs[2], bs[0], bs[1], bs[2], as[0], as[1], as[2], q, sh.fmask,
@@ -594,7 +606,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
 #pragma unroll
         for (int c = 0; c < 6; ++c) s.g[wv][c][lane] = 0.0;
         __syncthreads();
-        const int np = (int)std::min<int64_t>(4, sh.n_pix - m0);
+        const int np = (int)std::min<int64_t>(4, me - m0);
         for (int p = 0; p < np; ++p) {
             const double *fs = acc + (size_t)(m0 + p) * n_w * 6, *ds = dS + (size_t)(m0 + p) * n_w;
             if (equal) {
@@ -611,24 +623,34 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
                 for (int t = 0; t < 3; ++t)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) sum[t][v] = 0.0;
+                // thread -> block a, offset h, component c of four blocks (192 of them); the next four's values are on
+                // their way while these multiply
+                const int c3 = tid % 3, h16 = tid / 3 % 16, a4 = tid / 48;
+                double fp[2], fm[2], dp, dm, wp, wm;
+                auto fetch = [&](int64_t w0) {
+                    const int64_t jp = w0 + kFdBlk * a4 + 16 + h16, jm = w0 + kFdBlk * a4 + 15 - h16;
+                    fp[0] = fp[1] = fm[0] = fm[1] = dp = dm = wp = wm = 0.0;
+                    if (tid >= 192) return;
+                    if (jp < n_w) {
+                        fp[0] = fs[jp * 6 + 2 * c3];
+                        fp[1] = fs[jp * 6 + 2 * c3 + 1];
+                        dp = ds[jp];
+                        wp = omega[jp];
+                    }
+                    if (jm < n_w) {
+                        fm[0] = fs[jm * 6 + 2 * c3];
+                        fm[1] = fs[jm * 6 + 2 * c3 + 1];
+                        dm = ds[jm];
+                        wm = omega[jm];
+                    }
+                };
+                fetch(0);
                 for (int64_t w0 = 0; w0 < n_w; w0 += 4 * kFdBlk) {
-                    if (tid < 192) {  // block a, offset h, component c
-                        const int c = tid % 3, h = tid / 3 % 16, a = tid / 48;
-                        const int64_t jp = w0 + kFdBlk * a + 16 + h, jm = w0 + kFdBlk * a + 15 - h;
-                        double cp[2] = {0, 0}, cm[2] = {0, 0}, wp = 0.0, wm = 0.0;
-                        if (jp < n_w) {
-                            cp[0] = ds[jp] * fs[jp * 6 + 2 * c];
-                            cp[1] = ds[jp] * fs[jp * 6 + 2 * c + 1];
-                            wp = omega[jp];
-                        }
-                        if (jm < n_w) {
-                            cm[0] = ds[jm] * fs[jm * 6 + 2 * c];
-                            cm[1] = ds[jm] * fs[jm * 6 + 2 * c + 1];
-                            wm = omega[jm];
-                        }
+                    if (tid < 192) {
+                        double cp[2] = {dp * fp[0], dp * fp[1]}, cm[2] = {dm * fm[0], dm * fm[1]};
 #pragma unroll
                         for (int z = 0; z < 2; ++z) {  // C, then w C
-                            double *o = &s.w[h][12 * a + 6 * z + 2 * c], *o2 = &s.w[16 + h][12 * a + 6 * z + 2 * c];
+                            double *o = &s.w[h16][12 * a4 + 6 * z + 2 * c3], *o2 = &s.w[16 + h16][12 * a4 + 6 * z + 2 * c3];
                             o[0] = cp[0] + cm[0];
                             o[1] = cp[1] + cm[1];
                             o2[0] = cp[1] - cm[1];
@@ -642,11 +664,13 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
                     }
                     {  // block wv's phase at sample `lane`
                         double cs = 0.0, sn = 0.0;
-                        if (w0 + kFdBlk * wv < n_w)
-                            fd_phasor(fd_cycles(fd_centre(omega, n_w, w0 / kFdBlk + wv, dw)), s.ta[p][lane], cs, sn);
+                        const int64_t A = w0 / kFdBlk + wv;
+                        if (A < na)
+                            fd_phasor(A < kFdNu ? s.nua[A] : fd_cycles(fd_centre(omega, n_w, A, dw)), s.ta[p][lane], cs, sn);
                         *(double2 *)s.p[wv][lane] = make_double2(cs, sn);
                     }
                     __syncthreads();
+                    fetch(w0 + 4 * kFdBlk);
                     v4d t3[3];
 #pragma unroll
                     for (int t = 0; t < 3; ++t) t3[t] = v4d{0.0, 0.0, 0.0, 0.0};
@@ -744,7 +768,10 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
         for (int c = 0; c < 3; ++c) {
             double v = s.red[0][3 * wv + c][lane];
             for (int w = 1; w < 4; ++w) v += s.red[w][3 * wv + c][lane];
-            out[so + c] += v;
+            if (gridDim.y > 1)
+                atomic_add(out + so + c, v);
+            else
+                out[so + c] += v;
         }
     }
 }
@@ -883,9 +910,14 @@ lw_status launch_direct_fd_bwd(const lw_traj_t *t, const lw_grid_t *gr, const do
     const int64_t blocks = t->n_particles * ((t->n_samples + 63) / 64);
     if (blocks > 0x7fffffff) return fail(LW_E_SHAPE, "lw_direct_fd_bwd: problem too large for one launch");
     const double two_f = 2.0 * t->dt * t->dt / (2.0 * kPi);
+    // pixels per block: a multiple of four (a wavefront each)
+    const int64_t quads = (gr->n_pix + 3) / 4, share = std::max<int64_t>(1, std::min(quads, (kFdBwdBlocks + blocks - 1) / blocks));
+    FdShape sb = sh;
+    sb.parts_per_group = (quads + share - 1) / share * 4;
+    const int64_t ny = (gr->n_pix + sb.parts_per_group - 1) / sb.parts_per_group;
     auto *k = geom == LW_GEOM_EXACT ? k_direct_fd_bwd<LW_GEOM_EXACT> : k_direct_fd_bwd<LW_GEOM_FARFIELD>;
-    k<<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, dS, d_r, d_beta,
-                                       d_beta_dot, sh, two_f);
+    k<<<dim3((unsigned)blocks, (unsigned)ny), 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, dS, d_r, d_beta,
+                                       d_beta_dot, sb, two_f);
     return check_launch("lw_direct_fd_bwd");
 }
 
