@@ -498,6 +498,15 @@ __device__ __forceinline__ void push_sample_fast(const PushState<double> &S, dou
 
 // state of one sample in the hand-over buffer: x, y, z, E_x, u (an odd pitch: the particles' entries
 // start in different banks)
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 template <int P, int S>
 struct PushLds {
     static constexpr int kPitch = 8 * S + 1;
@@ -623,13 +632,15 @@ __device__ void push_select(const double *__restrict__ init, int64_t n_particles
 // later.  The field at sample s0 is that of the step that reached it (same arguments, same bits).
 // The state at the last sample is left in `state` if given, and x, y, z and u half a step later of the samples
 // seg - 1, 2 seg - 1 ... (seg a multiple of kPushSteps) in ck [n_particles][ck_stride] if given.
-template <bool PAIR, bool OUT, int NC>
+// PRE: the deposit's arrival bases and flags of the samples as well (the rules of its pre-pass, whose reading of the
+// samples, 72 bytes each, was 3.8 of 29.1 ms for 10000 x 20001 samples; the launch here takes 2.4 ms more for them).
+template <bool PAIR, bool OUT, bool PRE, int NC>
 __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict__ init, int64_t n_particles, int64_t s0,
                                                        int64_t n_span, double t_start, double dt, LaserDev L, int sorted,
                                                        double *__restrict__ state, double *__restrict__ r,
                                                        double *__restrict__ beta, double *__restrict__ beta_dot,
                                                        double *__restrict__ rmax2, double *__restrict__ ck,
-                                                       int64_t ck_stride, int64_t seg)
+                                                       int64_t ck_stride, int64_t seg, DepositPre pre)
 {
     constexpr int P = PAIR ? 32 : 64, S = PAIR ? kPushSteps : kPushSteps / 2;
     using Lds = PushLds<P, S>;
@@ -784,10 +795,25 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
         double mx[NG];
 #pragma unroll
         for (int g = 0; g < NG; ++g) mx[g] = 0.0;
+        // PRE: the lanes' samples of the batch before, and flags
+        constexpr int NK = PRE ? NG : 1;
+        double last[NK][3];
+        bool bad[NK];
+#pragma unroll
+        for (int g = 0; g < NK; ++g) {
+            bad[g] = false;
+            last[g][0] = last[g][1] = last[g][2] = 0.0;
+        }
+        const double cdt = kC * dt, rc_o = PRE ? 1.0 / pre.dt_obs : 0.0;
+        auto qc = [&](double v) { return div_const(v, kC, K.rc_c); };
+        auto qo = [&](double v) { return div_const(v, pre.dt_obs, rc_o); };
         for (int64_t b = 0; b < nb; ++b) {
             __syncthreads();  // batch b is written
             const int64_t i = b * S + j;
-            if (i >= n_span) continue;
+            ArrivalTime tm;
+            if constexpr (PRE) tm = arrival_time(t_start, dt, (double)(s0 + i), pre.t0);
+            if constexpr (!PRE)
+                if (i >= n_span) continue;  // PRE: every lane hands its sample on
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
                 const int p = p0 + g * G;
@@ -796,9 +822,11 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                 Q.x = row[0];
                 Q.y = row[1];
                 Q.z = row[2];
-                mx[g] = fmax(mx[g], fma(Q.z, Q.z, fma(Q.y, Q.y, Q.x * Q.x)));
+                if (!PRE || i < n_span) mx[g] = fmax(mx[g], fma(Q.z, Q.z, fma(Q.y, Q.y, Q.x * Q.x)));
                 if constexpr (OUT) {
-                    if (idx[p] < 0) continue;
+                    const int k = idx[p];
+                    if constexpr (!PRE)
+                        if (k < 0) continue;
                     Q.Ex = row[3];
                     Q.By = -div_const(Q.Ex, kC, K.rc_c);
                     Q.usx = row[4];
@@ -806,7 +834,25 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                     Q.usz = row[6];
                     double rr[3], bb[3], aa[3];
                     push_sample_fast(Q, rr, bb, aa);
-                    const size_t o = ((size_t)idx[p] * n_span + i) * 3;
+                    if constexpr (PRE) {
+                        // the sample before: the neighbouring lane's, at a batch's first sample the last one's of
+                        // the batch before
+                        double dr[3];
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            const double a = dpp_double<0x111>(rr[c]), f = dpp_double<0x100 + S - 1>(last[g][c]);
+                            dr[c] = rr[c] - (j == 0 ? f : a);
+                            last[g][c] = rr[c];
+                        }
+                        if (k < 0 || i >= n_span) continue;
+                        const double d = arrival_base(tm, rr[2], pre.dt_obs, qc, qo);
+                        pre.base[(size_t)k * n_span + i] = d;
+                        const double s2 = dr[0] * dr[0] + dr[1] * dr[1] + dr[2] * dr[2];
+                        const double step = s2 > 1e-200 && s2 < 1e200 ? sqrt_plain(s2) : sqrt(s2);
+                        bad[g] = bad[g] || !sample_usable(rr, bb, aa) ||
+                                 (i > 0 && interval_slow(d, rr[0], rr[1], rr[2], step, cdt, pre.C));
+                    }
+                    const size_t o = ((size_t)k * n_span + i) * 3;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         r[o + c] = rr[c];
@@ -823,6 +869,14 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                 for (int off = S / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
                 const int k = idx[p0 + g * G];
                 if (j == 0 && k >= 0) rmax2[k] = m;
+            }
+        }
+        if constexpr (PRE) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const uint64_t m = __builtin_amdgcn_ballot_w64(bad[g]) >> (lane & ~(S - 1));
+                const int k = idx[p0 + g * G];
+                if (j == 0 && k >= 0) pre.pflag[k] = (m & ((1ull << S) - 1)) != 0 ? 1 : 0;
             }
         }
     }
@@ -1149,7 +1203,7 @@ LaserDev laser_dev(const lw_laser_t &l)
 // samples s0 .. s0 + n_span - 1 (r given) and / or max |r|^2 over them (rmax2 given)
 static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, double *state, double *r, double *beta,
                              double *beta_dot, double *rmax2, hipStream_t s, const char *what, double *ck = nullptr,
-                             int64_t seg = kPushSteps)
+                             int64_t seg = kPushSteps, const DepositPre &pre = DepositPre{})
 {
     if (t->n_particles == 0 || n_span == 0) return LW_OK;
     const LaserDev L = laser_dev(t->laser);
@@ -1162,14 +1216,14 @@ static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, dou
     // else two (10000 particles, 313 blocks: 7.6 ms with four, whose chains share SIMDs, 4.6 with two)
     auto go = [&](auto *k, int nc) {
         k<<<blocks, 64 * (1 + nc), 0, s>>>(t->init, t->n_particles, s0, n_span, t->t_start, t->dt, L, sorted, state, r, beta,
-                                          beta_dot, rmax2, ck, kTanStateDoubles, seg);
+                                          beta_dot, rmax2, ck, kTanStateDoubles, seg, pre);
     };
     if (pair && blocks <= 256)
-        r ? go(k_push<true, true, 4>, 4) : go(k_push<true, false, 4>, 4);
+        pre.base ? go(k_push<true, true, true, 4>, 4) : r ? go(k_push<true, true, false, 4>, 4) : go(k_push<true, false, false, 4>, 4);
     else if (pair)
-        r ? go(k_push<true, true, 2>, 2) : go(k_push<true, false, 2>, 2);
+        pre.base ? go(k_push<true, true, true, 2>, 2) : r ? go(k_push<true, true, false, 2>, 2) : go(k_push<true, false, false, 2>, 2);
     else
-        r ? go(k_push<false, true, 2>, 2) : go(k_push<false, false, 2>, 2);
+        pre.base ? go(k_push<false, true, true, 2>, 2) : r ? go(k_push<false, true, false, 2>, 2) : go(k_push<false, false, false, 2>, 2);
     return check_launch(what);
 }
 
@@ -1185,11 +1239,11 @@ lw_status launch_boris_rmax2(const lw_traj_t *t, double *rmax2, hipStream_t s)
 }
 
 lw_status launch_boris_span(const lw_traj_t *t, int64_t s0, int64_t n_span, double *state, double *r, double *beta,
-                            double *beta_dot, double *rmax2, hipStream_t s, double *tstate)
+                            double *beta_dot, double *rmax2, hipStream_t s, double *tstate, const DepositPre &pre)
 {
     const TanSegments g = tangent_segments(t->n_particles, n_span);
     return launch_push(t, s0, n_span, state, r, beta, beta_dot, rmax2, s, "lw_deposit_td (pusher span)",
-                       tstate && g.n > 1 ? tstate + kTanCk : nullptr, g.len);
+                       tstate && g.n > 1 ? tstate + kTanCk : nullptr, g.len, pre);
 }
 
 lw_status launch_boris_bwd_span(const lw_traj_t *t, int64_t s0, int64_t n_span, const double *state, double *tstate,

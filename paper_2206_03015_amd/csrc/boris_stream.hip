@@ -151,7 +151,8 @@ lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec
         if (st != LW_OK) return st;
         for (int64_t s0 = 0;;) {
             const int64_t n_span = std::min<int64_t>(P.span, ns - s0);
-            st = launch_boris_span(&push, s0, n_span, state, r, b, bd, whole ? rb2 : nullptr, s);
+            const DepositPre pre = deposit_pre(ws, nb, n_span, gr);
+            st = launch_boris_span(&push, s0, n_span, state, r, b, bd, whole ? rb2 : nullptr, s, nullptr, pre);
             if (st != LW_OK) return st;
             lw_traj_t sub = *t;
             sub.kind = LW_TRAJ_SAMPLES;
@@ -164,7 +165,7 @@ lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec
             sub.init = nullptr;
             sub.charge = t->charge ? t->charge + b0 : nullptr;
             st = launch_deposit(&sub, gr, prec, fmask, geom, accumulate || b0 > 0 || s0 > 0, E, diag, ws, dep_bytes,
-                                s, s0, rb2, acc_mode, det);
+                                s, s0, rb2, acc_mode, det, &pre);
             if (st != LW_OK) return st;
             if (s0 + n_span >= ns) break;
             s0 += n_span - 1;  // the next span starts at this span's last sample

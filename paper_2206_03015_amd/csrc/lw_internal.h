@@ -88,22 +88,37 @@ __host__ __device__ __forceinline__ void two_sum(double a, double b, double &s, 
     e = (a - (s - bb)) + (b - bb);
 }
 
-// d of sample idx (t_idx = t_start + idx dt) at height z
+// t_idx - t0 = a + alo, t_idx = t_start + idx dt
+struct ArrivalTime {
+    double a, alo;
+};
+__host__ __device__ __forceinline__ ArrivalTime arrival_time(double t_start, double dt, double idx, double t0)
+{
+    const double p = idx * dt, pe = fma(idx, dt, -p);  // idx dt = p + pe
+    double s, se, a, ae;
+    two_sum(t_start, p, s, se);  // t_idx = s + se + pe
+    two_sum(s, -t0, a, ae);
+    return {a, ae + (se + pe)};
+}
+// d at a time and height z; the quotients by c and by dt_obs are by_c's and by_o's (correctly rounded)
+template <typename QC, typename QO>
+__host__ __device__ __forceinline__ double arrival_base(const ArrivalTime &t, double z, double dt_obs, QC by_c, QO by_o)
+{
+    double n, ne;
+    const double q = by_c(z);
+    const double qr = by_c(fma(-q, kC, z));  // z/c = q + qr (the division's residual is exact)
+    two_sum(t.a, -q, n, ne);                 // t_idx - t0 - z/c = n + nlo
+    const double nlo = ne + (t.alo - qr);
+    const double h = by_o(n);
+    const double rem = fma(-h, dt_obs, n);
+    return h + by_o(rem + nlo);
+}
+// d of sample idx at height z
 __host__ __device__ __forceinline__ double arrival_base(double t_start, double dt, double idx, double t0, double dt_obs,
                                                         double z)
 {
-    const double p = idx * dt, pe = fma(idx, dt, -p);  // idx dt = p + pe
-    double s, se, a, ae, n, ne;
-    two_sum(t_start, p, s, se);  // t_idx = s + se + pe
-    two_sum(s, -t0, a, ae);      // t_idx - t0 = a + alo
-    const double alo = ae + (se + pe);
-    const double q = z / kC;
-    const double qr = fma(-q, kC, z) / kC;  // z/c = q + qr (the division's residual is exact)
-    two_sum(a, -q, n, ne);                  // t_idx - t0 - z/c = n + nlo
-    const double nlo = ne + (alo - qr);
-    const double h = n / dt_obs;
-    const double rem = fma(-h, dt_obs, n);
-    return h + (rem + nlo) / dt_obs;
+    return arrival_base(arrival_time(t_start, dt, idx, t0), z, dt_obs, [](double v) { return v / kC; },
+                        [=](double v) { return v / dt_obs; });
 }
 
 // Constants of one pixel: geometry and the coefficients of b.
@@ -419,6 +434,16 @@ __device__ __forceinline__ bool sample_usable(const double *r, const double *b, 
     return ok && (b[0] * b[0] + b[1] * b[1] + b[2] * b[2] < 1.0);
 }
 
+// Whether the deposit's fast path does not take the interval that ends at sample (x, y, z) of arrival base d, the
+// distance step from the sample before: not by more than rounding later than that one at every pixel.
+__device__ __forceinline__ bool interval_slow(double d, double x, double y, double z, double step, double cdt, double C)
+{
+    // bound of the rounding of tau (its terms: d, b ~ C (|x| + |y| + 2|z|), the path term)
+    const double scale = fabs(d) + 2.0 * (fabs(x) + fabs(y) + fabs(z)) * C + 1.0;
+    const double margin = (cdt - step) * C;  // lower bound of tau_i - tau_{i-1}
+    return !(margin > 1e-9 + 1e-13 * scale);
+}
+
 __device__ __forceinline__ void atomic_add(float *p, float v) { unsafeAtomicAdd(p, v); }
 __device__ __forceinline__ void atomic_add(double *p, double v) { unsafeAtomicAdd(p, v); }
 
@@ -439,10 +464,21 @@ struct DetAcc {
 // t_start + (sample0 + i) dt); 0 for whole trajectories.  rbound2: per particle, max |r|^2 over
 // the whole trajectory (nullptr: the max over the samples given), which decides the series forms
 // of the arrival time per particle and pixel.
+// pre: the workspace's arrival bases and flags are there already, from the pusher
 lw_status launch_deposit(const lw_traj_t *traj, const lw_grid_t *grid, int prec, int field_mask, int geom,
                          bool accumulate, void *E, int64_t *diag, void *ws, size_t ws_bytes, hipStream_t s,
                          int64_t sample0 = 0, const double *rbound2 = nullptr, int acc_mode = kAccFloat,
-                         DetAcc det = DetAcc{nullptr, nullptr});
+                         DetAcc det = DetAcc{nullptr, nullptr}, const struct DepositPre *pre = nullptr);
+// What the deposit's pre-pass leaves in a workspace (of at least deposit_ws_bytes of these sizes): the samples' arrival
+// bases [n_particles][n_samples] and the particles' flags (1: careful path).  base is null where the pusher
+// leaves them to the deposit: where the pre-pass has more to do (short trajectories, which may be dense), and for less
+// than kPrePushed particles.
+struct DepositPre {
+    double *base = nullptr;
+    int *pflag = nullptr;
+    double t0 = 0.0, dt_obs = 0.0, C = 0.0;
+};
+DepositPre deposit_pre(void *ws, int64_t n_particles, int64_t n_samples, const lw_grid_t *grid);
 // lw_deposit_td_det: FP64 deposit whose result does not depend on the order of the contributions
 // (acc: the high words and row scales, det_acc_bytes(n_pix, n_obs) bytes)
 lw_status launch_deposit_det(const lw_traj_t *traj, const lw_grid_t *grid, int field_mask, int geom, double *E,
@@ -472,9 +508,11 @@ lw_status launch_boris_rmax2(const lw_traj_t *traj, double *rmax2, hipStream_t s
 // samples s0 .. s0 + n_span - 1 of every particle of traj (LW_TRAJ_BORIS), starting from init
 // (s0 = 0) or from the pusher state [n_particles][9] left by the span that ended at sample s0;
 // rmax2 (or nullptr): max |r|^2 over the span's samples; tstate (or nullptr): the tangents' state, which takes
-// the pusher's state at the starts of their segments
+// the pusher's state at the starts of their segments; pre: the deposit's arrival bases and flags of the
+// span's samples (base null: neither)
 lw_status launch_boris_span(const lw_traj_t *traj, int64_t s0, int64_t n_span, double *state, double *r,
-                            double *beta, double *beta_dot, double *rmax2, hipStream_t s, double *tstate = nullptr);
+                            double *beta, double *beta_dot, double *rmax2, hipStream_t s, double *tstate = nullptr,
+                            const DepositPre &pre = DepositPre{});
 lw_status launch_boris_bwd(const lw_traj_t *traj, const double *g_r, const double *g_beta,
                            const double *g_beta_dot, double *grad_init, double *grad_a0, hipStream_t s);
 // the pusher's tangents over samples s0 .. s0 + n_span - 1 (gradients g_* [n_particles][n_span][3]),

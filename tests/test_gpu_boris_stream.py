@@ -71,6 +71,31 @@ def test_stream_spans_equal_stored_trajectories(prec, span):
     assert int(do[3]) > 0
 
 
+@pytest.mark.parametrize("n_p, n_samples, span, prec", [(2047, 1025, 0, "fp64"), (2048, 1025, 0, "mixed"),
+                                                        (2079, 1026, 0, "fp64"), (2100, 3001, 1025, "mixed"),
+                                                        (2100, 2500, 1030, "fp64"), (8200, 1032, 0, "fp64"),
+                                                        (32768 + 40, 1029, 0, "fp64")])
+def test_pushed_arrival_bases_equal_the_pre_pass(n_p, n_samples, span, prec):
+    """From 2048 particles and spans of more than 1024 samples on the pusher leaves the arrival bases and flags that the
+    deposit's pre-pass forms of stored samples: at the ends of its batches (8 samples, 4 beyond 32768
+    particles) and with spans that leave less than that.  Among the particles one whose arrival times nearly stand still and one of undefined samples (careful path).
+    Tolerances: the order of the sums alone differs, as in the tests above."""
+    from paper_2206_03015_amd import lw
+    W = inputs.workload("bunch").scaled(n_p=n_p, n_steps=n_samples - 1, n_side=3, n_obs=1 << 18)
+    L = W.laser
+    i0 = inputs.bunch_init(W)
+    i0[1, 5] = 1e7
+    i0[2, 4] = np.nan
+    init, x_det = T(i0), T(inputs.pixel_positions(W.n_side, W.theta_max, W.D))
+    args = (W.n_samples, W.t_start, W.dt, L.a0, L.lam, L.w0, L.n_cycles)
+    grid = (x_det, W.t0, W.dt_obs, W.n_obs)
+    Es, ds = lw.deposit_td_boris(init, *args, *grid, prec=prec, span=span)
+    r, b, bd = lw.trajectory_boris(init, *args)
+    Eo, do = lw.deposit_td(r, b, bd, W.t_start, W.dt, *grid, prec=prec)
+    assert ds.tolist() == do.tolist() and int(do[3]) > 0
+    assert float((Es - Eo).abs().max()) <= (1e-12 if prec == "fp64" else 1e-6) * float(Eo.abs().max())
+
+
 def test_stream_long_trajectory_small_workspace():
     """2e5 samples per particle through a workspace that holds 512-sample spans of the four
     particles (beyond the deposit's fixed part, the pixel table, under 1 % of the stored
