@@ -75,12 +75,13 @@ FD_TERM_FLOPS = 18
 ADJ_TRIPLE_F64_FLOPS = 6
 ADJ_POINT_F64_FLOPS = 2 * (FIELD_F32_FLOPS + 2 * FIELD_F32_FLOPS) + 20
 DEPOSIT_SOURCES = ("paper_2206_03015_amd/csrc/deposit.hip", "paper_2206_03015_amd/csrc/lw_internal.h")
+# counter summaries, where committed
 SUMMARIES = {
-    "precision": {"traffic": "profiles/k_scan_precision_mixed_hbm_traffic.md",
-                  "valu": "profiles/k_scan_precision_mixed_valu.md",
+    "precision": {"traffic": "profiles/k_sweep_precision_mixed_hbm_traffic.md",
+                  "valu": "profiles/k_sweep_precision_mixed_valu.md",
                   "types": "profiles/valu_fp32_fp64_precision.md"},
-    "bunch": {"traffic": "profiles/k_scan_bunch_mixed_exact_hbm_traffic.md",
-              "valu": "profiles/k_scan_bunch_mixed_exact_valu.md",
+    "bunch": {"traffic": "profiles/k_sweep_bunch_mixed_exact_hbm_traffic.md",
+              "valu": "profiles/k_sweep_bunch_mixed_exact_valu.md",
               "types": "profiles/valu_fp32_fp64_bunch.md"},
 }
 
@@ -168,7 +169,7 @@ def deposit_roofline(triples, hits, kernel_s, launches, summaries=None, profiled
     peak = work / t_roof / 1e12
     achieved = work / kernel_s / 1e12
     roof = {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-            "traffic": None, "kernel": "k_scan", "launches": launches, "kernel_ms": kernel_s * 1e3,
+            "traffic": None, "kernel": "k_sweep", "launches": launches, "kernel_ms": kernel_s * 1e3,
             "work": {"f64_flops": f64, "f32_flops": f32, "triples": triples, "deposited_points": hits,
                      "f64_flops_per_deposited_point": POINT_F64_FLOPS,
                      "f32_flops_per_deposited_point": HIT_F32_FLOPS},
@@ -805,7 +806,7 @@ def full_size_adjoint(torch, dev, W, init):
            "deposit_bwd_kernel_ms": bwd_ms, "boris_tangent_kernel_ms": tan_ms, "tangent_launches": tan_n,
            "deposit_bwd_roofline": roof, "grad_init_norm": float(torch.linalg.vector_norm(g_init))}
     log(f"[large] adjoint kernels: k_deposit_bwd {bwd_ms:.0f} ms in {bwd_n} launches (roofline fraction "
-        f"{roof['frac']:.3f}), k_boris_tangent_span {tan_ms:.0f} ms in {tan_n} launches")
+        f"{roof['frac']:.3f}), k_tangent_segment {tan_ms:.0f} ms in {tan_n} launches")
     log(f"[large] adjoint on {len(cen)} pixels: forward {rec['forward_ms']:.0f} ms, FFT adjoint "
         f"{rec['fft_bwd_ms']:.1f} ms, deposit+pusher adjoint {rec['deposit_boris_bwd_ms']:.0f} ms; dJ/da0 "
         f"{dj_da0:.6e} vs central difference {fd:.6e} (rel {rec['rel_diff']:.1e})")

@@ -342,7 +342,7 @@ lw_status lw_spectrum_fft_bwd(const void *E, const void *dS, int64_t n_pix, int6
  * n_samples, prec) bytes (each particle's max |r_i|^2).  Arrival times take the
  * forward FP64 deposit's forms: for pixels at the distance of pixel 0 and
  * particles with max_i |r_i|^2 <= 1e-8 |x_m|^2 the polynomial in the pixel term
- * b of the deposit's records (the same coefficients), else from the compensated
+ * b of the deposit (the same coefficients), else from the compensated
  * arrival base with the third-order series of the path correction in that range
  * (exact to rounding) or the square-root form.
  */

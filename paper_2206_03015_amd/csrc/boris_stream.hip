@@ -18,8 +18,8 @@ namespace {
 
 // default workspace budget of a plan
 constexpr size_t kBatchBytes = size_t(16) << 30;
-// the pusher runs one lane per particle through every step of a span, so its time is the
-// per-step latency of one wavefront times the span length for up to one wavefront per SIMD
+// a particle's steps are one serial chain, so the pusher's time is the per-step latency of one
+// wavefront's chain times the span length for up to one such wavefront per SIMD
 // (1024 SIMDs x 64 lanes): batches of up to that many particles, spans as long as fit
 constexpr int64_t kFillParticles = 65536;
 // spans shorter than this give way to smaller batches (each span is one deposit launch)

@@ -2,8 +2,8 @@
 // Sec. "Interpolation"), forward pass.
 //
 // Work decomposition (one GPU's share of the paper's detector decomposition):
-//   * a pre-pass writes, for every (particle, sample), the sample's arrival base d
-//     (the two large, cancelling terms of the arrival time, carried in double-double and
+//   * a pre-pass (for many pushed particles the pusher) writes, for every (particle, sample), the
+//     sample's arrival base d (the two large, cancelling terms of the arrival time, carried in double-double and
 //     rounded once), flags particles whose arrival times are not provably increasing and finds
 //     each particle's max |r|^2; a pixel table holds each pixel's constants;
 //   * fast path (k_sweep, particles whose arrival times provably increase): for each pixel the grid
@@ -28,9 +28,9 @@
 // same operations (tau_eval), and the field with one function, so a contribution's bits do not
 // depend on the path that finds it.  LW_CULL asks for what the fast path does anyway.
 //
-// Arrival-time forms (exact geometry): the polynomial records hold the path term's series
+// Arrival-time forms (exact geometry): the polynomials in the pixel variable b hold the path term's series
 // (first order with single-precision fields, third order with double ones; valid where
-// |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory) for pixels at the records' distance
+// |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory) for pixels at the reference distance
 // (|x_m| of the first pixel), evaluated to a lower degree where the terms above it are provably
 // negligible for the particle and the tile's pixels (kModeRecLow); a tile whose pixels
 // sit at another distance, or a particle outside the series bound, evaluates arrival_tau per
@@ -80,12 +80,12 @@ constexpr int kPT = 16;
 constexpr int64_t kPixTabMax = 16384;
 static_assert(kPixTabMax % kTilePix == 0, "whole tiles per pixel pass");
 
-// scan modes: polynomial records (degree 3 or 5 in b, exact geometry), far field (tau = d + b),
+// scan modes: polynomials (degree 3 or 5 in b, exact geometry), far field (tau = d + b),
 // or arrival_tau per pixel in one of its forms
 constexpr int kModeRec3 = 0, kModeRec5 = 1, kModeFar = 2;
 // arrival_tau per pixel with the form of each pixel (series where rb2 |x_m|^-2 <= kSeriesBound)
 constexpr int kModeMixed = 6;
-// polynomial records evaluated to a lower degree (RecLayout::LOW: 2 of 3 with single-precision
+// polynomials evaluated to a lower degree (RecLayout::LOW: 2 of 3 with single-precision
 // fields, 3 of 5 with double ones) where tail_negligible holds for the particle and the tile
 constexpr int kModeRecLow = 7;
 
@@ -127,7 +127,7 @@ __device__ __forceinline__ double uniform_double(double v)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// The records are written by the pre-pass launch and only read while the deposit kernel runs, so
+// The arrival bases are written by an earlier launch and only read while the deposit kernel runs, so
 // a wavefront-uniform sample's is read through the constant address space: with the address in
 // scalar registers these become scalar loads.
 typedef const __attribute__((address_space(4))) double *cdptr;
@@ -203,7 +203,7 @@ __device__ __forceinline__ PixC pixc_row(P row)
 
 // The values of a sample that a scan mode's arrival time takes (N of them; X: offset of the position):
 //   far field:             d, x, y, z
-//   polynomial records:    c_0 .. c_{DEG-1}, x, y, z (the leading coefficient is the same for every sample)
+//   polynomials:           c_0 .. c_{DEG-1}, x, y, z (the leading coefficient is the same for every sample)
 //   kModeMixed:            x, y, z, d
 template <int GEOM, bool F64, int MODE>
 struct ScanVals {
@@ -232,7 +232,7 @@ __device__ __forceinline__ void scan_vals(double d, double x, double y, double z
 }
 
 // Arrival time of one (sample, pixel) in scan mode MODE from the sample's values v (scan_vals) and the
-// pixel constants P: far field tau = d + b; polynomial records tau = sum_j c_j b^j (c_DEG = cK; up to
+// pixel constants P: far field tau = d + b; polynomials tau = sum_j c_j b^j (c_DEG = cK; up to
 // j = LOW in kModeRecLow); else
 // arrival_tau in the pixel's form (series where rb2 |x_m|^-2 <= kSeriesBound).  A (sample, pixel)
 // gets the same bits wherever it is evaluated.
@@ -304,9 +304,10 @@ __host__ __device__ __forceinline__ int *dense_flag(double *pt) { return (int *)
 
 // ---------------------------------------------------------------------------------------------
 // pre-pass: one block per (particle, chunk of samples): arrival bases, per-particle max |r|^2 and the flags: 1 for the
-// careful path, 2 for a dense particle (k_gather, where x_mid is given), 0 for k_sweep.  Bound by memory: 72 bytes of a sample read, 8 written (with the polynomial's coefficients
-// and the position stored beside the base, 64 or 80 written, the pre-pass of 2000 x 20001 samples took
-// 1.75 ms; the coefficients are formed where a step's samples are staged instead)
+// careful path, 2 for a dense particle (k_gather, where x_mid is given), 0 for k_sweep.  Bound by memory: 72 bytes of a
+// sample read, 8 written (with the polynomial's coefficients and the position stored beside the base, 64 or 80 written,
+// the pre-pass of 2000 x 20001 samples took 1.75 ms, now 0.79; the coefficients are formed where a step's samples are
+// staged instead)
 __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, const double *__restrict__ beta,
                                                  const double *__restrict__ beta_dot, int64_t n_samples, int chunk,
                                                  int64_t sample0, double t_start, double dt, double t0,
@@ -432,8 +433,8 @@ struct Wave {
     const double *__restrict__ pt;    // pixel table of this pass
     T *__restrict__ E;
     DepShape sh;
-    double cK;   // leading coefficient of the polynomial records
-    double Dref; // the records' pixel distance
+    double cK;   // leading coefficient of the polynomials
+    double Dref; // the polynomials' pixel distance
     double rb2;  // the current particle's bound of |r|^2 over its whole trajectory
     int lane;
     int64_t tile, k0;
@@ -445,7 +446,7 @@ struct Wave {
 
     __device__ __forceinline__ static uint32_t qwrap(uint32_t v) { return v >= kQCap ? v - kQCap : v; }
 
-    // Arrival time of pixel h from the scan values v of a sample's record (wavefront-uniform)
+    // Arrival time of pixel h from the scan values v of a sample (wavefront-uniform)
     template <int MODE>
     __device__ __forceinline__ double tau_of(int h, const double *v) const
     {
@@ -656,7 +657,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
     int64_t m[kPPL];
     bool pix_in[kPPL], lane_ok[kPPL];
     double id2 = 0.0, s2 = 0.0;
-    const double Dref = pix_geo(x_det, 0).D;  // the records' pixel distance
+    const double Dref = pix_geo(x_det, 0).D;  // the polynomials' pixel distance
     bool far_off = false;                     // a pixel of this wavefront at another distance
 #pragma unroll
     for (int h = 0; h < kPPL; ++h) {
@@ -755,6 +756,9 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 // a step wait for the next one where that completes their 64 bytes, which is what the second half of the ring is
 // for: 12.8 to a request.  2000 x 20001 samples, 4096 pixels, mixed: 51.3 -> 34.5 ms,
 // 6.4e8 requests; with whole requests per wavefront (lanes idle where a step starts or ends inside one) the same.
+// The ring's 512 samples (as many as two blocks a compute unit have LDS for) in three steps of 170 intervals or four of
+// 127 hold points back longer: 6.15e8 requests, but the steps' own work is there 1.5 or 2 times, 38.7 and 46.1 ms of
+// the whole deposit and spectrum instead of 37.6.  (Pixels on the axis have 5 points in 255 intervals.)
 template <typename T>
 struct SweepCfg {
     static constexpr int NT = sizeof(T) == 8 ? 128 : 256;  // samples of a step, neighbouring steps sharing one
@@ -1160,7 +1164,7 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     if (tid < 4) lds.red[tid] = 0ull;
     const int64_t m = tile * kTilePix + p;
     const bool pix_in = m < sh.n_pix;
-    const double Dref = pix_geo(x_det, 0).D;  // the records' pixel distance
+    const double Dref = pix_geo(x_det, 0).D;  // the polynomials' pixel distance
     bool lane_ok, far_off = false;
     double id2 = 0.0, s2 = 0.0;
     {
@@ -1639,7 +1643,7 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
     const int64_t n_chunks_s = (ns + kPrepassChunk - 1) / kPrepassChunk;
     if (n_chunks_s > 65535) return fail(LW_E_SHAPE, "lw_deposit_td: too many samples");
     // pixel passes of at most kPixTabMax pixels (the pixel table's share of the workspace); each
-    // pass is a deposit of its own pixels (records take the pass's first pixel as reference)
+    // pass is a deposit of its own pixels (its first pixel is the reference)
     for (int64_t m0 = 0; m0 < n_pix; m0 += kPixTabMax) {
         const int64_t npx = std::min<int64_t>(kPixTabMax, n_pix - m0);
         const double *xd = gr->x_det + 3 * m0;

@@ -16,9 +16,9 @@
 // arrival time (a DPP lane shift).  Those intervals are queued in LDS and evaluated 64 at a time,
 // one per lane (fields at both ends, the adjoint, the field and arrival-time Jacobians); the
 // results go to LDS accumulators of the wavefront's samples, written out once at the end.  Arrival
-// times are those of the FP64 deposit: for a chunk of pixels all at the records' distance and
+// times are those of the FP64 deposit: for a chunk of pixels all at the reference distance and
 // in the series range (the particle's max |r|^2 over its whole trajectory <= 1e-8 |x_m|^2) the
-// records' polynomial in b (coefficients from the lane's sample), else per pixel the compensated
+// polynomial in b (coefficients from the lane's sample), else per pixel the compensated
 // base d plus the pixel terms with the path term as its third-order series in that range, else
 // its square root form.
 #include "lw_internal.h"
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64) void k_deposit_bwd(const double *__restrict__ r
     const double rb2 = rbound2[k];
     const double q = charge ? charge[k] : -kQe;
     const double nob = (double)sh.n_obs, nob2 = nob - 2.0;
-    // the FP64 deposit's records: tau(b) as a polynomial of degree 5 for pixels at the distance
+    // the FP64 deposit's form: tau(b) as a polynomial of degree 5 for pixels at the distance
     // of pixel 0, its coefficients from this lane's sample (the same function and inputs as the
     // deposit's pre-pass, so the same bits of tau where both use them)
     const double Dref = GEOM == LW_GEOM_EXACT ? pix_geo(x_det, 0).D : 1.0;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(64) void k_deposit_bwd(const double *__restrict__ r
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const int cnt = (int)std::min<int64_t>(64, sh.n_pix - m0);
-        // the records apply to this chunk of pixels if every pixel is at the reference distance
+        // the polynomials apply to this chunk of pixels if every pixel is at the reference distance
         // and in the series range of this particle (the deposit's rule for its tiles)
         bool rec_chunk = false, rec_low = false;
         if (GEOM == LW_GEOM_EXACT) {

@@ -269,7 +269,7 @@ static lw_status deposit_entry(const char *fn, const lw_traj_t *traj, const lw_g
         if (det) return launch_deposit_det(traj, grid, field_mask, g, (double *)E, diag, acc, ws, ws_bytes, stream);
         return launch_deposit_boris(traj, grid, prec, field_mask, gc, accum, E, diag, ws, ws_bytes, stream);
     }
-    // any workspace that holds one particle's records is accepted (the particles are then taken
+    // any workspace that holds one particle's arrival bases is accepted (the particles are then taken
     // in chunks); lw_workspace_bytes gives the size that takes them all at once
     const size_t need = deposit_ws_bytes(1, traj->n_samples);
     if (traj->n_particles > 0 && grid->n_pix > 0 && (!ws || ws_bytes < need))

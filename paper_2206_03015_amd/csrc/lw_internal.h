@@ -167,10 +167,10 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 
 // (|r|/|x|)^2 up to which the series forms of the exact-geometry arrival time are used
 constexpr double kSeriesBound = 1e-8;
-// pixels whose |x_m| is within this relative distance of the records' distance use the records
+// pixels whose |x_m| is within this relative distance of the reference distance use the polynomials
 // (tau_poly at that distance)
 constexpr double kSameDistance = 4.0 * 2.220446049250313e-16;
-// The polynomial records (tau_poly) are evaluated to a lower degree -- 2 of 3 with
+// The polynomials (tau_poly) are evaluated to a lower degree -- 2 of 3 with
 // single-precision fields, 3 of 5 with double ones -- where the terms left out stay within
 // kTailBound grid units for the particle's whole trajectory and the pixels of a 128-pixel tile:
 // 1e-7 (about the rounding of the single-precision interpolation weights), resp. 1e-12 (far
@@ -178,7 +178,7 @@ constexpr double kSameDistance = 4.0 * 2.220446049250313e-16;
 template <bool F64>
 constexpr double kTailBound = F64 ? 1e-12 : 1e-7;
 // Whether that holds for a particle with |r|^2 <= rb2 over its trajectory and pixels with
-// 2 (1 - n_z) <= s2 at the records' distance D: b = C (e_z - n) . r, so
+// 2 (1 - n_z) <= s2 at the reference distance D: b = C (e_z - n) . r, so
 // |b| <= C |e_z - n| |r| = C sqrt(2 (1 - n_z)) |r|.  Degree 3 (cK = K e): the cubic term K e b^3.
 // Degree 5 (cK = 7 K e^3 / 4): |c_4| <= 1.3 K e^2 within the series range (|r| <= 1e-4 D;
 // 1.251 K e^2 is its maximum there), and K e^2 = (4/7) cK C D, so
@@ -225,7 +225,7 @@ __device__ __forceinline__ double arrival_tau(const PixC &p, double d, double rx
     return tau;
 }
 
-// The series forms as polynomials in b for pixels at one distance D (the scan's records):
+// The series forms as polynomials in b for pixels at one distance D (the deposit's):
 // with s = z - b/C, |r_perp|^2 = (rho + 2 z' b - b^2)/C^2 (rho = C^2 (x^2 + y^2), z' = C z),
 // x = s/D = u - e b (u = z/D, e = 1/(C D)) and K = e/2,
 //   kTauShort:  corr = K P (1 + x)                                    (degree 3 in b)
@@ -484,7 +484,7 @@ DepositPre deposit_pre(void *ws, int64_t n_particles, int64_t n_samples, const l
 lw_status launch_deposit_det(const lw_traj_t *traj, const lw_grid_t *grid, int field_mask, int geom, double *E,
                              int64_t *diag, void *acc, void *ws, size_t ws_bytes, hipStream_t s);
 size_t det_acc_bytes(int64_t n_pix, int64_t n_obs);
-// workspace of a deposit launch that holds the records of all its particles (a smaller one makes
+// workspace of a deposit launch that holds the arrival bases of all its particles (a smaller one makes
 // it process the particles in chunks)
 size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples);
 lw_status launch_fft(const void *E, int64_t n_pix, int64_t n_obs, double dt_obs, int prec, void *S, void *ws,
