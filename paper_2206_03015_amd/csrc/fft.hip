@@ -1213,7 +1213,7 @@ __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type
 // pass C (k_bwd_cols_fast): the columns back, real and imaginary parts to the two packed components.
 //
 // Three reads and three writes of the traces' size, with nothing in LDS but a row: 256 pixels of 2^16 points in FP64
-// 1022 us with two LDS buffers, radix 4 and a sine/cosine pair per element of every pass -> 515 us.
+// 1022 us with two LDS buffers, radix 4 and a sine/cosine pair per element of every pass -> 510 us.
 template <typename T>
 __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_waves_per_eu(FastCfg<T>::kRowWaves))) void k_bwd_rows_fast(
     typename C2<T>::type *__restrict__ Y, const T *__restrict__ dS, FwdShape sh, T scale)
@@ -1225,6 +1225,7 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     constexpr int NT = L / R;
     __shared__ T2 buf[L + L / R];
     __shared__ T2 tab[tab_slots(tab_entries_rows<T>())];
+    __shared__ T2 tw[2][R];  // the rows' W_N^{NT r k}
     const int tid = threadIdx.x;
     const int N1 = 1 << sh.lg1;
     const int64_t N = (int64_t)1 << sh.lg, ldS = N / 2 + 1;
@@ -1236,7 +1237,9 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     const int ka = rp, kb = (N1 - rp) & (N1 - 1);
     const bool two = ka != kb, row0 = ka == 0;
     const int rho = row0 ? ((NT - tid) & (NT - 1)) : NT - 1 - tid;
+    const double inv_n = ldexp(1.0, -sh.lg);
     for (int q = tid; q < tab_entries_rows<T>(); q += NT) tab[tabi(q)] = twiddle<T2>(q, L);
+    if (tid < 2 * R) tw[tid >> LGR][tid & (R - 1)] = phasor_mod<T2>((int64_t)NT * (tid & (R - 1)) * (tid < R ? ka : kb), N, inv_n);
     __syncthreads();
     const T2 wa = tab[tabi(tid)], wb = row0 && tid == 0 ? twiddle<T2>(1, R) : tab[tabi(rho)];
     const AtRow<LGR> at;
@@ -1249,18 +1252,14 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
         d0[q] = h * dS[m0 * ldS + js];
         d1[q] = has1 ? h * dS[m1 * ldS + js] : (T)0;
     }
-    // inverse twiddles W_N^{-n2 k} of a row, n2 = tid + NT r: the conjugate of base step^r
-    const double inv_n = ldexp(1.0, -sh.lg);
-    const T2 base_a = phasor_mod<T2>((int64_t)tid * ka, N, inv_n), step_a = phasor_mod<T2>((int64_t)NT * ka, N, inv_n);
-    const T2 base_b = phasor_mod<T2>((int64_t)tid * kb, N, inv_n), step_b = phasor_mod<T2>((int64_t)NT * kb, N, inv_n);
-    auto store_row = [&](T2 *dst, const T2 *O, T2 base, T2 step) {  // conjugates of O times the forward twiddles
-        // opaque: the powers are formed per transform, not held in registers through the others
-        asm volatile("" : "+v"(step.x), "+v"(step.y));
-        T2 sp[R];
-        powers<R>(step, sp);
+    // inverse twiddles W_N^{-n2 k} of a row, n2 = tid + NT r: the conjugate of base tw[r].  tw is the block's, formed once
+    // (powers of a step multiplied up by every thread: 784 us instead of 779 at the size above, and an error of
+    // 9.1e-16 instead of 8.9e-16)
+    const T2 base_a = phasor_mod<T2>((int64_t)tid * ka, N, inv_n), base_b = phasor_mod<T2>((int64_t)tid * kb, N, inv_n);
+    auto store_row = [&](T2 *dst, const T2 *O, T2 base, const T2 *step) {  // conjugates of O times the forward twiddles
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            T2 v = cmul(O[r], r ? cmul(base, sp[r < 1 ? 1 : r]) : base);
+            T2 v = cmul(O[r], r ? cmul(base, step[r]) : base);
             v.y = -v.y;
             dst[tid + NT * r] = v;
         }
@@ -1308,12 +1307,12 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
         passes(A, u, two ? nullptr : after);
         asm volatile("" : "+v"(w0.x), "+v"(w0.y));
         last_pass_w<LGR, LGL>(buf, at, u, w0, O);
-        store_row(Y + (pl * 3 + t) * N + (int64_t)ka * L, O, base_a, step_a);
+        store_row(Y + (pl * 3 + t) * N + (int64_t)ka * L, O, base_a, tw[0]);
         if (two) {
             passes(B, v, after);
             asm volatile("" : "+v"(w0.x), "+v"(w0.y));
             last_pass_w<LGR, LGL>(buf, at, u, w0, O);
-            store_row(Y + (pl * 3 + t) * N + (int64_t)kb * L, O, base_b, step_b);
+            store_row(Y + (pl * 3 + t) * N + (int64_t)kb * L, O, base_b, tw[1]);
         }
     }
 }
