@@ -1155,10 +1155,29 @@ __global__ __launch_bounds__(256) void k_fft_rows_bwd(typename C2<T>::type *__re
     }
 }
 
+// The adjoint's factor dt_obs^2 / pi, applied where dE is stored.  In single precision as two factors, since it is a
+// denormal float for grid steps below 1.9e-19 s (1.2e-42 for the precision workload's 1.9e-21 s: ten bits, and fewer in
+// a product with dS); a gradient that is a normal number then is one after each factor.
+template <typename T>
+struct BwdScale {
+    T a, b;
+    explicit BwdScale(double dt_obs)
+    {
+        if constexpr (sizeof(T) == 4) {
+            a = (T)dt_obs;
+            b = (T)(dt_obs / kPi);
+        } else {
+            a = dt_obs * dt_obs / kPi;
+            b = 1.0;
+        }
+    }
+    __device__ __forceinline__ T operator()(T v) const { return sizeof(T) == 4 ? b * (a * v) : a * v; }
+};
+
 // pass C: inverse column transforms; real / imaginary parts are the two packed components of dE
 template <typename T>
 __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type *__restrict__ Y, T *__restrict__ dE,
-                                                      FftShape sh, T scale)
+                                                      FftShape sh, BwdScale<T> scale)
 {
     using T2 = typename C2<T>::type;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1198,8 +1217,8 @@ __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type
         const int n1 = idx / C, cc = idx - n1 * C;
         const T2 v = res[cc * N1 + n1];
         const int64_t n = (int64_t)n1 * N2 + c0 + cc;
-        re[n] = scale * v.x;
-        if (im) im[n] = -scale * v.y;
+        re[n] = scale(v.x);
+        if (im) im[n] = -scale(v.y);
     }
 }
 
@@ -1208,7 +1227,7 @@ __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type
 //
 // pass B' (k_bwd_rows_fast): a row pair (k1, N1 - k1) of the three packed transforms per block, in place: the
 // forward row passes leave the pair's outputs in registers with their partners (as in pass B), the product with
-// h dS is formed there, and since a thread holds elements u + NT m of a row it is the input of the inverse
+// h dS is formed there (no scale: see BwdScale), and since a thread holds elements u + NT m of a row it is the input of the inverse
 // passes' first one.  The pair's L values of dS per pixel serve all three transforms.
 // pass C (k_bwd_cols_fast): the columns back, real and imaginary parts to the two packed components.
 //
@@ -1216,7 +1235,7 @@ __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type
 // 1022 us with two LDS buffers, radix 4 and a sine/cosine pair per element of every pass -> 510 us.
 template <typename T>
 __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_waves_per_eu(FastCfg<T>::kRowWaves))) void k_bwd_rows_fast(
-    typename C2<T>::type *__restrict__ Y, const T *__restrict__ dS, FwdShape sh, T scale)
+    typename C2<T>::type *__restrict__ Y, const T *__restrict__ dS, FwdShape sh)
 {
     using T2 = typename C2<T>::type;
     using Cfg = FastCfg<T>;
@@ -1243,12 +1262,12 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     __syncthreads();
     const T2 wa = tab[tabi(tid)], wb = row0 && tid == 0 ? twiddle<T2>(1, R) : tab[tabi(rho)];
     const AtRow<LGR> at;
-    // scale h dS of output tid + NT q of row ka and its partner
+    // h dS of output tid + NT q of row ka and its partner
     T d0[R], d1[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         const int64_t j = ka + ((int64_t)(tid + NT * q) << sh.lg1), js = j < N - j ? j : N - j;
-        const T h = (js == 0 || js == N / 2) ? scale : (T)0.5 * scale;
+        const T h = (js == 0 || js == N / 2) ? (T)1 : (T)0.5;
         d0[q] = h * dS[m0 * ldS + js];
         d1[q] = has1 ? h * dS[m1 * ldS + js] : (T)0;
     }
@@ -1319,7 +1338,8 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
 
 // pass C: C = 2^LGC adjacent columns of one packed transform of one pixel pair per block
 template <typename T, int LG1>
-__global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::type *__restrict__ Y, T *__restrict__ dE, FwdShape sh)
+__global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::type *__restrict__ Y, T *__restrict__ dE, FwdShape sh,
+                                                       BwdScale<T> scale)
 {
     using T2 = typename C2<T>::type;
     constexpr int LGET = cols_lget<T>(LG1), ET = 1 << LGET;
@@ -1363,8 +1383,8 @@ __global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::typ
 #pragma unroll
     for (int r = 0; r < ET; ++r) {
         const int n = ((g + TPC * r) << sh.lg2) + n2;
-        re[n] = O[r].x;
-        if (im) im[n] = -O[r].y;
+        re[n] = scale(O[r].x);
+        if (im) im[n] = -scale(O[r].y);
     }
 }
 
@@ -1399,7 +1419,7 @@ ColsKernel<T> pick_cols_fast(int lg1)
 }
 
 template <typename T>
-using ColsBwdKernel = void (*)(const typename C2<T>::type *, T *, FwdShape);
+using ColsBwdKernel = void (*)(const typename C2<T>::type *, T *, FwdShape, BwdScale<T>);
 template <typename T, int LG1>
 ColsBwdKernel<T> pick_cols_bwd(int lg1)
 {
@@ -1461,6 +1481,7 @@ lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, dou
     using T2 = typename C2<T>::type;
     using Cfg = FwdCfg<T>;
     const int lg = ilog2(n_obs);
+    const BwdScale<T> scale(dt_obs);
     // the forward path's shapes, where its columns have a compile-time pass
     if (const ColsBwdKernel<T> inv = pick_cols_bwd<T, 1>(lg - Cfg::kLgRow)) {
         FwdShape f;
@@ -1479,9 +1500,8 @@ lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, dou
             f.pair0 = p0;
             f.nbatch = nb;
             cols<<<dim3(gx_c, 3, (unsigned)nb), 256, 0, s>>>(E, Y, f, (T)1);
-            k_bwd_rows_fast<T><<<(unsigned)((nb + 7) / 8 * 8 * gx_r), FastCfg<T>::kRowThreads, 0, s>>>(
-                Y, dS, f, (T)(dt_obs * dt_obs / kPi));
-            inv<<<dim3(gx_c, 3, (unsigned)nb), 256, 0, s>>>(Y, dE, f);
+            k_bwd_rows_fast<T><<<(unsigned)((nb + 7) / 8 * 8 * gx_r), FastCfg<T>::kRowThreads, 0, s>>>(Y, dS, f);
+            inv<<<dim3(gx_c, 3, (unsigned)nb), 256, 0, s>>>(Y, dE, f, scale);
         }
         return check_launch("lw_spectrum_fft_bwd");
     }
@@ -1508,7 +1528,6 @@ lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, dou
     const int64_t pairs = (n_pix + 1) / 2;
     const int64_t batch = std::min<int64_t>({pairs, (int64_t)(ws_bytes / per_pair_bytes<T>(n_obs)), kMaxGridYZ});
     T2 *Y = (T2 *)ws;
-    const T scale = (T)(dt_obs * dt_obs / kPi);
     for (int64_t p0 = 0; p0 < pairs; p0 += batch) {
         const int64_t nb = std::min(batch, pairs - p0);
         sh.pair0 = p0;
