@@ -428,7 +428,11 @@ __device__ __forceinline__ double div_by(double a, double b, double y)
     return fma(fma(-b, q, a), y, q);
 }
 
-// One step of the pusher (push_step's arithmetic and rounding) where u, the phase and the field are of
+// The phases that push_fast and tangent_step take: below 2^30 in carrier and envelope (phi / (2 n_cycles), the larger one
+// for less than half a cycle), with room for the rounding of a bound's sum.
+__device__ __forceinline__ double phase_bound(const PushConst &K) { return 0x1p29 * fmin(1.0, K.nc2); }
+
+// One step of the pusher (push_step's arithmetic and rounding) where u, the phase (phase_bound) and the field are of
 // moderate size: nothing here branches, so that the chain's dependent sequences (the field's sines, cosines and
 // exponential, the roots and quotients) overlap as far as they can.  Returns u at the sample.
 template <bool PAIR>
@@ -713,7 +717,9 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
         const double lim = kPi * L.nc, far = lim + 2.01 * S * fabs(L.wl * dt) + 1e-6;
         double *ck_at = ck ? ck + k * ck_stride : nullptr;
         int64_t ck_next = seg / S - 1;  // the batch after which the next checkpoint falls
-        const bool moderate = far < 1e9 && fabs(L.e0_per_a0 * L.a0) < 1e100;
+        // a step's fast form needs the phases of the whole batch within its bound: far more than covers the batch's change
+        const double most = phase_bound(K) - far;
+        const bool moderate = fabs(L.e0_per_a0 * L.a0) < 1e100;
         for (int64_t b = 0; b < nb; ++b) {
             const int n = (int)std::min<int64_t>(S, n_span - b * S);
             row = lds.b.st[b & 1] + p * Lds::kPitch - (b == 0 ? 0 : 8);
@@ -739,7 +745,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                 } else {
                     for (int j = j0; j < n; ++j) coast();
                 }
-            } else if (moderate && __builtin_amdgcn_ballot_w64(!(phi0 < 1e9) || !(u2 < 1e200)) == 0) {
+            } else if (moderate && __builtin_amdgcn_ballot_w64(!(phi0 < most) || !(u2 < 1e200)) == 0) {
                 have_cg = false;
                 for (int j = j0; j < n; ++j) {
                     at += 1.0;
@@ -1013,8 +1019,9 @@ __device__ __forceinline__ double tangent_run(const LaserDev &L, const PushConst
     double acc = 0.0;
     const bool tame = S.uhx.v * S.uhx.v + S.uhy.v * S.uhy.v + S.uhz.v * S.uhz.v < 1e200 &&
                       S.usx.v * S.usx.v + S.usy.v * S.usy.v + S.usz.v * S.usz.v < 1e200 &&
-                      fabs(laser_phase(L, K, S.z.v, t_start + (double)(s0 + i0) * dt)) < 1e8 &&
-                      2.01 * fabs(L.wl * dt) * (double)(i1 - i0) + kPi * L.nc < 1e8 && fabs(L.e0_per_a0 * L.a0) < 1e100;
+                      fabs(laser_phase(L, K, S.z.v, t_start + (double)(s0 + i0) * dt)) +
+                              2.01 * fabs(L.wl * dt) * (double)(i1 - i0) < phase_bound(K) &&
+                      fabs(L.e0_per_a0 * L.a0) < 1e100;
     if (__ballot(!tame) == 0) {
         // the gradients of kAhead samples are on their way while the kAhead before them are used: a step takes
         // less than a miss of their lines
