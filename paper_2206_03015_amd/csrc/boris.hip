@@ -331,9 +331,10 @@ __device__ __forceinline__ double sqrt_plain(double x)
     return x < 1e300 ? g : x;  // infinite (or not a number)
 }
 
-// the quotients' constants
+// the quotients' constants; tame: the beam radius's square and its reciprocal are of moderate size
 struct PushConst {
     double rc_c, nc2, rnc2, rnc, w02, rw02;
+    bool tame;
 };
 __device__ __forceinline__ PushConst push_const(const LaserDev &L)
 {
@@ -344,6 +345,7 @@ __device__ __forceinline__ PushConst push_const(const LaserDev &L)
     K.rnc = 1.0 / L.nc;
     K.w02 = L.w0 > 0.0 ? L.w0 * L.w0 : 1.0;
     K.rw02 = 1.0 / K.w02;
+    K.tame = K.w02 > 1e-100 && K.w02 < 1e100;
     return K;
 }
 
@@ -363,14 +365,14 @@ __device__ __forceinline__ double laser_phase(const LaserDev &L, const PushConst
     return L.wl * (t + div_const(z, kC, K.rc_c));
 }
 
-// laser_eb's field E_x (B_y = -E_x / c)
+// laser_eb's field E_x (B_y = -E_x / c), for any parameters
 template <bool PAIR>
 __device__ __forceinline__ double laser_ex(const LaserDev &L, const PushConst &K, double x, double y, double z, double t,
                                            bool odd)
 {
     const double phi = laser_phase(L, K, z, t);
     if (!(fabs(phi) < kPi * L.nc)) return 0.0;
-    const double half = div_const(phi, K.nc2, K.rnc2);
+    const double half = phi / K.nc2;
     double sh, ch, sp, cp;
     if constexpr (PAIR) {
         double sn, cs;
@@ -384,10 +386,10 @@ __device__ __forceinline__ double laser_ex(const LaserDev &L, const PushConst &K
         ::sincos(phi, &sp, &cp);
     }
     const double g = ch * ch;
-    const double gp = -div_const(sh * ch, L.nc, K.rnc);
+    const double gp = -(sh * ch / L.nc);
     const double dS = gp * sp + g * cp;
     double T = 1.0;
-    if (L.w0 > 0.0) T = ::exp(-div_const(x * x + y * y, K.w02, K.rw02));
+    if (L.w0 > 0.0) T = ::exp(-((x * x + y * y) / (L.w0 * L.w0)));
     return -(L.e0_per_a0 * (L.a0 * T * dS));
 }
 
@@ -432,8 +434,8 @@ __device__ __forceinline__ double div_by(double a, double b, double y)
 // for less than half a cycle), with room for the rounding of a bound's sum.
 __device__ __forceinline__ double phase_bound(const PushConst &K) { return 0x1p29 * fmin(1.0, K.nc2); }
 
-// One step of the pusher (push_step's arithmetic and rounding) where u, the phase (phase_bound) and the field are of
-// moderate size: nothing here branches, so that the chain's dependent sequences (the field's sines, cosines and
+// One step of the pusher (push_step's arithmetic and rounding) where u, the phase (phase_bound), the beam radius and the
+// field are of moderate size: nothing here branches, so that the chain's dependent sequences (the field's sines, cosines and
 // exponential, the roots and quotients) overlap as far as they can.  Returns u at the sample.
 template <bool PAIR>
 __device__ __forceinline__ void push_fast(const LaserDev &L, const PushConst &K, double t_next, double dt, bool odd, double &x,
@@ -719,7 +721,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
         int64_t ck_next = seg / S - 1;  // the batch after which the next checkpoint falls
         // a step's fast form needs the phases of the whole batch within its bound: far more than covers the batch's change
         const double most = phase_bound(K) - far;
-        const bool moderate = fabs(L.e0_per_a0 * L.a0) < 1e100;
+        const bool moderate = K.tame && fabs(L.e0_per_a0 * L.a0) < 1e100;
         for (int64_t b = 0; b < nb; ++b) {
             const int n = (int)std::min<int64_t>(S, n_span - b * S);
             row = lds.b.st[b & 1] + p * Lds::kPitch - (b == 0 ? 0 : 8);
@@ -1021,7 +1023,7 @@ __device__ __forceinline__ double tangent_run(const LaserDev &L, const PushConst
                       S.usx.v * S.usx.v + S.usy.v * S.usy.v + S.usz.v * S.usz.v < 1e200 &&
                       fabs(laser_phase(L, K, S.z.v, t_start + (double)(s0 + i0) * dt)) +
                               2.01 * fabs(L.wl * dt) * (double)(i1 - i0) < phase_bound(K) &&
-                      fabs(L.e0_per_a0 * L.a0) < 1e100;
+                      K.tame && fabs(L.e0_per_a0 * L.a0) < 1e100;
     if (__ballot(!tame) == 0) {
         // the gradients of kAhead samples are on their way while the kAhead before them are used: a step takes
         // less than a miss of their lines

@@ -1,5 +1,6 @@
 """The pusher and its tangents at the ends of the range that their fast step takes (phases below 2^30 in carrier and
-envelope), with a particle beside one in the pulse that lies in or outside it.  A particle's samples are the same bits whichever step pushes it; tolerances
+envelope, beam radii whose squares are finite), with a particle beside one in the pulse, or a beam radius, that lies
+in or outside it.  A particle's samples are the same bits whichever step pushes it; tolerances
 against the oracle as in test_gpu_boris_push.py."""
 import numpy as np
 import pytest
@@ -49,3 +50,31 @@ def test_a_distant_particle_beside_one_in_the_pulse(n_cycles, phase):
     assert float((gi[:1] - hi).abs().max()) <= 1e-12 * float(hi.abs().max())
     assert float((ga[:1] - ha).abs().max()) <= 1e-12 * float(ha.abs().max())
     assert bool(torch.isfinite(gi).all()) and bool(torch.isfinite(ga).all())
+
+
+@pytest.mark.parametrize("w0", [1e51, 1e160, 9e299])
+def test_a_beam_so_wide_that_its_square_overflows_is_a_plane_wave(w0):
+    from paper_2206_03015_amd import lw
+    ns, dt = 300, 0.02 * LAM / inputs.C_LIGHT
+    init = electrons(33)
+    args, plane = [(ns, -0.1 * dt * ns, dt, A0, LAM, w, 20.0) for w in (w0, 0.0)]
+    got, ref = lw.trajectory_boris(T(init), *args), lw.trajectory_boris(T(init), *plane)
+    for a, b in zip(got, ref):
+        assert torch.equal(a, b)
+    g = [torch.randn((33, ns, 3), dtype=torch.float64, device=DEV, generator=torch.Generator(DEV).manual_seed(c))
+         for c in range(3)]
+    for a, b in zip(lw.trajectory_boris_bwd(T(init), *args, *g), lw.trajectory_boris_bwd(T(init), *plane, *g)):
+        assert float((a - b).abs().max()) <= 1e-12 * float(b.abs().max())
+
+
+@pytest.mark.parametrize("w0", [1e-60, 1e-160])
+def test_a_beam_of_no_width_reaches_nobody(w0):
+    """Off the axis the field is exp(-huge) = 0: straight lines, whatever the size of the radius's square."""
+    from paper_2206_03015_amd import lw
+    ns, dt = 300, 0.02 * LAM / inputs.C_LIGHT
+    init = electrons(33)
+    r, b, bd = lw.trajectory_boris(T(init), ns, -0.1 * dt * ns, dt, A0, LAM, w0, 20.0)
+    u = T(init[:, 3:])
+    beta = u / torch.sqrt(1 + (u * u).sum(1, keepdim=True))
+    assert float(bd.abs().max()) == 0.0
+    assert float((b - beta[:, None]).abs().max()) <= 1e-15
