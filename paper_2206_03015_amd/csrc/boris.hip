@@ -318,7 +318,7 @@ __device__ __forceinline__ double div_plain(double a, double b)
     const double q = a * y;
     return __builtin_amdgcn_div_fixup(fma(fma(-b, q, a), y, q), b, a);
 }
-// sqrt(x) for x >= 1
+// sqrt(x) for 1e-200 < x < 1e300
 __device__ __forceinline__ double sqrt_plain(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
@@ -327,8 +327,7 @@ __device__ __forceinline__ double sqrt_plain(double x)
     g = fma(g, r, g);
     h = fma(h, r, h);
     g = fma(fma(-g, g, x), h, g);
-    g = fma(fma(-g, g, x), h, g);
-    return x < 1e300 ? g : x;  // infinite (or not a number)
+    return fma(fma(-g, g, x), h, g);
 }
 
 // the quotients' constants; tame: the beam radius's square and its reciprocal are of moderate size
@@ -391,22 +390,6 @@ __device__ __forceinline__ double laser_ex(const LaserDev &L, const PushConst &K
     double T = 1.0;
     if (L.w0 > 0.0) T = ::exp(-((x * x + y * y) / (L.w0 * L.w0)));
     return -(L.e0_per_a0 * (L.a0 * T * dS));
-}
-
-// kick, with the quotients and the square root of this kernel
-__device__ __forceinline__ void kick_plain(double &ux, double &uy, double &uz, double Ex, double By, double h)
-{
-    const double q = -kQe, m = kMe;
-    const double a = q * h / (2.0 * m * kC);
-    const double mx = ux + a * Ex, my = uy, mz = uz;
-    const double gm = sqrt_plain(1.0 + (mx * mx + my * my + mz * mz));
-    const double ty = div_plain((q * h / (2.0 * m)) * By, gm);
-    const double sy = div_plain(2.0 * ty, 1.0 + ty * ty);
-    const double px = mx - mz * ty, pz = mz + mx * ty;
-    const double nx = mx - pz * sy, nz = mz + px * sy;
-    ux = nx + a * Ex;
-    uy = my;
-    uz = nz;
 }
 
 // sqrt(x) for x >= 1 and finite, as sqrt_plain, and 1/sqrt(x) from the same iteration
@@ -685,7 +668,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
             uhy = usy = in0[4];
             uhz = usz = in0[5];
             Ex = laser_ex<PAIR>(L, K, x, y, z, t_start, odd);
-            kick_plain(uhx, uhy, uhz, Ex, -div_const(Ex, kC, K.rc_c), 0.5 * dt);
+            kick<double>(uhx, uhy, uhz, Ex, -(Ex / kC), 0.5 * dt);
         } else {
             x = st[0];
             y = st[1];
@@ -728,7 +711,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
             const int j0 = b == 0 ? 1 : 0;
             // one kind of step for the whole batch and wavefront
             const double phi0 = fabs(L.wl * fma(z, K.rc_c, t_start + at * dt));
-            const double u2 = uhx * uhx + uhy * uhy + uhz * uhz;
+            const double u2 = uhx * uhx + uhy * uhy + uhz * uhz, rho2 = x * x + y * y;
             if (__builtin_amdgcn_ballot_w64(!(phi0 > far) || !(have_cg || u2 < 1e200)) == 0) {
                 // no field on the way: the kick changes nothing, u at the sample is u half a step later
                 if (!have_cg) cg = div_plain(kC * dt, sqrt_plain(1.0 + u2));
@@ -747,7 +730,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                 } else {
                     for (int j = j0; j < n; ++j) coast();
                 }
-            } else if (moderate && __builtin_amdgcn_ballot_w64(!(phi0 < most) || !(u2 < 1e200)) == 0) {
+            } else if (moderate && __builtin_amdgcn_ballot_w64(!(phi0 < most) || !(u2 + rho2 < 1e200)) == 0) {
                 have_cg = false;
                 for (int j = j0; j < n; ++j) {
                     at += 1.0;
@@ -759,13 +742,13 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                 have_cg = false;
                 for (int j = j0; j < n; ++j) {
                     at += 1.0;
-                    cg = div_plain(kC * dt, sqrt_plain(1.0 + (uhx * uhx + uhy * uhy + uhz * uhz)));
+                    cg = (kC * dt) / sqrt(1.0 + (uhx * uhx + uhy * uhy + uhz * uhz));
                     x = x + cg * uhx;
                     y = y + cg * uhy;
                     z = z + cg * uhz;
                     double nx = uhx, ny = uhy, nz = uhz;
                     Ex = laser_ex<PAIR>(L, K, x, y, z, t_start + at * dt, odd);
-                    kick_plain(nx, ny, nz, Ex, -div_const(Ex, kC, K.rc_c), dt);
+                    kick<double>(nx, ny, nz, Ex, -(Ex / kC), dt);
                     row += 8;
                     put(0.5 * (uhx + nx), 0.5 * (uhy + ny), 0.5 * (uhz + nz), Ex);
                     uhx = nx;
@@ -1019,7 +1002,7 @@ __device__ __forceinline__ double tangent_run(const LaserDev &L, const PushConst
 {
     using D = Dual<1>;
     double acc = 0.0;
-    const bool tame = S.uhx.v * S.uhx.v + S.uhy.v * S.uhy.v + S.uhz.v * S.uhz.v < 1e200 &&
+    const bool tame = S.x.v * S.x.v + S.y.v * S.y.v < 1e200 && S.uhx.v * S.uhx.v + S.uhy.v * S.uhy.v + S.uhz.v * S.uhz.v < 1e200 &&
                       S.usx.v * S.usx.v + S.usy.v * S.usy.v + S.usz.v * S.usz.v < 1e200 &&
                       fabs(laser_phase(L, K, S.z.v, t_start + (double)(s0 + i0) * dt)) +
                               2.01 * fabs(L.wl * dt) * (double)(i1 - i0) < phase_bound(K) &&

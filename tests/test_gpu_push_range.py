@@ -1,6 +1,6 @@
 """The pusher and its tangents at the ends of the range that their fast step takes (phases below 2^30 in carrier and
-envelope, beam radii whose squares are finite), with a particle beside one in the pulse, or a beam radius, that lies
-in or outside it.  A particle's samples are the same bits whichever step pushes it; tolerances
+envelope, beam radii, momenta and positions whose squares are finite), with a particle beside one in the pulse, or a
+beam radius, that lies in or outside it.  A particle's samples are the same bits whichever step pushes it; tolerances
 against the oracle as in test_gpu_boris_push.py."""
 import numpy as np
 import pytest
@@ -78,3 +78,20 @@ def test_a_beam_of_no_width_reaches_nobody(w0):
     beta = u / torch.sqrt(1 + (u * u).sum(1, keepdim=True))
     assert float(bd.abs().max()) == 0.0
     assert float((b - beta[:, None]).abs().max()) <= 1e-15
+
+
+@pytest.mark.parametrize("component, value", [(5, 1e90), (5, 1e120), (5, 3e150), (3, -1e153), (0, 1e90), (0, 1e120), (1, -1e160)])
+def test_extreme_momenta_and_positions(component, value):
+    """One particle of 40 far beyond the others in one component (momenta: its gamma's square is still finite)."""
+    from paper_2206_03015_amd import lw
+    ns, dt = 300, 0.02 * LAM / inputs.C_LIGHT
+    init = electrons(40)
+    init[3, component] = value
+    args = (ns, -0.1 * dt * ns, dt, A0, LAM, 10e-6, 20.0)
+    got = [v.cpu().numpy() for v in lw.trajectory_boris(T(init), *args)]
+    ref = oracle.boris(init, *args)
+    rest = np.arange(40) != 3
+    for g, o, tol in zip(got, ref, (1e-12, 1e-12, 1e-9)):
+        assert np.max(np.abs(g[rest] - o[rest])) <= tol * np.max(np.abs(o[rest]))
+        for c in range(3):
+            assert np.max(np.abs(g[3, :, c] - o[3, :, c])) <= tol * max(np.max(np.abs(o[3, :, c])), np.max(np.abs(o[rest][..., c])))
