@@ -525,7 +525,7 @@ __device__ __forceinline__ float pulse_time(const double *__restrict__ init, int
 
 // idx[p], p < P: the block's particles (-1: none).  All threads of the block; ends with a barrier.
 template <int P, int NT>
-__device__ void push_select(const double *__restrict__ init, int64_t n_particles, int64_t kb, float early, PushSort &q, int *idx)
+__device__ void push_select(const double *__restrict__ init, int64_t n_particles, int64_t kb, float early, PushSort &q, int64_t *idx)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = (int)n_particles;
     float lo = 3e38f, hi = -3e38f;
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
         Lds b;
         PushSort q;
     } lds;
-    __shared__ int idx[P];
+    __shared__ int64_t idx[P];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t kb = (int64_t)blockIdx.x * P;
     bool ranked = false;
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
             push_select<P, 64 * (1 + NC)>(init, n_particles, kb, (float)(-kPi * L.nc / L.wl - t_start), lds.q, idx);
     }
     if (!ranked) {
-        if (threadIdx.x < P) idx[threadIdx.x] = kb + threadIdx.x < n_particles ? (int)(kb + threadIdx.x) : -1;
+        if (threadIdx.x < P) idx[threadIdx.x] = kb + threadIdx.x < n_particles ? kb + threadIdx.x : -1;
         __syncthreads();
     }
     const PushConst K = push_const(L);
@@ -815,7 +815,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                 Q.z = row[2];
                 if (!PRE || i < n_span) mx[g] = fmax(mx[g], fma(Q.z, Q.z, fma(Q.y, Q.y, Q.x * Q.x)));
                 if constexpr (OUT) {
-                    const int k = idx[p];
+                    const int64_t k = idx[p];
                     if constexpr (!PRE)
                         if (k < 0) continue;
                     Q.Ex = row[3];
@@ -858,7 +858,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
             for (int g = 0; g < NG; ++g) {
                 double m = mx[g];
                 for (int off = S / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-                const int k = idx[p0 + g * G];
+                const int64_t k = idx[p0 + g * G];
                 if (j == 0 && k >= 0) rmax2[k] = m;
             }
         }
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
                 const uint64_t m = __builtin_amdgcn_ballot_w64(bad[g]) >> (lane & ~(S - 1));
-                const int k = idx[p0 + g * G];
+                const int64_t k = idx[p0 + g * G];
                 if (j == 0 && k >= 0) pre.pflag[k] = (m & ((1ull << S) - 1)) != 0 ? 1 : 0;
             }
         }
