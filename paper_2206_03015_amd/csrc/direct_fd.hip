@@ -803,7 +803,11 @@ FdShape fd_shape(const lw_traj_t *t, const lw_grid_t *gr, int64_t n_omega, int f
     return sh;
 }
 
-// chunks of samples per group, so that about `rounds` times `resident` blocks run; returns the blocks (0: too many)
+// most (pixel, frequency tile) pairs, resp. chunks of 64 samples, of a launch: a grid's threads count in 32 bits (at
+// most 2^24 blocks of 256); more of them take several launches, a range of pixels resp. particles each
+constexpr int64_t kFdLaunch = int64_t(1) << 22;
+
+// chunks of samples per group, so that about `rounds` times `resident` blocks run; returns the blocks
 int64_t fd_groups(FdShape &sh, int64_t chunk, int64_t resident, int64_t rounds)
 {
     const int64_t base = sh.n_pix * sh.n_wblocks;
@@ -811,13 +815,21 @@ int64_t fd_groups(FdShape &sh, int64_t chunk, int64_t resident, int64_t rounds)
     const int64_t groups = std::max<int64_t>(1, std::min(units, resident * rounds / base));
     sh.parts_per_group = (units + groups - 1) / groups;
     sh.n_groups = (units + sh.parts_per_group - 1) / sh.parts_per_group;
-    const int64_t blocks = base * sh.n_groups;
-    return blocks > 0x7fffffff ? 0 : blocks;
+    return base * sh.n_groups;
+}
+
+// launch(n_pix, x_det, acc) for ranges of pixels (a pixel's sums: 6 n_omega doubles in either layout of acc)
+template <typename F>
+void fd_launches(const FdShape &sh, const double *x_det, double *acc, F launch)
+{
+    const int64_t most = std::max<int64_t>(1, kFdLaunch / sh.n_wblocks);
+    for (int64_t m0 = 0; m0 < sh.n_pix; m0 += most)
+        launch(std::min(most, sh.n_pix - m0), x_det + 3 * m0, acc + m0 * 6 * sh.n_omega);
 }
 
 // FP64 sums F_c(w), added into acc
-lw_status launch_sums64(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, FdShape sh, int geom, double *acc,
-                        hipStream_t s, const char *what)
+void launch_sums64(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, FdShape sh, int geom, double *acc,
+                   hipStream_t s)
 {
     // frequencies per block: one tile of 256, 512 or 1024
     const int W = sh.n_omega > 512 ? 4 : sh.n_omega > 256 ? 2 : 1;
@@ -826,20 +838,22 @@ lw_status launch_sums64(const lw_traj_t *t, const lw_grid_t *gr, const double *o
     // with 6 atomics per frequency)
     const int64_t units = sh.n_particles * ((sh.n_samples + kFdChunk - 1) / kFdChunk);
     const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(4, units * sh.n_pix * sh.n_wblocks / (512 * 8)));
-    const int64_t blocks = fd_groups(sh, kFdChunk, 512, rounds);
-    if (!blocks) return fail(LW_E_SHAPE, "%s: problem too large for one launch", what);
     auto go = [&](auto *k) {
-        k<<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
+        fd_launches(sh, gr->x_det, acc, [&](int64_t n_pix, const double *x_det, double *a) {
+            FdShape part = sh;
+            part.n_pix = n_pix;
+            const int64_t blocks = fd_groups(part, kFdChunk, 512, rounds);
+            k<<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, x_det, omega, a, part);
+        });
     };
     if (geom == LW_GEOM_EXACT)
         W == 4 ? go(k_direct_fd<LW_GEOM_EXACT, 4>) : W == 2 ? go(k_direct_fd<LW_GEOM_EXACT, 2>) : go(k_direct_fd<LW_GEOM_EXACT, 1>);
     else
         W == 4 ? go(k_direct_fd<LW_GEOM_FARFIELD, 4>) : W == 2 ? go(k_direct_fd<LW_GEOM_FARFIELD, 2>) : go(k_direct_fd<LW_GEOM_FARFIELD, 1>);
-    return LW_OK;
 }
 
 template <int GEOM, int K>
-lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, FdShape sh, double *acc, hipStream_t s)
+void launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, FdShape sh, double *acc, hipStream_t s)
 {
     // wavefronts per block: four where they all have frequencies (or nearly), else two or one
     const int64_t waves = (sh.n_omega + 64 * K - 1) / (64 * K);
@@ -848,27 +862,29 @@ lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *om
     // up to eight rounds of the resident blocks (two wavefronts per SIMD), of at least eight chunks each
     const int64_t units = sh.n_particles * ((sh.n_samples + 64 * W - 1) / (64 * W)), resident = 2048 / W;
     const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(8, units * sh.n_pix * sh.n_wblocks / (resident * 8)));
-    const int64_t blocks = fd_groups(sh, 64 * W, resident, rounds);
-    if (!blocks) return fail(LW_E_SHAPE, "lw_direct_fd: problem too large for one launch");
     auto go = [&](auto *k) {
-        k<<<(unsigned)blocks, 64 * W, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, sh);
+        fd_launches(sh, gr->x_det, acc, [&](int64_t n_pix, const double *x_det, double *a) {
+            FdShape part = sh;
+            part.n_pix = n_pix;
+            const int64_t blocks = fd_groups(part, 64 * W, resident, rounds);
+            k<<<(unsigned)blocks, 64 * W, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, x_det, omega, a, part);
+        });
     };
     W == 4 ? go(k_direct_fd_mixed<GEOM, K, 4>) : W == 2 ? go(k_direct_fd_mixed<GEOM, K, 2>) : go(k_direct_fd_mixed<GEOM, K, 1>);
-    return LW_OK;
 }
 
 // frequencies per lane: the largest power of two <= 8 that still fills a wavefront
 int fd_per_lane(int64_t n_omega) { return n_omega >= 64 * 8 ? 8 : n_omega >= 64 * 4 ? 4 : n_omega >= 64 * 2 ? 2 : 1; }
 
 template <int GEOM>
-lw_status launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, const FdShape &sh, double *acc,
-                       hipStream_t s)
+void launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, const FdShape &sh, double *acc,
+                  hipStream_t s)
 {
     switch (fd_per_lane(sh.n_omega)) {
-    case 8: return launch_mixed<GEOM, 8>(t, gr, omega, sh, acc, s);
-    case 4: return launch_mixed<GEOM, 4>(t, gr, omega, sh, acc, s);
-    case 2: return launch_mixed<GEOM, 2>(t, gr, omega, sh, acc, s);
-    default: return launch_mixed<GEOM, 1>(t, gr, omega, sh, acc, s);
+    case 8: launch_mixed<GEOM, 8>(t, gr, omega, sh, acc, s); break;
+    case 4: launch_mixed<GEOM, 4>(t, gr, omega, sh, acc, s); break;
+    case 2: launch_mixed<GEOM, 2>(t, gr, omega, sh, acc, s); break;
+    default: launch_mixed<GEOM, 1>(t, gr, omega, sh, acc, s);
     }
 }
 
@@ -883,11 +899,12 @@ lw_status launch_direct_fd(const lw_traj_t *t, const lw_grid_t *gr, const double
     k_fd_zero<<<(int)std::min<int64_t>((6 * nS + 255) / 256, 65536), 256, 0, s>>>(acc, 6 * nS);
     if (t->n_particles > 0 && t->n_samples > 0) {
         const FdShape sh = fd_shape(t, gr, n_omega, fmask);
-        const lw_status st = prec == LW_PREC_FP64 ? launch_sums64(t, gr, omega, sh, geom, acc, s, "lw_direct_fd")
-                             : geom == LW_GEOM_EXACT
-                                 ? launch_mixed<LW_GEOM_EXACT>(t, gr, omega, sh, acc, s)
-                                 : launch_mixed<LW_GEOM_FARFIELD>(t, gr, omega, sh, acc, s);
-        if (st != LW_OK) return st;
+        if (prec == LW_PREC_FP64)
+            launch_sums64(t, gr, omega, sh, geom, acc, s);
+        else if (geom == LW_GEOM_EXACT)
+            launch_mixed<LW_GEOM_EXACT>(t, gr, omega, sh, acc, s);
+        else
+            launch_mixed<LW_GEOM_FARFIELD>(t, gr, omega, sh, acc, s);
     }
     const double f = t->dt * t->dt / (2.0 * kPi);
     k_fd_finish<<<(int)std::min<int64_t>((nS + 255) / 256, 65536), 256, 0, s>>>(acc, S, nS, n_omega,
@@ -905,10 +922,8 @@ lw_status launch_direct_fd_bwd(const lw_traj_t *t, const lw_grid_t *gr, const do
     const int64_t nS = gr->n_pix * n_omega;
     k_fd_zero<<<(int)std::min<int64_t>((6 * nS + 255) / 256, 65536), 256, 0, s>>>(acc, 6 * nS);
     const FdShape sh = fd_shape(t, gr, n_omega, fmask);
-    const lw_status st = launch_sums64(t, gr, omega, sh, geom, acc, s, "lw_direct_fd_bwd");
-    if (st != LW_OK) return st;
-    const int64_t blocks = t->n_particles * ((t->n_samples + 63) / 64);
-    if (blocks > 0x7fffffff) return fail(LW_E_SHAPE, "lw_direct_fd_bwd: problem too large for one launch");
+    const int64_t chunks = (t->n_samples + 63) / 64, blocks = t->n_particles * chunks;
+    launch_sums64(t, gr, omega, sh, geom, acc, s);
     const double two_f = 2.0 * t->dt * t->dt / (2.0 * kPi);
     // pixels per block: a multiple of four (a wavefront each)
     const int64_t quads = (gr->n_pix + 3) / 4, share = std::max<int64_t>(1, std::min(quads, (kFdBwdBlocks + blocks - 1) / blocks));
@@ -916,8 +931,13 @@ lw_status launch_direct_fd_bwd(const lw_traj_t *t, const lw_grid_t *gr, const do
     sb.parts_per_group = (quads + share - 1) / share * 4;
     const int64_t ny = (gr->n_pix + sb.parts_per_group - 1) / sb.parts_per_group;
     auto *k = geom == LW_GEOM_EXACT ? k_direct_fd_bwd<LW_GEOM_EXACT> : k_direct_fd_bwd<LW_GEOM_FARFIELD>;
-    k<<<dim3((unsigned)blocks, (unsigned)ny), 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, gr->x_det, omega, acc, dS, d_r, d_beta,
-                                       d_beta_dot, sb, two_f);
+    const int64_t most = std::max<int64_t>(1, kFdLaunch / chunks);
+    for (int64_t k0 = 0; k0 < t->n_particles; k0 += most) {
+        const size_t o = (size_t)k0 * t->n_samples * 3;
+        k<<<dim3((unsigned)(std::min(most, t->n_particles - k0) * chunks), (unsigned)ny), 256, 0, s>>>(
+            t->r + o, t->beta + o, t->beta_dot + o, t->charge ? t->charge + k0 : nullptr, gr->x_det, omega, acc, dS, d_r + o,
+            d_beta + o, d_beta_dot + o, sb, two_f);
+    }
     return check_launch("lw_direct_fd_bwd");
 }
 
