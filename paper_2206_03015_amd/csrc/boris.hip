@@ -1221,7 +1221,18 @@ static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, dou
 
 lw_status launch_boris(const lw_traj_t *t, double *r, double *beta, double *beta_dot, hipStream_t s)
 {
-    return launch_push(t, 0, t->n_samples, nullptr, r, beta, beta_dot, nullptr, s, "lw_trajectory_boris");
+    // a grid counts its threads in 32 bits (three per particle): more particles take several launches
+    constexpr int64_t kMost = int64_t(1) << 28;
+    lw_traj_t part = *t;
+    for (int64_t k0 = 0; k0 < t->n_particles; k0 += kMost) {
+        part.n_particles = std::min(kMost, t->n_particles - k0);
+        part.init = t->init + 6 * k0;
+        const size_t o = (size_t)k0 * t->n_samples * 3;
+        const lw_status st = launch_push(&part, 0, t->n_samples, nullptr, r + o, beta + o, beta_dot + o, nullptr, s,
+                                         "lw_trajectory_boris");
+        if (st != LW_OK) return st;
+    }
+    return LW_OK;
 }
 
 lw_status launch_boris_rmax2(const lw_traj_t *t, double *rmax2, hipStream_t s)
