@@ -70,6 +70,8 @@ constexpr int kMaxPartsPerGroup = 64;  // at most a wavefront's lanes
 constexpr int64_t kFillBlocks = 2048;
 // particles per block of the careful path
 constexpr int kMaxPartsCareful = 4;
+// most particles, and particles times tiles, of a launch
+constexpr int64_t kMaxParticles = int64_t(1) << 23, kMaxUnits = int64_t(1) << 26;
 // samples per block of the pre-pass: at most kPrepassChunk, less where that leaves fewer than
 // kPrepassBlocks blocks (one electron of 20001 samples: 65 us in 3 blocks)
 constexpr int kPrepassChunk = 8192;
@@ -1632,8 +1634,11 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
         if (!accumulate) setup(nullptr, nullptr);
         return check_launch("deposit fill");
     }
-    // particles per launch: all of them, or as many as the workspace holds arrival bases for
-    int64_t chunk = n_p;
+    // particles per launch: all of them, or as many as the workspace holds arrival bases for and the grids
+    // reach: those count their threads in 32 bits (256 per particle in the pre-pass, 16 per particle and tile in
+    // k_careful, 8 per particle, tile and segment in k_sweep)
+    const int64_t most_tiles = (std::min<int64_t>(n_pix, kPixTabMax) + kTilePix - 1) / kTilePix;
+    int64_t chunk = std::min<int64_t>({n_p, kMaxParticles, std::max<int64_t>(1, kMaxUnits / most_tiles)});
     while (chunk > 1 && ws_bytes_for(chunk, ns) > ws_bytes) chunk = std::max<int64_t>(1, chunk / 2);
     if (ws_bytes_for(chunk, ns) > ws_bytes)
         return fail(LW_E_WORKSPACE, "lw_deposit_td: workspace of %zu bytes holds no particle (%zu needed)", ws_bytes,
@@ -1678,7 +1683,6 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             shc.parts_per_group = std::max<int64_t>(1, std::min<int64_t>(kMaxPartsCareful, units / kTargetBlocks));
             shc.n_groups = (np + shc.parts_per_group - 1) / shc.parts_per_group;
             const int64_t blocks_careful = (shc.n_groups + 7) / 8 * 8 * sh.n_tiles;
-            if (np > 0x7fffffff) return fail(LW_E_SHAPE, "lw_deposit_td: too many particles");
             if (std::max(blocks, blocks_careful) > 0x7fffffff)
                 return fail(LW_E_SHAPE, "lw_deposit_td: problem too large for one launch");
             const DepWs w = carve(ws, np);
