@@ -275,7 +275,10 @@ size_t lw_noalloc_scratch_bytes(void);
  * samples are skipped.  In the far field with the acceleration term only,
  * 2 eps0 c |x_m|^2 S is the right-hand side of Eq. inty_dft.
  * grid: x_det and t0 are used (dt_obs, n_obs ignored).  omega: [n_omega]
- * rad/s (device).  prec: FP64 = all double; MIXED = phase in double reduced
+ * rad/s (device).  prec: FP64 = all double (a list that is equally spaced to
+ * 4 x 2^-53 of the larger of each frequency and the centre of its block of 32 is
+ * summed as its line, block centres and multiples of the spacing, any other
+ * list as it stands); MIXED = phase in double reduced
  * to one revolution, sin/cos and the sums' terms in float, sums in double;
  * where each block of 512 consecutive frequencies is equally spaced (to 1e-13
  * relative), the phasors of 8 consecutive frequencies come from one float

@@ -92,7 +92,11 @@ __device__ __forceinline__ void stage_sample(const double *__restrict__ r, const
 // 20 x 2001 samples, 9 pixels, 1024 frequencies: 997 us with a sine/cosine pair per term -> 156 us (57 us of it
 // the matrix product at this card's FP64 rate, the rest the phasors and the exchange through LDS).
 constexpr int kFdBlk = 32;
-constexpr double kFdTol64 = 1e-15;  // a few roundings of a frequency: what the phase product's rounding is
+// How far a frequency may lie from its block's line, relative to the larger of it and the block's centre: 4 x 2^-53, what
+// the two or three roundings of lists made by linspace, arange or multiples of 2 pi / (N dt) come to
+// (3000 lists of each with 2 to 5000 entries: at most 3.99).  The line then stands for the list, so a phase is off by
+// up to as much of itself; a sine/cosine pair per term rounds it by 2.4 x 2^-53 (frequency / 2 pi, times t).
+constexpr double kFdTol64 = 4.0 * 0x1p-53;
 constexpr double kInv2Pi = 0.15915494309189535, kInv2PiLo = -9.839338337591243e-18;
 typedef double v4d __attribute__((ext_vector_type(4)));
 
