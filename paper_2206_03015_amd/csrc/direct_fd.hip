@@ -42,6 +42,7 @@ struct FdShape {
     int64_t n_groups, parts_per_group;  // groups of chunks of samples, chunks per group
     double t_start, dt, t0, inv_cdt, cdt;
     int fmask;
+    int flat;  // FP64 sums: chunks of several particles' samples
 };
 
 // how equal the spacing of a mixed wavefront's frequencies must be (relative) for the recurrence over
@@ -156,6 +157,7 @@ struct alignas(16) Fd64Lds {
             double l[kSub][kPitch], r[kSub][kPitchR];
         };
         double sum[kRows][kFdBlk];
+        double part[4][6][256];  // any frequencies: the wavefronts' sums
     };
 };
 
@@ -170,28 +172,41 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd(const double *__restrict__
     using Lds = Fd64Lds<W>;
     __shared__ Lds s;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    // equal spacing takes the blocks of blockIdx.y = 0 (which start first); with any other list a block takes 256 of the
+    // tile's frequencies
+    const int sub = blockIdx.y;
     const int64_t per_pix = sh.n_wblocks * sh.n_groups;
     const int64_t m = blockIdx.x / per_pix, rem = blockIdx.x - m * per_pix;
     const int64_t wb = rem / sh.n_groups, grp = rem - wb * sh.n_groups;
     const int64_t w0 = wb * 256 * W;
-    const int64_t upp = (sh.n_samples + kFdChunk - 1) / kFdChunk;  // chunks per particle
-    const int64_t u0 = grp * sh.parts_per_group, u1 = std::min(u0 + sh.parts_per_group, upp * sh.n_particles);
+    if (w0 + 256 * sub >= sh.n_omega) return;
+    // chunks of one particle, or (flat) of the samples of one particle after the other
+    const int64_t ns = sh.n_samples, upp = sh.flat ? 1 : (ns + kFdChunk - 1) / kFdChunk, all = sh.n_particles * ns;
+    const int64_t u0 = grp * sh.parts_per_group;
+    const int64_t u1 = std::min(u0 + sh.parts_per_group, sh.flat ? (all + kFdChunk - 1) / kFdChunk : upp * sh.n_particles);
     const PixGeo g = pix_geo(x_det, m);
     const double *xm = x_det + 3 * m;
     const int64_t left = sh.n_omega - w0;  // frequencies of the tile
     const double dw = fd_step(omega, sh.n_omega);
     // stage chunk u: arrival times and E kappa; returns its number of samples
     auto stage = [&](int64_t u) {
-        const int64_t k = u / upp, i0 = (u - k * upp) * kFdChunk;
+        int64_t k = u / upp, i0 = (u - k * upp) * kFdChunk, i = i0 + tid, end = ns - i0;
+        if (sh.flat) {
+            end = all - u * kFdChunk;
+            const int64_t at = u * kFdChunk + (tid < end ? tid : 0);
+            k = at / ns;
+            i = tid < end ? at - k * ns : ns;
+        }
         double ta, ex, ey, ez;
-        stage_sample<double, GEOM>(r, beta, beta_dot, g, xm, charge ? charge[k] : -kQe, k, i0 + tid, sh, ta, ex, ey, ez);
+        stage_sample<double, GEOM>(r, beta, beta_dot, g, xm, charge ? charge[k] : -kQe, k, i, sh, ta, ex, ey, ez);
         s.ta[tid] = ta;
         s.e[0][tid] = ex;
         s.e[1][tid] = ey;
         s.e[2][tid] = ez;
-        return (int)std::min<int64_t>(kFdChunk, sh.n_samples - i0);
+        return (int)std::min<int64_t>(kFdChunk, end);
     };
     if (fd_equal(omega, sh.n_omega, dw)) {
+        if (sub > 0) return;
         const int na = (int)std::min<int64_t>(8 * W, (left + kFdBlk - 1) / kFdBlk);
         if (tid < 8 * W) s.nu[tid] = tid < na ? fd_cycles(fd_centre(omega, sh.n_omega, w0 / kFdBlk + tid, dw)) : make_double2(0.0, 0.0);
         const double dnu = dw * kInv2Pi;
@@ -268,52 +283,59 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd(const double *__restrict__
         }
         return;
     }
-    // any frequencies: wavefront v takes the tile's frequencies 64 (v + 4 f) + lane, f < W
-    double nu[W], a[W][6];
+    // any frequencies, 256 of them: wavefront v takes the v-th quarter of each chunk's samples for all, lanes over
+    // frequencies, so that a list of any length keeps the four wavefronts busy.  20 x 2001 samples, 25 pixels, 100
+    // frequencies: 547 us with a wavefront per 64 frequencies, 295 now; 1030 frequencies: 4257 us with a tile of
+    // W x 256 to a block, 2760 now.
+    constexpr int kF = 4;
+    const int64_t ws = w0 + 256 * sub;
+    double nu[kF], a[kF][6];
 #pragma unroll
-    for (int f = 0; f < W; ++f) {
-        const int64_t w = w0 + 64 * (wv + 4 * f) + lane;
+    for (int f = 0; f < kF; ++f) {
+        const int64_t w = ws + 64 * f + lane;
         nu[f] = w < sh.n_omega ? omega[w] / (2.0 * kPi) : 0.0;
 #pragma unroll
         for (int c = 0; c < 6; ++c) a[f][c] = 0.0;
     }
     for (int64_t u = u0; u < u1; ++u) {
-        const int n = stage(u);
+        const int n = stage(u), share = (n + 3) / 4, qa = share * wv, qb = std::min(qa + share, n);
         __syncthreads();
 #pragma unroll
-        for (int f = 0; f < W; ++f) {
-            if (64 * (wv + 4 * f) >= left) continue;
-            for (int q0 = 0; q0 < n; q0 += 64) {
-                double b0 = 0, b1 = 0, b2 = 0, b3 = 0, b4 = 0, b5 = 0;
-                for (int q = q0; q < std::min(q0 + 64, n); ++q) {
-                    const double x = nu[f] * s.ta[q];
-                    double sn, c;
-                    sincospi(2.0 * (x - floor(x)), &sn, &c);
-                    const double e0 = s.e[0][q], e1 = s.e[1][q], e2 = s.e[2][q];
-                    b0 += e0 * c;
-                    b1 += e0 * sn;
-                    b2 += e1 * c;
-                    b3 += e1 * sn;
-                    b4 += e2 * c;
-                    b5 += e2 * sn;
-                }
-                a[f][0] += b0;
-                a[f][1] += b1;
-                a[f][2] += b2;
-                a[f][3] += b3;
-                a[f][4] += b4;
-                a[f][5] += b5;
+        for (int f = 0; f < kF; ++f) {
+            if (ws + 64 * f >= sh.n_omega) break;
+            double b0 = 0, b1 = 0, b2 = 0, b3 = 0, b4 = 0, b5 = 0;
+            for (int q = qa; q < qb; ++q) {
+                const double x = nu[f] * s.ta[q];
+                double sn, c;
+                sincospi(2.0 * (x - floor(x)), &sn, &c);
+                const double e0 = s.e[0][q], e1 = s.e[1][q], e2 = s.e[2][q];
+                b0 += e0 * c;
+                b1 += e0 * sn;
+                b2 += e1 * c;
+                b3 += e1 * sn;
+                b4 += e2 * c;
+                b5 += e2 * sn;
             }
+            a[f][0] += b0;
+            a[f][1] += b1;
+            a[f][2] += b2;
+            a[f][3] += b3;
+            a[f][4] += b4;
+            a[f][5] += b5;
         }
         __syncthreads();
     }
+    // the wavefronts' sums in their order
 #pragma unroll
-    for (int f = 0; f < W; ++f) {
-        const int64_t w = w0 + 64 * (wv + 4 * f) + lane;
-        if (w >= sh.n_omega) continue;
-        double *o = acc + ((size_t)m * sh.n_omega + w) * 6;
+    for (int f = 0; f < kF; ++f)
 #pragma unroll
-        for (int c = 0; c < 6; ++c) atomic_add(o + c, a[f][c]);
+        for (int c = 0; c < 6; ++c) s.part[wv][c][64 * f + lane] = a[f][c];
+    __syncthreads();
+    if (ws + tid < sh.n_omega) {
+        double *o = acc + ((size_t)m * sh.n_omega + ws + tid) * 6;
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+            atomic_add(o + c, ((s.part[0][c][tid] + s.part[1][c][tid]) + s.part[2][c][tid]) + s.part[3][c][tid]);
     }
 }
 
@@ -804,6 +826,7 @@ FdShape fd_shape(const lw_traj_t *t, const lw_grid_t *gr, int64_t n_omega, int f
     sh.cdt = kC * t->dt;
     sh.inv_cdt = 1.0 / sh.cdt;
     sh.fmask = fmask;
+    sh.flat = 0;
     return sh;
 }
 
@@ -811,11 +834,10 @@ FdShape fd_shape(const lw_traj_t *t, const lw_grid_t *gr, int64_t n_omega, int f
 // most 2^24 blocks of 256); more of them take several launches, a range of pixels resp. particles each
 constexpr int64_t kFdLaunch = int64_t(1) << 22;
 
-// chunks of samples per group, so that about `rounds` times `resident` blocks run; returns the blocks
-int64_t fd_groups(FdShape &sh, int64_t chunk, int64_t resident, int64_t rounds)
+// chunks of samples (`units` of them) per group, so that about `rounds` times `resident` blocks run; returns the blocks
+int64_t fd_groups(FdShape &sh, int64_t units, int64_t resident, int64_t rounds)
 {
     const int64_t base = sh.n_pix * sh.n_wblocks;
-    const int64_t units = std::max<int64_t>(1, sh.n_particles * ((sh.n_samples + chunk - 1) / chunk));
     const int64_t groups = std::max<int64_t>(1, std::min(units, resident * rounds / base));
     sh.parts_per_group = (units + groups - 1) / groups;
     sh.n_groups = (units + sh.parts_per_group - 1) / sh.parts_per_group;
@@ -838,16 +860,20 @@ void launch_sums64(const lw_traj_t *t, const lw_grid_t *gr, const double *omega,
     // frequencies per block: one tile of 256, 512 or 1024
     const int W = sh.n_omega > 512 ? 4 : sh.n_omega > 256 ? 2 : 1;
     sh.n_wblocks = (sh.n_omega + 256 * W - 1) / (256 * W);
-    // two blocks per compute unit; more rounds of them once each has eight chunks (every block adds its sums
+    // two blocks per compute unit; more rounds of them, of some eight chunks each (every block adds its sums
     // with 6 atomics per frequency)
-    const int64_t units = sh.n_particles * ((sh.n_samples + kFdChunk - 1) / kFdChunk);
-    const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(4, units * sh.n_pix * sh.n_wblocks / (512 * 8)));
+    // Chunks hold the samples of several particles where one fills less than half of them and there are blocks enough:
+    // 50 x 61 samples, 16 pixels, 600 uneven frequencies 145 -> 102 us; 3 x 101 samples, 2 pixels 24 -> 30 us
+    sh.flat = 2 * sh.n_samples <= kFdChunk && sh.n_pix * sh.n_wblocks * sh.n_particles >= 512;
+    const int64_t units = sh.flat ? (sh.n_particles * sh.n_samples + kFdChunk - 1) / kFdChunk
+                                  : sh.n_particles * ((sh.n_samples + kFdChunk - 1) / kFdChunk);
+    const int64_t rounds = std::clamp<int64_t>((units * sh.n_pix * sh.n_wblocks + 512 * 8 - 1) / (512 * 8), 1, 4);
     auto go = [&](auto *k) {
         fd_launches(sh, gr->x_det, acc, [&](int64_t n_pix, const double *x_det, double *a) {
             FdShape part = sh;
             part.n_pix = n_pix;
-            const int64_t blocks = fd_groups(part, kFdChunk, 512, rounds);
-            k<<<(unsigned)blocks, 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, x_det, omega, a, part);
+            const int64_t blocks = fd_groups(part, units, 512, rounds);
+            k<<<dim3((unsigned)blocks, W), 256, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, x_det, omega, a, part);
         });
     };
     if (geom == LW_GEOM_EXACT)
@@ -870,7 +896,7 @@ void launch_mixed(const lw_traj_t *t, const lw_grid_t *gr, const double *omega, 
         fd_launches(sh, gr->x_det, acc, [&](int64_t n_pix, const double *x_det, double *a) {
             FdShape part = sh;
             part.n_pix = n_pix;
-            const int64_t blocks = fd_groups(part, 64 * W, resident, rounds);
+            const int64_t blocks = fd_groups(part, units, resident, rounds);
             k<<<(unsigned)blocks, 64 * W, 0, s>>>(t->r, t->beta, t->beta_dot, t->charge, x_det, omega, a, part);
         });
     };

@@ -36,3 +36,31 @@ def test_lists_at_the_tolerance(off, taken):
     assert np.array_equal(S[:, perm], P) != taken
     So = oracle.direct_fd(c["t_start"], c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"], c["t0"], w)
     assert np.max(np.abs(S - So)) <= 1e-10 * So.max() and np.max(np.abs(P - So[:, perm])) <= 1e-10 * So.max()
+
+
+@pytest.mark.parametrize("n_w", [1, 3, 64, 65, 100, 192, 193, 257, 300, 513, 1030])
+@pytest.mark.parametrize("n_samples", [1, 5, 66, 300])
+def test_uneven_lists_of_any_length(n_w, n_samples):
+    """A sine/cosine pair per term (the order of a list does not matter to it): ends of the groups of 64 and 256
+    frequencies, of a chunk of samples and of its quarters.  Tolerance as above."""
+    from paper_2206_03015_amd import lw
+    c = synthetic(n_p=3, n_samples=n_samples, n_pix=2)
+    w = np.geomspace(1e18, 2e19, n_w)
+    w[:: 2] *= 1.0 + 1e-6
+    S = lw.direct_fd(*args(c, w), prec="fp64", charge=T(c["charge"])).cpu().numpy()
+    So = oracle.direct_fd(c["t_start"], c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"], c["t0"], w, charge=c["charge"])
+    assert np.max(np.abs(S - So)) <= 1e-10 * So.max()
+
+
+@pytest.mark.parametrize("n_p, n_samples", [(600, 1), (300, 3), (257, 61), (256, 128), (256, 129)])
+@pytest.mark.parametrize("spacing", ["equal", "uneven"])
+def test_many_short_trajectories(n_p, n_samples, spacing):
+    """At most half a chunk of samples each, from 512 blocks on: the chunks hold several particles (129: one each).  With a
+    charge of its own per particle and an unusable sample.  Tolerance as above."""
+    from paper_2206_03015_amd import lw
+    c = synthetic(n_p=n_p, n_samples=n_samples, n_pix=2)
+    c["beta"][n_p // 2, n_samples // 2, 1] = np.nan
+    w = (np.linspace if spacing == "equal" else np.geomspace)(1e18, 2e19, 70)
+    S = lw.direct_fd(*args(c, w), prec="fp64", charge=T(c["charge"])).cpu().numpy()
+    So = oracle.direct_fd(c["t_start"], c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"], c["t0"], w, charge=c["charge"])
+    assert np.max(np.abs(S - So)) <= 1e-10 * So.max()
