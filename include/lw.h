@@ -381,9 +381,14 @@ lw_status lw_deposit_td_bwd_boris(const lw_traj_t *traj, const lw_grid_t *grid, 
  * f = dt^2/2pi, chained through the field formula, kappa = 1 - n.beta and the arrival
  * time (dt/dr = -n/c).  Adds (accumulates) into d_r, d_beta, d_beta_dot
  * [n_particles][n_samples][3] (double); each sample is written by one thread, no
- * atomics.  prec: LW_PREC_FP64 only (MIXED returns LW_E_UNSUPPORTED).  Unusable
- * samples get no gradient.  ws: >= lw_workspace_bytes(LW_WS_DIRECT_FD_BWD, n_pix,
- * n_omega, prec) bytes, 256-byte aligned.
+ * atomics (the sums F_c(w) are added with atomics: their last bits, and with them the
+ * gradient's, may differ between runs).  prec: LW_PREC_FP64 only (MIXED returns
+ * LW_E_UNSUPPORTED).  Unusable samples get no gradient.
+ * ws: >= lw_workspace_bytes(LW_WS_DIRECT_FD_BWD, n_pix, n_omega, prec) bytes,
+ * 256-byte aligned.  With s x 72 bytes per sample more, s blocks share the pixels of
+ * 64 samples and their partial gradients are added in order (used up to s =
+ * min(n_pix / 4, 2048 / blocks), rounded up, with n_particles x ceil(n_samples / 64)
+ * blocks; worth it for a few thousand samples and many pixels).
  */
 lw_status lw_direct_fd_bwd(const lw_traj_t *traj, const lw_grid_t *grid, const double *omega, int64_t n_omega,
                            int prec, int field_mask, int geom, const double *dS, double *d_r, double *d_beta,

@@ -156,7 +156,7 @@ struct alignas(16) Fd64Lds {
         struct {
             double l[kSub][kPitch], r[kSub][kPitchR];
         };
-        double sum[kRows][kFdBlk];
+        double sum[4 / W][kRows][kFdBlk];
         double part[4][6][256];  // any frequencies: the wavefronts' sums
     };
 };
@@ -258,28 +258,32 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd(const double *__restrict__
                 __syncthreads();
             }
         }
-        // rows (block, component, re / im) x (cos h, sin h), summed over the wavefronts that share them
-        for (int it = tid; it < Lds::kRows * kFdBlk; it += 256) ((double *)s.sum)[it] = 0.0;
-        __syncthreads();
+        // rows (block, component, re / im) x (cos h, sin h), summed over the wavefronts that share them in their order
         if (mine) {
 #pragma unroll
             for (int i = 0; i < 3; ++i)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    double *o = s.sum[48 * fw + 16 * i + (lane >> 4) + 4 * v] + (lane & 15);
-                    atomicAdd(o, d[i][0][v]);
-                    atomicAdd(o + 16, d[i][1][v]);
+                    double *o = s.sum[sw][48 * fw + 16 * i + (lane >> 4) + 4 * v] + (lane & 15);
+                    o[0] = d[i][0][v];
+                    o[16] = d[i][1][v];
                 }
         }
         __syncthreads();
         for (int it = tid; it < (int)std::min<int64_t>(left, 256 * W) * 3; it += 256) {
             const int j = it / 3, c = it - 3 * j, b = j % kFdBlk;
-            const double *re = s.sum[j / kFdBlk * 6 + 2 * c], *im = s.sum[j / kFdBlk * 6 + 2 * c + 1];
+            const int row = j / kFdBlk * 6 + 2 * c;
+            auto sum = [&](int r, int col) {
+                double v = s.sum[0][r][col];
+#pragma unroll
+                for (int w = 1; w < 4 / W; ++w) v += s.sum[w][r][col];
+                return v;
+            };
             const int h = b >= 16 ? b - 16 : 15 - b;
             const double sg = b >= 16 ? 1.0 : -1.0;
             double *o = acc + ((size_t)m * sh.n_omega + w0 + j) * 6 + 2 * c;
-            atomic_add(o, fma(-sg, im[16 + h], re[h]));
-            atomic_add(o + 1, fma(sg, re[16 + h], im[h]));
+            atomic_add(o, fma(-sg, sum(row + 1, 16 + h), sum(row, h)));
+            atomic_add(o + 1, fma(sg, sum(row, 16 + h), sum(row + 1, h)));
         }
         return;
     }
@@ -559,8 +563,11 @@ __global__ void k_fd_finish(const double *__restrict__ acc, double *__restrict__
 //   sum_w C e^{-iwt} = sum_A e^{-i w_A t} sum_h [cos h dw t (C+ + C-) - i sin h dw t (C+ - C-)]_A,
 // the inner sum a matrix product over the 32 cosines and sines of a sample, 12 columns (6 quantities, re and
 // im) per block of 32 frequencies, four blocks (48 columns) at a time: 12 multiply-adds a term on the matrix
-// cores and 1/32 sine/cosine pair.  The pixels are shared out over blocks until there are kFdBwdBlocks of them (a block's
-// chain of pixels and frequency blocks is its time, and two fit a compute unit).
+// cores and 1/32 sine/cosine pair.  Where the workspace has room for their partial gradients, the pixels are shared out
+// over blocks until there are kFdBwdBlocks of them (a block's chain of pixels and frequency blocks is its time, and two
+// fit a compute unit), and k_fd_add sums the partial gradients in their order; otherwise a block takes all pixels.  Within a
+// block the parts of a sum go through LDS and are added in a fixed order too: for given sums F_c(w) a call's bits
+// are the same on every run.
 // 20 x 2001 samples, 9 pixels, 1024 frequencies: 2071 us with a sine/cosine pair per term -> 350 us (112 us of it
 // the matrix product).
 constexpr int64_t kFdBwdBlocks = 2048;
@@ -574,8 +581,10 @@ struct alignas(16) FdBwdLds {
             double w[32][50];    // coefficients of the four blocks (pitch as in Fd64Lds)
             double p[4][64][2];  // cos, sin of w_A t
         };
-        double row[4][64][8];  // any-frequency path: dS, w dS, R_x, I_x, R_y, I_y, R_z, I_z
-        double red[4][9][64];  // the wavefronts' gradients
+        double row[4][64][8];   // any-frequency path: dS, w dS, R_x, I_x, R_y, I_y, R_z, I_z
+        double part[4][6][64];  // and the wavefronts' sums
+        double col[48][65];     // equal spacing: a pixel's 48 columns of sums (odd pitch: writes of 16 columns at a time)
+        double red[4][9][64];   // the wavefronts' gradients
     };
 };
 
@@ -587,7 +596,8 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
                                                           const double *__restrict__ omega,
                                                           const double *__restrict__ acc, const double *__restrict__ dS,
                                                           double *__restrict__ d_r, double *__restrict__ d_beta,
-                                                          double *__restrict__ d_beta_dot, FdShape sh, double two_f)
+                                                          double *__restrict__ d_beta_dot, FdShape sh, double two_f,
+                                                          int64_t share_stride)
 {
     __shared__ FdBwdLds s;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -629,8 +639,6 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
             ok = isfinite(ta) && isfinite(A[0]) && isfinite(A[1]) && isfinite(A[2]);
         }
         s.ta[wv][lane] = ok ? ta : 0.0;
-#pragma unroll
-        for (int c = 0; c < 6; ++c) s.g[wv][c][lane] = 0.0;
         __syncthreads();
         const int np = (int)std::min<int64_t>(4, me - m0);
         for (int p = 0; p < np; ++p) {
@@ -719,11 +727,21 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
                 }
 #pragma unroll
                 for (int t = 0; t < 3; ++t) {
-                    const int col = 16 * t + (lane & 15), z = col % 12 / 2, ri = col & 1;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        atomicAdd(&s.g[p][z][16 * wv + (lane >> 4) + 4 * v], z >= 3 && ri == 0 ? -sum[t][v] : sum[t][v]);
+                    for (int v = 0; v < 4; ++v) s.col[16 * t + (lane & 15)][16 * wv + (lane >> 4) + 4 * v] = sum[t][v];
                 }
+                __syncthreads();
+                for (int it = tid; it < 6 * 64; it += 256) {
+                    const int z = it >> 6, q = it & 63;
+                    double v = 0.0;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        const double re = s.col[12 * a + 2 * z][q], im = s.col[12 * a + 2 * z + 1][q];
+                        v += z >= 3 ? im - re : re + im;
+                    }
+                    s.g[p][z][q] = v;
+                }
+                __syncthreads();
             } else {
                 // any frequencies: lanes over samples, wavefront v takes every fourth 64 frequencies
                 const double tl = s.ta[p][lane];
@@ -753,10 +771,17 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                 }
+                __syncthreads();  // the rows are read
                 for (int c = 0; c < 3; ++c) {
-                    atomicAdd(&s.g[p][c][lane], G[c]);
-                    atomicAdd(&s.g[p][3 + c][lane], K[c]);
+                    s.part[wv][c][lane] = G[c];
+                    s.part[wv][3 + c][lane] = K[c];
                 }
+                __syncthreads();
+                for (int it = tid; it < 6 * 64; it += 256) {
+                    const int z = it >> 6, q = it & 63;
+                    s.g[p][z][q] = ((s.part[0][z][q] + s.part[1][z][q]) + s.part[2][z][q]) + s.part[3][z][q];
+                }
+                __syncthreads();
             }
         }
         __syncthreads();
@@ -794,11 +819,25 @@ __global__ __launch_bounds__(256, 2) void k_direct_fd_bwd(const double *__restri
         for (int c = 0; c < 3; ++c) {
             double v = s.red[0][3 * wv + c][lane];
             for (int w = 1; w < 4; ++w) v += s.red[w][3 * wv + c][lane];
-            if (gridDim.y > 1)
-                atomic_add(out + so + c, v);
+            if (share_stride)  // a share of the pixels: partial gradients
+                out[(size_t)blockIdx.y * share_stride + so + c] = v;
             else
                 out[so + c] += v;
         }
+    }
+}
+
+// d_r, d_beta, d_beta_dot (n elements each) += their partial gradients [n_shares][3][n], in order
+__global__ void k_fd_add(const double *__restrict__ part, int n_shares, int64_t n, double *__restrict__ d_r,
+                         double *__restrict__ d_beta, double *__restrict__ d_beta_dot)
+{
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
+        double v[3] = {0.0, 0.0, 0.0};
+        for (int y = 0; y < n_shares; ++y)
+            for (int a = 0; a < 3; ++a) v[a] += part[((size_t)y * 3 + a) * n + j];
+        d_r[j] += v[0];
+        d_beta[j] += v[1];
+        d_beta_dot[j] += v[2];
     }
 }
 
@@ -955,19 +994,26 @@ lw_status launch_direct_fd_bwd(const lw_traj_t *t, const lw_grid_t *gr, const do
     const int64_t chunks = (t->n_samples + 63) / 64, blocks = t->n_particles * chunks;
     launch_sums64(t, gr, omega, sh, geom, acc, s);
     const double two_f = 2.0 * t->dt * t->dt / (2.0 * kPi);
-    // pixels per block: a multiple of four (a wavefront each)
-    const int64_t quads = (gr->n_pix + 3) / 4, share = std::max<int64_t>(1, std::min(quads, (kFdBwdBlocks + blocks - 1) / blocks));
+    // pixels per block: a multiple of four (a wavefront each); shares of them as far as the workspace has room
+    const int64_t n = t->n_particles * t->n_samples * 3, quads = (gr->n_pix + 3) / 4;
+    const size_t room = ws_bytes - direct_fd_ws_bytes(gr->n_pix, n_omega), per_share = (size_t)n * 3 * sizeof(double);
+    int64_t share = std::min({quads, (kFdBwdBlocks + blocks - 1) / blocks, (int64_t)(room / per_share)});
+    if (share < 2) share = 1;
     FdShape sb = sh;
     sb.parts_per_group = (quads + share - 1) / share * 4;
     const int64_t ny = (gr->n_pix + sb.parts_per_group - 1) / sb.parts_per_group;
+    double *part = acc + 6 * nS;
+    double *const out[3] = {ny > 1 ? part : d_r, ny > 1 ? part + n : d_beta, ny > 1 ? part + 2 * n : d_beta_dot};
     auto *k = geom == LW_GEOM_EXACT ? k_direct_fd_bwd<LW_GEOM_EXACT> : k_direct_fd_bwd<LW_GEOM_FARFIELD>;
     const int64_t most = std::max<int64_t>(1, kFdLaunch / chunks);
     for (int64_t k0 = 0; k0 < t->n_particles; k0 += most) {
         const size_t o = (size_t)k0 * t->n_samples * 3;
         k<<<dim3((unsigned)(std::min(most, t->n_particles - k0) * chunks), (unsigned)ny), 256, 0, s>>>(
-            t->r + o, t->beta + o, t->beta_dot + o, t->charge ? t->charge + k0 : nullptr, gr->x_det, omega, acc, dS, d_r + o,
-            d_beta + o, d_beta_dot + o, sb, two_f);
+            t->r + o, t->beta + o, t->beta_dot + o, t->charge ? t->charge + k0 : nullptr, gr->x_det, omega, acc, dS, out[0] + o,
+            out[1] + o, out[2] + o, sb, two_f, ny > 1 ? 3 * n : 0);
     }
+    if (ny > 1)
+        k_fd_add<<<(unsigned)std::min<int64_t>((n + 255) / 256, 65536), 256, 0, s>>>(part, (int)ny, n, d_r, d_beta, d_beta_dot);
     return check_launch("lw_direct_fd_bwd");
 }
 

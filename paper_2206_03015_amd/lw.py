@@ -371,6 +371,13 @@ def deposit_td_bwd(r, beta, beta_dot, t_start, dt, x_det, t0, dt_obs, n_obs, dE,
     return d_r, d_b, d_bd
 
 
+def _fd_shares(n_p, n_s, n_pix):
+    """Shares of the pixels for which lw_direct_fd_bwd has a use in a larger workspace (72 bytes a sample each)."""
+    blocks = n_p * ((n_s + 63) // 64)
+    shares = min((n_pix + 3) // 4, -(-2048 // blocks)) if blocks else 0
+    return shares if shares > 1 else 0
+
+
 def direct_fd_bwd(r, beta, beta_dot, t_start, dt, x_det, t0, omega, dS, field_mask=FIELD_ACCEL, geom="exact",
                   charge=None, out=None, ws=None):
     """lw_direct_fd_bwd (FP64): adds dJ/d(r, beta, beta_dot) for J = sum(dS * S_FD) into `out` (zeros if None)."""
@@ -386,7 +393,8 @@ def direct_fd_bwd(r, beta, beta_dot, t_start, dt, x_det, t0, omega, dS, field_ma
     for t, nm in ((d_r, "d_r"), (d_b, "d_beta"), (d_bd, "d_beta_dot")):
         _need(t, torch.float64, tuple(r.shape), nm)
     if ws is None:
-        ws = _workspace(workspace_bytes(WS_DIRECT_FD_BWD, gr.n_pix, n_w, "fp64"), r.device)
+        ws = _workspace(workspace_bytes(WS_DIRECT_FD_BWD, gr.n_pix, n_w, "fp64") +
+                        _fd_shares(tr.n_particles, tr.n_samples, gr.n_pix) * 72 * tr.n_particles * tr.n_samples, r.device)
     _check(lib.lw_direct_fd_bwd(ctypes.byref(tr), ctypes.byref(gr), _ptr(omega), n_w, PREC["fp64"], int(field_mask),
                                 GEOM[geom], _ptr(dS), _ptr(d_r), _ptr(d_b), _ptr(d_bd), _ptr(ws), ws.numel(),
                                 _stream()))

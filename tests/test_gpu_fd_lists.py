@@ -64,3 +64,31 @@ def test_many_short_trajectories(n_p, n_samples, spacing):
     S = lw.direct_fd(*args(c, w), prec="fp64", charge=T(c["charge"])).cpu().numpy()
     So = oracle.direct_fd(c["t_start"], c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"], c["t0"], w, charge=c["charge"])
     assert np.max(np.abs(S - So)) <= 1e-10 * So.max()
+
+
+@pytest.mark.parametrize("n_w, spacing", [(150, "equal"), (150, "uneven"), (4200, "equal")])
+@pytest.mark.parametrize("n_p, n_samples, n_pix", [(1, 200, 13), (3, 70, 5), (2, 64, 4)])
+def test_adjoint_adds_in_order(n_p, n_samples, n_pix, n_w, spacing):
+    """The adjoint with the least workspace (a block takes all pixels) and with room for shares of them, repeated on sums of
+    one chunk (n_p = 1, no atomics that meet): the same bits each time; both against each other and added to what
+    is there.  4200 frequencies: more blocks of them than keep their centres in LDS."""
+    from paper_2206_03015_amd import lw
+    c = synthetic(n_p=n_p, n_samples=n_samples, n_pix=n_pix)
+    w = (np.linspace if spacing == "equal" else np.geomspace)(1e18, 2e19, n_w)
+    dS = T(np.random.default_rng(2).random((n_pix, n_w)) * 1e30)
+    least = lw.workspace_bytes(lw.WS_DIRECT_FD_BWD, n_pix, n_w, "fp64")
+    out = {}
+    for extra in (0, 2 * 72 * n_p * n_samples + 8, None):
+        ws = None if extra is None else torch.empty((least + extra + 255) // 256 * 256, dtype=torch.uint8, device=DEV)[:least + extra]
+        for rep in range(8 if n_p == 1 else 1):
+            g = lw.direct_fd_bwd(*args(c, w), dS, ws=ws)
+            if rep:
+                assert all(torch.equal(a, b) for a, b in zip(g, out[extra]))
+            out[extra] = g
+    for a, b, d in zip(out[0], out[None], out[2 * 72 * n_p * n_samples + 8]):
+        assert float(a.abs().max()) > 0
+        assert float((a - b).abs().max()) <= 1e-12 * float(a.abs().max())
+        assert float((a - d).abs().max()) <= 1e-12 * float(a.abs().max())
+    twice = lw.direct_fd_bwd(*args(c, w), dS, out=tuple(a.clone() for a in out[None]))
+    for a, b in zip(twice, out[None]):
+        assert float((a - 2 * b).abs().max()) <= 1e-12 * float(b.abs().max())
