@@ -376,7 +376,7 @@ __global__ __launch_bounds__(64 * W, 2) void k_direct_fd_mixed(const double *__r
 {
     constexpr int NS = 64 * W;
     __shared__ float4 s_t[W][NS];  // per wavefront's frequencies: t_a - t_ref (s), e^{i dw t_a}
-    __shared__ float s_e[NS][4];   // E kappa
+    __shared__ __align__(16) float s_e[NS][4];  // E kappa
     __shared__ double s_tref[W], s_dnu[W];
     __shared__ int s_eq[W];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;

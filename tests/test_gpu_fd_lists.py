@@ -92,3 +92,25 @@ def test_adjoint_adds_in_order(n_p, n_samples, n_pix, n_w, spacing):
     twice = lw.direct_fd_bwd(*args(c, w), dS, out=tuple(a.clone() for a in out[None]))
     for a, b in zip(twice, out[None]):
         assert float((a - 2 * b).abs().max()) <= 1e-12 * float(b.abs().max())
+
+
+@pytest.mark.parametrize("n_w, layout", [(1537, "equal"), (2048, "equal"), (2048, "piecewise"), (2048, "uneven"), (4097, "equal"),
+                                         (4097, "piecewise")])
+@pytest.mark.parametrize("n_samples", [5, 257, 300])
+def test_mixed_sums_with_four_wavefronts_to_a_block(n_w, layout, n_samples):
+    """From 1537 frequencies on (four wavefronts of 512, or nine: the last block's second to fourth have none and only stage
+    samples) 256 samples are staged once for the block's wavefronts.  "piecewise" changes its spacing inside the third
+    wavefront, which takes a sine/cosine pair per phasor beside the others' recurrence.  Tolerance of the mixed sums:
+    1e-4 of the largest."""
+    from paper_2206_03015_amd import lw
+    c = synthetic(n_p=2, n_samples=n_samples, n_pix=3)
+    w = np.linspace(1e17, 2e19, n_w)
+    if layout == "piecewise":
+        w[1300:] = w[1300] + 1.3 * (w[1300:] - w[1300])
+    elif layout == "uneven":
+        w = np.sort(np.random.default_rng(5).uniform(1e17, 2e19, n_w))
+    S = lw.direct_fd(*args(c, w), prec="mixed", charge=T(c["charge"])).cpu().numpy()
+    So = oracle.direct_fd(c["t_start"], c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"], c["t0"], w, charge=c["charge"])
+    err = np.max(np.abs(S - So)) / So.max()
+    print(f"mixed, {n_w} {layout} frequencies, {n_samples} samples: rel err {err:.2e}")
+    assert err <= 1e-4
