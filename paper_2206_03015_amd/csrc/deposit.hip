@@ -66,7 +66,7 @@ constexpr int kLongRun = 8;
 // short.  Precision cut 35.8 -> 29.1 ms, 1000-electron bunch FP64 3.42 -> 2.68 ms (4096 intervals: 3.2).
 constexpr int64_t kSegIntervals = 4096, kSegIntervals64 = 2048;
 constexpr int64_t kTargetBlocks = 16384;
-constexpr int kMaxPartsPerGroup = 64;  // at most a wavefront's lanes
+constexpr int kMaxPartsPerGroup = 64;
 constexpr int64_t kFillBlocks = 2048;
 // particles per block of the careful path
 constexpr int kMaxPartsCareful = 4;
@@ -269,7 +269,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct DepWs {
     double *pt;                 // [kPixTabMax][kPT] pixel table of the current pass
-    int *pflag;                 // [n_p] see k_prepass
+    int *pflag;                 // [n_p] 0 = fast path
     unsigned long long *rmax2;  // [n_p] bits of max_i |r_i|^2 (non-negative doubles order as integers)
     double *d;                  // [n_p][n_s] arrival bases
 };
@@ -298,24 +298,16 @@ DepWs carve(void *ws, int64_t n_p)
     return w;
 }
 
-constexpr double kGatherDensity = 1.0;
-constexpr int64_t kGatherSamples = 1024;  // longest trajectory (every sample that bounds a window is evaluated)
-
-// where k_prepass notes that there are dense particles: in the padding of the pixel table's first row
-__host__ __device__ __forceinline__ int *dense_flag(double *pt) { return (int *)(pt + kPT - 1); }
-
 // ---------------------------------------------------------------------------------------------
-// pre-pass: one block per (particle, chunk of samples): arrival bases, per-particle max |r|^2 and the flags: 1 for the
-// careful path, 2 for a dense particle (k_gather, where x_mid is given), 0 for k_sweep.  Bound by memory: 72 bytes of a
-// sample read, 8 written (with the polynomial's coefficients and the position stored beside the base, 64 or 80 written,
-// the pre-pass of 2000 x 20001 samples took 1.75 ms, now 0.79; the coefficients are formed where a step's samples are
-// staged instead)
+// pre-pass: one block per (particle, chunk of samples): arrival bases, per-particle max |r|^2 and the
+// careful-path flag.  Bound by memory: 72 bytes of a sample read, 8 written (with the polynomial's coefficients
+// and the position stored beside the base, 64 or 80 written, the pre-pass of 2000 x 20001 samples took
+// 1.75 ms, now 0.79; the coefficients are formed where a step's samples are staged instead)
 __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, const double *__restrict__ beta,
                                                  const double *__restrict__ beta_dot, int64_t n_samples, int chunk,
                                                  int64_t sample0, double t_start, double dt, double t0,
                                                  double dt_obs, double C, double *__restrict__ base,
-                                                 int *__restrict__ pflag, unsigned long long *__restrict__ rmax2,
-                                                 const double *__restrict__ x_mid, int geom, double *pt)
+                                                 int *__restrict__ pflag, unsigned long long *__restrict__ rmax2)
 {
     __shared__ unsigned long long s_max[4];
     __shared__ int s_bad[4];
@@ -363,20 +355,6 @@ __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, c
         }
         atomicMax(rmax2 + k, m);
         if (bb) atomicOr(pflag + k, 1);
-        if (x_mid && blockIdx.y == 0) {
-            // dense: by the first and last arrival times at a pixel in the middle of the detector
-            const PixC P = pix_const(x_mid, 0, C);
-            auto tau = [&](int64_t i) {
-                const double *ri = r + 3 * (k * n_samples + i);
-                const double d = arrival_base(t_start, dt, (double)(sample0 + i), t0, dt_obs, ri[2]);
-                return geom == LW_GEOM_EXACT ? arrival_tau<LW_GEOM_EXACT, kTauSqrt>(P, d, ri[0], ri[1], ri[2], 0.0, C)
-                                             : arrival_tau<LW_GEOM_FARFIELD, kTauSqrt>(P, d, ri[0], ri[1], ri[2], 0.0, C);
-            };
-            if (tau(n_samples - 1) - tau(0) >= kGatherDensity * (double)(n_samples - 1)) {
-                atomicOr(pflag + k, 2);
-                *dense_flag(pt) = 1;
-            }
-        }
     }
 }
 
@@ -645,7 +623,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
     const int64_t k1 = grp < sh.n_groups ? std::min(k0 + sh.parts_per_group, sh.n_particles) : k0;
     {
         bool any = false;
-        for (int64_t k = k0 + (threadIdx.x & 63); k < k1; k += 64) any |= (pflag[k] & 1) != 0;
+        for (int64_t k = k0 + (threadIdx.x & 63); k < k1; k += 64) any |= pflag[k] != 0;
         if (__ballot(any) == 0) return;  // whole block (one wavefront)
     }
     __shared__ uint2 q_all[kQCap];
@@ -709,7 +687,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 
     unsigned long long c0 = 0, c1 = 0, c2 = 0, c3 = 0;
     for (int64_t k = k0; k < k1; ++k) {
-        if (!(pflag[k] & 1)) continue;  // fast path: k_sweep, k_gather
+        if (pflag[k] == 0) continue;  // fast path: k_sweep
         // series forms where |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory (the max over the
         // whole trajectory when given, else over the samples of this call), decided per pixel
         w.rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
@@ -1157,11 +1135,6 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     if (grp >= sh.n_groups) return;  // padding block
     const int64_t k0 = grp * sh.parts_per_group, k1 = std::min(k0 + sh.parts_per_group, sh.n_particles);
     const int st0 = seg * sw.per_seg, st1 = min(st0 + sw.per_seg, sw.n_steps);
-    {
-        // no particle of the group is this kernel's (a group is at most a wavefront's lanes)
-        const int64_t k = k0 + (tid & 63);
-        if (__ballot(k < k1 && pflag[k] == 0) == 0) return;
-    }
 
     if (tid < 4) lds.red[tid] = 0ull;
     const int64_t m = tile * kTilePix + p;
@@ -1245,7 +1218,7 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     for (int kk = __builtin_amdgcn_readfirstlane(tid >> 6); kk < nk; kk += SweepCfg<T>::kThreads / 64) {
         const int64_t k = k0 + kk;
         int hit = 0;
-        if (pflag[k] == 0) {  // else careful path (k_careful) or dense (k_gather)
+        if (pflag[k] == 0) {  // else careful path: k_careful
             const size_t s0 = (size_t)k * sh.n_samples;
             with_mode(k, [&](auto mode) {
                 constexpr int MODE = decltype(mode)::value;
@@ -1297,197 +1270,6 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     if (c3) atomicAdd(&lds.red[3], c3);
     __syncthreads();
     if (diag && tid < 4 && lds.red[tid]) atomicAdd(diag + tid, lds.red[tid]);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Dense particles (k_prepass: at least kGatherDensity grid points per interval) of short trajectories: an observer grid much
-// finer than the samples, where a particle's points run over thousands of grid points and the particles' runs
-// overlap.  A block owns a window of grid points of one pixel, finds the particles whose arrival times pass it, forms
-// their arrival times and fields at the samples that bound it and adds the interpolated values to its grid points in
-// registers: one read and write of the trace instead of three atomics per point, which bound k_sweep here (18 G
-// requests/s).  1280 particles x 101 samples on 2^20 points, one pixel, mixed: 134 -> 93 us.
-template <typename T>
-struct GatherCfg {
-    static constexpr int U = 16 / (int)sizeof(T);  // grid points per thread (twice that: 20 us more, half: 30 more)
-    static constexpr int W = 256 * U;
-};
-
-template <typename T, int GEOM>
-__global__ __launch_bounds__(256) void k_gather(const double *__restrict__ r, const double *__restrict__ beta,
-                                                const double *__restrict__ beta_dot, const double *__restrict__ charge,
-                                                const double *__restrict__ x_det, const double *__restrict__ base,
-                                                double *pt, const int *__restrict__ pflag,
-                                                const unsigned long long *__restrict__ rmax2,
-                                                const double *__restrict__ rbound2, T *__restrict__ E,
-                                                unsigned long long *__restrict__ diag, DepShape sh)
-{
-    constexpr bool kF64 = sizeof(T) == 8;
-    constexpr int kRec = kF64 ? kModeRec5 : kModeRec3, U = GatherCfg<T>::U, W = GatherCfg<T>::W;
-    if (*dense_flag(pt) == 0) return;
-    __shared__ double s_tau[256];
-    __shared__ T s_e[3][256];
-    __shared__ int s_list[256], s_cnt[4];
-    __shared__ double s_red[2][2];
-    __shared__ uint64_t s_far[2];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t m = blockIdx.y, U0 = (int64_t)blockIdx.x * W, U1 = std::min<int64_t>(U0 + W, sh.n_obs);
-    const PixC P = pixc_row(pt + m * kPT);
-    const bool counts = diag && blockIdx.x == 0;  // the first window's blocks keep the counters
-    if (!P.g.ok && !counts) return;
-    const double xm[3] = {x_det[3 * m], x_det[3 * m + 1], x_det[3 * m + 2]};
-    unsigned long long n_bad = 0, n_out = 0, n_in = 0;
-    const double Dref = pix_geo(x_det, 0).D, nob = (double)sh.n_obs;
-    // the pixel's tile decides the arrival-time form, as in k_sweep
-    if (tid < kTilePix) {
-        const int64_t mt = m / kTilePix * kTilePix + tid;
-        const PixC pc = pixc_row(pt + mt * kPT);  // padding rows: not usable
-        const bool ok = mt < sh.n_pix && pc.g.ok;
-        double id2 = ok ? pc.g.invD * pc.g.invD : 0.0, s2 = ok ? fmax(0.0, 2.0 * (1.0 - pc.g.nz)) : 0.0;
-        const uint64_t far = __ballot(ok && !(fabs(pc.g.D - Dref) <= kSameDistance * Dref));
-        for (int off = 32; off > 0; off >>= 1) {
-            id2 = fmax(id2, __shfl_xor(id2, off));
-            s2 = fmax(s2, __shfl_xor(s2, off));
-        }
-        if (lane == 0) {
-            s_red[wv][0] = id2;
-            s_red[wv][1] = s2;
-            s_far[wv] = far;
-        }
-    }
-    __syncthreads();
-    const double invD2max = fmax(s_red[0][0], s_red[1][0]), s2max = fmax(s_red[0][1], s_red[1][1]);
-    const bool rec_ok = GEOM == LW_GEOM_EXACT && (s_far[0] | s_far[1]) == 0;
-    double cK;
-    {
-        double c[6];
-        tau_poly<kF64 ? 5 : 3>(0.0, 0.0, 0.0, 0.0, sh.C, Dref, c);
-        cK = c[kF64 ? 5 : 3];
-    }
-    auto with_mode = [&](int64_t k, auto f) {
-        const double rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
-        if constexpr (GEOM == LW_GEOM_FARFIELD) {
-            f(std::integral_constant<int, kModeFar>{}, rb2);
-        } else {
-            if (rb2 * invD2max <= kSeriesBound && rec_ok) {
-                if (tail_negligible<kF64>(rb2, s2max, sh.C, cK, Dref))
-                    f(std::integral_constant<int, kModeRecLow>{}, rb2);
-                else
-                    f(std::integral_constant<int, kRec>{}, rb2);
-            } else
-                f(std::integral_constant<int, kModeMixed>{}, rb2);
-        }
-    };
-    auto tau_of = [&](auto mode, double rb2, int64_t s) {  // of sample s (of all particles)
-        constexpr int MODE = decltype(mode)::value;
-        double v[ScanVals<GEOM, kF64, MODE>::N];
-        scan_vals<GEOM, kF64, MODE>(base[s], r[3 * s], r[3 * s + 1], r[3 * s + 2], sh.C, Dref, v);
-        return tau_eval<GEOM, kF64, MODE>(P, v, cK, rb2, sh.C);
-    };
-    const int ns = (int)sh.n_samples;
-    T acc[U][3];
-#pragma unroll
-    for (int q = 0; q < U; ++q) acc[q][0] = acc[q][1] = acc[q][2] = (T)0;
-    bool any = false;  // the same in every thread
-    for (int64_t kb = 0; kb < sh.n_particles; kb += 256) {
-        const int64_t k = kb + tid;
-        bool hit = false;
-        if (k < sh.n_particles && pflag[k] == 2 && P.g.ok) {
-            with_mode(k, [&](auto mode, double rb2) {
-                const double t0 = tau_of(mode, rb2, k * ns), t1 = tau_of(mode, rb2, k * ns + ns - 1);
-                const int64_t c0 = grid_count(t0, nob), c1 = grid_count(t1, nob);
-                hit = c1 > c0 && c1 > U0 && c0 < U1;
-                n_in += (unsigned long long)(c1 - c0);
-                n_out += (unsigned long long)((int64_t)(floor(t1) - floor(t0)) - (c1 - c0));
-            });
-        } else if (k < sh.n_particles && pflag[k] == 2) {
-            n_bad += (unsigned long long)(ns - 1);
-        }
-        const uint64_t hm = __ballot(hit);
-        __syncthreads();  // the previous list is done with
-        if (lane == 0) s_cnt[wv] = (int)__popcll(hm);
-        __syncthreads();
-        int before = 0, total = 0;
-        for (int v = 0; v < 4; ++v) {
-            before += v < wv ? s_cnt[v] : 0;
-            total += s_cnt[v];
-        }
-        if (hit) s_list[before + (int)lanes_below(hm)] = tid;
-        __syncthreads();
-        any |= total > 0;
-        for (int e = 0; e < total; ++e) {
-            const int64_t kk = kb + s_list[e], s0 = kk * ns;
-            const double q = charge ? charge[kk] : -kQe;
-            with_mode(kk, [&](auto mode, double rb2) {
-                for (int j0 = 0; j0 + 1 < ns; j0 += 255) {
-                    const int n = min(255, ns - 1 - j0);
-                    __syncthreads();  // the previous samples are read
-                    if (tid <= n) s_tau[tid] = tau_of(mode, rb2, s0 + j0 + tid);
-                    __syncthreads();
-                    const int64_t c0 = grid_count(s_tau[0], nob), c1 = grid_count(s_tau[n], nob);
-                    if (c1 <= U0) continue;
-                    if (c0 >= U1) break;
-                    // fields at the samples of intervals that reach into the window
-                    if (tid <= n && s_tau[min(tid + 1, n)] >= (double)U0 && s_tau[max(tid - 1, 0)] < (double)U1) {
-                        const int64_t s = s0 + j0 + tid;
-                        const double bx = beta[3 * s], by = beta[3 * s + 1], bz = beta[3 * s + 2];
-                        T x, y, z;
-                        lw_field_ib<T, GEOM>(P.g, xm, r[3 * s], r[3 * s + 1], r[3 * s + 2], bx, by, bz, inv_beta<T>(bx, by, bz),
-                                             (T)beta_dot[3 * s], (T)beta_dot[3 * s + 1], (T)beta_dot[3 * s + 2], q, sh.fmask, x,
-                                             y, z);
-                        s_e[0][tid] = x;
-                        s_e[1][tid] = y;
-                        s_e[2][tid] = z;
-                    }
-                    __syncthreads();
-#pragma unroll
-                    for (int i = 0; i < U; ++i) {
-                        const int64_t u = U0 + tid + 256 * i;
-                        if (u < c0 || u >= c1) continue;  // c1 <= n_obs
-                        const double ud = (double)u;
-                        int lo = 0, hi = n;
-                        double ta = s_tau[0], tb = s_tau[n];
-                        for (int it = 0; hi - lo > 1; ++it) {
-                            int g = lo + (int)((float)(hi - lo) * ((float)(ud - ta) * __builtin_amdgcn_rcpf((float)(tb - ta))));
-                            g = (it & 3) == 3 ? (lo + hi) >> 1 : min(max(g, lo + 1), hi - 1);
-                            const double tg = s_tau[g];
-                            if (tg >= ud) {
-                                hi = g;
-                                tb = tg;
-                            } else {
-                                lo = g;
-                                ta = tg;
-                            }
-                        }
-                        const T inv = kF64 ? (T)(1.0 / (tb - ta)) : (T)__builtin_amdgcn_rcpf((float)(tb - ta));
-                        const T w = (T)(ud - ta) * inv, w1 = (T)1 - w;
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) acc[i][c] += w1 * s_e[c][lo] + w * s_e[c][hi];
-                    }
-                }
-            });
-        }
-    }
-    if (counts) {
-        for (int off = 32; off > 0; off >>= 1) {
-            n_bad += __shfl_xor(n_bad, off);
-            n_out += __shfl_xor(n_out, off);
-            n_in += __shfl_xor(n_in, off);
-        }
-        if (lane == 0) {
-            if (n_bad) atomicAdd(diag + 1, n_bad);
-            if (n_out) atomicAdd(diag + 2, n_out);
-            if (n_in) atomicAdd(diag + 3, n_in);
-        }
-    }
-    if (!any) return;
-#pragma unroll
-    for (int i = 0; i < U; ++i) {
-        const int64_t u = U0 + tid + 256 * i;
-        if (u >= U1) continue;
-        T *o = E + (size_t)m * 3 * (size_t)sh.n_obs + (size_t)u;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) o[(size_t)c * (size_t)sh.n_obs] += acc[i][c];
-    }
 }
 
 // Row scales of the fixed-point pass from the first pass's max |v| per element (bits of a
@@ -1587,10 +1369,10 @@ size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples)
 // adjoint, 10000 x 20001 29.1 -> 27.7.
 constexpr int64_t kPrePushed = 2048;
 
-DepositPre deposit_pre(void *ws, int64_t n_p, int64_t ns, const lw_grid_t *gr)
+DepositPre deposit_pre(void *ws, int64_t n_p, const lw_grid_t *gr)
 {
     DepositPre pre;
-    if (ns <= kGatherSamples || n_p < kPrePushed) return pre;
+    if (n_p < kPrePushed) return pre;
     const DepWs w = carve(ws, n_p);
     pre.base = w.d;
     pre.pflag = w.pflag;
@@ -1643,7 +1425,7 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
     if (ws_bytes_for(chunk, ns) > ws_bytes)
         return fail(LW_E_WORKSPACE, "lw_deposit_td: workspace of %zu bytes holds no particle (%zu needed)", ws_bytes,
                     ws_bytes_for(1, ns));
-    if (prepassed && (chunk < n_p || ns <= kGatherSamples || !rbound2))
+    if (prepassed && (chunk < n_p || !rbound2))
         return fail(LW_E_WORKSPACE, "lw_deposit_td: pushed arrival bases of a part of the particles");
     const int64_t n_chunks_s = (ns + kPrepassChunk - 1) / kPrepassChunk;
     if (n_chunks_s > 65535) return fail(LW_E_SHAPE, "lw_deposit_td: too many samples");
@@ -1697,11 +1479,9 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             int pchunk = kPrepassChunk;
             while (pchunk > 256 && np * ((ns + pchunk - 1) / pchunk) < kPrepassBlocks) pchunk /= 2;
             const dim3 pgrid((unsigned)np, (unsigned)((ns + pchunk - 1) / pchunk));
-            // short trajectories on a long grid may be dense (k_gather)
-            const bool gather = acc_mode == kAccFloat && ns >= 2 && ns <= kGatherSamples && n_obs >= 4 * ns;
             if (!prepassed)
                 k_prepass<<<pgrid, 256, 0, s>>>(r, b, bd, ns, pchunk, sample0, t->t_start, t->dt, gr->t0, gr->dt_obs, C, w.d,
-                                                w.pflag, w.rmax2, gather ? xd + 3 * (npx / 2) : nullptr, geom, w.pt);
+                                                w.pflag, w.rmax2);
             unsigned long long *dg = (unsigned long long *)diag;
             const dim3 grid((unsigned)blocks), grid_careful((unsigned)blocks_careful);
             if (acc_mode != kAccFloat) {
@@ -1734,18 +1514,6 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
                 if (geom == LW_GEOM_EXACT) LW_SWEEP_LAUNCH(double, LW_GEOM_EXACT); else LW_SWEEP_LAUNCH(double, LW_GEOM_FARFIELD);
             } else {
                 if (geom == LW_GEOM_EXACT) LW_SWEEP_LAUNCH(float, LW_GEOM_EXACT); else LW_SWEEP_LAUNCH(float, LW_GEOM_FARFIELD);
-            }
-            if (gather) {
-                auto go = [&](auto *k, auto *e, int win) {
-                    k<<<dim3((unsigned)((n_obs + win - 1) / win), (unsigned)npx), 256, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag,
-                                                                                               w.rmax2, rb2, e, dg, sh);
-                };
-                if (f64)
-                    go(geom == LW_GEOM_EXACT ? k_gather<double, LW_GEOM_EXACT> : k_gather<double, LW_GEOM_FARFIELD>, (double *)Ep,
-                       GatherCfg<double>::W);
-                else
-                    go(geom == LW_GEOM_EXACT ? k_gather<float, LW_GEOM_EXACT> : k_gather<float, LW_GEOM_FARFIELD>, (float *)Ep,
-                       GatherCfg<float>::W);
             }
             timing_end(LW_KERNEL_DEPOSIT, ev, s);
             if (f64) {
