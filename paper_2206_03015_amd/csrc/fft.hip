@@ -1474,6 +1474,22 @@ lw_status run_fft(const T *E, int64_t n_pix, int64_t n_obs, double dt_obs, T *S,
     return check_launch("lw_spectrum_fft");
 }
 
+// Whether the adjoint has so few pixels that the runtime-shaped passes are faster: theirs are many small blocks, whereas a
+// block of k_bwd_rows_fast takes its row pairs' twelve transforms one after the other (some 25 us, however few there
+// are).  Lines between measured sizes; us with the runtime-shaped passes against the others:
+//   2^13 points FP32, N1 = 2:  32 pixels 31.1, 31.9;  64 44.1, 37.0    2^12 FP64:  32 26.5, 27.2;  64 33.8, 31.1
+//   2^14 points FP32, N1 = 4:   5 pixels 28.1, 42.5;  64 49.5, 55.1    2^13 FP64:  16 27.1, 38.0;  64 46.5, 48.1
+//   2^16 points FP32, N1 = 16: 16 pixels 52.1, 59.5;  32 90.1, 58.9    2^15 FP64:  16 46.7, 52.7;  32 79.4, 52.6
+//   2^17 points FP32, N1 = 32:  4 pixels 49.5, 51.5;   8 67.9, 57.7    2^16 FP64:   5 42.8, 48.0;   8 50.4, 49.6
+//   2^18 points FP32, N1 = 64:  1 pixel  42.7, 36.5                    2^17 FP64:   1 36.0, 31.7
+template <typename T>
+bool bwd_few(int64_t n_pix, int lg)
+{
+    const int lg1 = lg - FwdCfg<T>::kLgRow;
+    const int64_t bytes = ((n_pix + 1) / 2) * (int64_t(sizeof(T)) << lg), mib = int64_t(1) << 20;
+    return lg1 == 1 ? bytes < mib : lg1 <= 4 ? bytes <= 2 * mib : lg1 == 5 && bytes < 2 * mib;
+}
+
 template <typename T>
 lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, double dt_obs, T *dE, void *ws,
                       size_t ws_bytes, hipStream_t s)
@@ -1482,8 +1498,8 @@ lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, dou
     using Cfg = FwdCfg<T>;
     const int lg = ilog2(n_obs);
     const BwdScale<T> scale(dt_obs);
-    // the forward path's shapes, where its columns have a compile-time pass
-    if (const ColsBwdKernel<T> inv = pick_cols_bwd<T, 1>(lg - Cfg::kLgRow)) {
+    // the forward path's shapes, where its columns have a compile-time pass and there are pixels enough
+    if (const ColsBwdKernel<T> inv = bwd_few<T>(n_pix, lg) ? nullptr : pick_cols_bwd<T, 1>(lg - Cfg::kLgRow)) {
         FwdShape f;
         f.n_pix = n_pix;
         f.lg = lg;

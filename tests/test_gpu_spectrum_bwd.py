@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
 
 
-# 2^10 and 2^12 points take the runtime-shaped passes, the others the compile-time ones
+# the larger of these take the compile-time passes, the others the runtime-shaped ones
 @pytest.mark.parametrize("name, size, n_obs", [("bunch", 1.0, 1 << 18), ("bunch", 1e-4, 1 << 18), ("bunch", 1e-8, 1 << 18),
                                                ("bunch", 1.0, 1 << 10), ("bunch", 1e-4, 1 << 14),
                                                ("precision", 1.0, 1 << 18), ("precision", 1e-4, 1 << 18),
@@ -30,3 +30,23 @@ def test_mixed_adjoint_at_the_workloads_grid_steps(name, size, n_obs):
     err = np.max(np.abs(dE - ref)) / np.max(np.abs(ref))
     print(f"{name} dS {size:g} n_obs {n_obs}: rel err {err:.2e}")
     assert err <= 1e-5
+
+
+# (pixels on both sides of the line between the runtime-shaped and the compile-time passes, odd ones among them)
+@pytest.mark.parametrize("prec, lg, n_pix", [("mixed", 13, 62), ("mixed", 13, 63), ("mixed", 14, 64), ("mixed", 14, 67), ("mixed", 15, 33),
+                                             ("mixed", 16, 16), ("mixed", 16, 17), ("mixed", 17, 6), ("mixed", 17, 7), ("mixed", 18, 1),
+                                             ("fp64", 12, 62), ("fp64", 12, 63), ("fp64", 13, 64), ("fp64", 13, 65), ("fp64", 14, 35),
+                                             ("fp64", 15, 16), ("fp64", 15, 17), ("fp64", 16, 6), ("fp64", 16, 7), ("fp64", 17, 1),
+                                             ("fp64", 17, 2)])
+def test_adjoint_on_both_sides_of_the_few_pixels_line(prec, lg, n_pix):
+    """Against the formula in FP64; bounds 1e-5 as above and 1e-14 (the same roundings of 2^-53)."""
+    from paper_2206_03015_amd import lw
+    n_obs, dtype = 1 << lg, torch.float64 if prec == "fp64" else torch.float32
+    rng = np.random.default_rng(lg + n_pix)
+    E = torch.as_tensor(rng.normal(size=(n_pix, 3, n_obs)) * 1e5, dtype=dtype)
+    dS = torch.as_tensor(rng.normal(size=(n_pix, n_obs // 2 + 1)), dtype=dtype)
+    ref = og.spectrum_vjp(E.double().numpy(), dS.double().numpy(), 4.7e-20)
+    dE = lw.spectrum_fft_bwd(E.to(DEV), dS.to(DEV), 4.7e-20, prec).double().cpu().numpy()
+    err = np.max(np.abs(dE - ref)) / np.max(np.abs(ref))
+    print(f"{prec} 2^{lg}, {n_pix} pixels: rel err {err:.2e}")
+    assert err <= (1e-14 if prec == "fp64" else 1e-5)
