@@ -22,8 +22,8 @@
 // one XCD so that those partial lines merge in its L2.  For N <= L one kernel reads the traces
 // (k_fwd_row_direct), and columns longer than 256 points take the runtime-shaped k_fwd_cols.
 //
-// Adjoint path: N1 = 2^ceil(lg/2), N2 = 2^floor(lg/2), radix-4 Stockham passes between two
-// LDS buffers.
+// Adjoint path: the forward path's shapes with twiddles from tables (k_bwd_rows_fast, k_bwd_cols_fast); for few pixels and
+// lengths without such shapes N1 = 2^ceil(lg/2), N2 = 2^floor(lg/2), radix-4 Stockham passes between two LDS buffers.
 #include "lw_internal.h"
 
 #include <algorithm>
@@ -237,8 +237,8 @@ __device__ __forceinline__ T2 mul_mi(T2 a)  // a * (-i)
     return r;
 }
 
-// a * W_16^M, W_16 = exp(-2 pi i / 16), 0 <= M < 16, exact special cases
-template <int M, typename T2>
+// a * W_16^M, W_16 = exp(-2 pi i / 16), 0 <= M < 16, exact special cases (EXACT: the adjoint's)
+template <int M, bool EXACT, typename T2>
 __device__ __forceinline__ T2 w16mul(T2 a)
 {
     using T = decltype(a.x);
@@ -260,10 +260,22 @@ __device__ __forceinline__ T2 w16mul(T2 a)
     } else {
         constexpr double cs[16] = {1, c1, h, s1, 0, -s1, -h, -c1, -1, -c1, -h, -s1, 0, s1, h, c1};
         constexpr double sn[16] = {0, s1, h, c1, 1, c1, h, s1, 0, -s1, -h, -c1, -1, -c1, -h, -s1};
-        const T wr = (T)cs[m], wi = (T)(-sn[m]);  // exp(-2 pi i m/16)
+        constexpr T wr = (T)cs[m], wi = (T)(-sn[m]);  // exp(-2 pi i m/16)
+        if constexpr (!EXACT) {
+            T2 r;
+            r.x = a.x * wr - a.y * wi;
+            r.y = a.x * wi + a.y * wr;
+            return r;
+        }
+        // EXACT: and what their rounding left out (the double constants' own residuals for double).  The same constant meets
+        // an element in several passes, so that its error adds up rather than averages out.
+        constexpr double c1e = 1.7645047084336677e-17, s1e = -1.0050772696461588e-17, he = -4.833646656726457e-17;
+        constexpr double ce[16] = {0, c1e, he, s1e, 0, -s1e, -he, -c1e, 0, -c1e, -he, -s1e, 0, s1e, he, c1e};
+        constexpr double se[16] = {0, s1e, he, c1e, 0, c1e, he, s1e, 0, -s1e, -he, -c1e, 0, -c1e, -he, -s1e};
+        constexpr T er = (T)((cs[m] - (double)wr) + ce[m]), ei = (T)((-sn[m] - (double)wi) - se[m]);
         T2 r;
-        r.x = a.x * wr - a.y * wi;
-        r.y = a.x * wi + a.y * wr;
+        r.x = fma(a.x, wr, fma(a.x, er, fma(-a.y, ei, -(a.y * wi))));
+        r.y = fma(a.x, wi, fma(a.x, ei, fma(a.y, er, a.y * wr)));
         return r;
     }
 }
@@ -279,7 +291,7 @@ __device__ __forceinline__ void dft4v(T2 &v0, T2 &v1, T2 &v2, T2 &v3)
 }
 
 // in-place DFT of R points, natural order in and out: X[k] = sum_r v[r] exp(-2 pi i r k / R)
-template <int R, typename T2>
+template <int R, bool EXACT = false, typename T2>
 __device__ __forceinline__ void dftR(T2 *v)
 {
     if constexpr (R == 2) {
@@ -292,9 +304,9 @@ __device__ __forceinline__ void dftR(T2 *v)
         // inner 4-point DFTs over v[2b + a], twiddle W_8^{a k1}, outer 2-point over a
         dft4v(v[0], v[2], v[4], v[6]);
         dft4v(v[1], v[3], v[5], v[7]);
-        v[3] = w16mul<2>(v[3]);
-        v[5] = w16mul<4>(v[5]);
-        v[7] = w16mul<6>(v[7]);
+        v[3] = w16mul<2, EXACT>(v[3]);
+        v[5] = w16mul<4, EXACT>(v[5]);
+        v[7] = w16mul<6, EXACT>(v[7]);
         T2 x[8];
 #pragma unroll
         for (int k1 = 0; k1 < 4; ++k1) {
@@ -311,15 +323,15 @@ __device__ __forceinline__ void dftR(T2 *v)
         dft4v(v[1], v[5], v[9], v[13]);
         dft4v(v[2], v[6], v[10], v[14]);
         dft4v(v[3], v[7], v[11], v[15]);
-        v[5] = w16mul<1>(v[5]);
-        v[6] = w16mul<2>(v[6]);
-        v[7] = w16mul<3>(v[7]);
-        v[9] = w16mul<2>(v[9]);
-        v[10] = w16mul<4>(v[10]);
-        v[11] = w16mul<6>(v[11]);
-        v[13] = w16mul<3>(v[13]);
-        v[14] = w16mul<6>(v[14]);
-        v[15] = w16mul<9>(v[15]);
+        v[5] = w16mul<1, EXACT>(v[5]);
+        v[6] = w16mul<2, EXACT>(v[6]);
+        v[7] = w16mul<3, EXACT>(v[7]);
+        v[9] = w16mul<2, EXACT>(v[9]);
+        v[10] = w16mul<4, EXACT>(v[10]);
+        v[11] = w16mul<6, EXACT>(v[11]);
+        v[13] = w16mul<3, EXACT>(v[13]);
+        v[14] = w16mul<6, EXACT>(v[14]);
+        v[15] = w16mul<9, EXACT>(v[15]);
         T2 x[16];
 #pragma unroll
         for (int k1 = 0; k1 < 4; ++k1) {
@@ -728,7 +740,7 @@ __device__ __forceinline__ void twiddle_apply(T2 *v, T2 w1)
 // First Stockham pass (Ns = 1, no twiddles) from registers: the thread's butterflies are
 // j = j0 + JS s (s < NB), and X[s + NB r] holds element j + r (sequence length / RP).
 // The RP outputs of a butterfly are adjacent (inside one pad period of the row layout).
-template <int RP, int NB, int JS, typename T2, typename At>
+template <int RP, int NB, int JS, bool EXACT = false, typename T2, typename At>
 __device__ __forceinline__ void first_pass(const T2 *X, T2 *buf, const At &at, int j0)
 {
     T2 *pw = buf + at(j0 * RP);
@@ -737,7 +749,7 @@ __device__ __forceinline__ void first_pass(const T2 *X, T2 *buf, const At &at, i
         T2 v[RP];
 #pragma unroll
         for (int r = 0; r < RP; ++r) v[r] = X[s + NB * r];
-        dftR<RP>(v);
+        dftR<RP, EXACT>(v);
 #pragma unroll
         for (int r = 0; r < RP; ++r) pw[At::far(JS * s * RP) + At::near(r)] = v[r];
     }
@@ -809,6 +821,75 @@ __device__ __forceinline__ void last_pass(const T2 *buf, const At &at, int j, co
     }
 }
 
+// The same passes with every twiddle from a table, for the adjoint: a power formed as a product chain has the errors of its
+// factors and products, and two transforms in a row add them up.  Root mean square error of 10 pixels of 2^16 points in
+// FP64 6.1e-16 with the chains, 3.8e-16 so (radix 4 with tables of all powers 3.7e-16), of 64 in single precision 5.3e-7
+// and 2.2e-7 (2.2e-7); time of 256 pixels in FP64 500 and 507 us, of 256 pixels of 2^18 points in single precision 1065
+// and 1133 us (with a quarter of a circle in the table 3 % more: the turns by 90 degrees).  The table holds the first
+// half of W_L^q (L = 2^LGTAB: 2^(LGTAB - 1) entries); the other half is its negative.
+template <int LGTAB, typename T2>
+__device__ __forceinline__ T2 half_table(const T2 *tab, int q)
+{
+    T2 w = tab[tabi(q & ((1 << (LGTAB - 1)) - 1))];
+    const bool neg = (q >> (LGTAB - 1)) & 1;
+    w.x = neg ? -w.x : w.x;
+    w.y = neg ? -w.y : w.y;
+    return w;
+}
+template <typename T>
+constexpr int tab_entries_half()
+{
+    return 1 << (FastCfg<T>::kLgL - 1);
+}
+// v[r] *= W_L^(r q) for 1 <= r < RP
+template <int RP, int LGTAB, typename T2>
+__device__ __forceinline__ void twiddle_table(T2 *v, const T2 *tab, int q)
+{
+#pragma unroll
+    for (int r = 1; r < RP; ++r) v[r] = cmul(v[r], half_table<LGTAB>(tab, r * q));
+}
+template <int LGRP, int LGN, int LGNS, int NB, int JS, int LGTAB, typename T2, typename At>
+__device__ __forceinline__ void mid_pass_q(T2 *buf, const At &at, int j0, const T2 *tab)
+{
+    constexpr int RP = 1 << LGRP, M = (1 << LGN) / RP, NS = 1 << LGNS;
+    T2 v[NB][RP];
+    const T2 *pr = buf + at(j0);
+#pragma unroll
+    for (int s = 0; s < NB; ++s)
+#pragma unroll
+        for (int r = 0; r < RP; ++r) v[s][r] = pr[At::far(JS * s + r * M)];
+    __syncthreads();
+    const int k = j0 & (NS - 1);
+    T2 *pw = buf + at((j0 - k) * RP + k);
+#pragma unroll
+    for (int s = 0; s < NB; ++s) {
+        if constexpr (LGNS > 0) twiddle_table<RP, LGTAB>(v[s], tab, k << (LGTAB - LGNS - LGRP));
+        dftR<RP, true>(v[s]);
+#pragma unroll
+        for (int r = 0; r < RP; ++r) pw[At::far(JS * s * RP + r * NS)] = v[s][r];
+    }
+    __syncthreads();
+}
+template <int LGRP, int LGN, int LGNS, int LGEND, int LGTAB, typename T2, typename At>
+__device__ __forceinline__ void mid_passes_q(T2 *buf, const At &at, int j, const T2 *tab)
+{
+    if constexpr (LGNS < LGEND) {
+        mid_pass_q<LGRP, LGN, LGNS, 1, 1, LGTAB>(buf, at, j, tab);
+        mid_passes_q<LGRP, LGN, LGNS + LGRP, LGEND, LGTAB>(buf, at, j, tab);
+    }
+}
+// out[r] = X[j + Ns r] for q = j, X[j + Ns ((r + 1) mod RP)] for q = j + Ns (in units of the transform's own length)
+template <int LGRP, int LGN, int LGTAB, typename T2, typename At>
+__device__ __forceinline__ void last_pass_q(const T2 *buf, const At &at, int j, int q, const T2 *tab, T2 *out)
+{
+    constexpr int RP = 1 << LGRP, NS = (1 << LGN) / RP;
+    const T2 *pr = buf + at(j);
+#pragma unroll
+    for (int r = 0; r < RP; ++r) out[r] = pr[At::far(r * NS)];
+    if constexpr (NS > 1) twiddle_table<RP, LGTAB>(out, tab, q << (LGTAB - LGN));
+    dftR<RP, true>(out);
+}
+
 // exp(-2 pi i q / N) for 0 <= q (reduced mod N = 2^lg), argument exact in the working type
 template <typename T2>
 __device__ __forceinline__ T2 phasor_mod(int64_t q, int64_t N, double inv_n);
@@ -836,8 +917,8 @@ constexpr int cols_lget(int lg1)
 }
 
 // pass A: C = 2^LGC adjacent columns (of N1 = 2^LG1 points) of one packed transform of one pixel
-// pair per block
-template <typename T, int LG1>
+// pair per block (ADJ: for the adjoint, with twiddles from tables and directly)
+template <typename T, int LG1, bool ADJ>
 __global__ __launch_bounds__(256) void k_fwd_cols_fast(const T *__restrict__ E, typename C2<T>::type *__restrict__ Y,
                                                        FwdShape sh, T sc)
 {
@@ -849,7 +930,8 @@ __global__ __launch_bounds__(256) void k_fwd_cols_fast(const T *__restrict__ E, 
     constexpr int LGR0 = LG1 % LGET ? LG1 % LGET : LGET, NB0 = ET >> LGR0;
     constexpr bool kLds = LG1 > LGET;
     __shared__ T2 buf[kLds ? (C << LG1) : 1];
-    __shared__ T2 tab[tab_slots(tab_entries_cols<T>())];
+    constexpr int kTab = ADJ ? tab_entries_half<T>() : tab_entries_cols<T>();
+    __shared__ T2 tab[tab_slots(kTab)];
     const int tid = threadIdx.x, c = tid & (C - 1), g = tid >> LGC;
     const int t = blockIdx.y;
     const int64_t pl = blockIdx.z, p = sh.pair0 + pl;
@@ -866,29 +948,47 @@ __global__ __launch_bounds__(256) void k_fwd_cols_fast(const T *__restrict__ E, 
         X[m].y = im ? im[n] : (T)0;
     }
     if constexpr (kLds) {  // while the loads are in flight
-        for (int q = tid; q < tab_entries_cols<T>(); q += 256) tab[tabi(q)] = twiddle<T2>(q, 1 << LGTAB);
+        for (int q = tid; q < kTab; q += 256) tab[tabi(q)] = twiddle<T2>(q, 1 << LGTAB);
     }
     T2 O[ET];
     if constexpr (!kLds) {
 #pragma unroll
         for (int r = 0; r < ET; ++r) O[r] = X[r];
-        dftR<ET>(O);
+        dftR<ET, ADJ>(O);
     } else {
         const AtCol<LGC> at{c};
-        first_pass<1 << LGR0, NB0, TPC>(X, buf, at, g);
+        first_pass<1 << LGR0, NB0, TPC, ADJ>(X, buf, at, g);
         __syncthreads();
-        mid_passes<LGET, LG1, LGR0, LG1 - LGET, LGTAB>(buf, at, g, tab);
-        last_pass<LGET, LG1, LGTAB>(buf, at, g, tab, O);
+        if constexpr (ADJ) {
+            mid_passes_q<LGET, LG1, LGR0, LG1 - LGET, LGTAB>(buf, at, g, tab);
+            last_pass_q<LGET, LG1, LGTAB>(buf, at, g, g, tab, O);
+        } else {
+            mid_passes<LGET, LG1, LGR0, LG1 - LGET, LGTAB>(buf, at, g, tab);
+            last_pass<LGET, LG1, LGTAB>(buf, at, g, tab, O);
+        }
     }
     // sc W_N^{n2 k1} for k1 = g + TPC r: bw (W_N^{n2 TPC})^r, the power a product chain of depth
     // <= LGET, bw = sc W_N^{n2 g} (the trace scale sc rides on the twiddle)
     const double inv_n = ldexp(1.0, -sh.lg);
+    T2 *Yt = Y + (pl * 3 + t) * N;
+    if constexpr (ADJ) {  // r = 4 b + a: one product of two exact factors
+        T2 lo[4];
+#pragma unroll
+        for (int v = 1; v < 4 && v < ET; ++v) lo[v] = phasor_mod<T2>((int64_t)n2 * TPC * v, N, inv_n);
+#pragma unroll
+        for (int r = 0; r < ET; r += 4) {
+            const T2 hi = phasor_mod<T2>((int64_t)n2 * (g + TPC * r), N, inv_n);
+#pragma unroll
+            for (int v = 0; v < 4 && r + v < ET; ++v)
+                Yt[((g + TPC * (r + v)) << sh.lg2) + n2] = cmul(O[r + v], v ? cmul(hi, lo[v]) : hi);
+        }
+        return;
+    }
     T2 bw = phasor_mod<T2>((int64_t)n2 * g, N, inv_n);
     bw.x *= sc;
     bw.y *= sc;
     T2 sp[ET];
     powers<ET>(phasor_mod<T2>((int64_t)n2 * TPC, N, inv_n), sp);
-    T2 *Yt = Y + (pl * 3 + t) * N;
     Yt[(g << sh.lg2) + n2] = cmul(O[0], bw);
 #pragma unroll
     for (int r = 1; r < ET; ++r) Yt[((g + TPC * r) << sh.lg2) + n2] = cmul(O[r], cmul(bw, sp[r]));
@@ -1232,7 +1332,7 @@ __global__ __launch_bounds__(256) void k_fft_cols_inv(const typename C2<T>::type
 // pass C (k_bwd_cols_fast): the columns back, real and imaginary parts to the two packed components.
 //
 // Three reads and three writes of the traces' size, with nothing in LDS but a row: 256 pixels of 2^16 points in FP64
-// 1022 us with two LDS buffers, radix 4 and a sine/cosine pair per element of every pass -> 510 us.
+// 941 us with two LDS buffers, radix 4 and a sine/cosine pair per element of every pass -> 507 us.
 template <typename T>
 __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_waves_per_eu(FastCfg<T>::kRowWaves))) void k_bwd_rows_fast(
     typename C2<T>::type *__restrict__ Y, const T *__restrict__ dS, FwdShape sh)
@@ -1243,7 +1343,7 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     constexpr int REM = LGL % LGR;
     constexpr int NT = L / R;
     __shared__ T2 buf[L + L / R];
-    __shared__ T2 tab[tab_slots(tab_entries_rows<T>())];
+    __shared__ T2 tab[tab_slots(tab_entries_half<T>())];
     __shared__ T2 tw[2][R];  // the rows' W_N^{NT r k}
     const int tid = threadIdx.x;
     const int N1 = 1 << sh.lg1;
@@ -1257,10 +1357,10 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     const bool two = ka != kb, row0 = ka == 0;
     const int rho = row0 ? ((NT - tid) & (NT - 1)) : NT - 1 - tid;
     const double inv_n = ldexp(1.0, -sh.lg);
-    for (int q = tid; q < tab_entries_rows<T>(); q += NT) tab[tabi(q)] = twiddle<T2>(q, L);
+    for (int q = tid; q < tab_entries_half<T>(); q += NT) tab[tabi(q)] = twiddle<T2>(q, L);
     if (tid < 2 * R) tw[tid >> LGR][tid & (R - 1)] = phasor_mod<T2>((int64_t)NT * (tid & (R - 1)) * (tid < R ? ka : kb), N, inv_n);
     __syncthreads();
-    const T2 wa = tab[tabi(tid)], wb = row0 && tid == 0 ? twiddle<T2>(1, R) : tab[tabi(rho)];
+    const int qb = row0 && tid == 0 ? NT : rho;  // rotated outputs
     const AtRow<LGR> at;
     // h dS of output tid + NT q of row ka and its partner
     T d0[R], d1[R];
@@ -1272,8 +1372,6 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
         d1[q] = has1 ? h * dS[m1 * ldS + js] : (T)0;
     }
     // inverse twiddles W_N^{-n2 k} of a row, n2 = tid + NT r: the conjugate of base tw[r].  tw is the block's, formed once
-    // (powers of a step multiplied up by every thread: 784 us instead of 779 at the size above, and an error of
-    // 9.1e-16 instead of 8.9e-16)
     const T2 base_a = phasor_mod<T2>((int64_t)tid * ka, N, inv_n), base_b = phasor_mod<T2>((int64_t)tid * kb, N, inv_n);
     auto store_row = [&](T2 *dst, const T2 *O, T2 base, const T2 *step) {  // conjugates of O times the forward twiddles
 #pragma unroll
@@ -1291,26 +1389,27 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
     T2 X[R];
     auto passes = [&](const T2 *in, int j0, const T2 *next) {  // next: the row to load into X meanwhile, or null
         __syncthreads();  // the previous row's last pass has read the buffer
-        first_pass<R, 1, 1>(in, buf, at, j0);
+        first_pass<R, 1, 1, true>(in, buf, at, j0);
         if (next) load_row_lanes<R, NT>(X, next, tid);
         __syncthreads();
-        if constexpr (REM > 0) mid_pass<REM, LGL, LGR, (L >> REM) / NT, NT, LGL>(buf, at, tid, tab);
-        mid_passes<LGR, LGL, LGR + REM, LGL - LGR, LGL>(buf, at, tid, tab);
+        int w = tid;  // opaque: the passes' twiddles are read where they are used
+        asm volatile("" : "+v"(w));
+        if constexpr (REM > 0) mid_pass_q<REM, LGL, LGR, (L >> REM) / NT, NT, LGL>(buf, at, w, tab);
+        mid_passes_q<LGR, LGL, LGR + REM, LGL - LGR, LGL>(buf, at, w, tab);
     };
     load_row_lanes<R, NT>(X, row_ptr(0, false), tid);
 #pragma unroll 1
     for (int tt = 0; tt < nt; ++tt) {
         const int t = (!has1 && tt == 1) ? 2 : tt;
         const T2 *after = tt + 1 < nt ? row_ptr(tt + 1, false) : nullptr;
-        // opaque per transform: keeps their powers and the addresses from being held through the loop
-        T2 w0 = wa, w1 = wb;
-        int u = tid, v = rho;
-        asm volatile("" : "+v"(w0.x), "+v"(w0.y), "+v"(w1.x), "+v"(w1.y), "+v"(u), "+v"(v));
+        // opaque per transform: keeps the twiddles and the addresses from being held through the loop
+        int u = tid, v = rho, qv = qb;
+        asm volatile("" : "+v"(u), "+v"(v), "+v"(qv));
         T2 A[R], B[R];
         passes(X, u, two ? row_ptr(tt, true) : nullptr);
-        last_pass_w<LGR, LGL>(buf, at, u, w0, A);
+        last_pass_q<LGR, LGL, LGL>(buf, at, u, u, tab, A);
         if (two) passes(X, u, nullptr);
-        last_pass_w<LGR, LGL>(buf, at, v, w1, B);
+        last_pass_q<LGR, LGL, LGL>(buf, at, v, qv, tab, B);
         // conj(G) of the outputs (Z0, Z1: d Z; Z2: sp Z + sm conj(partner)); partners: A[q] and B[R - 1 - q]
 #pragma unroll
         for (int q = 0; q < R; ++q) {
@@ -1324,13 +1423,13 @@ __global__ __launch_bounds__(FastCfg<T>::kRowThreads) __attribute__((amdgpu_wave
         }
         T2 O[R];
         passes(A, u, two ? nullptr : after);
-        asm volatile("" : "+v"(w0.x), "+v"(w0.y));
-        last_pass_w<LGR, LGL>(buf, at, u, w0, O);
+        asm volatile("" : "+v"(u));
+        last_pass_q<LGR, LGL, LGL>(buf, at, u, u, tab, O);
         store_row(Y + (pl * 3 + t) * N + (int64_t)ka * L, O, base_a, tw[0]);
         if (two) {
             passes(B, v, after);
-            asm volatile("" : "+v"(w0.x), "+v"(w0.y));
-            last_pass_w<LGR, LGL>(buf, at, u, w0, O);
+            asm volatile("" : "+v"(u));
+            last_pass_q<LGR, LGL, LGL>(buf, at, u, u, tab, O);
             store_row(Y + (pl * 3 + t) * N + (int64_t)kb * L, O, base_b, tw[1]);
         }
     }
@@ -1349,7 +1448,7 @@ __global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::typ
     constexpr int LGR0 = LG1 % LGET ? LG1 % LGET : LGET, NB0 = ET >> LGR0;
     constexpr bool kLds = LG1 > LGET;
     __shared__ T2 buf[kLds ? (C << LG1) : 1];
-    __shared__ T2 tab[tab_slots(tab_entries_cols<T>())];
+    __shared__ T2 tab[tab_slots(tab_entries_half<T>())];
     const int tid = threadIdx.x, c = tid & (C - 1), g = tid >> LGC;
     const int t = blockIdx.y;
     const int64_t pl = blockIdx.z, p = sh.pair0 + pl;
@@ -1360,7 +1459,7 @@ __global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::typ
     T *re = const_cast<T *>(re0), *im = const_cast<T *>(im0);
     const int n2 = blockIdx.x * C + c;
     if constexpr (kLds) {
-        for (int q = tid; q < tab_entries_cols<T>(); q += 256) tab[tabi(q)] = twiddle<T2>(q, 1 << LGTAB);
+        for (int q = tid; q < tab_entries_half<T>(); q += 256) tab[tabi(q)] = twiddle<T2>(q, 1 << LGTAB);
     }
     const T2 *Yt = Y + (pl * 3 + t) * N;
     T2 X[ET], O[ET];
@@ -1372,13 +1471,13 @@ __global__ __launch_bounds__(256) void k_bwd_cols_fast(const typename C2<T>::typ
     if constexpr (!kLds) {
 #pragma unroll
         for (int r = 0; r < ET; ++r) O[r] = X[r];
-        dftR<ET>(O);
+        dftR<ET, true>(O);
     } else {
         const AtCol<LGC> at{c};
-        first_pass<1 << LGR0, NB0, TPC>(X, buf, at, g);
+        first_pass<1 << LGR0, NB0, TPC, true>(X, buf, at, g);
         __syncthreads();
-        mid_passes<LGET, LG1, LGR0, LG1 - LGET, LGTAB>(buf, at, g, tab);
-        last_pass<LGET, LG1, LGTAB>(buf, at, g, tab, O);
+        mid_passes_q<LGET, LG1, LGR0, LG1 - LGET, LGTAB>(buf, at, g, tab);
+        last_pass_q<LGET, LG1, LGTAB>(buf, at, g, g, tab, O);
     }
 #pragma unroll
     for (int r = 0; r < ET; ++r) {
@@ -1409,13 +1508,13 @@ constexpr int64_t kMaxGridYZ = 65535;
 constexpr int kFastColsMaxLg1 = 8;
 template <typename T>
 using ColsKernel = void (*)(const T *, typename C2<T>::type *, FwdShape, T);
-template <typename T, int LG1>
+template <typename T, bool ADJ, int LG1>
 ColsKernel<T> pick_cols_fast(int lg1)
 {
     if constexpr (LG1 > kFastColsMaxLg1)
         return nullptr;
     else
-        return lg1 == LG1 ? k_fwd_cols_fast<T, LG1> : pick_cols_fast<T, LG1 + 1>(lg1);
+        return lg1 == LG1 ? k_fwd_cols_fast<T, LG1, ADJ> : pick_cols_fast<T, ADJ, LG1 + 1>(lg1);
 }
 
 template <typename T>
@@ -1457,7 +1556,7 @@ lw_status run_fft(const T *E, int64_t n_pix, int64_t n_obs, double dt_obs, T *S,
     const int64_t batch = std::min<int64_t>({pairs, (int64_t)(ws_bytes / per_pair_bytes<T>(n_obs)), kMaxGridYZ});
     T2 *Y = (T2 *)ws;
     // N > L: the compile-time passes (pass A for columns of up to 2^kFastColsMaxLg1 points)
-    const ColsKernel<T> cols = pick_cols_fast<T, 1>(sh.lg1);
+    const ColsKernel<T> cols = pick_cols_fast<T, false, 1>(sh.lg1);
     const int lgC_fast = 8 + cols_lget<T>(sh.lg1) - sh.lg1;
     const unsigned gx_a = (unsigned)(1u << (sh.lg2 - (cols ? lgC_fast : sh.lgC))), gx_b = (unsigned)((1 << sh.lg1) / 2 + 1);
     for (int64_t p0 = 0; p0 < pairs; p0 += batch) {
@@ -1476,18 +1575,19 @@ lw_status run_fft(const T *E, int64_t n_pix, int64_t n_obs, double dt_obs, T *S,
 
 // Whether the adjoint has so few pixels that the runtime-shaped passes are faster: theirs are many small blocks, whereas a
 // block of k_bwd_rows_fast takes its row pairs' twelve transforms one after the other (some 25 us, however few there
-// are).  Lines between measured sizes; us with the runtime-shaped passes against the others:
-//   2^13 points FP32, N1 = 2:  32 pixels 31.1, 31.9;  64 44.1, 37.0    2^12 FP64:  32 26.5, 27.2;  64 33.8, 31.1
-//   2^14 points FP32, N1 = 4:   5 pixels 28.1, 42.5;  64 49.5, 55.1    2^13 FP64:  16 27.1, 38.0;  64 46.5, 48.1
-//   2^16 points FP32, N1 = 16: 16 pixels 52.1, 59.5;  32 90.1, 58.9    2^15 FP64:  16 46.7, 52.7;  32 79.4, 52.6
-//   2^17 points FP32, N1 = 32:  4 pixels 49.5, 51.5;   8 67.9, 57.7    2^16 FP64:   5 42.8, 48.0;   8 50.4, 49.6
-//   2^18 points FP32, N1 = 64:  1 pixel  42.7, 36.5                    2^17 FP64:   1 36.0, 31.7
+// are).  Lines between measured sizes; us with the runtime-shaped passes and the others:
+//   2^13 points FP32, N1 = 2:  32 pixels 31.1, 38.7;  64 44.1, 42.3    2^12 FP64:  32 26.8, 29.3;  64 34.0, 33.3
+//   2^14 points FP32, N1 = 4:   5 pixels 28.0, 52.4;  64 49.5, 65.8    2^13 FP64:  16 27.3, 42.4;  64 46.3, 52.6
+//   2^16 points FP32, N1 = 16: 16 pixels 52.2, 69.8;  32 90.2, 69.4    2^15 FP64:  16 46.8, 58.2;  32 79.5, 57.8
+//   2^17 points FP32, N1 = 32:  8 pixels 68.1, 70.3;  16 122,  74.0    2^16 FP64:   8 50.5, 55.3;  16 77.6, 58.5
+//   2^18 points FP32, N1 = 64:  2 pixels 56.2, 63.5;   4 75.4, 72.0    2^17 FP64:   2 48.3, 48.9;   4 66.3, 56.4
+//   2^19 points FP32, N1 = 128: 1 pixel  63.8, 50.9                    2^18 FP64:   1 49.6, 42.5
 template <typename T>
 bool bwd_few(int64_t n_pix, int lg)
 {
     const int lg1 = lg - FwdCfg<T>::kLgRow;
     const int64_t bytes = ((n_pix + 1) / 2) * (int64_t(sizeof(T)) << lg), mib = int64_t(1) << 20;
-    return lg1 == 1 ? bytes < mib : lg1 <= 4 ? bytes <= 2 * mib : lg1 == 5 && bytes < 2 * mib;
+    return lg1 == 1 ? bytes < mib : lg1 <= 5 ? bytes <= 2 * mib : lg1 == 6 && bytes <= mib;
 }
 
 template <typename T>
@@ -1506,7 +1606,7 @@ lw_status run_fft_bwd(const T *E, const T *dS, int64_t n_pix, int64_t n_obs, dou
         f.lg2 = Cfg::kLgRow;
         f.lg1 = lg - f.lg2;
         f.lgC = 8 + cols_lget<T>(f.lg1) - f.lg1;
-        const ColsKernel<T> cols = pick_cols_fast<T, 1>(f.lg1);
+        const ColsKernel<T> cols = pick_cols_fast<T, true, 1>(f.lg1);
         const unsigned gx_c = 1u << (f.lg2 - f.lgC), gx_r = (unsigned)((1 << f.lg1) / 2 + 1);
         const int64_t pairs = (n_pix + 1) / 2;
         const int64_t batch = std::min<int64_t>({pairs, (int64_t)(ws_bytes / per_pair_bytes<T>(n_obs)), kMaxGridYZ});
