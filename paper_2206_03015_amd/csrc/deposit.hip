@@ -1377,10 +1377,11 @@ size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples)
     return ws_bytes_for(n_particles, n_samples);
 }
 
-// The pusher forms a sample's base in 0.027 us of its chain's time (four wavefronts a block forming samples), the
-// pre-pass reads n_p samples in the same time at about 1500 particles: 1000 x 10001 samples 11.56 -> 11.7 ms with the
-// adjoint, 10000 x 20001 29.1 -> 27.7.
-constexpr int64_t kPrePushed = 2048;
+// Particles from which the pusher leaves the arrival bases: its chains take longer for them, the pre-pass reads every
+// sample again.  Deposit of pushed trajectories of 10001 samples, bases from the pre-pass and from the pusher: 500
+// particles 2.82 and 2.88 ms, 1000 2.84 and 2.82, 1500 3.10 and 2.99, 2048 3.22 and 2.99, 8192 4.57 and 3.24; of 1001
+// samples 1500 464 and 456 us, 8192 833 and 668.
+constexpr int64_t kPrePushed = 1500;
 
 DepositPre deposit_pre(void *ws, int64_t n_p, const lw_grid_t *gr)
 {

@@ -1,4 +1,4 @@
-"""Short pushed trajectories and spans of 2048 particles and more, whose arrival bases and flags the pusher leaves: as the
+"""Short pushed trajectories and spans of 1500 particles and more, whose arrival bases and flags the pusher leaves: as the
 deposit of the stored samples.  Tolerances as in test_gpu_boris_stream.py (the order of the sums alone differs)."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
 
 
-@pytest.mark.parametrize("n_p, n_samples, span, prec", [(2048, 1, 0, "fp64"), (2048, 2, 0, "mixed"), (2100, 7, 0, "fp64"), (2100, 9, 2, "fp64"),
+@pytest.mark.parametrize("n_p, n_samples, span, prec", [(1499, 2, 0, "fp64"), (1500, 1, 0, "fp64"), (1500, 2, 0, "mixed"), (2100, 7, 0, "fp64"), (2100, 9, 2, "fp64"),
                                                         (2079, 301, 0, "mixed"), (2100, 1025, 9, "fp64"), (2100, 3001, 1000, "mixed"),
                                                         (32768 + 40, 6, 0, "fp64")])
 def test_short_spans(n_p, n_samples, span, prec):
