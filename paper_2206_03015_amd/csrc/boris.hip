@@ -296,9 +296,10 @@ constexpr int kStateDoubles = 9;  // of the pusher, carried between spans
 //   * quotients by constants are a product with the rounded reciprocal and one residual correction
 //     (Markstein: the correctly rounded quotient), the other quotients and the square roots
 //     Newton/Goldschmidt iterations without the range scaling that arguments of this size do not
-//     need, and a root's reciprocal comes from the root's own iteration.
+//     need, and a root's reciprocal comes from the root's own iteration (batches that leave the range of these forms
+//     take plain roots and quotients).
 // All of these round as the plain expressions do, so the samples keep their bits.  A step takes 0.47 us
-// inside the pulse and 0.08 us outside: 17.0 ms at first, 10.4 with the second wavefront and the paired
+// inside the pulse and 0.08 us outside: 17.3 ms at first, 10.4 with the second wavefront and the paired
 // lanes, 5.0 now for 4000 particles x 20001 samples.  What is left is the latency of the dependent chain.
 constexpr int kPushSteps = 8;                  // steps per hand-over of a paired block (32 particles)
 constexpr int64_t kPairParticles = 32 * 1024;  // 1024 SIMDs
@@ -485,8 +486,7 @@ __device__ __forceinline__ void push_sample_fast(const PushState<double> &S, dou
     push_sample(S, ig, rr, bb, aa);
 }
 
-// state of one sample in the hand-over buffer: x, y, z, E_x, u (an odd pitch: the particles' entries
-// start in different banks)
+// v of the lane that CTRL names, 0 where there is none
 template <int CTRL>
 __device__ __forceinline__ double dpp_double(double v)
 {
@@ -496,6 +496,8 @@ __device__ __forceinline__ double dpp_double(double v)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// The hand-over buffer: x, y, z, E_x, u of S samples of P particles (an odd pitch: the particles' entries start in
+// different banks)
 template <int P, int S>
 struct PushLds {
     static constexpr int kPitch = 8 * S + 1;

@@ -39,7 +39,7 @@ inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 // workspace of a plan.  Forward: deposit scratch (arrival bases of the span), pusher states, the
 // particles' max |r|^2, r, beta, beta_dot of the span.  Adjoint (bwd): tangent states, pusher
 // states, the particles' max |r|^2, the span's samples and their gradients.
-size_t plan_bytes(int64_t B, int64_t L, int prec, bool bwd)
+size_t plan_bytes(int64_t B, int64_t L, bool bwd)
 {
     const size_t arr = align256((size_t)B * (size_t)L * 3 * sizeof(double));
     const size_t rb = align256((size_t)B * sizeof(double));
@@ -51,25 +51,25 @@ size_t plan_bytes(int64_t B, int64_t L, int prec, bool bwd)
 size_t per_sample_bytes(bool bwd) { return bwd ? 144 : 80; }
 
 // longest span (<= lmax) of B particles within `bytes` (0 if not even one sample fits)
-int64_t fit_span(int64_t B, int64_t lmax, size_t bytes, int prec, bool bwd)
+int64_t fit_span(int64_t B, int64_t lmax, size_t bytes, bool bwd)
 {
-    const size_t fixed = plan_bytes(B, 1, prec, bwd);
+    const size_t fixed = plan_bytes(B, 1, bwd);
     if (fixed > bytes) return 0;
     const size_t per_sample = (size_t)B * per_sample_bytes(bwd);
     int64_t L = std::min<int64_t>(lmax, 1 + (int64_t)((bytes - fixed) / per_sample));
-    while (L > 1 && plan_bytes(B, L, prec, bwd) > bytes) --L;
+    while (L > 1 && plan_bytes(B, L, bwd) > bytes) --L;
     return L;
 }
 
 // largest batch (<= bmax) with spans of L samples within `bytes` (0 if none)
-int64_t fit_batch(int64_t bmax, int64_t L, size_t bytes, int prec, bool bwd)
+int64_t fit_batch(int64_t bmax, int64_t L, size_t bytes, bool bwd)
 {
-    const size_t fixed = plan_bytes(1, L, prec, bwd);
+    const size_t fixed = plan_bytes(1, L, bwd);
     if (fixed > bytes) return 0;
     const size_t per_particle_bytes = (size_t)L * per_sample_bytes(bwd) + kStateBytes + 3 * sizeof(double) +
                                       (bwd ? kTanStateBytes : 0);
     int64_t B = std::min<int64_t>(bmax, 1 + (int64_t)((bytes - fixed) / per_particle_bytes));
-    while (B > 1 && plan_bytes(B, L, prec, bwd) > bytes) --B;
+    while (B > 1 && plan_bytes(B, L, bwd) > bytes) --B;
     return B;
 }
 
@@ -84,35 +84,35 @@ __global__ void k_zero(double *__restrict__ p, int64_t n)
 // Batch and span from the workspace: batches of min(n_p, kFillParticles) particles over the
 // longest spans that fit (whole trajectories when they do); spans shorter than kMinSpan give
 // way to smaller batches; a requested span fixes L and leaves the batch to the workspace.
-BorisPlan boris_plan_fit(int64_t n_p, int64_t ns, int64_t span_req, size_t ws_bytes, int prec, bool bwd)
+BorisPlan boris_plan_fit(int64_t n_p, int64_t ns, int64_t span_req, size_t ws_bytes, bool bwd)
 {
     const int64_t b0 = std::max<int64_t>(1, std::min<int64_t>(n_p, bwd ? kFillParticlesBwd : kFillParticles));
     const int64_t lmax = std::min<int64_t>(ns, kMaxSpan);
     const int64_t lmin = std::min<int64_t>(lmax, 2);  // a span must advance (one interval at least)
     if (span_req > 0) {
         const int64_t L = std::max<int64_t>(lmin, std::min<int64_t>(span_req, lmax));
-        return {fit_batch(b0, L, ws_bytes, prec, bwd), L};
+        return {fit_batch(b0, L, ws_bytes, bwd), L};
     }
-    const int64_t L0 = fit_span(b0, lmax, ws_bytes, prec, bwd);
+    const int64_t L0 = fit_span(b0, lmax, ws_bytes, bwd);
     if (L0 >= std::min<int64_t>(lmax, kMinSpan)) return {b0, L0};
     const int64_t Lm = std::min<int64_t>(lmax, kMinSpan);
-    const int64_t B = fit_batch(b0, Lm, ws_bytes, prec, bwd);
+    const int64_t B = fit_batch(b0, Lm, ws_bytes, bwd);
     if (B >= 1) return {B, Lm};
-    const int64_t L1 = fit_span(1, lmax, ws_bytes, prec, bwd);
+    const int64_t L1 = fit_span(1, lmax, ws_bytes, bwd);
     if (L1 >= lmin) return {1, L1};
     return {0, 0};
 }
 
-BorisPlan boris_plan_default(int64_t n_p, int64_t ns, int prec, bool bwd)
+BorisPlan boris_plan_default(int64_t n_p, int64_t ns, bool bwd)
 {
-    const BorisPlan p = boris_plan_fit(n_p, ns, 0, kBatchBytes, prec, bwd);
+    const BorisPlan p = boris_plan_fit(n_p, ns, 0, kBatchBytes, bwd);
     // a budget too small for even one particle's two-sample span cannot happen at 16 GiB
     return p.batch > 0 ? p : BorisPlan{1, std::min<int64_t>(ns, 2)};
 }
 
-size_t boris_plan_ws_bytes(const BorisPlan &p, int prec, bool bwd)
+size_t boris_plan_ws_bytes(const BorisPlan &p, bool bwd)
 {
-    return plan_bytes(std::max<int64_t>(p.batch, 1), p.span, prec, bwd);
+    return plan_bytes(std::max<int64_t>(p.batch, 1), p.span, bwd);
 }
 
 lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec, int fmask, int geom,
@@ -129,7 +129,7 @@ lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec
         return launch_deposit(&sub, gr, prec, fmask, geom, accumulate, E, diag, ws, ws_bytes, s, 0, nullptr, acc_mode,
                               det);
     }
-    const BorisPlan P = boris_plan_fit(n_p, ns, t->span, ws_bytes, prec);
+    const BorisPlan P = boris_plan_fit(n_p, ns, t->span, ws_bytes);
     if (P.batch < 1 || (ns > 1 && P.span < 2)) return fail(LW_E_WORKSPACE, "lw_deposit_td: workspace holds no span");
     const size_t dep_bytes = align256(deposit_ws_bytes(P.batch, P.span));
     char *p = (char *)ws + dep_bytes;
@@ -184,7 +184,7 @@ lw_status launch_deposit_bwd_boris(const lw_traj_t *t, const lw_grid_t *gr, int 
         k_zero<<<(int)std::min<int64_t>((n_p + 255) / 256, 65536), 256, 0, s>>>(grad_a0, n_p);
         return check_launch("lw_deposit_td_bwd_boris");
     }
-    const BorisPlan P = boris_plan_fit(n_p, ns, t->span, ws_bytes, LW_PREC_FP64, true);
+    const BorisPlan P = boris_plan_fit(n_p, ns, t->span, ws_bytes, true);
     if (P.batch < 1 || P.span < 2) return fail(LW_E_WORKSPACE, "lw_deposit_td_bwd_boris: workspace holds no span");
     char *p = (char *)ws;
     double *tstate = (double *)p;

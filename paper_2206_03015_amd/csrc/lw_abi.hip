@@ -218,10 +218,9 @@ size_t lw_workspace_bytes(int which, int64_t n_a, int64_t n_b, int prec)
     case LW_WS_DIRECT_FD_BWD:
         return direct_fd_ws_bytes(n_a, n_b);
     case LW_WS_DEPOSIT_BORIS:
-        return n_b >= 1 ? boris_plan_ws_bytes(boris_plan_default(n_a, n_b, prec), prec) : 0;
+        return n_b >= 1 ? boris_plan_ws_bytes(boris_plan_default(n_a, n_b)) : 0;
     case LW_WS_DEPOSIT_BWD_BORIS:
-        return n_b >= 1 ? boris_plan_ws_bytes(boris_plan_default(n_a, n_b, LW_PREC_FP64, true), LW_PREC_FP64, true)
-                        : 0;
+        return n_b >= 1 ? boris_plan_ws_bytes(boris_plan_default(n_a, n_b, true), true) : 0;
     case LW_WS_DEPOSIT_DET_ACC:
         return n_a >= 0 && n_b >= 0 ? det_acc_bytes(n_a, n_b) : 0;
     default:
@@ -261,11 +260,11 @@ static lw_status deposit_entry(const char *fn, const lw_traj_t *traj, const lw_g
     }
     if (boris) {
         const bool work = traj->n_particles > 0 && grid->n_pix > 0;
-        const BorisPlan plan = boris_plan_fit(traj->n_particles, traj->n_samples, traj->span, ws_bytes, prec);
+        const BorisPlan plan = boris_plan_fit(traj->n_particles, traj->n_samples, traj->span, ws_bytes);
         const int64_t lmin = std::min<int64_t>(traj->n_samples, 2);
         if (work && (!ws || plan.batch < 1 || plan.span < lmin))
             return fail(LW_E_WORKSPACE, "%s: workspace of %zu bytes holds no span (one particle needs %zu)", fn,
-                        ws_bytes, boris_plan_ws_bytes(BorisPlan{1, traj->span > 0 ? traj->span : lmin}, prec));
+                        ws_bytes, boris_plan_ws_bytes(BorisPlan{1, traj->span > 0 ? traj->span : lmin}));
         if (det) return launch_deposit_det(traj, grid, field_mask, g, (double *)E, diag, acc, ws, ws_bytes, stream);
         return launch_deposit_boris(traj, grid, prec, field_mask, gc, accum, E, diag, ws, ws_bytes, stream);
     }
@@ -450,11 +449,11 @@ lw_status lw_deposit_td_bwd_boris(const lw_traj_t *traj, const lw_grid_t *grid, 
         return fail(LW_E_ALIGN, "%s: misaligned pointer", fn);
     if (work && grid->n_pix > 0 && traj->n_samples >= 2) {
         const BorisPlan plan =
-            boris_plan_fit(traj->n_particles, traj->n_samples, traj->span, ws_bytes, LW_PREC_FP64, true);
+            boris_plan_fit(traj->n_particles, traj->n_samples, traj->span, ws_bytes, true);
         if (!ws || plan.batch < 1 || plan.span < 2)
             return fail(LW_E_WORKSPACE, "%s: workspace of %zu bytes holds no span (one particle needs %zu)", fn,
                         ws_bytes,
-                        boris_plan_ws_bytes(BorisPlan{1, traj->span > 0 ? traj->span : 2}, LW_PREC_FP64, true));
+                        boris_plan_ws_bytes(BorisPlan{1, traj->span > 0 ? traj->span : 2}, true));
     }
     return launch_deposit_bwd_boris(traj, grid, field_mask, geom, (const double *)dE, grad_init, grad_a0, ws, ws_bytes,
                                     stream);

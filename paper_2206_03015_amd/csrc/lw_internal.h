@@ -533,9 +533,9 @@ struct BorisPlan {
     int64_t batch, span;  // particles per batch, samples per span (spans share their boundary sample)
 };
 // bwd: the adjoint's plan (sample arrays and their gradients, tangent states)
-BorisPlan boris_plan_default(int64_t n_p, int64_t ns, int prec, bool bwd = false);
-BorisPlan boris_plan_fit(int64_t n_p, int64_t ns, int64_t span_req, size_t ws_bytes, int prec, bool bwd = false);
-size_t boris_plan_ws_bytes(const BorisPlan &p, int prec, bool bwd = false);
+BorisPlan boris_plan_default(int64_t n_p, int64_t ns, bool bwd = false);
+BorisPlan boris_plan_fit(int64_t n_p, int64_t ns, int64_t span_req, size_t ws_bytes, bool bwd = false);
+size_t boris_plan_ws_bytes(const BorisPlan &p, bool bwd = false);
 lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec, int fmask, int geom,
                                bool accumulate, void *E, int64_t *diag, void *ws, size_t ws_bytes, hipStream_t s,
                                int acc_mode = kAccFloat, DetAcc det = DetAcc{nullptr, nullptr});
