@@ -527,7 +527,7 @@ __device__ __forceinline__ float pulse_time(const double *__restrict__ init, int
 
 // idx[p], p < P: the block's particles (-1: none).  All threads of the block; ends with a barrier.
 template <int P, int NT>
-__device__ void push_select(const double *__restrict__ init, int64_t n_particles, int64_t kb, float early, PushSort &q, int64_t *idx)
+__device__ void push_select(const double *__restrict__ init, int64_t n_particles, int64_t kb, float early, PushSort &q, int *idx)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = (int)n_particles;
     float lo = 3e38f, hi = -3e38f;
@@ -639,7 +639,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
         Lds b;
         PushSort q;
     } lds;
-    __shared__ int64_t idx[P];
+    __shared__ int idx[P];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t kb = (int64_t)blockIdx.x * P;
     bool ranked = false;
@@ -649,7 +649,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
             push_select<P, 64 * (1 + NC)>(init, n_particles, kb, (float)(-kPi * L.nc / L.wl - t_start), lds.q, idx);
     }
     if (!ranked) {
-        if (threadIdx.x < P) idx[threadIdx.x] = kb + threadIdx.x < n_particles ? kb + threadIdx.x : -1;
+        if (threadIdx.x < P) idx[threadIdx.x] = kb + threadIdx.x < n_particles ? (int)(kb + threadIdx.x) : -1;
         __syncthreads();
     }
     const PushConst K = push_const(L);
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
                 Q.z = row[2];
                 if (!PRE || i < n_span) mx[g] = fmax(mx[g], fma(Q.z, Q.z, fma(Q.y, Q.y, Q.x * Q.x)));
                 if constexpr (OUT) {
-                    const int64_t k = idx[p];
+                    const int k = idx[p];
                     if constexpr (!PRE)
                         if (k < 0) continue;
                     Q.Ex = row[3];
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
             for (int g = 0; g < NG; ++g) {
                 double m = mx[g];
                 for (int off = S / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-                const int64_t k = idx[p0 + g * G];
+                const int k = idx[p0 + g * G];
                 if (j == 0 && k >= 0) rmax2[k] = m;
             }
         }
@@ -868,7 +868,7 @@ __global__ __launch_bounds__(64 * (1 + NC)) void k_push(const double *__restrict
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
                 const uint64_t m = __builtin_amdgcn_ballot_w64(bad[g]) >> (lane & ~(S - 1));
-                const int64_t k = idx[p0 + g * G];
+                const int k = idx[p0 + g * G];
                 if (j == 0 && k >= 0) pre.pflag[k] = (m & ((1ull << S) - 1)) != 0 ? 1 : 0;
             }
         }
@@ -1223,7 +1223,8 @@ static lw_status launch_push(const lw_traj_t *t, int64_t s0, int64_t n_span, dou
 
 lw_status launch_boris(const lw_traj_t *t, double *r, double *beta, double *beta_dot, hipStream_t s)
 {
-    // a grid counts its threads in 32 bits (three per particle): more particles take several launches
+    // a grid counts its threads in 32 bits (three per particle), and a block's indices are 32 bits: more particles take
+    // several launches
     constexpr int64_t kMost = int64_t(1) << 28;
     lw_traj_t part = *t;
     for (int64_t k0 = 0; k0 < t->n_particles; k0 += kMost) {
