@@ -737,7 +737,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 //     the interval of its grid point (bracket from the pixel's arrival times at five samples of the step, then
 //     three-point interpolation), evaluates the field at its two ends and adds the interpolated
 //     value to the trace;
-//   * dense steps (deposit_dense; at least kDensePoints grid points per interval): per pixel, lanes
+//   * dense steps (deposit_dense; at least kDensePoints grid points per interval of a whole step): per pixel, lanes
 //     over samples form every arrival time and field of the step in LDS, then lanes over grid
 //     points interpolate.
 // The interval found is the one with tau_{i-1} < u <= tau_i whichever way it is found, and the
@@ -762,7 +762,9 @@ struct SweepCfg {
     static constexpr int kDensePix = sizeof(T) == 8 ? 1 : 2;  // pixels of a dense step at a time
 };
 constexpr int kSteps = 64;      // steps per mask
-// grid points per interval of the step's live pixels from which a step is dense
+// Grid points of a live pixel, per interval of a whole step, from which a step is dense: forming every arrival time and
+// field of a step takes a pixel about the same time however few its intervals are.  427 particles of 2 samples, 5687 pixels, at
+// most one point each: 1859 us with the step's own intervals in the rule, 507 so.
 constexpr float kDensePoints = 0.6f;
 
 template <typename T, int GEOM>
@@ -1106,7 +1108,7 @@ struct Sweep {
                     s.node[par][c][p] = lane_ok ? tau_at<MODE>(pixel<MODE>(p), i0 + ((c * n) >> 2)) : 0.0;
                 __syncthreads();
                 const bool dense = (float)(s.fresh[0] + s.fresh[1]) >=
-                                   kDensePoints * (float)((__popcll(s.live[0]) + __popcll(s.live[1])) * n);
+                                   kDensePoints * (float)((__popcll(s.live[0]) + __popcll(s.live[1])) * Cfg::H);
                 const int d = dense ? 1 : 0, tot0 = s.tot[d][0], total = tot0 + s.tot[d][1];
                 deposit_points<MODE>(s.cum[d], i0, n, prev, par, tot0, total);
                 if (dense) {
