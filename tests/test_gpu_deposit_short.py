@@ -24,12 +24,13 @@ def check(c, prec):
 
 
 def short(n_p, n_samples, n_pix, points):
-    """All start from one point, so that the window holds `points` grid points of particle 0's at pixel 0."""
+    """All start from one point, so that the window holds `points` grid points of particle 0's at pixel 0; its first and
+    last arrival times lie between grid points (on one, the last bit of either side would decide)."""
     c = synthetic(n_p=n_p, n_samples=n_samples, n_pix=n_pix, n_obs=16, seed=n_samples)
     c["r"] = c["r"] - c["r"][:, :1]
     tau, _, _ = oracle.eval_samples(0.0, c["dt"], c["r"], c["beta"], c["beta_dot"], c["x_det"][:1], 0.0, 1.0)
     c["dt_obs"] = float(np.ptp(tau[0, 0])) / points
-    c["t0"] = float(np.min(tau)) - 2 * c["dt_obs"]
+    c["t0"] = float(np.min(tau)) - 2.37 * c["dt_obs"]
     c["n_obs"] = 2 * points + 4
     return c
 
