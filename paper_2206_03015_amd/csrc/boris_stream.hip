@@ -151,7 +151,7 @@ lw_status launch_deposit_boris(const lw_traj_t *t, const lw_grid_t *gr, int prec
         if (st != LW_OK) return st;
         for (int64_t s0 = 0;;) {
             const int64_t n_span = std::min<int64_t>(P.span, ns - s0);
-            const DepositPre pre = deposit_pre(ws, nb, gr);
+            const DepositPre pre = deposit_pre(ws, nb, n_span, whole, gr, acc_mode);
             st = launch_boris_span(&push, s0, n_span, state, r, b, bd, whole ? rb2 : nullptr, s, nullptr, pre);
             if (st != LW_OK) return st;
             lw_traj_t sub = *t;

@@ -70,7 +70,7 @@ constexpr int64_t kTargetBlocks = 16384;
 // of up to 128 samples, 1 to 1e5 particles, 1 to 2e4 pixels: 5 % faster in the mean than with kTargetBlocks (8192 blocks
 // 3 %, 2048 6 %, with more of them slower); 15077 particles of 8 samples, 160 pixels, most out of the window 333 -> 110 us
 constexpr int64_t kTargetBlocksShort = 4096;
-constexpr int kMaxPartsPerGroup = 64;
+constexpr int kMaxPartsPerGroup = 64;  // at most a wavefront's lanes
 constexpr int64_t kFillBlocks = 2048;
 // particles per block of the careful path
 constexpr int kMaxPartsCareful = 4;
@@ -273,7 +273,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct DepWs {
     double *pt;                 // [kPixTabMax][kPT] pixel table of the current pass
-    int *pflag;                 // [n_p] 0 = fast path
+    int *pflag;                 // [n_p] see k_prepass
     unsigned long long *rmax2;  // [n_p] bits of max_i |r_i|^2 (non-negative doubles order as integers)
     double *d;                  // [n_p][n_s] arrival bases
 };
@@ -302,20 +302,146 @@ DepWs carve(void *ws, int64_t n_p)
     return w;
 }
 
+// Whether dense particles (at least kGatherDensity grid points per interval at a pixel in the middle of the detector) of
+// short trajectories go to k_gather, and what that is decided by: their number, their grid points and the windows these
+// touch, and in at most 512 bins of windows how many particles overlap.  The rule compares estimates of both kernels'
+// times, fitted to 240 drawn calls of 1 to 1e5 particles of 2 to 1000 samples on 1 to 3000 pixels (k_gather: nine of ten
+// within 0.46 to 1.26 of the measured times; k_sweep without its cost of the trace's zeros and the launches):
+//   k_gather  5 us, 6 ns a window and pixel, 5 ps more for each particle to look at, 2.2 us a particle that
+//             the fullest window takes (one after the other), 4.1 us a particle and window on 1536 resident blocks
+//   k_sweep   13 ps a grid point (FP64 20), 10 ns a particle and tile; at least 0.85 ns (1.7) a grid point of one block
+// and takes k_gather where it is faster by half: in 65 of the draws, where k_sweep takes 1.07 to 19 times as long.  By their
+// density alone k_gather would be the slower one in 144 of the draws, up to 58 times.  Where k_sweep keeps them, the rule
+// and the idle launch cost 4 us (calls too small for k_gather on any account have neither).
+constexpr double kGatherDensity = 1.0;
+constexpr float kGatherMargin = 1.5f;
+constexpr int64_t kGatherSamples = 1024;  // longest trajectory (every sample that bounds a window is evaluated)
+constexpr int kGatherBins = 512, kRuleBlocks = 64;
+constexpr int64_t kGatherBlocks = 4095;  // odd, so that no block takes the same window of every pixel (an idle block takes 0.7 ns)
+struct GatherRule {
+    int64_t n_p;           // blocks from this one on are the rule's
+    const double *x_mid;
+    double n_obs;
+    int64_t n_win, window, bin;  // windows of a pixel, grid points of a window and a bin
+    float fixed, per_most, per_window, per_point, per_particle, per_mean;  // us
+    // of the fullest window's particles, the windows, points and particles
+    __host__ __device__ __forceinline__ bool gathered(float most, float windows, float points, float particles) const
+    {
+        const float gather = fixed + per_most * most + per_window * windows;
+        const float sweep = fmaxf(per_point * points + per_particle * particles, per_mean * points / fmaxf(particles, 1.0f));
+        return kGatherMargin * gather < sweep;
+    }
+};
+// In the padding of the pixel table (zero at the start of a pixel pass): the tenth and eleventh elements of row j hold the
+// changes of the overlap at bins 4 j to 4 j + 3, the first row's others the rest
+struct GatherStats {
+    double *pt;
+    __device__ __forceinline__ int *step(int j) const { return (int *)(pt + (int64_t)(j >> 2) * kPT + 9) + (j & 3); }
+    __device__ __forceinline__ unsigned long long *sum(int i) const { return (unsigned long long *)(pt + 11 + i); }  // points, windows, particles
+    __device__ __forceinline__ unsigned *blocks() const { return (unsigned *)(pt + 14); }
+};
+// the decision: 1 where k_gather takes the dense particles
+__device__ __forceinline__ const int *gather_flag(const double *pt) { return (const int *)(pt + kPT - 1); }
+static_assert(kGatherBins <= 4 * kTilePix, "bins in the rows of the first tile");
+
+template <typename T>
+__device__ __forceinline__ T load_shared_by_blocks(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Block b of n_blocks (of 256 threads): flags the dense particles; the last block to end decides.  In blocks of their own beside
+// the pre-pass's: added up there, particle by particle, the sums took 60 ns a particle.
+__device__ __forceinline__ void gather_rule(const GatherRule &rule, int b, int n_blocks, const double *__restrict__ r,
+                                            int64_t n_samples, int64_t sample0, double t_start, double dt, double t0,
+                                            double dt_obs, double C, int geom, int *__restrict__ pflag, double *pt)
+{
+    __shared__ int s_step[kGatherBins];
+    __shared__ unsigned long long s_sum[3];
+    __shared__ bool s_last;
+    const int tid = threadIdx.x;
+    for (int j = tid; j < kGatherBins; j += 256) s_step[j] = 0;
+    if (tid < 3) s_sum[tid] = 0ull;
+    __syncthreads();
+    const PixC P = pix_const(rule.x_mid, 0, C);
+    unsigned long long v[3] = {0ull, 0ull, 0ull};
+    for (int64_t k = (int64_t)b * 256 + tid; k < rule.n_p; k += (int64_t)n_blocks * 256) {
+        // by the first and last arrival times
+        auto tau = [&](int64_t i) {
+            const double *ri = r + 3 * (k * n_samples + i);
+            const double d = arrival_base(t_start, dt, (double)(sample0 + i), t0, dt_obs, ri[2]);
+            return geom == LW_GEOM_EXACT ? arrival_tau<LW_GEOM_EXACT, kTauSqrt>(P, d, ri[0], ri[1], ri[2], 0.0, C)
+                                         : arrival_tau<LW_GEOM_FARFIELD, kTauSqrt>(P, d, ri[0], ri[1], ri[2], 0.0, C);
+        };
+        const double ta = tau(0), tb = tau(n_samples - 1);
+        if (!(tb - ta >= kGatherDensity * (double)(n_samples - 1))) continue;
+        atomicOr(pflag + k, 2);
+        const int64_t c0 = grid_count(ta, rule.n_obs), c1 = grid_count(tb, rule.n_obs);
+        if (c1 <= c0) continue;
+        v[0] += (unsigned long long)(c1 - c0);
+        v[1] += (unsigned long long)((c1 - 1) / rule.window - c0 / rule.window + 1);
+        v[2] += 1ull;
+        atomicAdd(s_step + (int)(c0 / rule.bin), 1);
+        const int64_t after = (c1 - 1) / rule.bin + 1;
+        if (after < kGatherBins) atomicAdd(s_step + (int)after, -1);
+    }
+    for (int i = 0; i < 3; ++i) {
+        for (int off = 32; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off);
+        if ((tid & 63) == 0) atomicAdd(s_sum + i, v[i]);
+    }
+    __syncthreads();
+    const GatherStats st{pt};
+    for (int j = tid; j < kGatherBins; j += 256)
+        if (s_step[j]) atomicAdd(st.step(j), s_step[j]);
+    if (tid < 3 && s_sum[tid]) atomicAdd(st.sum(tid), s_sum[tid]);
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) s_last = atomicAdd(st.blocks(), 1u) == (unsigned)n_blocks - 1u;
+    __syncthreads();
+    if (!s_last || tid >= 64) return;
+    __threadfence();
+    // a lane takes neighbouring bins: their running sums, raised by what precedes the lane
+    constexpr int kPer = kGatherBins / 64;
+    int sum = 0, most = -0x7fffffff;
+    for (int j = 0; j < kPer; ++j) {
+        sum += load_shared_by_blocks(st.step(kPer * tid + j));
+        most = max(most, sum);
+    }
+    int upto = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(upto, off);
+        if (tid >= off) upto += o;
+    }
+    most += upto - sum;
+    for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off));
+    if (tid == 0) {
+        auto sum_of = [&](int i) { return (float)load_shared_by_blocks(st.sum(i)); };
+        *const_cast<int *>(gather_flag(pt)) = rule.gathered((float)most, sum_of(1), sum_of(0), sum_of(2)) ? 1 : 0;
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
-// pre-pass: one block per (particle, chunk of samples): arrival bases, per-particle max |r|^2 and the
-// careful-path flag.  Bound by memory: 72 bytes of a sample read, 8 written (with the polynomial's coefficients
-// and the position stored beside the base, 64 or 80 written, the pre-pass of 2000 x 20001 samples took
-// 1.75 ms, now 0.79; the coefficients are formed where a step's samples are staged instead)
+// pre-pass: one block per (particle, chunk of samples): arrival bases, per-particle max |r|^2 and the flags: 1 for the
+// careful path, 2 for a dense particle (gather_rule), 0 else.  Bound by memory: 72 bytes of a
+// sample read, 8 written (with the polynomial's coefficients and the position stored beside the base, 64 or 80 written,
+// the pre-pass of 2000 x 20001 samples took 1.75 ms, now 0.79; the coefficients are formed where a step's samples are
+// staged instead)
 __global__ __launch_bounds__(256) void k_prepass(const double *__restrict__ r, const double *__restrict__ beta,
                                                  const double *__restrict__ beta_dot, int64_t n_samples, int chunk,
                                                  int64_t sample0, double t_start, double dt, double t0,
                                                  double dt_obs, double C, double *__restrict__ base,
-                                                 int *__restrict__ pflag, unsigned long long *__restrict__ rmax2)
+                                                 int *__restrict__ pflag, unsigned long long *__restrict__ rmax2,
+                                                 int geom, GatherRule rule, double *pt)
 {
     __shared__ unsigned long long s_max[4];
     __shared__ int s_bad[4];
     const int64_t k = blockIdx.x;
+    if (k >= rule.n_p) {
+        if (blockIdx.y == 0)
+            gather_rule(rule, (int)(k - rule.n_p), (int)(gridDim.x - rule.n_p), r, n_samples, sample0, t_start, dt, t0, dt_obs, C, geom,
+                        pflag, pt);
+        return;
+    }
     const int64_t i_begin = (int64_t)blockIdx.y * chunk;
     const int64_t i_end = std::min<int64_t>(i_begin + chunk, n_samples);
     const double cdt_step = kC * dt;
@@ -638,7 +764,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
     const int64_t k1 = grp < sh.n_groups ? std::min(k0 + sh.parts_per_group, sh.n_particles) : k0;
     {
         bool any = false;
-        for (int64_t k = k0 + (threadIdx.x & 63); k < k1; k += 64) any |= pflag[k] != 0;
+        for (int64_t k = k0 + (threadIdx.x & 63); k < k1; k += 64) any |= (pflag[k] & 1) != 0;
         if (__ballot(any) == 0) return;  // whole block (one wavefront)
     }
     __shared__ uint2 q_all[kQCap];
@@ -704,7 +830,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
 
     unsigned long long c0 = 0, c1 = 0, c2 = 0, c3 = 0;
     for (int64_t k = k0; k < k1; ++k) {
-        if (pflag[k] == 0) continue;  // fast path: k_sweep
+        if (!(pflag[k] & 1)) continue;  // fast path: k_sweep, k_gather
         // series forms where |r|^2 <= 1e-8 |x_m|^2 over the whole trajectory (the max over the
         // whole trajectory when given, else over the samples of this call), decided per pixel
         w.rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
@@ -1154,6 +1280,12 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     if (grp >= sh.n_groups) return;  // padding block
     const int64_t k0 = grp * sh.parts_per_group, k1 = std::min(k0 + sh.parts_per_group, sh.n_particles);
     const int st0 = seg * sw.per_seg, st1 = min(st0 + sw.per_seg, sw.n_steps);
+    const int others = *gather_flag(pt) ? 3 : 1;  // flags of other kernels' particles
+    {
+        // no particle of the group is this kernel's (a group is at most a wavefront's lanes)
+        const int64_t k = k0 + (tid & 63);
+        if (__ballot(k < k1 && (pflag[k] & others) == 0) == 0) return;
+    }
 
     if (tid < 4) lds.red[tid] = 0ull;
     const int64_t m = tile * kTilePix + p;
@@ -1237,7 +1369,7 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     for (int kk = __builtin_amdgcn_readfirstlane(tid >> 6); kk < nk; kk += SweepCfg<T>::kThreads / 64) {
         const int64_t k = k0 + kk;
         int hit = 0;
-        if (pflag[k] == 0) {  // else careful path: k_careful
+        if ((pflag[k] & others) == 0) {  // else careful path (k_careful) or dense (k_gather)
             const size_t s0 = (size_t)k * sh.n_samples;
             with_mode(k, [&](auto mode) {
                 constexpr int MODE = decltype(mode)::value;
@@ -1289,6 +1421,201 @@ __global__ __launch_bounds__(SweepCfg<T>::kThreads) __attribute__((amdgpu_waves_
     if (c3) atomicAdd(&lds.red[3], c3);
     __syncthreads();
     if (diag && tid < 4 && lds.red[tid]) atomicAdd(diag + tid, lds.red[tid]);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Dense particles (gather_rule) of short trajectories: an observer grid much finer than the samples, where a particle's
+// points run over thousands of grid points.  A block owns a window of grid points of one pixel, finds the particles whose
+// arrival times pass it, forms their arrival times and fields at the samples that bound it and adds the interpolated values to
+// its grid points in registers: one read and write of the trace instead of three atomics per point, which bound k_sweep here
+// (18 G requests/s).  1280 particles x 101 samples on 2^20 points, one pixel, mixed: 174 -> 140 us.  Four wavefronts per
+// SIMD: with three (139 registers instead of 128) 43851 particles x 22 samples on 526165 points, 3 pixels, 2814 us, so 2347.
+template <typename T>
+struct GatherCfg {
+    static constexpr int U = 16 / (int)sizeof(T);  // grid points per thread (twice that: 20 us more, half: 30 more)
+    static constexpr int W = 256 * U;
+};
+
+template <typename T, int GEOM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_gather(const double *__restrict__ r, const double *__restrict__ beta,
+                                                const double *__restrict__ beta_dot, const double *__restrict__ charge,
+                                                const double *__restrict__ x_det, const double *__restrict__ base,
+                                                const double *__restrict__ pt, const int *__restrict__ pflag,
+                                                const unsigned long long *__restrict__ rmax2,
+                                                const double *__restrict__ rbound2, T *__restrict__ E,
+                                                unsigned long long *__restrict__ diag, DepShape sh)
+{
+    constexpr bool kF64 = sizeof(T) == 8;
+    constexpr int kRec = kF64 ? kModeRec5 : kModeRec3, U = GatherCfg<T>::U, W = GatherCfg<T>::W;
+    if (*gather_flag(pt) == 0) return;
+    __shared__ double s_tau[256];
+    __shared__ T s_e[3][256];
+    __shared__ int s_list[256], s_cnt[4];
+    __shared__ double s_red[2][2];
+    __shared__ uint64_t s_far[2];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const double Dref = pix_geo(x_det, 0).D, nob = (double)sh.n_obs;
+    const int ns = (int)sh.n_samples;
+    double cK;
+    {
+        double c[6];
+        tau_poly<kF64 ? 5 : 3>(0.0, 0.0, 0.0, 0.0, sh.C, Dref, c);
+        cK = c[kF64 ? 5 : 3];
+    }
+    const int64_t n_win = (sh.n_obs + W - 1) / W;
+    for (int64_t item = blockIdx.x; item < n_win * sh.n_pix; item += gridDim.x) {
+        const int64_t m = item / n_win, U0 = (item - m * n_win) * W, U1 = std::min<int64_t>(U0 + W, sh.n_obs);
+        const PixC P = pixc_row(pt + m * kPT);
+        const bool counts = diag && U0 == 0;  // the first window's blocks keep the counters
+        if (!P.g.ok && !counts) continue;
+        const double xm[3] = {x_det[3 * m], x_det[3 * m + 1], x_det[3 * m + 2]};
+        unsigned long long n_bad = 0, n_out = 0, n_in = 0;
+        // the pixel's tile decides the arrival-time form, as in k_sweep
+        __syncthreads();  // the previous window is done with
+        if (tid < kTilePix) {
+            const int64_t mt = m / kTilePix * kTilePix + tid;
+            const PixC pc = pixc_row(pt + mt * kPT);  // padding rows: not usable
+            const bool ok = mt < sh.n_pix && pc.g.ok;
+            double id2 = ok ? pc.g.invD * pc.g.invD : 0.0, s2 = ok ? fmax(0.0, 2.0 * (1.0 - pc.g.nz)) : 0.0;
+            const uint64_t far = __ballot(ok && !(fabs(pc.g.D - Dref) <= kSameDistance * Dref));
+            for (int off = 32; off > 0; off >>= 1) {
+                id2 = fmax(id2, __shfl_xor(id2, off));
+                s2 = fmax(s2, __shfl_xor(s2, off));
+            }
+            if (lane == 0) {
+                s_red[wv][0] = id2;
+                s_red[wv][1] = s2;
+                s_far[wv] = far;
+            }
+        }
+        __syncthreads();
+        const double invD2max = fmax(s_red[0][0], s_red[1][0]), s2max = fmax(s_red[0][1], s_red[1][1]);
+        const bool rec_ok = GEOM == LW_GEOM_EXACT && (s_far[0] | s_far[1]) == 0;
+        auto with_mode = [&](int64_t k, auto f) {
+            const double rb2 = rbound2 ? rbound2[k] : __longlong_as_double((long long)rmax2[k]);
+            if constexpr (GEOM == LW_GEOM_FARFIELD) {
+                f(std::integral_constant<int, kModeFar>{}, rb2);
+            } else {
+                if (rb2 * invD2max <= kSeriesBound && rec_ok) {
+                    if (tail_negligible<kF64>(rb2, s2max, sh.C, cK, Dref))
+                        f(std::integral_constant<int, kModeRecLow>{}, rb2);
+                    else
+                        f(std::integral_constant<int, kRec>{}, rb2);
+                } else
+                    f(std::integral_constant<int, kModeMixed>{}, rb2);
+            }
+        };
+        auto tau_of = [&](auto mode, double rb2, int64_t s) {  // of sample s (of all particles)
+            constexpr int MODE = decltype(mode)::value;
+            double v[ScanVals<GEOM, kF64, MODE>::N];
+            scan_vals<GEOM, kF64, MODE>(base[s], r[3 * s], r[3 * s + 1], r[3 * s + 2], sh.C, Dref, v);
+            return tau_eval<GEOM, kF64, MODE>(P, v, cK, rb2, sh.C);
+        };
+        T acc[U][3];
+#pragma unroll
+        for (int q = 0; q < U; ++q) acc[q][0] = acc[q][1] = acc[q][2] = (T)0;
+        bool any = false;  // the same in every thread
+        for (int64_t kb = 0; kb < sh.n_particles; kb += 256) {
+            const int64_t k = kb + tid;
+            bool hit = false;
+            if (k < sh.n_particles && pflag[k] == 2 && P.g.ok) {
+                with_mode(k, [&](auto mode, double rb2) {
+                    const double t0 = tau_of(mode, rb2, k * ns), t1 = tau_of(mode, rb2, k * ns + ns - 1);
+                    const int64_t c0 = grid_count(t0, nob), c1 = grid_count(t1, nob);
+                    hit = c1 > c0 && c1 > U0 && c0 < U1;
+                    n_in += (unsigned long long)(c1 - c0);
+                    n_out += (unsigned long long)((int64_t)(floor(t1) - floor(t0)) - (c1 - c0));
+                });
+            } else if (k < sh.n_particles && pflag[k] == 2) {
+                n_bad += (unsigned long long)(ns - 1);
+            }
+            const uint64_t hm = __ballot(hit);
+            __syncthreads();  // the previous list is done with
+            if (lane == 0) s_cnt[wv] = (int)__popcll(hm);
+            __syncthreads();
+            int before = 0, total = 0;
+            for (int v = 0; v < 4; ++v) {
+                before += v < wv ? s_cnt[v] : 0;
+                total += s_cnt[v];
+            }
+            if (hit) s_list[before + (int)lanes_below(hm)] = tid;
+            __syncthreads();
+            any |= total > 0;
+            for (int e = 0; e < total; ++e) {
+                const int64_t kk = kb + s_list[e], s0 = kk * ns;
+                const double q = charge ? charge[kk] : -kQe;
+                with_mode(kk, [&](auto mode, double rb2) {
+                    for (int j0 = 0; j0 + 1 < ns; j0 += 255) {
+                        const int n = min(255, ns - 1 - j0);
+                        __syncthreads();  // the previous samples are read
+                        if (tid <= n) s_tau[tid] = tau_of(mode, rb2, s0 + j0 + tid);
+                        __syncthreads();
+                        const int64_t c0 = grid_count(s_tau[0], nob), c1 = grid_count(s_tau[n], nob);
+                        if (c1 <= U0) continue;
+                        if (c0 >= U1) break;
+                        // fields at the samples of intervals that reach into the window
+                        if (tid <= n && s_tau[min(tid + 1, n)] >= (double)U0 && s_tau[max(tid - 1, 0)] < (double)U1) {
+                            const int64_t s = s0 + j0 + tid;
+                            const double bx = beta[3 * s], by = beta[3 * s + 1], bz = beta[3 * s + 2];
+                            T x, y, z;
+                            lw_field_ib<T, GEOM>(P.g, xm, r[3 * s], r[3 * s + 1], r[3 * s + 2], bx, by, bz, inv_beta<T>(bx, by, bz),
+                                                 (T)beta_dot[3 * s], (T)beta_dot[3 * s + 1], (T)beta_dot[3 * s + 2], q, sh.fmask, x,
+                                                 y, z);
+                            s_e[0][tid] = x;
+                            s_e[1][tid] = y;
+                            s_e[2][tid] = z;
+                        }
+                        __syncthreads();
+#pragma unroll
+                        for (int i = 0; i < U; ++i) {
+                            const int64_t u = U0 + tid + 256 * i;
+                            if (u < c0 || u >= c1) continue;  // c1 <= n_obs
+                            const double ud = (double)u;
+                            int lo = 0, hi = n;
+                            double ta = s_tau[0], tb = s_tau[n];
+                            for (int it = 0; hi - lo > 1; ++it) {
+                                int g = lo + (int)((float)(hi - lo) * ((float)(ud - ta) * __builtin_amdgcn_rcpf((float)(tb - ta))));
+                                g = (it & 3) == 3 ? (lo + hi) >> 1 : min(max(g, lo + 1), hi - 1);
+                                const double tg = s_tau[g];
+                                if (tg >= ud) {
+                                    hi = g;
+                                    tb = tg;
+                                } else {
+                                    lo = g;
+                                    ta = tg;
+                                }
+                            }
+                            const T inv = kF64 ? (T)(1.0 / (tb - ta)) : (T)__builtin_amdgcn_rcpf((float)(tb - ta));
+                            const T w = (T)(ud - ta) * inv, w1 = (T)1 - w;
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) acc[i][c] += w1 * s_e[c][lo] + w * s_e[c][hi];
+                        }
+                    }
+                });
+            }
+        }
+        if (counts) {
+            for (int off = 32; off > 0; off >>= 1) {
+                n_bad += __shfl_xor(n_bad, off);
+                n_out += __shfl_xor(n_out, off);
+                n_in += __shfl_xor(n_in, off);
+            }
+            if (lane == 0) {
+                if (n_bad) atomicAdd(diag + 1, n_bad);
+                if (n_out) atomicAdd(diag + 2, n_out);
+                if (n_in) atomicAdd(diag + 3, n_in);
+            }
+        }
+        if (!any) continue;
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int64_t u = U0 + tid + 256 * i;
+            if (u >= U1) continue;
+            T *o = E + (size_t)m * 3 * (size_t)sh.n_obs + (size_t)u;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[(size_t)c * (size_t)sh.n_obs] += acc[i][c];
+        }
+    }
 }
 
 // Row scales of the fixed-point pass from the first pass's max |v| per element (bits of a
@@ -1389,10 +1716,18 @@ size_t deposit_ws_bytes(int64_t n_particles, int64_t n_samples)
 // samples 1500 464 and 456 us, 8192 833 and 668.
 constexpr int64_t kPrePushed = 1500;
 
-DepositPre deposit_pre(void *ws, int64_t n_p, const lw_grid_t *gr)
+// whether k_gather may take dense particles: whole short trajectories (every span of a longer one takes the same path)
+// on a grid that is long against them
+static bool gather_allowed(int64_t ns, bool whole, int64_t n_obs, int acc_mode)
+{
+    return acc_mode == kAccFloat && whole && ns >= 2 && ns <= kGatherSamples && n_obs >= 4 * ns;
+}
+
+DepositPre deposit_pre(void *ws, int64_t n_p, int64_t ns, bool whole, const lw_grid_t *gr, int acc_mode)
 {
     DepositPre pre;
-    if (n_p < kPrePushed) return pre;
+    pre.whole = whole;
+    if (gather_allowed(ns, whole, gr->n_obs, acc_mode) || n_p < kPrePushed) return pre;
     const DepWs w = carve(ws, n_p);
     pre.base = w.d;
     pre.pflag = w.pflag;
@@ -1498,10 +1833,31 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
             const double *rb2 = rbound2 ? rbound2 + p0 : nullptr;
             int pchunk = kPrepassChunk;
             while (pchunk > 256 && np * ((ns + pchunk - 1) / pchunk) < kPrepassBlocks) pchunk /= 2;
-            const dim3 pgrid((unsigned)np, (unsigned)((ns + pchunk - 1) / pchunk));
+            dim3 pgrid((unsigned)np, (unsigned)((ns + pchunk - 1) / pchunk));
+            // (the pixel table's padding is zero for the first launch of a pixel pass only)
+            bool gather = !prepassed && chunk == n_p && gather_allowed(ns, !pre || pre->whole, n_obs, acc_mode);
+            GatherRule rule{};
+            rule.n_p = np;
+            if (gather) {
+                rule.window = f64 ? GatherCfg<double>::W : GatherCfg<float>::W;
+                rule.n_win = (n_obs + rule.window - 1) / rule.window;
+                rule.bin = rule.window * ((rule.n_win + kGatherBins - 1) / kGatherBins);
+                rule.x_mid = xd + 3 * (npx / 2);
+                rule.n_obs = (double)n_obs;
+                rule.fixed = 5.0f + ((float)rule.n_win * (float)npx) * (6e-3f + 5e-6f * (float)np);
+                rule.per_most = 2.2f;
+                rule.per_window = 4.1f / 1536.0f * (float)npx;
+                rule.per_point = (f64 ? 20e-6f : 13e-6f) * (float)npx;
+                rule.per_particle = 0.01f * (float)sh.n_tiles;
+                rule.per_mean = (f64 ? 1.7e-3f : 0.85e-3f) * (float)std::min<int64_t>(npx, kTilePix) * (float)sh.parts_per_group /
+                                (float)std::max(1, sw.n_seg);
+                // a call too small for it, were all particles' points in one window or over all of the grid
+                gather = rule.gathered(1.0f, (float)np, (float)np * (float)n_obs, (float)np);
+            }
+            if (gather) pgrid.x += (unsigned)std::min<int64_t>((np + 255) / 256, kRuleBlocks);
             if (!prepassed)
                 k_prepass<<<pgrid, 256, 0, s>>>(r, b, bd, ns, pchunk, sample0, t->t_start, t->dt, gr->t0, gr->dt_obs, C, w.d,
-                                                w.pflag, w.rmax2);
+                                                w.pflag, w.rmax2, geom, rule, w.pt);
             unsigned long long *dg = (unsigned long long *)diag;
             const dim3 grid((unsigned)blocks), grid_careful((unsigned)blocks_careful);
             if (acc_mode != kAccFloat) {
@@ -1534,6 +1890,16 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
                 if (geom == LW_GEOM_EXACT) LW_SWEEP_LAUNCH(double, LW_GEOM_EXACT); else LW_SWEEP_LAUNCH(double, LW_GEOM_FARFIELD);
             } else {
                 if (geom == LW_GEOM_EXACT) LW_SWEEP_LAUNCH(float, LW_GEOM_EXACT); else LW_SWEEP_LAUNCH(float, LW_GEOM_FARFIELD);
+            }
+            if (gather) {
+                auto go = [&](auto *k, auto *e) {
+                    k<<<dim3((unsigned)std::min(rule.n_win * npx, kGatherBlocks)), 256, 0, s>>>(r, b, bd, charge, xd, w.d, w.pt, w.pflag, w.rmax2, rb2, e,
+                                                                           dg, sh);
+                };
+                if (f64)
+                    go(geom == LW_GEOM_EXACT ? k_gather<double, LW_GEOM_EXACT> : k_gather<double, LW_GEOM_FARFIELD>, (double *)Ep);
+                else
+                    go(geom == LW_GEOM_EXACT ? k_gather<float, LW_GEOM_EXACT> : k_gather<float, LW_GEOM_FARFIELD>, (float *)Ep);
             }
             timing_end(LW_KERNEL_DEPOSIT, ev, s);
             if (f64) {

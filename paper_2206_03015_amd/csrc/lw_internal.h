@@ -471,13 +471,15 @@ lw_status launch_deposit(const lw_traj_t *traj, const lw_grid_t *grid, int prec,
                          DetAcc det = DetAcc{nullptr, nullptr}, const struct DepositPre *pre = nullptr);
 // What the deposit's pre-pass leaves in a workspace (of at least deposit_ws_bytes of these sizes): the samples' arrival
 // bases [n_particles][n_samples] and the particles' flags (1: careful path).  base is null where the pusher
-// leaves them to the deposit (less than kPrePushed particles).
+// leaves them to the deposit (less than kPrePushed particles, or short trajectories that may be dense).  whole: the samples
+// are whole trajectories, not spans of them.
 struct DepositPre {
     double *base = nullptr;
     int *pflag = nullptr;
     double t0 = 0.0, dt_obs = 0.0, C = 0.0;
+    bool whole = true;
 };
-DepositPre deposit_pre(void *ws, int64_t n_particles, const lw_grid_t *grid);
+DepositPre deposit_pre(void *ws, int64_t n_particles, int64_t n_samples, bool whole, const lw_grid_t *grid, int acc_mode);
 // lw_deposit_td_det: FP64 deposit whose result does not depend on the order of the contributions
 // (acc: the high words and row scales, det_acc_bytes(n_pix, n_obs) bytes)
 lw_status launch_deposit_det(const lw_traj_t *traj, const lw_grid_t *grid, int field_mask, int geom, double *E,
