@@ -97,7 +97,7 @@ def parse():
     p.add_argument("--no-fd", action="store_true")
     p.add_argument("--no-cpu-baseline", action="store_true")
     p.add_argument("--no-grad", action="store_true")
-    p.add_argument("--no-cull", action="store_true", help="skip the culled-variant leg")
+    p.add_argument("--no-cull", action="store_true", help="accepted, no effect: the deposit skips what misses the window with and without LW_CULL")
     p.add_argument("--no-bunch", action="store_true", help="skip the bunch-workload leg of the headline line")
     p.add_argument("--cpu-seconds", type=float, default=15.0)
     p.add_argument("--cost-model", action="store_true",
@@ -180,7 +180,7 @@ def deposit_roofline(triples, hits, kernel_s, launches, summaries=None, profiled
                                      "frac": dense_s / kernel_s}
     if profiled and summaries:
         roof["traffic"] = _summary_value(summaries["traffic"], "hbm_bytes_per_step")
-        valu = _summary_value(summaries["valu"], "valu_insts_per_step")
+        valu = _summary_value(summaries["valu"], "sweep_valu_insts_per_step")
         if valu is not None:
             roof["executed_valu_insts"] = valu
             roof["valu_issue_frac"] = valu * 4 / (CUS * 4 * CLOCK_GHZ * 1e9 * kernel_s)
@@ -256,15 +256,15 @@ def headline(torch, dev, args):
         torch.cuda.empty_cache()
     ws_f = torch.empty(lw.workspace_bytes(lw.WS_FFT, n_pix, n_obs, "mixed"), dtype=torch.uint8, device=dev)
 
-    def deposit(prec, E, diag, ws, cull=False):
+    def deposit(prec, E, diag, ws):
         if in_call:
             lw.deposit_td_boris(init, W.n_samples, W.t_start, W.dt, L.a0, L.lam, L.w0, L.n_cycles, x_det, W.t0,
-                                W.dt_obs, n_obs, prec=prec, geom=args.geom, out=E, diag=diag, ws=ws, cull=cull)
+                                W.dt_obs, n_obs, prec=prec, geom=args.geom, out=E, diag=diag, ws=ws)
         else:
             lw.deposit_td(r, b, bd, W.t_start, W.dt, x_det, W.t0, W.dt_obs, n_obs, prec=prec, geom=args.geom,
-                          out=E, diag=diag, ws=ws, cull=cull)
+                          out=E, diag=diag, ws=ws)
 
-    def run(prec, steps, warmup, cull=False):
+    def run(prec, steps, warmup):
         dt = torch.float64 if prec == "fp64" else torch.float32
         E = torch.empty((n_pix, 3, n_obs), dtype=dt, device=dev)
         S = torch.empty((n_pix, n_obs // 2 + 1), dtype=dt, device=dev)
@@ -282,7 +282,7 @@ def headline(torch, dev, args):
                 lw.timing_enable(True)
                 t_start = time.time()
             ev[0].record()
-            deposit(prec, E, diag, ws_d, cull)
+            deposit(prec, E, diag, ws_d)
             ev[1].record()
             lw.spectrum_fft(E, W.dt_obs, prec, out=S, ws=wsf)
             ev[2].record()
@@ -293,7 +293,7 @@ def headline(torch, dev, args):
                 kern_n += n
                 dep_ms.append(ev[0].elapsed_time(ev[1]))
                 fft_ms.append(ev[1].elapsed_time(ev[2]))
-                log(f"[bench] {prec}{' culled' if cull else ''} step {it - warmup}: deposit {dep_ms[-1]:.1f} ms "
+                log(f"[bench] {prec} step {it - warmup}: deposit {dep_ms[-1]:.1f} ms "
                     f"(kernel {ms:.1f} ms in {n} launches), fft {fft_ms[-1]:.1f} ms")
         torch.cuda.synchronize()
         wall = (time.time() - t_start) / steps * 1e3
@@ -320,15 +320,6 @@ def headline(torch, dev, args):
         out["diag_fp64_equal"] = res64["diag"] == mixed["diag"]
         del S64
         torch.cuda.empty_cache()
-    if not args.no_cull:
-        # the same call with LW_CULL: same spectra (the deposit skips what misses the window either way)
-        cul = run("mixed", 1, 0, cull=True)
-        S_c = cul.pop("S")
-        diff = float(torch.max(torch.abs(S_c - S_mixed)) / torch.max(torch.abs(S_mixed)))
-        out["culled"] = {"ms_per_step": cul["ms_per_step"], "deposit_ms": cul["deposit_ms"],
-                         "fft_ms": cul["fft_ms"], "evals_per_s": triples / (cul["ms_per_step"] / 1e3),
-                         "diag_equal": cul["diag"] == mixed["diag"], "max_rel_diff_vs_full": diff}
-        del S_c
     del S_mixed
     if not in_call:
         del r, b, bd

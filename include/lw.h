@@ -174,8 +174,9 @@ size_t lw_workspace_bytes(int which, int64_t n_a, int64_t n_b, int prec);
  * prec:       LW_PREC_FP64 (E is double) or LW_PREC_MIXED (E is float; tau and
  *             the crossing decisions are still computed in double).  In the exact
  *             geometry, a particle with max_i |r_i|^2 <= 1e-8 |x_m|^2 over its whole
- *             trajectory (for LW_TRAJ_BORIS the max over every pushed sample, found
- *             by a first pass of the pusher) has its path correction expanded in
+ *             trajectory (for LW_TRAJ_BORIS the max over every pushed sample, from the
+ *             push itself or, where a trajectory takes several spans, from a pass of
+ *             the pusher before it) has its path correction expanded in
  *             |r|/|x_m|: to third order in FP64 mode (exact to rounding), to first
  *             order in MIXED mode (relative error of the correction <= 1.25e-8);
  *             where every pixel of a 128-pixel tile is at the first pixel's
