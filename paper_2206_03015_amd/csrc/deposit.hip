@@ -309,9 +309,9 @@ DepWs carve(void *ws, int64_t n_p)
 // within 0.46 to 1.26 of the measured times; k_sweep without its cost of the trace's zeros and the launches):
 //   k_gather  5 us, 6 ns a window and pixel, 5 ps more for each particle to look at, 2.2 us a particle that
 //             the fullest window takes (one after the other), 4.1 us a particle and window on 1536 resident blocks
-//   k_sweep   13 ps a grid point (FP64 20), 10 ns a particle and tile; at least 1.7 ns a grid point of one block's
-//             pixels, kDensePix of them at a time
-// and takes k_gather where it is faster by half: in 65 of the draws, where k_sweep takes 1.07 to 19 times as long.  By their
+//   k_sweep   13 ps a grid point (FP64 20), 10 ns a particle and tile, and of one block's particles and pixels,
+//             kDensePix at a time, 1 us and 1.7 ns a grid point
+// and takes k_gather where it is faster by half: in 77 of the draws, where k_sweep takes 1.07 to 19 times as long.  By their
 // density alone k_gather would be the slower one in 144 of the draws, up to 58 times.  Where k_sweep keeps them, the rule
 // and the idle launch cost 4 us (calls too small for k_gather on any account have neither).
 constexpr double kGatherDensity = 1.0;
@@ -324,12 +324,12 @@ struct GatherRule {
     const double *x_mid;
     double n_obs;
     int64_t n_win, window, bin;  // windows of a pixel, grid points of a window and a bin
-    float fixed, per_most, per_window, per_point, per_particle, per_mean;  // us
+    float fixed, per_most, per_window, per_point, per_particle, per_pass, per_mean;  // us
     // of the fullest window's particles, the windows, points and particles
     __host__ __device__ __forceinline__ bool gathered(float most, float windows, float points, float particles) const
     {
         const float gather = fixed + per_most * most + per_window * windows;
-        const float sweep = fmaxf(per_point * points + per_particle * particles, per_mean * points / fmaxf(particles, 1.0f));
+        const float sweep = per_point * points + per_particle * particles + per_pass + per_mean * points / fmaxf(particles, 1.0f);
         return kGatherMargin * gather < sweep;
     }
 };
@@ -1851,8 +1851,8 @@ lw_status launch_deposit(const lw_traj_t *t, const lw_grid_t *gr, int prec, int 
                 rule.per_point = (f64 ? 20e-6f : 13e-6f) * (float)npx;
                 rule.per_particle = 0.01f * (float)sh.n_tiles;
                 const int at_once = f64 ? SweepCfg<double>::kDensePix : SweepCfg<float>::kDensePix;
-                rule.per_mean = 1.7e-3f * (float)((std::min<int64_t>(npx, kTilePix) + at_once - 1) / at_once) *
-                                (float)sh.parts_per_group / (float)std::max(1, sw.n_seg);
+                rule.per_pass = (float)((std::min<int64_t>(npx, kTilePix) + at_once - 1) / at_once) * (float)sh.parts_per_group;
+                rule.per_mean = 1.7e-3f * rule.per_pass / (float)std::max(1, sw.n_seg);
                 // a call too small for it, were all particles' points in one window or over all of the grid
                 gather = rule.gathered(1.0f, (float)np, (float)np * (float)n_obs, (float)np);
             }
